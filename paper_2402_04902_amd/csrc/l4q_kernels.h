@@ -90,9 +90,11 @@ double launch_mfma_probe(const bf16_t* data, int iterations, int workgroups, flo
 void launch_gemm_bf16_kmajor_f32(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, int64_t M, int64_t N,
                                  int64_t K, float* C, int64_t ldc, hipStream_t stream);
 
-// ---- binary32 GEMM with arbitrary strides: C[m,n] = scale * sum_k A[m*a_rs + k*a_cs] B[k*b_rs + n*b_cs] ----
+// ---- binary32 GEMM: C[m,n] = scale * sum_k A[m*a_rs + k*a_cs] B[k*b_rs + n*b_cs] (accumulate: added to C[m,n]);
+// one stride of each operand is 1 ----
 void launch_sgemm(const float* A, int64_t a_rs, int64_t a_cs, const float* B, int64_t b_rs, int64_t b_cs,
-                  float* C, int64_t ldc, int64_t M, int64_t N, int64_t K, float scale, hipStream_t stream);
+                  float* C, int64_t ldc, int64_t M, int64_t N, int64_t K, float scale, hipStream_t stream,
+                  bool accumulate = false);
 
 // ---- unfused quantizer gradients: reads dWq [o,i] (binary32), recomputes w, code, mask; writes
 // dscale, dzero [o,G], dB partial-free result dB [o,r], and overwrites dWq with mask * dWq ----

@@ -1,66 +1,12 @@
-// Straightforward kernels: a strided binary32 GEMM, the unfused quantizer-gradient pass and the
-// two-pass dA reduction.  They serve the binary32 mode end to end and the unfused backward of
-// the bfloat16 mode; they make no assumption on shapes beyond the library's divisibility rules.
+// Straightforward kernels: the unfused quantizer-gradient pass and the two-pass dA reduction.  They
+// serve the binary32 mode and the unfused backward of the bfloat16 mode; they make no assumption on
+// shapes beyond the library's divisibility rules.
 #include "l4q_device.h"
 #include "l4q_kernels.h"
 
 namespace l4q {
 
 namespace {
-
-// ------------------------------------------------------------------ strided SGEMM
-// 64 x 64 output tile, 16-deep k step, 256 threads, 4 x 4 outputs per thread.
-constexpr int SG_BM = 64, SG_BN = 64, SG_BK = 16;
-
-__global__ __launch_bounds__(256) void sgemm_kernel(const float* __restrict__ A, int64_t a_rs, int64_t a_cs,
-                                                     const float* __restrict__ B, int64_t b_rs, int64_t b_cs,
-                                                     float* __restrict__ C, int64_t ldc, int64_t M, int64_t N,
-                                                     int64_t K, float scale) {
-  __shared__ float As[SG_BK][SG_BM + 4];
-  __shared__ float Bs[SG_BK][SG_BN + 4];
-  const int tid = threadIdx.x;
-  const int tx = tid & 15, ty = tid >> 4;
-  const int64_t m0 = (int64_t)blockIdx.y * SG_BM, n0 = (int64_t)blockIdx.x * SG_BN;
-  float acc[4][4] = {};
-  for (int64_t k0 = 0; k0 < K; k0 += SG_BK) {
-    // 64 x 16 elements per operand, 4 per thread.  The faster-varying thread index follows the
-    // operand's unit-stride axis where there is one.
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int idx = tid + e * 256;
-      int mm, kk;
-      if (a_cs == 1) { kk = idx & 15; mm = idx >> 4; } else { mm = idx & 63; kk = idx >> 6; }
-      const int64_t m = m0 + mm, k = k0 + kk;
-      As[kk][mm] = (m < M && k < K) ? A[m * a_rs + k * a_cs] : 0.f;
-      int nn, kb;
-      if (b_rs == 1) { kb = idx & 15; nn = idx >> 4; } else { nn = idx & 63; kb = idx >> 6; }
-      const int64_t n = n0 + nn, k2 = k0 + kb;
-      Bs[kb][nn] = (n < N && k2 < K) ? B[k2 * b_rs + n * b_cs] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < SG_BK; ++kk) {
-      float a[4], b[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) { a[u] = As[kk][ty * 4 + u]; b[u] = Bs[kk][tx * 4 + u]; }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) acc[u][v] = fmaf(a[u], b[v], acc[u][v]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int64_t m = m0 + ty * 4 + u;
-    if (m >= M) continue;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int64_t n = n0 + tx * 4 + v;
-      if (n < N) C[m * ldc + n] = scale * acc[u][v];
-    }
-  }
-}
 
 // ------------------------------------------------------------------ quantizer gradients, unfused
 // One wave per weight row p; a lane owns 4 consecutive columns per 256-column step.
@@ -270,12 +216,6 @@ void launch_adamw(const AdamwArgs& a, hipStream_t stream) {
   int64_t blocks = (n + 255) / 256;
   if (blocks > 4096) blocks = 4096;
   hipLaunchKernelGGL(adamw_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, a);
-}
-
-void launch_sgemm(const float* A, int64_t a_rs, int64_t a_cs, const float* B, int64_t b_rs, int64_t b_cs,
-                  float* C, int64_t ldc, int64_t M, int64_t N, int64_t K, float scale, hipStream_t stream) {
-  dim3 grid((unsigned)((N + SG_BN - 1) / SG_BN), (unsigned)((M + SG_BM - 1) / SG_BM));
-  hipLaunchKernelGGL(sgemm_kernel, grid, dim3(256), 0, stream, A, a_rs, a_cs, B, b_rs, b_cs, C, ldc, M, N, K, scale);
 }
 
 template <class T>

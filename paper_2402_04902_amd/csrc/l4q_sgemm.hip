@@ -1,0 +1,293 @@
+// Binary32 products on the matrix cores:  C[m,n] = scale * sum_k A[m,k] B[k,n]  (+ C[m,n] with accumulate), each operand
+// with one unit-stride axis.  Serves the binary32 mode end to end (forward, dX, dWq, dB) and the LoRA products of the
+// binary32 QAT-LoRA layer.
+//
+// v_mfma_f32_32x32x2_f32 multiplies and adds in binary32 like the vector unit, at the vector unit's peak rate, but one
+// instruction is 64 cycles of work on two registers of operands, so neither instruction issue nor LDS reads are in the
+// way.  (The vector kernel this replaces, 64 x 64 tiles with 4 x 4 outputs per thread, reached 26 TFLOP/s: two LDS
+// reads per four multiply-adds, element-wise loads, one tile per compute unit and nothing in flight across its barriers.)
+//
+// Operand fragments.  A matrix op takes two k-values, one per half-wave, and the order of k in a sum is free as long as
+// both operands agree: op j of four contracts k = j (lanes 0..31) and k = 4 + j (lanes 32..63) of a run of 8.  A lane of
+// a K-contiguous operand therefore reads 4 consecutive k of its row (one 16-byte read); a K-major operand is read one
+// float per op, 32 consecutive columns per half-wave.  No transposition in either form.
+#include "l4q_device.h"
+#include "l4q_gemm_core.h"
+#include "l4q_kernels.h"
+
+namespace l4q {
+
+namespace {
+
+typedef float f32x4u_t __attribute__((ext_vector_type(4), aligned(4)));  // 16-byte global access at 4-byte alignment: rows
+                                                                         // of an odd number of floats
+typedef gemm::f32x16_t f32x16_t;
+
+struct SgemmArgs {
+  const float* A;
+  const float* B;
+  float* C;
+  int64_t lda, ldb, ldc;  // stride of the axis that is not unit-stride
+  int64_t M, N, K;
+  float scale;
+  bool accumulate;
+};
+
+__device__ __forceinline__ void store_out(const SgemmArgs& a, int64_t m, int64_t n, float v) {
+  float* dst = a.C + m * a.ldc + n;
+  *dst = a.accumulate ? *dst + a.scale * v : a.scale * v;
+}
+
+// ------------------------------------------------------------------ tiled form
+// 4 waves (2 x 2); k in steps of 32, the next two steps' operands travelling to registers while the current one is
+// multiplied out of LDS; two LDS buffers, one barrier per step.  K-contiguous operands lie in LDS as rows
+// of 32 k + 4 floats of padding (16-byte reads of 16 consecutive rows meet all banks once), K-major ones as they come.
+constexpr int SG_BK = 32;
+constexpr int SG_KPITCH = SG_BK + 4;
+
+// One operand tile of ROWS rows (its M or N axis) x 32 k-values, ROWS / 8 floats per thread.
+template <int ROWS, bool KMAJOR>
+struct SgemmOperand {
+  static constexpr int NV = ROWS * SG_BK / 4 / 256;  // 16-byte pieces per thread
+  static constexpr int PITCH = KMAJOR ? ROWS + 4 : SG_KPITCH;
+  static constexpr int FLOATS = KMAJOR ? SG_BK * PITCH : ROWS * PITCH;
+  f32x4u_t v[NV];
+
+  // piece e of thread tid: row and first column of 4 consecutive elements along the unit-stride axis
+  __device__ static void place(int tid, int e, int& row, int& col) {
+    constexpr int PER_ROW = (KMAJOR ? ROWS : SG_BK) / 4;
+    const int q = tid + e * 256;
+    row = q / PER_ROW;
+    col = (q % PER_ROW) * 4;
+  }
+  // P: the operand; r0 .. extent: its M / N axis; k0 .. K
+  __device__ void load(const float* __restrict__ P, int64_t ld, int64_t r0, int64_t extent, int64_t k0, int64_t K, int tid) {
+#pragma unroll
+    for (int e = 0; e < NV; ++e) {
+      int row, col;
+      place(tid, e, row, col);
+      const int64_t outer = (KMAJOR ? k0 : r0) + row, outer_end = KMAJOR ? K : extent;
+      const int64_t inner = (KMAJOR ? r0 : k0) + col, inner_end = KMAJOR ? extent : K;
+      f32x4u_t t = {0.f, 0.f, 0.f, 0.f};
+      if (outer < outer_end) {
+        const float* p = P + outer * ld + inner;
+        if (inner + 3 < inner_end) t = *reinterpret_cast<const f32x4u_t*>(p);
+        else {
+          if (inner < inner_end) t[0] = p[0];
+          if (inner + 1 < inner_end) t[1] = p[1];
+          if (inner + 2 < inner_end) t[2] = p[2];
+        }
+      }
+      v[e] = t;
+    }
+  }
+  __device__ void store(float* lds, int tid) const {
+#pragma unroll
+    for (int e = 0; e < NV; ++e) {
+      int row, col;
+      place(tid, e, row, col);
+      *reinterpret_cast<float4*>(lds + row * PITCH + col) = make_float4(v[e][0], v[e][1], v[e][2], v[e][3]);
+    }
+  }
+  // the 4 k-values of run kk (8 k-values) this lane feeds to the 4 matrix ops, for row `row` of the tile
+  __device__ static void fragment(const float* lds, int row, int kk, int half, float (&f)[4]) {
+    if constexpr (KMAJOR) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) f[j] = lds[(kk * 8 + half * 4 + j) * PITCH + row];
+    } else {
+      const float4 t = *reinterpret_cast<const float4*>(lds + row * PITCH + kk * 8 + half * 4);
+      f[0] = t.x; f[1] = t.y; f[2] = t.z; f[3] = t.w;
+    }
+  }
+};
+
+template <int BM, int BN, bool A_KM, bool B_KM>
+__global__ __launch_bounds__(256) void sgemm_tile_kernel(SgemmArgs a) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  typedef SgemmOperand<BM, A_KM> OpA;
+  typedef SgemmOperand<BN, B_KM> OpB;
+  constexpr int STAGE = OpA::FLOATS + OpB::FLOATS;
+  constexpr int TM = BM / 64, TN = BN / 64;  // 32 x 32 accumulator tiles per wave
+  __shared__ __align__(16) float lds[2 * STAGE];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, half = lane >> 5;
+  const int tiles_m = (int)((a.M + BM - 1) / BM), tiles_n = (int)((a.N + BN - 1) / BN);
+  int tm, tn;
+  gemm::tile_of_block((int)blockIdx.x, tiles_m, tiles_n, tm, tn);
+  const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
+  const int wm = (wave >> 1) * (BM / 2), wn = (wave & 1) * (BN / 2);
+
+  f32x16_t acc[TM][TN];
+#pragma unroll
+  for (int x = 0; x < TM; ++x)
+#pragma unroll
+    for (int y = 0; y < TN; ++y)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[x][y][e] = 0.f;
+
+  OpA oa[2];
+  OpB ob[2];
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    oa[p].load(a.A, a.lda, m0, a.M, p * SG_BK, a.K, tid);
+    ob[p].load(a.B, a.ldb, n0, a.N, p * SG_BK, a.K, tid);
+  }
+  for (int64_t k0 = 0; k0 < a.K; k0 += 2 * SG_BK) {
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {  // steps of one buffer and register set each
+      if (p == 1 && k0 + SG_BK >= a.K) break;
+      float* la = lds + p * STAGE;
+      float* lb = la + OpA::FLOATS;
+      oa[p].store(la, tid);
+      ob[p].store(lb, tid);
+      __syncthreads();  // (the buffer's previous readers passed the barrier of the step between)
+      const int64_t next = k0 + (p + 2) * SG_BK;
+      if (next < a.K) {
+        oa[p].load(a.A, a.lda, m0, a.M, next, a.K, tid);
+        ob[p].load(a.B, a.ldb, n0, a.N, next, a.K, tid);
+      }
+#pragma unroll
+      for (int kk = 0; kk < SG_BK / 8; ++kk) {
+        float fa[TM][4], fb[TN][4];
+#pragma unroll
+        for (int x = 0; x < TM; ++x) OpA::fragment(la, wm + x * 32 + l32, kk, half, fa[x]);
+#pragma unroll
+        for (int y = 0; y < TN; ++y) OpB::fragment(lb, wn + y * 32 + l32, kk, half, fb[y]);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int x = 0; x < TM; ++x)
+#pragma unroll
+            for (int y = 0; y < TN; ++y)
+              acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[x][j], fb[y][j], acc[x][y], 0, 0, 0);
+      }
+    }
+  }
+  // accumulator: lane = column n, register e = row 8 (e / 4) + 4 half + e % 4
+#pragma unroll
+  for (int x = 0; x < TM; ++x)
+#pragma unroll
+    for (int y = 0; y < TN; ++y) {
+      const int64_t n = n0 + wn + y * 32 + l32;
+      if (n >= a.N) continue;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int64_t m = m0 + wm + x * 32 + 8 * (e / 4) + 4 * half + (e % 4);
+        if (m < a.M) store_out(a, m, n, acc[x][y][e]);
+      }
+    }
+#endif
+}
+
+// ------------------------------------------------------------------ sliced form
+// Few output tiles: a workgroup of NWV waves owns 32 x 32 outputs, each wave takes every NWV-th run of 8 k-values
+// straight from memory into registers, and the waves' sums meet in LDS, added in wave order.
+template <bool KMAJOR>
+__device__ __forceinline__ void sliced_fragment(const float* __restrict__ P, int64_t ld, int64_t row, bool row_ok, int64_t k,
+                                                int64_t K, float (&f)[4]) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) f[j] = 0.f;
+  if (!row_ok) return;
+  if constexpr (KMAJOR) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (k + j < K) f[j] = P[(k + j) * ld + row];
+  } else {
+    const float* p = P + row * ld + k;
+    if (k + 3 < K) {
+      const f32x4u_t t = *reinterpret_cast<const f32x4u_t*>(p);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) f[j] = t[j];
+    } else {
+#pragma unroll
+      for (int j = 0; j < 3; ++j)
+        if (k + j < K) f[j] = p[j];
+    }
+  }
+}
+
+constexpr int SL_WAVES = 8;
+constexpr int SL_UNROLL = 4;  // runs of 8 k-values in flight per wave
+
+template <bool A_KM, bool B_KM>
+__global__ __launch_bounds__(64 * SL_WAVES) void sgemm_sliced_kernel(SgemmArgs a) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __shared__ float part[SL_WAVES][32][33];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, half = lane >> 5;
+  const int tiles_n = (int)((a.N + 31) / 32);
+  const int64_t m0 = (int64_t)(blockIdx.x / tiles_n) * 32, n0 = (int64_t)(blockIdx.x % tiles_n) * 32;
+  const bool m_ok = m0 + l32 < a.M, n_ok = n0 + l32 < a.N;
+  f32x16_t acc;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+  for (int64_t k0 = (int64_t)wave * 8; k0 < a.K; k0 += SL_WAVES * 8 * SL_UNROLL) {
+    float fa[SL_UNROLL][4], fb[SL_UNROLL][4];
+#pragma unroll
+    for (int u = 0; u < SL_UNROLL; ++u) {
+      const int64_t k = k0 + u * (SL_WAVES * 8) + half * 4;
+      sliced_fragment<A_KM>(a.A, a.lda, m0 + l32, m_ok, k, a.K, fa[u]);
+      sliced_fragment<B_KM>(a.B, a.ldb, n0 + l32, n_ok, k, a.K, fb[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < SL_UNROLL; ++u)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[u][j], fb[u][j], acc, 0, 0, 0);
+  }
+#pragma unroll
+  for (int e = 0; e < 16; ++e) part[wave][8 * (e / 4) + 4 * half + (e % 4)][l32] = acc[e];
+  __syncthreads();
+  for (int q = tid; q < 32 * 32; q += 64 * SL_WAVES) {
+    const int r = q >> 5, c = q & 31;
+    float v = part[0][r][c];
+#pragma unroll
+    for (int w = 1; w < SL_WAVES; ++w) v += part[w][r][c];
+    if (m0 + r < a.M && n0 + c < a.N) store_out(a, m0 + r, n0 + c, v);
+  }
+#endif
+}
+
+// Which form, in us (K-contiguous operands; sliced / 64 x 64 / 128 x 128 tiles):
+//   64-wide tiles   16 (100 x 512 x 1024)   11 / 29 / 82        the vector kernel took 36 .. 44 us on a 4-tile product
+//                   80 (300 x 1024 x 1024)  21 / 30 / 82        of K = 256 (sliced form: 4.8) and 318 .. 363 us on
+//                  128 (512 x 1024 x 2048)  41 / 56 / 160       1000 x 2048 x 2048
+//                  160 (1000 x 600 x 2048)  63 / 57 / 159
+//                  256 (1000 x 1024 x 1024) 42 / 31 / 82
+//                  512 (1000 x 2048 x 2048) 152 / 89 / 158      (95 TFLOP/s; matrix peak 157)
+//                 1024 (2048 x 2048 x 1000) 144 / 88 / 85
+//                 2048 (2048 x 4096 x 2048) 606 / 322 / 284     (121 TFLOP/s)
+// A 64-wide tile occupies a compute unit for its whole k range with one wave per SIMD, so below 5/8 of the units' number
+// the sliced form, eight times as many waves on a quarter of the tile, is ahead; 128-wide tiles halve the operand
+// traffic and win once there are two of them per compute unit.
+template <bool A_KM, bool B_KM>
+void launch_sgemm_form(const SgemmArgs& a, hipStream_t stream) {
+  auto tiles = [&](int64_t bm, int64_t bn) { return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
+  const int64_t cus = device_compute_units();
+  if (tiles(64, 64) * 8 < cus * 5)
+    hipLaunchKernelGGL((sgemm_sliced_kernel<A_KM, B_KM>), dim3((unsigned)tiles(32, 32)), dim3(64 * SL_WAVES), 0, stream, a);
+  else if (tiles(128, 128) < 2 * cus)
+    hipLaunchKernelGGL((sgemm_tile_kernel<64, 64, A_KM, B_KM>), dim3((unsigned)tiles(64, 64)), dim3(256), 0, stream, a);
+  else
+    hipLaunchKernelGGL((sgemm_tile_kernel<128, 128, A_KM, B_KM>), dim3((unsigned)tiles(128, 128)), dim3(256), 0, stream, a);
+}
+
+}  // namespace
+
+void launch_sgemm(const float* A, int64_t a_rs, int64_t a_cs, const float* B, int64_t b_rs, int64_t b_cs, float* C,
+                  int64_t ldc, int64_t M, int64_t N, int64_t K, float scale, hipStream_t stream, bool accumulate) {
+  SgemmArgs a;
+  a.A = A; a.B = B; a.C = C;
+  a.M = M; a.N = N; a.K = K;
+  a.ldc = ldc;
+  a.scale = scale;
+  a.accumulate = accumulate;
+  const bool a_km = a_cs != 1, b_km = b_rs != 1;  // (one of an operand's strides is 1)
+  a.lda = a_km ? a_cs : a_rs;
+  a.ldb = b_km ? b_rs : b_cs;
+  if (a_km && b_km) launch_sgemm_form<true, true>(a, stream);
+  else if (a_km) launch_sgemm_form<true, false>(a, stream);
+  else if (b_km) launch_sgemm_form<false, true>(a, stream);
+  else launch_sgemm_form<false, false>(a, stream);
+}
+
+}  // namespace l4q

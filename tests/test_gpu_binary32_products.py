@@ -1,0 +1,21 @@
+"""Binary32 layers at the edges of the product kernels' forms (few tiles: k-slices over a workgroup's waves; 64-wide;
+128-wide tiles): odd token and out-feature counts end tiles and k-steps everywhere, against the fp64 oracle."""
+import pytest
+
+from paper_2402_04902_amd.inputs import DTYPE_F32, LayerSpec
+
+from test_gpu_parity import run_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,i,o,r,g", [
+    (1, 4, 1, 1, 4),            # one element of everything
+    (33, 36, 31, 5, 4),         # sliced form, k tails shorter than a run of 8
+    (7, 260, 129, 8, 4),        # sliced form, K = 7 and K = 129
+    (1037, 1028, 1031, 3, 4),   # 64-wide tiles in the forward product, dX and dWq; K = 1031, 1037
+    (16, 2052, 2051, 2, 4),     # 64-wide tiles on one k-step of 16 (dWq)
+    (35, 2948, 2949, 2, 4),     # 128-wide tiles (dWq: 24 x 24), K = 35
+])
+def test_binary32_product_forms(T, i, o, r, g):
+    run_case(LayerSpec(f"f32_prod_{T}x{i}x{o}", T, i, o, r, 2.0 * r, 4, g, DTYPE_F32), seed=T + i, shrink=0.8)
