@@ -89,7 +89,7 @@ struct BwdWs {
   bf16_t* bT;        // [r,opad]                   (bf16 fused)
   float* dB_part;    // [2 tiles_n, o, r]          (bf16 fused)
   float* dwq;        // [o,i]                      (binary32 mode, bf16 unfused)
-  float* dA_part;    // [tiles_m or ceil(o/kDaRowBlock), r, i]
+  float* dA_part;    // [tiles_m or lora_tn_blocks(o), r, i]
   float* splitk;     // [slices][T][i] binary32 tiles of the dX product's k-slices (bf16, few tokens), else null
   int64_t opad;
   int tiles_m, tiles_n;
@@ -119,7 +119,7 @@ BwdWs carve_bwd(const l4q_desc* d, void* ws) {
   // Wq^T is zero-padded along its out-feature axis to the k-step of the matrix-core kernels
   w.opad = (int64_t)align_up(o, 32);
   const LayerDims L = dims_of(d);
-  const size_t nrb = (o + l4q::kDaRowBlock - 1) / l4q::kDaRowBlock;
+  const size_t nrb = (size_t)l4q::lora_tn_blocks(d->out_features);
   if (d->dtype == L4Q_DTYPE_BF16) {
     w.fused = !(d->flags & L4Q_FLAG_UNFUSED_BACKWARD) && l4q::dw_fused_supported(L);
     w.masked = !(d->flags & L4Q_FLAG_UNFUSED_BACKWARD) && l4q::dw_masked_supported(L);
@@ -399,7 +399,7 @@ int l4q_backward(const l4q_desc* desc, const void* X, const void* dY, const void
     if (!w.fused && !w.masked) {
       l4q::launch_gemm_bf16_kmajor_f32((const bf16_t*)dY, d.o, (const bf16_t*)X, d.i, d.o, d.i, d.T, w.dwq, d.i, stream);
       l4q::launch_quant_grads<bf16_t>(d, W0b, Ab, Bb, scale, zero, w.dwq, dscale, dzero, dB, stream);
-      l4q::launch_dA<bf16_t>(d, Bb, w.dwq, w.dA_part, dA, stream);
+      l4q::launch_tn<float, bf16_t>(Bb, w.dwq, d.o, d.i, d.r, false, w.dA_part, d.gamma, dA, d.accumulate, stream);
     }
   } else {
     const float* W0f = (const float*)W0;
@@ -415,7 +415,7 @@ int l4q_backward(const l4q_desc* desc, const void* X, const void* dY, const void
     // dWq[p,j] = sum_t dY[t,p] X[t,j]
     l4q::launch_sgemm((const float*)dY, 1, d.o, (const float*)X, d.i, 1, w.dwq, d.i, d.o, d.i, d.T, 1.f, stream);
     l4q::launch_quant_grads<float>(d, W0f, Af, Bf, scale, zero, w.dwq, dscale, dzero, dB, stream);
-    l4q::launch_dA<float>(d, Bf, w.dwq, w.dA_part, dA, stream);
+    l4q::launch_tn<float, float>(Bf, w.dwq, d.o, d.i, d.r, false, w.dA_part, d.gamma, dA, d.accumulate, stream);
   }
   return launch_status();
 }
@@ -605,8 +605,8 @@ int l4q_qatlora_backward(const l4q_desc* desc, const void* X, const void* dY, co
     l4q::launch_gemm_bf16_kmajor_f32(dYb, d.o, Xb, d.i, d.o, d.i, d.T, w.dwq, d.i, stream);
     l4q::launch_quant_grads<bf16_t>(dq, W0b, Ab, Bb, scale, zero, w.dwq, dscale, dzero, dB, stream);  // its dB term is gamma = 0
     l4q::launch_lora_down<bf16_t>(Xb, d.T, d.i, Ab, d.r, false, w.xa, stream);
-    l4q::launch_lora_tn<bf16_t>(w.dyb, Xb, d.T, d.i, d.r, false, w.part, d.gamma, dA, d.accumulate, stream);
-    l4q::launch_lora_tn<bf16_t>(w.xa, dYb, d.T, d.o, d.r, true, w.part, d.gamma, dB, d.accumulate, stream);
+    l4q::launch_tn<bf16_t, float>(w.dyb, Xb, d.T, d.i, d.r, false, w.part, d.gamma, dA, d.accumulate, stream);
+    l4q::launch_tn<bf16_t, float>(w.xa, dYb, d.T, d.o, d.r, true, w.part, d.gamma, dB, d.accumulate, stream);
   } else {
     const float *Xf = (const float*)X, *dYf = (const float*)dY, *W0f = (const float*)W0, *Af = (const float*)A,
                 *Bf = (const float*)B;
@@ -620,8 +620,8 @@ int l4q_qatlora_backward(const l4q_desc* desc, const void* X, const void* dY, co
     l4q::launch_sgemm(dYf, 1, d.o, Xf, d.i, 1, w.dwq, d.i, d.o, d.i, d.T, 1.f, stream);
     l4q::launch_quant_grads<float>(dq, W0f, Af, Bf, scale, zero, w.dwq, dscale, dzero, dB, stream);
     l4q::launch_lora_down<float>(Xf, d.T, d.i, Af, d.r, false, w.xa, stream);
-    l4q::launch_lora_tn<float>(w.dyb, Xf, d.T, d.i, d.r, false, w.part, d.gamma, dA, d.accumulate, stream);
-    l4q::launch_lora_tn<float>(w.xa, dYf, d.T, d.o, d.r, true, w.part, d.gamma, dB, d.accumulate, stream);
+    l4q::launch_tn<float, float>(w.dyb, Xf, d.T, d.i, d.r, false, w.part, d.gamma, dA, d.accumulate, stream);
+    l4q::launch_tn<float, float>(w.xa, dYf, d.T, d.o, d.r, true, w.part, d.gamma, dB, d.accumulate, stream);
   }
   return launch_status();
 }

@@ -103,11 +103,6 @@ void launch_quant_grads(const LayerDims& d, const T* W0, const T* A, const T* B,
                         const float* zero, float* dWq_inout, float* dscale, float* dzero, float* dB,
                         hipStream_t stream);
 
-// ---- dA = gamma * B^T . dWp  (reduction over the o rows), two deterministic passes ----
-// partial: [ceil(o / kDaRowBlock), r, i] floats
-constexpr int kDaRowBlock = 128;
-template <class T>
-void launch_dA(const LayerDims& d, const T* B, const float* dWp, float* partial, float* dA, hipStream_t stream);
 
 // out[e] = scale * sum_b partial[b * n + e], b ascending (fixed summation order); accumulate: added to out[e]
 void launch_reduce_partials(const float* partial, int64_t nblocks, int64_t n, float scale, float* out,
@@ -169,10 +164,11 @@ void launch_lora_down(const S* Xs, int64_t T, int64_t n, const S* M, int r, bool
 template <class S>
 void launch_lora_up(S* Out, int64_t T, int64_t n, const float* U, const S* M, int r, bool m_is_n_by_r, float gamma,
                     hipStream_t stream);                      // Out += gamma U . M
-int64_t lora_tn_blocks(int64_t T);                            // token blocks of the partial sums below
-// out = gamma * sum_t U[t,:]^T Xs[t,:] as [r, n], or as [n, r] with out_n_by_r; partial: lora_tn_blocks(T) * r * n floats
-template <class S>
-void launch_lora_tn(const float* U, const S* Xs, int64_t T, int64_t n, int r, bool out_n_by_r, float* partial,
-                    float gamma, float* out, bool accumulate, hipStream_t stream);
+// out = gamma * sum_t U[t,:]^T Xs[t,:] (U [T, r]) as [r, n], or as [n, r] with out_n_by_r, in two passes of fixed summation
+// order; partial: lora_tn_blocks(T) * r * n floats.  Also dA = gamma * B^T . (m * dWq) of the unfused backward.
+int64_t lora_tn_blocks(int64_t T);  // row blocks of the partial sums
+template <class S, class UT>
+void launch_tn(const UT* U, const S* Xs, int64_t T, int64_t n, int r, bool out_n_by_r, float* partial, float gamma,
+               float* out, bool accumulate, hipStream_t stream);
 
 }  // namespace l4q

@@ -121,32 +121,108 @@ __global__ __launch_bounds__(256) void lora_up_kernel(S* __restrict__ Out, int64
     }
 }
 
-// part[tb][k][j] (or [tb][j][k] when NR) = sum over the 128 tokens of block tb of U[t, k] Xs[t, j]
+// part[tb][k][j] (or [tb][j][k] when NR) = sum over the 128 rows of block tb of U[t, k] Xs[t, j].
+// Bound: Xs read once.  v_mfma_f32_16x16x4_f32 takes 16 ranks x 4 rows x 16 columns in binary32: lane (h = lane / 16,
+// c = lane % 16) holds row h of four and 4 consecutive columns, one per op, so its loads are 8 or 16 consecutive bytes, 16
+// lanes a run of 128 or 256, and no operand passes through LDS but U.  A workgroup takes 64 columns; each of its 4 waves
+// 32 of the rows, all requested at once and kept in registers for every 16 ranks; the waves' sums meet in LDS and are
+// added in wave order.  2048 x 4096 bf16 at 16 ranks: 122 .. 129 us with one column per thread and a row's U fetched by
+// scalar loads ahead of every 16 multiply-adds, 15.5 us as vector multiply-adds on U broadcast from LDS (the vector rate
+// itself is half the matrix rate), 9.1 us in
+// this form (10.0 written as [n, r]); 2048 x 2048 binary32 99, 15.0, 7.0 us; 256 x 256 binary32 65, 12.3, 5.1 us.
 constexpr int LR_TB = 128;
-template <class S, bool NR>
-__global__ __launch_bounds__(256) void lora_tn_partial_kernel(const float* __restrict__ U, const S* __restrict__ Xs,
-                                                               int64_t T, int64_t n, int r,
-                                                               float* __restrict__ part) {
-  const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t tb = blockIdx.y;
-  const int k0 = blockIdx.z * LR_KC;
-  const int64_t t_begin = tb * LR_TB, t_end = t_begin + LR_TB < T ? t_begin + LR_TB : T;
-  float acc[LR_KC];
-#pragma unroll
-  for (int k = 0; k < LR_KC; ++k) acc[k] = 0.f;
-  if (j < n) {
-    for (int64_t t = t_begin; t < t_end; ++t) {
-      const float x = load1(Xs + t * n + j);
-      const float* u = U + t * r + k0;  // uniform
-#pragma unroll
-      for (int k = 0; k < LR_KC; ++k)
-        if (k0 + k < r) acc[k] = fmaf(u[k], x, acc[k]);
-    }
-    float* dst = part + tb * (int64_t)r * n;
-#pragma unroll
-    for (int k = 0; k < LR_KC; ++k)
-      if (k0 + k < r) dst[NR ? j * r + k0 + k : (int64_t)(k0 + k) * n + j] = acc[k];
+
+// 4 consecutive elements as they lie in memory
+template <class S> struct Row4;
+template <> struct Row4<float> {
+  typedef float vec_t __attribute__((ext_vector_type(4), aligned(4)));  // (rows of an odd number of floats)
+  typedef float raw_t __attribute__((ext_vector_type(4)));
+  static __device__ __forceinline__ raw_t load(const float* p) { return *reinterpret_cast<const vec_t*>(p); }
+  static __device__ __forceinline__ float get(const raw_t& v, int c) { return v[c]; }
+  static __device__ __forceinline__ void set(raw_t& v, int c, const float* p) { v[c] = *p; }
+};
+template <> struct Row4<bf16_t> {  // (rows are whole 16-byte pieces)
+  typedef uint32_t raw_t __attribute__((ext_vector_type(2)));
+  static __device__ __forceinline__ raw_t load(const bf16_t* p) { return *reinterpret_cast<const raw_t*>(p); }
+  static __device__ __forceinline__ float get(const raw_t& v, int c) {
+    return __uint_as_float(c & 1 ? v[c >> 1] & 0xFFFF0000u : v[c >> 1] << 16);
   }
+  static __device__ __forceinline__ void set(raw_t& v, int c, const bf16_t* p) {
+    v[c >> 1] |= (uint32_t)*p << (c & 1 ? 16 : 0);
+  }
+};
+
+template <class S, class UT, bool NR>
+__global__ __launch_bounds__(256) void tn_partial_kernel(const UT* __restrict__ U, const S* __restrict__ Xs, int64_t T,
+                                                          int64_t n, int r, float* __restrict__ part) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  typedef float f32x4_t __attribute__((ext_vector_type(4)));
+  typedef Row4<float>::vec_t vec_t;
+  constexpr int STEPS = LR_TB / 4 / 4;  // groups of 4 rows per wave
+  __shared__ __align__(16) float sums[4][LR_KC][64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int h = lane >> 4, c16 = lane & 15;
+  // the last workgroup of a row takes the last 64 columns, some of them its neighbour's (same sums, written twice);
+  // rows of 4 to 63 columns end in lanes that repeat the last 4
+  const int64_t j0 = n < 64 ? 0 : (int64_t)blockIdx.x * 64 < n - 64 ? (int64_t)blockIdx.x * 64 : n - 64;
+  const int jl = n < 4 ? 0 : j0 + c16 * 4 < n - 4 ? c16 * 4 : (int)(n - 4 - j0);  // this lane's first column, from j0
+  const int64_t tb = blockIdx.y, t0 = tb * LR_TB + wave * (LR_TB / 4) + h;
+  typename Row4<S>::raw_t x[STEPS];
+#pragma unroll
+  for (int q = 0; q < STEPS; ++q) {
+    const int64_t t = t0 + 4 * q;
+    const S* p = Xs + (t < T ? t : T - 1) * n + j0;
+    if (n >= 4) x[q] = Row4<S>::load(p + jl);
+    else {
+      x[q] = typename Row4<S>::raw_t(0);
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+        if (c < n) Row4<S>::set(x[q], c, p + c);
+    }
+    if (t >= T) x[q] = typename Row4<S>::raw_t(0);
+  }
+  float* dst = part + tb * (int64_t)r * n;
+  for (int k0 = 0; k0 < r; k0 += LR_KC) {
+    float u[STEPS];
+#pragma unroll
+    for (int q = 0; q < STEPS; ++q) {
+      const int64_t t = t0 + 4 * q;
+      const bool live = t < T && k0 + c16 < r;
+      const float v = load1(U + (live ? t * r + k0 + c16 : 0));
+      u[q] = live ? v : 0.f;
+    }
+    f32x4_t acc[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int q = 0; q < STEPS; ++q)
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(u[q], Row4<S>::get(x[q], c), acc[c], 0, 0, 0);
+    if (k0 > 0) __syncthreads();  // the previous ranks' sums have been read
+#pragma unroll
+    for (int e = 0; e < 4; ++e)  // accumulator: rank 4 h + e, column c16 of op c
+      *reinterpret_cast<vec_t*>(&sums[wave][4 * h + e][jl]) = vec_t{acc[0][e], acc[1][e], acc[2][e], acc[3][e]};
+    __syncthreads();
+    auto total = [&](int k, int j) { return ((sums[0][k][j] + sums[1][k][j]) + sums[2][k][j]) + sums[3][k][j]; };
+    if constexpr (NR) {
+      const int j = tid >> 2, k = (tid & 3) * 4;
+      if (j0 + j < n) {
+        float* q = dst + (j0 + j) * r + k0 + k;
+        if (k0 + k + 3 < r) *reinterpret_cast<vec_t*>(q) = vec_t{total(k, j), total(k + 1, j), total(k + 2, j), total(k + 3, j)};
+        else
+          for (int c = 0; c < 3; ++c)
+            if (k0 + k + c < r) q[c] = total(k + c, j);
+      }
+    } else {
+      if (j0 + lane < n) {
+#pragma unroll
+        for (int k = wave; k < LR_KC; k += 4)
+          if (k0 + k < r) dst[(int64_t)(k0 + k) * n + j0 + lane] = total(k, lane);
+      }
+    }
+  }
+#endif
 }
 
 }  // namespace
@@ -169,13 +245,13 @@ void launch_lora_up(S* Out, int64_t T, int64_t n, const float* U, const S* M, in
 
 int64_t lora_tn_blocks(int64_t T) { return (T + LR_TB - 1) / LR_TB; }
 
-template <class S>
-void launch_lora_tn(const float* U, const S* Xs, int64_t T, int64_t n, int r, bool out_n_by_r, float* partial,
-                    float gamma, float* out, bool accumulate, hipStream_t stream) {
+template <class S, class UT>
+void launch_tn(const UT* U, const S* Xs, int64_t T, int64_t n, int r, bool out_n_by_r, float* partial, float gamma,
+               float* out, bool accumulate, hipStream_t stream) {
   const int64_t nb = lora_tn_blocks(T);
-  dim3 grid((unsigned)((n + 255) / 256), (unsigned)nb, (unsigned)((r + LR_KC - 1) / LR_KC));
-  if (out_n_by_r) hipLaunchKernelGGL((lora_tn_partial_kernel<S, true>), grid, dim3(256), 0, stream, U, Xs, T, n, r, partial);
-  else hipLaunchKernelGGL((lora_tn_partial_kernel<S, false>), grid, dim3(256), 0, stream, U, Xs, T, n, r, partial);
+  dim3 grid((unsigned)((n + 63) / 64), (unsigned)nb);
+  if (out_n_by_r) hipLaunchKernelGGL((tn_partial_kernel<S, UT, true>), grid, dim3(256), 0, stream, U, Xs, T, n, r, partial);
+  else hipLaunchKernelGGL((tn_partial_kernel<S, UT, false>), grid, dim3(256), 0, stream, U, Xs, T, n, r, partial);
   launch_reduce_partials(partial, nb, (int64_t)r * n, gamma, out, accumulate, stream);
 }
 
@@ -183,9 +259,11 @@ template void launch_lora_down<float>(const float*, int64_t, int64_t, const floa
 template void launch_lora_down<bf16_t>(const bf16_t*, int64_t, int64_t, const bf16_t*, int, bool, float*, hipStream_t);
 template void launch_lora_up<float>(float*, int64_t, int64_t, const float*, const float*, int, bool, float, hipStream_t);
 template void launch_lora_up<bf16_t>(bf16_t*, int64_t, int64_t, const float*, const bf16_t*, int, bool, float, hipStream_t);
-template void launch_lora_tn<float>(const float*, const float*, int64_t, int64_t, int, bool, float*, float, float*, bool,
-                                    hipStream_t);
-template void launch_lora_tn<bf16_t>(const float*, const bf16_t*, int64_t, int64_t, int, bool, float*, float, float*, bool,
-                                     hipStream_t);
+template void launch_tn<float, float>(const float*, const float*, int64_t, int64_t, int, bool, float*, float, float*, bool,
+                                      hipStream_t);
+template void launch_tn<bf16_t, float>(const float*, const bf16_t*, int64_t, int64_t, int, bool, float*, float, float*,
+                                       bool, hipStream_t);
+template void launch_tn<float, bf16_t>(const bf16_t*, const float*, int64_t, int64_t, int, bool, float*, float, float*,
+                                       bool, hipStream_t);
 
 }  // namespace l4q

@@ -1,6 +1,6 @@
-// Straightforward kernels: the unfused quantizer-gradient pass and the two-pass dA reduction.  They
-// serve the binary32 mode and the unfused backward of the bfloat16 mode; they make no assumption on
-// shapes beyond the library's divisibility rules.
+// The unfused quantizer-gradient pass (binary32 mode, unfused backward of the bfloat16 mode, QAT-LoRA),
+// the fixed-order sums of partial results, and the AdamW step.  No assumption on shapes beyond the
+// library's divisibility rules.
 #include "l4q_device.h"
 #include "l4q_kernels.h"
 
@@ -95,42 +95,16 @@ __global__ __launch_bounds__(256) void quant_grads_kernel(LayerDims d, const T* 
   }
 }
 
-// ------------------------------------------------------------------ dA = gamma * B^T dWp
-// pass 1: a thread owns one column j and sums B[p,k] * dWp[p,j] over a block of rows
-template <class T>
-__global__ __launch_bounds__(256) void dA_partial_kernel(LayerDims d, const T* __restrict__ B,
-                                                          const float* __restrict__ dWp,
-                                                          float* __restrict__ partial) {
-  const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t p0 = (int64_t)blockIdx.y * kDaRowBlock;
-  const int64_t p1 = p0 + kDaRowBlock < d.o ? p0 + kDaRowBlock : d.o;
-  if (j >= d.i) return;
-  for (int k0 = 0; k0 < d.r; k0 += QG_KCHUNK) {
-    const int kn = d.r - k0 < QG_KCHUNK ? d.r - k0 : QG_KCHUNK;
-    float acc[QG_KCHUNK];
-#pragma unroll
-    for (int k = 0; k < QG_KCHUNK; ++k) acc[k] = 0.f;
-    for (int64_t p = p0; p < p1; ++p) {
-      const float gv = dWp[p * d.i + j];
-#pragma unroll
-      for (int k = 0; k < QG_KCHUNK; ++k)
-        if (k < kn) acc[k] = fmaf(load1(B + p * d.r + k0 + k), gv, acc[k]);
-    }
-#pragma unroll
-    for (int k = 0; k < QG_KCHUNK; ++k)
-      if (k < kn) partial[((int64_t)blockIdx.y * d.r + k0 + k) * d.i + j] = acc[k];
-  }
-}
-
 }  // namespace
 
-// pass 2 (also used by the fused backward): out[e] = scale * sum_b partial[b * n + e], b ascending
+// second pass of launch_tn: out[e] = scale * sum_b partial[b * n + e], b ascending
 __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __restrict__ partial, int64_t nblocks,
                                                                int64_t n, float scale, float* __restrict__ out,
                                                                bool accumulate) {
   const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (e >= n) return;
   float acc = 0.f;
+#pragma unroll 8
   for (int64_t b = 0; b < nblocks; ++b) acc += partial[b * n + e];
   out[e] = accumulate ? out[e] + scale * acc : scale * acc;
 }
@@ -227,21 +201,9 @@ void launch_quant_grads(const LayerDims& d, const T* W0, const T* A, const T* B,
                      dzero, dB);
 }
 
-template <class T>
-void launch_dA(const LayerDims& d, const T* B, const float* dWp, float* partial, float* dA, hipStream_t stream) {
-  const int64_t nrb = (d.o + kDaRowBlock - 1) / kDaRowBlock;
-  dim3 grid((unsigned)((d.i + 255) / 256), (unsigned)nrb);
-  hipLaunchKernelGGL(dA_partial_kernel<T>, grid, dim3(256), 0, stream, d, B, dWp, partial);
-  const int64_t n = (int64_t)d.r * d.i;
-  hipLaunchKernelGGL(reduce_partials_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, partial, nrb, n,
-                     d.gamma, dA, d.accumulate);
-}
-
 template void launch_quant_grads<float>(const LayerDims&, const float*, const float*, const float*, const float*,
                                         const float*, float*, float*, float*, float*, hipStream_t);
 template void launch_quant_grads<bf16_t>(const LayerDims&, const bf16_t*, const bf16_t*, const bf16_t*,
                                          const float*, const float*, float*, float*, float*, float*, hipStream_t);
-template void launch_dA<float>(const LayerDims&, const float*, const float*, float*, float*, hipStream_t);
-template void launch_dA<bf16_t>(const LayerDims&, const bf16_t*, const float*, float*, float*, hipStream_t);
 
 }  // namespace l4q

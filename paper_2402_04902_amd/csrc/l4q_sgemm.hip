@@ -102,7 +102,7 @@ struct SgemmOperand {
 };
 
 template <int BM, int BN, bool A_KM, bool B_KM>
-__global__ __launch_bounds__(256) void sgemm_tile_kernel(SgemmArgs a) {
+__global__ __launch_bounds__(256, 2) void sgemm_tile_kernel(SgemmArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)
   typedef SgemmOperand<BM, A_KM> OpA;
   typedef SgemmOperand<BN, B_KM> OpB;
