@@ -603,7 +603,7 @@ int l4q_qatlora_backward(const l4q_desc* desc, const void* X, const void* dY, co
     l4q::launch_lora_up<bf16_t>((bf16_t*)dX, d.T, d.i, w.dyb, Ab, d.r, false, d.gamma, stream);
     // the weight gradient is materialised: scale and zero are updated from it
     l4q::launch_gemm_bf16_kmajor_f32(dYb, d.o, Xb, d.i, d.o, d.i, d.T, w.dwq, d.i, stream);
-    l4q::launch_quant_grads<bf16_t>(dq, W0b, Ab, Bb, scale, zero, w.dwq, dscale, dzero, dB, stream);  // its dB term is gamma = 0
+    l4q::launch_quant_grads<bf16_t>(dq, W0b, Ab, Bb, scale, zero, w.dwq, dscale, dzero, nullptr, stream);
     l4q::launch_lora_down<bf16_t>(Xb, d.T, d.i, Ab, d.r, false, w.xa, stream);
     l4q::launch_tn<bf16_t, float>(w.dyb, Xb, d.T, d.i, d.r, false, w.part, d.gamma, dA, d.accumulate, stream);
     l4q::launch_tn<bf16_t, float>(w.xa, dYb, d.T, d.o, d.r, true, w.part, d.gamma, dB, d.accumulate, stream);
@@ -618,7 +618,7 @@ int l4q_qatlora_backward(const l4q_desc* desc, const void* X, const void* dY, co
     l4q::launch_lora_down<float>(dYf, d.T, d.o, Bf, d.r, true, w.dyb, stream);
     l4q::launch_lora_up<float>((float*)dX, d.T, d.i, w.dyb, Af, d.r, false, d.gamma, stream);
     l4q::launch_sgemm(dYf, 1, d.o, Xf, d.i, 1, w.dwq, d.i, d.o, d.i, d.T, 1.f, stream);
-    l4q::launch_quant_grads<float>(dq, W0f, Af, Bf, scale, zero, w.dwq, dscale, dzero, dB, stream);
+    l4q::launch_quant_grads<float>(dq, W0f, Af, Bf, scale, zero, w.dwq, dscale, dzero, nullptr, stream);
     l4q::launch_lora_down<float>(Xf, d.T, d.i, Af, d.r, false, w.xa, stream);
     l4q::launch_tn<float, float>(w.dyb, Xf, d.T, d.i, d.r, false, w.part, d.gamma, dA, d.accumulate, stream);
     l4q::launch_tn<float, float>(w.xa, dYf, d.T, d.o, d.r, true, w.part, d.gamma, dB, d.accumulate, stream);

@@ -97,7 +97,8 @@ void launch_sgemm(const float* A, int64_t a_rs, int64_t a_cs, const float* B, in
                   bool accumulate = false);
 
 // ---- unfused quantizer gradients: reads dWq [o,i] (binary32), recomputes w, code, mask; writes
-// dscale, dzero [o,G], dB partial-free result dB [o,r], and overwrites dWq with mask * dWq ----
+// dscale, dzero [o,G], dB [o,r], and overwrites dWq with mask * dWq.  dB == nullptr (QAT-LoRA): the weight
+// is W0 alone (gamma, A and B are not looked at), only dscale and dzero are written ----
 template <class T>
 void launch_quant_grads(const LayerDims& d, const T* W0, const T* A, const T* B, const float* scale,
                         const float* zero, float* dWq_inout, float* dscale, float* dzero, float* dB,

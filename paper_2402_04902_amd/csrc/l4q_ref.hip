@@ -9,88 +9,153 @@ namespace l4q {
 namespace {
 
 // ------------------------------------------------------------------ quantizer gradients, unfused
-// One wave per weight row p; a lane owns 4 consecutive columns per 256-column step.
 //   dscale[p,q] = sum_j dWq * (m ? code - w : code)   (Eq. quant_lsq_s and App. A.1 case list)
 //   dzero [p,q] = sum_j dWq * (m ? 0 : 1)             (Eq. appen_lsq_b)
+// and, LORA (the L4Q layer; the QAT-LoRA quantizer sees the frozen weight alone and needs neither):
 //   dWq <- m * dWq                                    (Eq. appen_ste)
 //   dB[p,k]     = gamma * sum_j (m * dWq)[p,j] A[k,j] (Eq. appen_l4q_b)
+//
+// Bound: memory (dWq and W0 read once; LORA: the masked dWq written), with the IEEE divide and the rank sums close behind.
+// A workgroup takes QG_ROWS weight rows and deals their columns out to its 4 waves in units of 256 (or a whole group where
+// groups are longer), a lane owning 4 consecutive columns of all the rows: A is read once per QG_ROWS rows, and QG_ROWS
+// independent loads per operand are in flight.  One wave per row with one row's loads in flight, the form this replaces,
+// took 137 us on 4096 x 4096 bf16 of the QAT-LoRA layer (now 29: 100 MB at 3.4 TB/s) and 66 us on 2048 x 2048 binary32 at
+// rank 16 (now 32; on 256 x 256, where it is one chain of loads, rank sums and reductions, 8.5 against 10.5).
 constexpr int QG_KCHUNK = 16;
+constexpr int QG_ROWS = 4;
 
-template <class T>
-__global__ __launch_bounds__(256) void quant_grads_kernel(LayerDims d, const T* __restrict__ W0,
+// v[64] per lane -> the sum over the wave of v[lane]: each step halves the values held and adds the halves exchanged
+template <int OFF = 32>
+__device__ __forceinline__ float wave_sum_scatter(float (&v)[64], int lane) {
+  const bool upper = (lane & OFF) != 0;
+#pragma unroll
+  for (int c = 0; c < OFF; ++c) {
+    const float keep = upper ? v[c + OFF] : v[c], give = upper ? v[c] : v[c + OFF];
+    v[c] = keep + __shfl_xor(give, OFF, 64);
+  }
+  if constexpr (OFF > 1) return wave_sum_scatter<OFF / 2>(v, lane);
+  else return v[0];
+}
+
+template <class T, bool LORA>
+__global__ __launch_bounds__(256, 2) void quant_grads_kernel(LayerDims d, const T* __restrict__ W0,
                                                            const T* __restrict__ A, const T* __restrict__ B,
                                                            const float* __restrict__ scale,
                                                            const float* __restrict__ zero, float* __restrict__ dW,
                                                            float* __restrict__ dscale, float* __restrict__ dzero,
                                                            float* __restrict__ dB) {
-  const int lane = threadIdx.x & 63;
-  const int64_t p = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (p >= d.o) return;
+  static_assert(QG_ROWS * QG_KCHUNK == 64, "wave_sum_scatter leaves one of the dB sums in every lane");
+  __shared__ float dB_sums[4][64];
+  __shared__ float b_lds[QG_ROWS][LORA ? 256 : 1];  // the rows of B (rank <= 256)
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t p0 = (int64_t)blockIdx.x * QG_ROWS;
   const int64_t G = d.i / d.g;
-  const int lanes_per_group = d.g / 4;
-  const int width = lanes_per_group < 64 ? lanes_per_group : 64;
-  const int steps_per_group = lanes_per_group <= 64 ? 1 : lanes_per_group / 64;
+  const int width = d.g / 4 < 64 ? d.g / 4 : 64;  // lanes that share a group within a step of 256 columns
+  const int64_t unit = d.g > 256 ? d.g : 256;
+  int64_t row[QG_ROWS];  // rows past the end repeat the last one and store nothing
+#pragma unroll
+  for (int q = 0; q < QG_ROWS; ++q) row[q] = p0 + q < d.o ? p0 + q : d.o - 1;
+
+  if (LORA) {
+    for (int q = 0; q < QG_ROWS; ++q)
+      for (int k = threadIdx.x; k < d.r; k += 256) b_lds[q][k] = load1(B + row[q] * d.r + k);
+    __syncthreads();
+  }
 
   // pass 0 does everything for LoRA ranks 0..15; further passes only add dB for ranks 16.., re-reading
   // the already masked dW.
-  for (int k0 = 0; k0 < d.r; k0 += QG_KCHUNK) {
+  for (int k0 = 0; k0 < (LORA ? d.r : 1); k0 += QG_KCHUNK) {
     const int kn = d.r - k0 < QG_KCHUNK ? d.r - k0 : QG_KCHUNK;
-    float dBacc[QG_KCHUNK];
+    float dBacc[QG_ROWS * QG_KCHUNK];
 #pragma unroll
-    for (int k = 0; k < QG_KCHUNK; ++k) dBacc[k] = 0.f;
-    float ds = 0.f, db = 0.f;
-    int step_in_group = 0;
-    for (int64_t base = 0; base < d.i; base += 256) {
-      const int64_t j0 = base + lane * 4;
-      const bool active = j0 < d.i;
-      float g4[4] = {0.f, 0.f, 0.f, 0.f};
-      if (active) {
-        load4(dW + p * d.i + j0, g4);
+    for (int k = 0; k < QG_ROWS * QG_KCHUNK; ++k) dBacc[k] = 0.f;
+    for (int64_t u0 = wave * unit; u0 < d.i; u0 += 4 * unit) {
+      float ds[QG_ROWS] = {}, db[QG_ROWS] = {};
+      for (int64_t base = u0; base < u0 + unit && base < d.i; base += 256) {
+        const int64_t j0 = base + lane * 4;
+        const bool active = j0 < d.i;
+        const int64_t jc = active ? j0 : 0;
+        float g4[QG_ROWS][4];
+#pragma unroll
+        for (int q = 0; q < QG_ROWS; ++q) load4(dW + row[q] * d.i + jc, g4[q]);
         if (k0 == 0) {
-          const int64_t q = j0 / d.g;
-          const float s = scale[p * G + q], b = zero[p * G + q];
-          float wc[4];
-          merged_weight4<T>(W0 + p * d.i, A, B + p * d.r, d.i, d.r, j0, d.gamma, wc);
+          const int64_t grp = jc / d.g;
+          float w0[QG_ROWS][4], s[QG_ROWS], b[QG_ROWS], acc[QG_ROWS][4];
 #pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            const QuantOut qo = quantize_elem(wc[c], s, b, d.qn, d.qp);
-            const float dwq_ds = qo.in_range ? qo.code - qo.w : qo.code;
-            ds = fmaf(g4[c], dwq_ds, ds);
-            db += qo.in_range ? 0.f : g4[c];
-            g4[c] = qo.in_range ? g4[c] : 0.f;
+          for (int q = 0; q < QG_ROWS; ++q) {
+            load4(W0 + row[q] * d.i + jc, w0[q]);
+            s[q] = scale[row[q] * G + grp];
+            b[q] = zero[row[q] * G + grp];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc[q][c] = 0.f;
           }
-          store4(dW + p * d.i + j0, g4);
-        }
+          if (LORA) {  // rank sums, k ascending
+            const T* ap = A + jc;
+#pragma unroll 8
+            for (int k = 0; k < d.r; ++k, ap += d.i) {
+              float a[4];
+              load4(ap, a);
 #pragma unroll
-        for (int k = 0; k < QG_KCHUNK; ++k) {
-          if (k < kn) {
+              for (int q = 0; q < QG_ROWS; ++q)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) acc[q][c] = lora_mac<T>(acc[q][c], b_lds[q][k], a[c]);
+            }
+          }
+#pragma unroll
+          for (int q = 0; q < QG_ROWS; ++q) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+              const float wc = LORA ? w0[q][c] + d.gamma * acc[q][c] : w0[q][c];
+              const QuantOut qo = quantize_elem(wc, s[q], b[q], d.qn, d.qp);
+              const float gv = active ? g4[q][c] : 0.f;
+              ds[q] = fmaf(gv, qo.in_range ? qo.code - qo.w : qo.code, ds[q]);
+              db[q] += qo.in_range ? 0.f : gv;
+              g4[q][c] = qo.in_range ? gv : 0.f;
+            }
+            if (LORA && active && p0 + q < d.o) store4(dW + row[q] * d.i + jc, g4[q]);
+          }
+        }
+        if (LORA) {
+          const T* ap = A + (int64_t)k0 * d.i + jc;
+#pragma unroll
+          for (int k = 0; k < QG_KCHUNK; ++k) {
             float a[4];
-            load4(A + (int64_t)(k0 + k) * d.i + j0, a);
+            load4(ap, a);
+            ap += k + 1 < kn ? d.i : 0;  // (ranks past the last repeat it: those sums are not stored)
 #pragma unroll
-            for (int c = 0; c < 4; ++c) dBacc[k] = fmaf(g4[c], a[c], dBacc[k]);
+            for (int q = 0; q < QG_ROWS; ++q)
+#pragma unroll
+              for (int c = 0; c < 4; ++c)
+                dBacc[q * QG_KCHUNK + k] = fmaf(active ? g4[q][c] : 0.f, a[c], dBacc[q * QG_KCHUNK + k]);
           }
         }
-      }
-      if (k0 == 0 && ++step_in_group == steps_per_group) {
-        step_in_group = 0;
-        const float ds_sum = wave_sum_width(ds, width);
-        const float db_sum = wave_sum_width(db, width);
-        if (active && (lane & (width - 1)) == 0) {
-          const int64_t q = j0 / d.g;
-          dscale[p * G + q] = d.accumulate ? dscale[p * G + q] + ds_sum : ds_sum;
-          dzero[p * G + q] = d.accumulate ? dzero[p * G + q] + db_sum : db_sum;
+        if (k0 == 0 && (d.g <= 256 || base + 256 >= u0 + unit)) {  // the end of the lanes' groups
+#pragma unroll
+          for (int q = 0; q < QG_ROWS; ++q) {
+            const float ds_sum = wave_sum_width(ds[q], width), db_sum = wave_sum_width(db[q], width);
+            if (active && (lane & (width - 1)) == 0 && p0 + q < d.o) {
+              const int64_t at = row[q] * G + j0 / d.g;
+              dscale[at] = d.accumulate ? dscale[at] + ds_sum : ds_sum;
+              dzero[at] = d.accumulate ? dzero[at] + db_sum : db_sum;
+            }
+            ds[q] = 0.f;
+            db[q] = 0.f;
+          }
         }
-        ds = 0.f;
-        db = 0.f;
       }
     }
-#pragma unroll
-    for (int k = 0; k < QG_KCHUNK; ++k) {
-      const float tot = wave_sum_width(dBacc[k], 64);
-      if (lane == 0 && k < kn) {
-        const float v = d.gamma * tot;
-        dB[p * d.r + k0 + k] = d.accumulate ? dB[p * d.r + k0 + k] + v : v;
+    if (LORA) {
+      dB_sums[wave][lane] = wave_sum_scatter(dBacc, lane);
+      __syncthreads();
+      if (wave == 0) {
+        const int q = lane / QG_KCHUNK, k = lane % QG_KCHUNK;
+        if (k < kn && p0 + q < d.o) {
+          const float v = d.gamma * (((dB_sums[0][lane] + dB_sums[1][lane]) + dB_sums[2][lane]) + dB_sums[3][lane]);
+          float* dst = dB + (p0 + q) * d.r + k0 + k;
+          *dst = d.accumulate ? *dst + v : v;
+        }
       }
+      __syncthreads();
     }
   }
 }
@@ -196,9 +261,13 @@ template <class T>
 void launch_quant_grads(const LayerDims& d, const T* W0, const T* A, const T* B, const float* scale,
                         const float* zero, float* dWq_inout, float* dscale, float* dzero, float* dB,
                         hipStream_t stream) {
-  dim3 grid((unsigned)((d.o + 3) / 4));
-  hipLaunchKernelGGL(quant_grads_kernel<T>, grid, dim3(256), 0, stream, d, W0, A, B, scale, zero, dWq_inout, dscale,
-                     dzero, dB);
+  dim3 grid((unsigned)((d.o + QG_ROWS - 1) / QG_ROWS));
+  if (dB)
+    hipLaunchKernelGGL((quant_grads_kernel<T, true>), grid, dim3(256), 0, stream, d, W0, A, B, scale, zero, dWq_inout,
+                       dscale, dzero, dB);
+  else
+    hipLaunchKernelGGL((quant_grads_kernel<T, false>), grid, dim3(256), 0, stream, d, W0, A, B, scale, zero, dWq_inout,
+                       dscale, dzero, dB);
 }
 
 template void launch_quant_grads<float>(const LayerDims&, const float*, const float*, const float*, const float*,
