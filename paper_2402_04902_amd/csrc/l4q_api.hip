@@ -225,6 +225,13 @@ void gemm_nt(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, int64_t
   l4q::launch_gemm_bf16_nt(A, lda, B, ldb, M, N, K, K_algorithmic, C, ldc, stream, splitk);
 }
 
+// The same with the QAT-LoRA layer's LoRA term added to the product.
+void gemm_nt_rank(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t M, int64_t N, int64_t K, int64_t K_algorithmic,
+                  bf16_t* C, const l4q::RankTerm& term, hipStream_t stream) {
+  Timed t(stream, kKindGemm, 2.0 * (double)M * (double)N * (double)(K_algorithmic + term.r));
+  l4q::launch_gemm_bf16_nt_rank(A, lda, B, M, N, K, K_algorithmic, C, N, term, stream);
+}
+
 // The fused weight-gradient kernel is a GEMM launch too: time it the same way.
 void dw_fused(const LayerDims& d, const BwdWs& w, const bf16_t* dY, const bf16_t* X, const bf16_t* A, float* dscale,
               float* dzero, hipStream_t stream) {
@@ -558,9 +565,9 @@ int l4q_qatlora_forward(const l4q_desc* desc, const void* X, const void* W0, con
     mq.wq = wq;
     mq.ld_wq = w.ipad;
     l4q::launch_merge_quant<bf16_t>(dq, (const bf16_t*)W0, (const bf16_t*)A, (const bf16_t*)B, scale, zero, mq, stream);
-    gemm_nt((const bf16_t*)X, d.i, wq, w.ipad, d.T, d.o, w.ipad, d.i, (bf16_t*)Y, d.o, stream);
-    l4q::launch_lora_down<bf16_t>((const bf16_t*)X, d.T, d.i, (const bf16_t*)A, d.r, false, w.xa, stream);
-    l4q::launch_lora_up<bf16_t>((bf16_t*)Y, d.T, d.o, w.xa, (const bf16_t*)B, d.r, true, d.gamma, stream);
+    l4q::launch_lora_down((const bf16_t*)X, d.T, d.i, (const bf16_t*)A, d.r, w.xa, stream);
+    gemm_nt_rank((const bf16_t*)X, d.i, wq, d.T, d.o, w.ipad, d.i, (bf16_t*)Y, {w.xa, (const bf16_t*)B, d.r, d.gamma, true},
+                 stream);
   } else {
     float* wq = static_cast<float*>(w.wq);
     l4q::MergeQuantOut<float> mq;
@@ -568,8 +575,8 @@ int l4q_qatlora_forward(const l4q_desc* desc, const void* X, const void* W0, con
     mq.ld_wq = d.i;
     l4q::launch_merge_quant<float>(dq, (const float*)W0, (const float*)A, (const float*)B, scale, zero, mq, stream);
     l4q::launch_sgemm((const float*)X, d.i, 1, wq, 1, d.i, (float*)Y, d.o, d.T, d.o, d.i, 1.f, stream);
-    l4q::launch_lora_down<float>((const float*)X, d.T, d.i, (const float*)A, d.r, false, w.xa, stream);
-    l4q::launch_lora_up<float>((float*)Y, d.T, d.o, w.xa, (const float*)B, d.r, true, d.gamma, stream);
+    l4q::launch_sgemm((const float*)X, d.i, 1, (const float*)A, 1, d.i, w.xa, d.r, d.T, d.r, d.i, 1.f, stream);
+    l4q::launch_sgemm(w.xa, d.r, 1, (const float*)B, 1, d.r, (float*)Y, d.o, d.T, d.o, d.r, d.gamma, stream, true);
   }
   return launch_status();
 }
@@ -598,13 +605,14 @@ int l4q_qatlora_backward(const l4q_desc* desc, const void* X, const void* dY, co
     mq.wqT = w.wqT;
     mq.ld_wqT = w.opad;
     l4q::launch_merge_quant<bf16_t>(dq, W0b, Ab, Bb, scale, zero, mq, stream);
-    gemm_nt(dYb, d.o, w.wqT, w.opad, d.T, d.i, w.opad, d.o, (bf16_t*)dX, d.i, stream);
-    l4q::launch_lora_down<bf16_t>(dYb, d.T, d.o, Bb, d.r, true, w.dyb, stream);
-    l4q::launch_lora_up<bf16_t>((bf16_t*)dX, d.T, d.i, w.dyb, Ab, d.r, false, d.gamma, stream);
+    bf16_t* bT = (bf16_t*)w.part;  // B^T [r, o]: `part` (at least 4 r o bytes) is not in use yet
+    l4q::launch_transpose_small(Bb, d.o, d.r, bT, stream);
+    l4q::launch_lora_down(dYb, d.T, d.o, bT, d.r, w.dyb, stream);
+    gemm_nt_rank(dYb, d.o, w.wqT, d.T, d.i, w.opad, d.o, (bf16_t*)dX, {w.dyb, Ab, d.r, d.gamma, false}, stream);
     // the weight gradient is materialised: scale and zero are updated from it
     l4q::launch_gemm_bf16_kmajor_f32(dYb, d.o, Xb, d.i, d.o, d.i, d.T, w.dwq, d.i, stream);
     l4q::launch_quant_grads<bf16_t>(dq, W0b, Ab, Bb, scale, zero, w.dwq, dscale, dzero, nullptr, stream);
-    l4q::launch_lora_down<bf16_t>(Xb, d.T, d.i, Ab, d.r, false, w.xa, stream);
+    l4q::launch_lora_down(Xb, d.T, d.i, Ab, d.r, w.xa, stream);
     l4q::launch_tn<bf16_t, float>(w.dyb, Xb, d.T, d.i, d.r, false, w.part, d.gamma, dA, d.accumulate, stream);
     l4q::launch_tn<bf16_t, float>(w.xa, dYb, d.T, d.o, d.r, true, w.part, d.gamma, dB, d.accumulate, stream);
   } else {
@@ -615,11 +623,11 @@ int l4q_qatlora_backward(const l4q_desc* desc, const void* X, const void* dY, co
     mq.ld_wq = d.i;
     l4q::launch_merge_quant<float>(dq, W0f, Af, Bf, scale, zero, mq, stream);
     l4q::launch_sgemm(dYf, d.o, 1, w.wq32, d.i, 1, (float*)dX, d.i, d.T, d.i, d.o, 1.f, stream);
-    l4q::launch_lora_down<float>(dYf, d.T, d.o, Bf, d.r, true, w.dyb, stream);
-    l4q::launch_lora_up<float>((float*)dX, d.T, d.i, w.dyb, Af, d.r, false, d.gamma, stream);
+    l4q::launch_sgemm(dYf, d.o, 1, Bf, d.r, 1, w.dyb, d.r, d.T, d.r, d.o, 1.f, stream);
+    l4q::launch_sgemm(w.dyb, d.r, 1, Af, d.i, 1, (float*)dX, d.i, d.T, d.i, d.r, d.gamma, stream, true);
     l4q::launch_sgemm(dYf, 1, d.o, Xf, d.i, 1, w.dwq, d.i, d.o, d.i, d.T, 1.f, stream);
     l4q::launch_quant_grads<float>(dq, W0f, Af, Bf, scale, zero, w.dwq, dscale, dzero, nullptr, stream);
-    l4q::launch_lora_down<float>(Xf, d.T, d.i, Af, d.r, false, w.xa, stream);
+    l4q::launch_sgemm(Xf, d.i, 1, Af, 1, d.i, w.xa, d.r, d.T, d.r, d.i, 1.f, stream);
     l4q::launch_tn<float, float>(w.dyb, Xf, d.T, d.i, d.r, false, w.part, d.gamma, dA, d.accumulate, stream);
     l4q::launch_tn<float, float>(w.xa, dYf, d.T, d.o, d.r, true, w.part, d.gamma, dB, d.accumulate, stream);
   }

@@ -75,11 +75,81 @@ __device__ __forceinline__ void store_tile(gemm::Accum<T>& acc, int M, int N, vo
   }
 }
 
-// One macro tile: main loop, then the store epilogue.
-template <class T, bool OUT_BF16, bool A_KM, bool B_KM, bool MASK_A_K, bool B_BLK>
+// Adds gamma U . M^T (see RankTerm) to the tile's accumulators, operands straight from memory: gamma U is binary32 and
+// goes through the bfloat16 matrix op as the exact sum of three bfloat16 parts (8 significand bits each), so the product
+// is what binary32 operands would give.  At most 3 r / 16 matrix ops per accumulator tile against K / 16 of the main loop.
+template <class T>
+__device__ __forceinline__ void add_rank_term(gemm::Accum<T>& acc, const RankTerm& t, int M, int N, int m0, int n0) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  typedef gemm::bf16x8_t bf16x8_t;
+  const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int mw = m0 + (wave / T::WAVES_N) * T::WTM + l32, nw = n0 + (wave % T::WAVES_N) * T::WTN + l32;
+#pragma unroll 1
+  for (int k0 = 0; k0 < t.r; k0 += 16) {
+    const int kb = k0 + half * 8;
+    bf16x8_t fb[T::TN];
+#pragma unroll
+    for (int b = 0; b < T::TN; ++b) {
+      const int n = nw + b * 32 < N ? nw + b * 32 : N - 1;  // (columns and rows past the matrix are not stored)
+      if (t.n_by_r && (t.r & 7) == 0) {
+        const uint4 v = *reinterpret_cast<const uint4*>(t.M + (int64_t)n * t.r + (kb < t.r ? kb : 0));
+        fb[b] = __builtin_bit_cast(bf16x8_t, kb < t.r ? v : make_uint4(0, 0, 0, 0));
+      } else {
+        union { bf16_t h[8]; bf16x8_t v; } f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int k = kb + e < t.r ? kb + e : 0;
+          const bf16_t v = t.n_by_r ? t.M[(int64_t)n * t.r + k] : t.M[(int64_t)k * N + n];
+          f.h[e] = kb + e < t.r ? v : (bf16_t)0;
+        }
+        fb[b] = f.v;
+      }
+    }
+    float u[T::TM][8];  // all rows requested before the first is used
+#pragma unroll
+    for (int a = 0; a < T::TM; ++a) {
+      const int m = mw + a * 32 < M ? mw + a * 32 : M - 1;
+      const float* up = t.U + (int64_t)m * t.r;
+      if ((t.r & 7) == 0) {  // 16-byte rows, and a lane's 8 ranks are all inside or all outside
+        load4(up + (kb < t.r ? kb : 0), *reinterpret_cast<float(*)[4]>(&u[a][0]));
+        load4(up + (kb < t.r ? kb + 4 : 0), *reinterpret_cast<float(*)[4]>(&u[a][4]));
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) u[a][e] = up[kb + e < t.r ? kb + e : 0];
+      }
+    }
+#pragma unroll
+    for (int a = 0; a < T::TM; ++a) {
+      union { bf16_t h[8]; bf16x8_t v; } part[3];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        float x = kb + e < t.r ? t.gamma * u[a][e] : 0.f;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+          const bf16_t hi = f32_to_bf16(x);
+          part[q].h[e] = hi;
+          const float back = bf16_to_f32(hi);
+          x = fabsf(back) <= 3.4028235e38f ? x - back : 0.f;  // exact; an infinity has no remainder
+        }
+      }
+#pragma unroll
+      for (int q = 2; q >= 0; --q)
+#pragma unroll
+        for (int b = 0; b < T::TN; ++b)
+          acc.v[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[b], part[q].v, acc.v[a][b], 0, 0, 0);
+    }
+  }
+#endif
+}
+
+// One macro tile: main loop, then the store epilogue.  `term` (TERM): added before the main loop, while nothing else
+// of the tile is in registers.
+template <class T, bool OUT_BF16, bool A_KM, bool B_KM, bool MASK_A_K, bool B_BLK, bool TERM = false>
 __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ B,
                                           int64_t ldb, int M, int N, int K, int K_a, void* __restrict__ Cout,
-                                          int64_t ldc, int m0, int n0, unsigned char* lds) {
+                                          int64_t ldc, int m0, int n0, unsigned char* lds,
+                                          const RankTerm& term = RankTerm()) {
   gemm::Accum<T> acc;
 #pragma unroll
   for (int a = 0; a < T::TM; ++a)
@@ -87,6 +157,7 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int64_t 
     for (int b = 0; b < T::TN; ++b)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc.v[a][b][e] = 0.f;
+  if constexpr (TERM) add_rank_term<T>(acc, term, M, N, m0, n0);
   gemm::mainloop<T, A_KM, B_KM, gemm::NoTailLoads, MASK_A_K, B_BLK>(A, lda, B, ldb, M, N, K, m0, n0, lds, acc,
                                                                    gemm::NoTailLoads(), K_a);
   store_tile<T, OUT_BF16, T::LDS_BYTES>(acc, M, N, Cout, ldc, m0, n0, lds);
@@ -102,6 +173,19 @@ __global__ __launch_bounds__(T::NT) void gemm_bf16_nt_fast_kernel(const bf16_t* 
   gemm::tile_of_block(blockIdx.x, tiles_m, tiles_n, tile_m, tile_n);
   gemm_tile<T, OUT_BF16, A_KM, B_KM, MASK_A_K, B_BLK>(A, lda, B, ldb, M, N, K, K_a, Cout, ldc, tile_m * T::BM,
                                                       tile_n * T::BN, lds);
+}
+
+// C = A . B^T + gamma U . M^T: the QAT-LoRA layer's product and its LoRA path in one pass over C.
+template <class T, bool MASK_A_K>
+__global__ __launch_bounds__(T::NT) void gemm_bf16_nt_rank_kernel(const bf16_t* __restrict__ A, int64_t lda,
+                                                                   const bf16_t* __restrict__ B, int M, int N, int K,
+                                                                   int K_a, bf16_t* __restrict__ C, int64_t ldc,
+                                                                   int tiles_m, int tiles_n, RankTerm term) {
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[T::LDS_BYTES];
+  int tile_m, tile_n;
+  gemm::tile_of_block(blockIdx.x, tiles_m, tiles_n, tile_m, tile_n);
+  gemm_tile<T, true, false, false, MASK_A_K, true, true>(A, lda, B, 0, M, N, K, K_a, C, ldc, tile_m * T::BM,
+                                                         tile_n * T::BN, lds, term);
 }
 
 // One (tile, k-slice) of a product with few tiles: slice blockIdx.y of gridDim.y takes a run of whole stage pairs of
@@ -264,6 +348,19 @@ void launch_gemm_bf16_nt(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t 
     hipLaunchKernelGGL((gemm_bf16_nt_fast_kernel<F, true, false, false, true, true>),
                        dim3((unsigned)(tiles_m * tiles_n)), dim3(F::NT), 0, stream, A, lda, B, ldb, (int)M, (int)N, (int)K,
                        (int)K_a, (void*)C, ldc, tiles_m, tiles_n);
+}
+
+void launch_gemm_bf16_nt_rank(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t M, int64_t N, int64_t K, int64_t K_a,
+                              bf16_t* C, int64_t ldc, const RankTerm& term, hipStream_t stream) {
+  typedef gemm::Tile<256, 256, 32, 5, true, 4> F;
+  const int tiles_m = (int)((M + F::BM - 1) / F::BM), tiles_n = (int)((N + F::BN - 1) / F::BN);
+  const dim3 grid((unsigned)(tiles_m * tiles_n));
+  if (K_a == K)
+    hipLaunchKernelGGL((gemm_bf16_nt_rank_kernel<F, false>), grid, dim3(F::NT), 0, stream, A, lda, B, (int)M, (int)N, (int)K,
+                       (int)K_a, C, ldc, tiles_m, tiles_n, term);
+  else
+    hipLaunchKernelGGL((gemm_bf16_nt_rank_kernel<F, true>), grid, dim3(F::NT), 0, stream, A, lda, B, (int)M, (int)N, (int)K,
+                       (int)K_a, C, ldc, tiles_m, tiles_n, term);
 }
 
 void launch_gemm_bf16_kmajor_f32(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, int64_t M, int64_t N,

@@ -82,6 +82,18 @@ void launch_gemm_bf16_nt(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t 
                          int64_t K, int64_t K_a, bf16_t* C, int64_t ldc, hipStream_t stream,
                          float* partial = nullptr);
 
+// The same product in one pass with a term of rank r added before the rounding to bfloat16: C += gamma U . M^T, U [M, r]
+// binary32, M bfloat16 as [N, r] (n_by_r) or [r, N].
+struct RankTerm {
+  const float* U = nullptr;
+  const bf16_t* M = nullptr;
+  int r = 0;
+  float gamma = 0.f;
+  bool n_by_r = false;
+};
+void launch_gemm_bf16_nt_rank(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t M, int64_t N, int64_t K, int64_t K_a,
+                              bf16_t* C, int64_t ldc, const RankTerm& term, hipStream_t stream);
+
 // ---- matrix-core-only probe: `workgroups` x 4 waves x `iterations` x 16 MFMA 32x32x16 on fragments taken from the
 // first 64 KiB of `data`; sink [workgroups * 256] floats.  Returns the FLOPs the launch performs. ----
 double launch_mfma_probe(const bf16_t* data, int iterations, int workgroups, float* sink, hipStream_t stream);
@@ -157,14 +169,11 @@ void dw_masked_product_slices(const LayerDims& d, int* slices_a, int* slices_b);
 void launch_dw_masked_products(const LayerDims& d, const bf16_t* dWm, const bf16_t* A, const bf16_t* B, float* rawA,
                                float* rawB, hipStream_t stream);
 
-// ---- rank-r side products of the QAT-LoRA layer (Sec. 3.1): U binary32 [T, r]; the small matrix M is read as
-// [r, n] (A) or, with m_is_n_by_r, as [n, r] (B) ----
-template <class S>
-void launch_lora_down(const S* Xs, int64_t T, int64_t n, const S* M, int r, bool m_is_n_by_r, float* U,
-                      hipStream_t stream);                    // U = Xs . M^T  (sum over n)
-template <class S>
-void launch_lora_up(S* Out, int64_t T, int64_t n, const float* U, const S* M, int r, bool m_is_n_by_r, float gamma,
-                    hipStream_t stream);                      // Out += gamma U . M
+// ---- rank-r side products of the QAT-LoRA layer (Sec. 3.1) ----
+// U [T, r] (binary32) = Xs [T, n] . M [r, n]^T, n % 8 == 0
+void launch_lora_down(const bf16_t* Xs, int64_t T, int64_t n, const bf16_t* M, int r, float* U, hipStream_t stream);
+// out [r, n] = in [n, r]^T
+void launch_transpose_small(const bf16_t* in, int64_t n, int r, bf16_t* out, hipStream_t stream);
 // out = gamma * sum_t U[t,:]^T Xs[t,:] (U [T, r]) as [r, n], or as [n, r] with out_n_by_r, in two passes of fixed summation
 // order; partial: lora_tn_blocks(T) * r * n floats.  Also dA = gamma * B^T . (m * dWq) of the unfused backward.
 int64_t lora_tn_blocks(int64_t T);  // row blocks of the partial sums

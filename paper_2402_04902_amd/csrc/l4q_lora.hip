@@ -1,12 +1,12 @@
 // Rank-r side products of the QAT-LoRA layer (Sec. 3.1; Eq. lora_forward / lora_backward): the LoRA path kept
 // next to the quantized weight instead of being merged into it.
 //
-//   down   U[T,r]   = Xs[T,n] . M            M = A^T (U = X A^T)  or  M = B (U = dY B)
-//   up     Out[T,n] = Out + gamma U[T,r] . M  M = B^T (Y += gamma (X A^T) B^T)  or  M = A (dX += gamma (dY B) A)
+//   down   U[T,r]   = Xs[T,n] . M^T           U = X A^T, or U = dY B with B transposed first (bfloat16 operands; the
+//                                             binary32 layer uses the binary32 GEMM)
+//   up     Out[T,n] += gamma U[T,r] . M       inside the main product (RankTerm, l4q_gemm.hip), or the binary32 GEMM
 //   tn     G[r,n]   = sum_t U[t,:]^T Xs[t,:]  per block of 128 tokens, summed in fixed order by reduce_partials_kernel
 //                                             (dA = gamma (dY B)^T X,  dB^T = gamma (X A^T)^T dY)
-// All three stream their large operand once per chunk of 16 ranks and are bound by HBM; U is binary32 and
-// accumulation is binary32.  The small matrix is read either as [r, n] (rank-major, A) or as [n, r] (B).
+// U is binary32 and accumulation is binary32.
 #include "l4q_device.h"
 #include "l4q_kernels.h"
 
@@ -14,111 +14,83 @@ namespace l4q {
 
 namespace {
 
-constexpr int LR_KC = 16;  // ranks per pass
+constexpr int LR_KC = 16;  // ranks per matrix op
 
-// element (k, j) of the small matrix: rank-major [r, n] or [n, r]
-template <class S, bool NR>
-__device__ __forceinline__ float small_at(const S* __restrict__ M, int64_t n, int r, int k, int64_t j) {
-  return load1(NR ? M + j * r + k : M + (int64_t)k * n + j);
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+// U[t, k] = sum_j Xs[t, j] M[k, j].  Bound: Xs read once.  A workgroup takes 16 rows of Xs and NC x 16 ranks; its 16 waves
+// deal the 32-wide k-steps of v_mfma_f32_16x16x32_bf16 out among themselves (8 rows' worth of waves is all a few thousand
+// tokens give a chip of 256 compute units), four steps of loads in flight each, and their sums meet in LDS, added in wave
+// order.  2048 x 4096 at 16 ranks: 9.1 us; a wave per 4 rows with vector multiply-adds, which this replaces, 81 us
+// (127 us with B read as [n, r]).
+constexpr int LD_WAVES = 16;
+constexpr int LD_AHEAD = 4;
+
+template <int NC>
+__global__ __launch_bounds__(64 * LD_WAVES) void lora_down_kernel(const bf16_t* __restrict__ Xs, int64_t T, int64_t n,
+                                                                  const bf16_t* __restrict__ M, int r,
+                                                                  float* __restrict__ U) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __shared__ float sums[LD_WAVES][16][16 * NC + 1];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c16 = lane & 15, h = lane >> 4;
+  const int64_t t0 = (int64_t)blockIdx.x * 16;
+  const int k0 = blockIdx.y * (16 * NC);
+  // rows past T and ranks past r repeat the last one; they are not stored
+  const bf16_t* xp = Xs + (t0 + c16 < T ? t0 + c16 : T - 1) * n;
+  const bf16_t* mp[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) mp[c] = M + (int64_t)(k0 + c * 16 + c16 < r ? k0 + c * 16 + c16 : r - 1) * n;
+  f32x4_t acc[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) acc[c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int64_t j0 = wave * 32; j0 < n; j0 += LD_WAVES * LD_AHEAD * 32) {
+    bf16x8_t fx[LD_AHEAD], fm[LD_AHEAD][NC];
+    const bf16x8_t zero = {};
+#pragma unroll
+    for (int u = 0; u < LD_AHEAD; ++u) {
+      const int64_t j = j0 + u * (LD_WAVES * 32) + h * 8;
+      const bool live = j < n;  // (n % 8 == 0: a lane's 8 values are all inside or all outside)
+      const bf16x8_t x = *reinterpret_cast<const bf16x8_t*>(xp + (live ? j : 0));
+      fx[u] = live ? x : zero;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const bf16x8_t m = *reinterpret_cast<const bf16x8_t*>(mp[c] + (live ? j : 0));
+        fm[u][c] = live ? m : zero;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < LD_AHEAD; ++u)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) acc[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fx[u], fm[u][c], acc[c], 0, 0, 0);
+  }
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sums[wave][4 * h + e][c * 16 + c16] = acc[c][e];
+  __syncthreads();
+  for (int q = tid; q < 256 * NC; q += 64 * LD_WAVES) {
+    const int row = q / (16 * NC), k = q % (16 * NC);
+    float v = sums[0][row][k];
+#pragma unroll
+    for (int w = 1; w < LD_WAVES; ++w) v += sums[w][row][k];
+    if (t0 + row < T && k0 + k < r) U[(t0 + row) * r + k0 + k] = v;
+  }
+#endif
 }
 
-// A wave (one per workgroup) takes LR_RB token rows, so that what it reads of the small matrix is used LR_RB times:
-// U[t, k0 .. k0 + 15] = sum_j Xs[t, j] M(k, j).  Rank-major M (A, n % 4 == 0): a lane walks 4 consecutive columns
-// with vector loads.  M as [n, r] (B): a lane walks single columns and reads that column's ranks contiguously.
-constexpr int LR_RB = 4;
-
-template <class S, bool NR>
-__global__ __launch_bounds__(64) void lora_down_kernel(const S* __restrict__ Xs, int64_t T, int64_t n,
-                                                         const S* __restrict__ M, int r, float* __restrict__ U) {
+// out[k][j] = in[j][k]: 64 rows of `in` per workgroup through LDS
+__global__ __launch_bounds__(256) void transpose_small_kernel(const bf16_t* __restrict__ in, int64_t n, int r,
+                                                               bf16_t* __restrict__ out) {
+  __shared__ bf16_t tile[64][256 + 2];  // (rank <= 256)
+  const int64_t j0 = (int64_t)blockIdx.x * 64;
+  const int rows = n - j0 < 64 ? (int)(n - j0) : 64;
+  for (int q = threadIdx.x; q < rows * r; q += 256) tile[q / r][q % r] = in[j0 * r + q];
+  __syncthreads();
   const int lane = threadIdx.x & 63;
-  const int64_t t0 = (int64_t)blockIdx.x * LR_RB;  // one wave per block
-  if (t0 >= T) return;
-  const S* xrow[LR_RB];
-#pragma unroll
-  for (int q = 0; q < LR_RB; ++q) xrow[q] = Xs + (t0 + q < T ? t0 + q : T - 1) * n;
-  for (int k0 = 0; k0 < r; k0 += LR_KC) {
-    float acc[LR_RB][LR_KC];
-#pragma unroll
-    for (int q = 0; q < LR_RB; ++q)
-#pragma unroll
-      for (int k = 0; k < LR_KC; ++k) acc[q][k] = 0.f;
-    if (!NR) {
-      for (int64_t j = (int64_t)lane * 4; j < n; j += 256) {
-        float x[LR_RB][4];
-#pragma unroll
-        for (int q = 0; q < LR_RB; ++q) load4(xrow[q] + j, x[q]);
-#pragma unroll
-        for (int k = 0; k < LR_KC; ++k) {
-          float a[4];
-          load4(M + (int64_t)(k0 + k < r ? k0 + k : r - 1) * n + j, a);
-          if (k0 + k >= r) a[0] = a[1] = a[2] = a[3] = 0.f;
-#pragma unroll
-          for (int q = 0; q < LR_RB; ++q)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) acc[q][k] = fmaf(x[q][c], a[c], acc[q][k]);
-        }
-      }
-    } else {
-      for (int64_t j = lane; j < n; j += 64) {
-        float m[LR_KC];
-#pragma unroll
-        for (int k = 0; k < LR_KC; ++k) m[k] = k0 + k < r ? load1(M + j * r + k0 + k) : 0.f;
-#pragma unroll
-        for (int q = 0; q < LR_RB; ++q) {
-          const float x = load1(xrow[q] + j);
-#pragma unroll
-          for (int k = 0; k < LR_KC; ++k) acc[q][k] = fmaf(x, m[k], acc[q][k]);
-        }
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < LR_RB; ++q)
-#pragma unroll
-      for (int k = 0; k < LR_KC; ++k) {
-        const float v = wave_sum_width(acc[q][k], 64);
-        if (lane == 0 && k0 + k < r && t0 + q < T) U[(t0 + q) * r + k0 + k] = v;
-      }
-  }
-}
-
-template <class S> __device__ __forceinline__ float to_f32(S v);
-template <> __device__ __forceinline__ float to_f32<float>(float v) { return v; }
-template <> __device__ __forceinline__ float to_f32<bf16_t>(bf16_t v) { return bf16_to_f32(v); }
-__device__ __forceinline__ void store1(float* p, float v) { *p = v; }
-__device__ __forceinline__ void store1(bf16_t* p, float v) { *p = f32_to_bf16(v); }
-
-// Out[t, j] += gamma * sum_k U[t, k] M(k, j).  A thread owns one column and LR_UT consecutive tokens: its column
-// of the small matrix is read once per rank chunk and stays in registers; U[t, :] is uniform over the block.
-constexpr int LR_UT = 16;
-
-template <class S, bool NR>
-__global__ __launch_bounds__(256) void lora_up_kernel(S* __restrict__ Out, int64_t T, int64_t n,
-                                                       const float* __restrict__ U, const S* __restrict__ M, int r,
-                                                       float gamma) {
-  const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t t0 = (int64_t)blockIdx.y * LR_UT;
-  if (j >= n) return;
-  float acc[LR_UT];
-#pragma unroll
-  for (int q = 0; q < LR_UT; ++q) acc[q] = 0.f;
-  for (int k0 = 0; k0 < r; k0 += LR_KC) {
-    float m[LR_KC];
-#pragma unroll
-    for (int k = 0; k < LR_KC; ++k) m[k] = k0 + k < r ? small_at<S, NR>(M, n, r, k0 + k, j) : 0.f;
-#pragma unroll
-    for (int q = 0; q < LR_UT; ++q) {
-      const float* u = U + (t0 + q < T ? t0 + q : T - 1) * r + k0;  // uniform over the block
-#pragma unroll
-      for (int k = 0; k < LR_KC; ++k)
-        if (k0 + k < r) acc[q] = fmaf(u[k], m[k], acc[q]);
-    }
-  }
-#pragma unroll
-  for (int q = 0; q < LR_UT; ++q)
-    if (t0 + q < T) {
-      S* dst = Out + (t0 + q) * n + j;
-      store1(dst, to_f32<S>(*dst) + gamma * acc[q]);
-    }
+  if (lane < rows)
+    for (int k = threadIdx.x >> 6; k < r; k += 4) out[(int64_t)k * n + j0 + lane] = tile[lane][k];
 }
 
 // part[tb][k][j] (or [tb][j][k] when NR) = sum over the 128 rows of block tb of U[t, k] Xs[t, j].
@@ -156,7 +128,6 @@ template <class S, class UT, bool NR>
 __global__ __launch_bounds__(256) void tn_partial_kernel(const UT* __restrict__ U, const S* __restrict__ Xs, int64_t T,
                                                           int64_t n, int r, float* __restrict__ part) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  typedef float f32x4_t __attribute__((ext_vector_type(4)));
   typedef Row4<float>::vec_t vec_t;
   constexpr int STEPS = LR_TB / 4 / 4;  // groups of 4 rows per wave
   __shared__ __align__(16) float sums[4][LR_KC][64];
@@ -227,20 +198,19 @@ __global__ __launch_bounds__(256) void tn_partial_kernel(const UT* __restrict__ 
 
 }  // namespace
 
-template <class S>
-void launch_lora_down(const S* Xs, int64_t T, int64_t n, const S* M, int r, bool m_is_n_by_r, float* U,
-                      hipStream_t stream) {
-  dim3 grid((unsigned)((T + LR_RB - 1) / LR_RB));
-  if (m_is_n_by_r) hipLaunchKernelGGL((lora_down_kernel<S, true>), grid, dim3(64), 0, stream, Xs, T, n, M, r, U);
-  else hipLaunchKernelGGL((lora_down_kernel<S, false>), grid, dim3(64), 0, stream, Xs, T, n, M, r, U);
+void launch_lora_down(const bf16_t* Xs, int64_t T, int64_t n, const bf16_t* M, int r, float* U, hipStream_t stream) {
+  const unsigned tiles = (unsigned)((T + 15) / 16);
+  if (r <= 16)
+    hipLaunchKernelGGL(lora_down_kernel<1>, dim3(tiles), dim3(64 * LD_WAVES), 0, stream, Xs, T, n, M, r, U);
+  else if (r <= 32)
+    hipLaunchKernelGGL(lora_down_kernel<2>, dim3(tiles), dim3(64 * LD_WAVES), 0, stream, Xs, T, n, M, r, U);
+  else
+    hipLaunchKernelGGL(lora_down_kernel<4>, dim3(tiles, (unsigned)((r + 63) / 64)), dim3(64 * LD_WAVES), 0, stream, Xs, T, n,
+                       M, r, U);
 }
 
-template <class S>
-void launch_lora_up(S* Out, int64_t T, int64_t n, const float* U, const S* M, int r, bool m_is_n_by_r, float gamma,
-                    hipStream_t stream) {
-  dim3 grid((unsigned)((n + 255) / 256), (unsigned)((T + LR_UT - 1) / LR_UT));
-  if (m_is_n_by_r) hipLaunchKernelGGL((lora_up_kernel<S, true>), grid, dim3(256), 0, stream, Out, T, n, U, M, r, gamma);
-  else hipLaunchKernelGGL((lora_up_kernel<S, false>), grid, dim3(256), 0, stream, Out, T, n, U, M, r, gamma);
+void launch_transpose_small(const bf16_t* in, int64_t n, int r, bf16_t* out, hipStream_t stream) {
+  hipLaunchKernelGGL(transpose_small_kernel, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, stream, in, n, r, out);
 }
 
 int64_t lora_tn_blocks(int64_t T) { return (T + LR_TB - 1) / LR_TB; }
@@ -255,10 +225,6 @@ void launch_tn(const UT* U, const S* Xs, int64_t T, int64_t n, int r, bool out_n
   launch_reduce_partials(partial, nb, (int64_t)r * n, gamma, out, accumulate, stream);
 }
 
-template void launch_lora_down<float>(const float*, int64_t, int64_t, const float*, int, bool, float*, hipStream_t);
-template void launch_lora_down<bf16_t>(const bf16_t*, int64_t, int64_t, const bf16_t*, int, bool, float*, hipStream_t);
-template void launch_lora_up<float>(float*, int64_t, int64_t, const float*, const float*, int, bool, float, hipStream_t);
-template void launch_lora_up<bf16_t>(bf16_t*, int64_t, int64_t, const float*, const bf16_t*, int, bool, float, hipStream_t);
 template void launch_tn<float, float>(const float*, const float*, int64_t, int64_t, int, bool, float*, float, float*, bool,
                                       hipStream_t);
 template void launch_tn<bf16_t, float>(const float*, const bf16_t*, int64_t, int64_t, int, bool, float*, float, float*,

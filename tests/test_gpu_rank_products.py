@@ -1,0 +1,36 @@
+"""Rank-r products at the edges of their kernels: ranks that end inside a matrix op of 16 and inside a group of 64, rows
+of Xs that end inside a k-step and inside a column block, token counts one off a block, in the QAT-LoRA layer (both
+dtypes) and in the unfused L4Q backward, against the fp64 oracle."""
+import pytest
+
+from paper_2402_04902_amd.inputs import DTYPE_BF16, DTYPE_F32, LayerSpec
+
+from test_gpu_parity import run_case
+from test_gpu_qatlora import _run
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,i,o,r,g,dtype", [
+    (1, 8, 8, 1, 8, DTYPE_BF16),
+    (129, 264, 72, 17, 8, DTYPE_BF16),
+    (127, 1032, 1048, 24, 8, DTYPE_BF16),
+    (255, 320, 136, 70, 64, DTYPE_BF16),
+    (300, 576, 264, 200, 64, DTYPE_BF16),
+    (1, 4, 1, 1, 4, DTYPE_F32),
+    (129, 68, 3, 17, 4, DTYPE_F32),
+    (257, 132, 67, 33, 4, DTYPE_F32),
+])
+def test_qatlora_rank_products(T, i, o, r, g, dtype):
+    _run(LayerSpec(f"ql_{T}x{i}x{o}_r{r}", T, i, o, r, 2.0 * r, 4, g, dtype), seed=T + r, accumulate=r % 2 == 1)
+
+
+@pytest.mark.parametrize("T,i,o,r,g,dtype", [
+    (40, 512, 133, 1, 512, DTYPE_F32),      # groups longer than a step of 256 columns, rows past a group of four
+    (40, 1028, 129, 19, 4, DTYPE_F32),      # five column units over four waves, ranks past a chunk of 16
+    (40, 260, 3, 40, 4, DTYPE_F32),
+    (40, 2048, 136, 20, 1024, DTYPE_BF16),  # groups the fused epilogue does not take
+    (40, 264, 8, 5, 8, DTYPE_BF16),
+])
+def test_unfused_gradients(T, i, o, r, g, dtype):
+    run_case(LayerSpec(f"uf_{T}x{i}x{o}_r{r}", T, i, o, r, 2.0 * r, 3, g, dtype), seed=T + r, shrink=0.7, flags=1)
