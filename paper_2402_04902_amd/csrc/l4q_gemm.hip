@@ -302,65 +302,109 @@ int device_compute_units() {
   return cached[dev];
 }
 
-// Slices of the k range for a product with few tiles: as many as put a workgroup on every compute unit, each at
-// least four stage pairs (256 k) long, at most 8, and no more than keep the partial tiles (slices x M x N x 4 bytes,
-// written and read once) within the size of operand B (N x K x 2 bytes).
-int gemm_nt_splitk_slices(int64_t M, int64_t N, int64_t K) {
-  typedef gemm::Tile<256, 256, 32, 5, true, 4> F;
-  const int64_t tiles = ((M + F::BM - 1) / F::BM) * ((N + F::BN - 1) / F::BN);
-  const int64_t cus = device_compute_units();
-  if (tiles <= 0 || 2 * tiles > cus) return 1;
-  const int64_t pairs = ((K + F::BK - 1) / F::BK + 1) / 2;
-  int64_t s = cus / tiles;
-  if (s > pairs / 4) s = pairs / 4;
-  if (s > 8) s = 8;
-  if (s > K / (2 * M)) s = K / (2 * M);
-  return s < 1 ? 1 : (int)s;
+namespace {
+
+// Macro tiles of the K-contiguous products.  Both load 32-k stages.
+//   NtFull   256 x 256, 8 waves (2 x 4, two per SIMD, 128 x 64 each): a second wave on the SIMD keeps the matrix pipe busy
+//            while the first waits for a barrier or for operands (1.5 % over 2 x 2); stages loaded in cache-line pairs
+//   NtHalf   128 x 256, 4 waves (64 x 128 each), ring of six stages: 4/7 of a full tile's time for half its work, for
+//            products whose full tiles leave compute units idle
+typedef gemm::Tile<256, 256, 32, 5, true, 4> NtFull;
+typedef gemm::Tile<128, 256, 32, 6, false, 2> NtHalf;
+
+template <class F> int64_t nt_tiles(int64_t M, int64_t N) {
+  return ((M + F::BM - 1) / F::BM) * ((N + F::BN - 1) / F::BN);
 }
+
+// One pass over k: which tile.  In us (full / half; number of full, half tiles on 256 compute units; M x N x K):
+//    86,  172   73 / 45    512 x 11008 x 4096        172,  344   79 / 95    1024 x 11008 x 4096
+//   128,  256   74 / 57   2048 x  4096 x 4096        192,  384   84 / 95    3000 x  4096 x 4096
+//   128,  256  186 / 142  2048 x  4096 x 11008       256,  512  100 / 111   4096 x  4096 x 4096
+//   344,  688  169 / 152  2048 x 11008 x 4096        688, 1376  271 / 309   4096 x 11008 x 4096
+// i.e. rounds of tiles over the units, a round of half tiles counting 4/7.
+bool nt_use_half(int64_t M, int64_t N) {
+  const int64_t cus = device_compute_units();
+  const int64_t full = (nt_tiles<NtFull>(M, N) + cus - 1) / cus, half = (nt_tiles<NtHalf>(M, N) + cus - 1) / cus;
+  return 4 * half < 7 * full;
+}
+
+}  // namespace
+
+// Slices of the k range for a product of few tiles (full tiles on at most half of the compute units; always half tiles
+// then): at most one (tile, slice) per compute unit, each at least four stage pairs (256 k) long, at most 8, no more than
+// keep the partial tiles (slices x M x N x 4 bytes, written and read once) within the size of operand B (N x K x 2
+// bytes), nor more than fit the slices of full tiles; of those the number with the least estimated time: 9 us per 1024 k
+// of a slice, and beyond one slice 6 us for the second launch and the partial tiles at 5 TB/s.  Estimated, measured (us):
+//   301 x 4096 x 4096    4: 23, 25   5: 23, 25   1: 36, 40     512 x 4096 x 11008  4: 44, 52   3: 48, 53   1: 97, 103
+//   512 x 4096 x 4096    3: 28, 29   4: 28, 30   2: 31, 33    1024 x 4096 x 4096   1: 36, 42   2: 37, 42
+// (256 x 256 tiles in as many slices as fill the chip took 35, 63, 38 and 54.)
+int gemm_nt_splitk_slices(int64_t M, int64_t N, int64_t K) {
+  const int64_t full = nt_tiles<NtFull>(M, N), half = nt_tiles<NtHalf>(M, N);
+  const int64_t cus = device_compute_units();
+  if (full <= 0 || 2 * full > cus) return 1;
+  const int64_t pairs = ((K + NtHalf::BK - 1) / NtHalf::BK + 1) / 2;
+  int64_t most = cus / full;
+  if (most > cus / half) most = cus / half;
+  if (most > pairs / 4) most = pairs / 4;
+  if (most > 8) most = 8;
+  if (most > K / (2 * M)) most = K / (2 * M);
+  int best = 1;
+  double best_us = 9.0 * (double)K / 1024.0;
+  for (int s = 2; s <= most; ++s) {
+    const double us = 9.0 * (double)K / 1024.0 / s + 6.0 + (double)s * (double)M * (double)N * 8.0 / 5e6;
+    if (us < best_us) {
+      best = s;
+      best_us = us;
+    }
+  }
+  return best;
+}
+
+namespace {
+
+// `f` with the tile type and whether rows of A need masking past K_a (an instance of its own, so that the usual shapes do
+// not pay for the selection)
+template <class Fn> void nt_dispatch(bool half, bool mask, Fn&& f) {
+  if (half && mask) f(NtHalf(), std::true_type());
+  else if (half) f(NtHalf(), std::false_type());
+  else if (mask) f(NtFull(), std::true_type());
+  else f(NtFull(), std::false_type());
+}
+
+}  // namespace
 
 void launch_gemm_bf16_nt(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, int64_t M, int64_t N,
                          int64_t K, int64_t K_a, bf16_t* C, int64_t ldc, hipStream_t stream, float* partial) {
-  // K-contiguous operands: stages loaded in cache-line pairs; 8 waves (2 x 4, two per SIMD, 128 x 64 each): a second
-  // wave on the SIMD keeps the matrix pipe busy while the first waits for a barrier or for operands (1.5 % over 2 x 2)
-  typedef gemm::Tile<256, 256, 32, 5, true, 4> F;
-  const int tiles_m = (int)((M + F::BM - 1) / F::BM), tiles_n = (int)((N + F::BN - 1) / F::BN);
   const int slices = partial ? gemm_nt_splitk_slices(M, N, K) : 1;
-  if (slices > 1) {
-    dim3 grid((unsigned)(tiles_m * tiles_n), (unsigned)slices);
-    if (K_a == K)
-      hipLaunchKernelGGL((gemm_bf16_nt_splitk_kernel<F, false, true>), grid, dim3(F::NT), 0, stream, A, lda, B, ldb, (int)M,
-                         (int)N, (int)K, (int)K_a, partial, tiles_m, tiles_n);
-    else
-      hipLaunchKernelGGL((gemm_bf16_nt_splitk_kernel<F, true, true>), grid, dim3(F::NT), 0, stream, A, lda, B, ldb, (int)M,
-                         (int)N, (int)K, (int)K_a, partial, tiles_m, tiles_n);
-    const int64_t quads = M * N / 4;
-    hipLaunchKernelGGL(splitk_sum_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream, partial, slices,
-                       M, N, C, ldc);
-    return;
-  }
-  // rows of A end at K_a: where that is short of the k-step, the chunks past it are masked (a second instance, so
-  // that the usual shapes do not pay for the selection)
-  if (K_a == K)
-    hipLaunchKernelGGL((gemm_bf16_nt_fast_kernel<F, true, false, false, false, true>),
-                       dim3((unsigned)(tiles_m * tiles_n)), dim3(F::NT), 0, stream, A, lda, B, ldb, (int)M, (int)N, (int)K,
-                       (int)K_a, (void*)C, ldc, tiles_m, tiles_n);
-  else
-    hipLaunchKernelGGL((gemm_bf16_nt_fast_kernel<F, true, false, false, true, true>),
-                       dim3((unsigned)(tiles_m * tiles_n)), dim3(F::NT), 0, stream, A, lda, B, ldb, (int)M, (int)N, (int)K,
-                       (int)K_a, (void*)C, ldc, tiles_m, tiles_n);
+  nt_dispatch(slices > 1 || nt_use_half(M, N), K_a != K, [&](auto tile, auto mask) {
+    typedef decltype(tile) F;
+    constexpr bool MASK = decltype(mask)::value;
+    const int tiles_m = (int)((M + F::BM - 1) / F::BM), tiles_n = (int)((N + F::BN - 1) / F::BN);
+    if (slices > 1) {
+      if constexpr (std::is_same<F, NtHalf>::value) {
+        hipLaunchKernelGGL((gemm_bf16_nt_splitk_kernel<F, MASK, true>),
+                           dim3((unsigned)(tiles_m * tiles_n), (unsigned)slices), dim3(F::NT), 0, stream, A, lda, B, ldb,
+                           (int)M, (int)N, (int)K, (int)K_a, partial, tiles_m, tiles_n);
+        const int64_t quads = M * N / 4;
+        hipLaunchKernelGGL(splitk_sum_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream, partial,
+                           slices, M, N, C, ldc);
+      }
+    } else {
+      hipLaunchKernelGGL((gemm_bf16_nt_fast_kernel<F, true, false, false, MASK, true>),
+                         dim3((unsigned)(tiles_m * tiles_n)), dim3(F::NT), 0, stream, A, lda, B, ldb, (int)M, (int)N,
+                         (int)K, (int)K_a, (void*)C, ldc, tiles_m, tiles_n);
+    }
+  });
 }
 
 void launch_gemm_bf16_nt_rank(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t M, int64_t N, int64_t K, int64_t K_a,
                               bf16_t* C, int64_t ldc, const RankTerm& term, hipStream_t stream) {
-  typedef gemm::Tile<256, 256, 32, 5, true, 4> F;
-  const int tiles_m = (int)((M + F::BM - 1) / F::BM), tiles_n = (int)((N + F::BN - 1) / F::BN);
-  const dim3 grid((unsigned)(tiles_m * tiles_n));
-  if (K_a == K)
-    hipLaunchKernelGGL((gemm_bf16_nt_rank_kernel<F, false>), grid, dim3(F::NT), 0, stream, A, lda, B, (int)M, (int)N, (int)K,
-                       (int)K_a, C, ldc, tiles_m, tiles_n, term);
-  else
-    hipLaunchKernelGGL((gemm_bf16_nt_rank_kernel<F, true>), grid, dim3(F::NT), 0, stream, A, lda, B, (int)M, (int)N, (int)K,
-                       (int)K_a, C, ldc, tiles_m, tiles_n, term);
+  nt_dispatch(nt_use_half(M, N), K_a != K, [&](auto tile, auto mask) {
+    typedef decltype(tile) F;
+    const int tiles_m = (int)((M + F::BM - 1) / F::BM), tiles_n = (int)((N + F::BN - 1) / F::BN);
+    hipLaunchKernelGGL((gemm_bf16_nt_rank_kernel<F, decltype(mask)::value>), dim3((unsigned)(tiles_m * tiles_n)),
+                       dim3(F::NT), 0, stream, A, lda, B, (int)M, (int)N, (int)K, (int)K_a, C, ldc, tiles_m, tiles_n, term);
+  });
 }
 
 void launch_gemm_bf16_kmajor_f32(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, int64_t M, int64_t N,

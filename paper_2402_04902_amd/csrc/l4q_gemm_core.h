@@ -139,7 +139,7 @@ struct TailLoads {
   unsigned stage_bytes;             // added once per tail stage
 };
 
-// MASK_A_K (paired loop only): operand A is valid for k < K_a only (K_a a multiple of 8, K - 32 < K_a <= K) and what
+// MASK_A_K (K-contiguous A): operand A is valid for k < K_a only (K_a a multiple of 8, K - 32 < K_a <= K) and what
 // follows a row in memory is the next row, not padding: the 16-byte chunks of the last stage that start at k >= K_a
 // get an out-of-range offset and read as zero, so that a NaN or Inf in row m + 1 cannot reach row m of the product
 // through 0 x Inf.
@@ -218,15 +218,30 @@ __device__ __forceinline__ void mainloop(const bf16_t* __restrict__ A, int64_t l
   if constexpr (A_KM) setup_km(km_off_a, T::TM, wm * T::WTM);
   if constexpr (B_KM) setup_km(km_off_b, T::TN, wn * T::WTN);
 
+  const int nk = (K + T::BK - 1) / T::BK;
+  unsigned voffA_last[MASK_A_K ? T::A_INSTR : 1];  // offsets of operand A in the last stage: chunks past K_a masked
+  if constexpr (MASK_A_K) {
+    static_assert(!A_KM, "masking by 16-byte chunks of k");
+#pragma unroll
+    for (int c = 0; c < T::A_INSTR; ++c) {
+      const int row = (wave * T::A_INSTR + c) * T::RPI + lane / T::CPR;
+      const int ch = (lane % T::CPR) ^ ((row / T::RW) % T::CPR);
+      voffA_last[c] = (nk - 1) * T::BK + ch * 8 < K_a ? voffA[c] : OOB_OFFSET;
+    }
+  }
+
   // part `part` of `nparts` of the loads of stage `stage` < nk into ring slot `slot`
   auto issue_loads = [&](int stage, int slot, int part, int nparts) {
     const unsigned ka = (unsigned)stage * stage_bytes_a, kb = (unsigned)stage * stage_bytes_b;
     unsigned char* base = lds + slot * T::STAGE;
 #pragma unroll
     for (int c = 0; c < T::A_INSTR; ++c)
-      if (c * nparts / T::A_INSTR == part)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrcA, (lds_ptr_t)(base + (wave * T::A_INSTR + c) * 1024), 16,
-                                                 voffA[c] + ka, 0, 0, 0);
+      if (c * nparts / T::A_INSTR == part) {
+        unsigned v = voffA[c];
+        if constexpr (MASK_A_K) v = stage == nk - 1 ? voffA_last[c] : v;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrcA, (lds_ptr_t)(base + (wave * T::A_INSTR + c) * 1024), 16, v + ka, 0,
+                                                 0, 0);
+      }
 #pragma unroll
     for (int c = 0; c < T::B_INSTR; ++c)
       if (c * nparts / T::B_INSTR == part)
@@ -293,7 +308,6 @@ __device__ __forceinline__ void mainloop(const bf16_t* __restrict__ A, int64_t l
         acc.v[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[set][b], fa[set][a], acc.v[a][b], 0, 0, 0);
   };
 
-  const int nk = (K + T::BK - 1) / T::BK;
   constexpr int LOADS = T::A_INSTR + T::B_INSTR;
   static_assert(T::A_INSTR % T::KK == 0 && T::B_INSTR % T::KK == 0, "loads are spread evenly over the k-steps");
   constexpr int LPK = LOADS / T::KK;                 // loads issued per k-step
@@ -303,7 +317,6 @@ __device__ __forceinline__ void mainloop(const bf16_t* __restrict__ A, int64_t l
   constexpr int EXTRA = NDA + NDB + LPK > NMF ? NDA + NDB + LPK - NMF : 0;  // reads that share a matrix op
   static_assert(2 * EXTRA <= NDA + NDB, "too many LDS reads per matrix op");
   static_assert(!Tail::ENABLED || !T::PAIR, "tail loads are wired into the non-paired loop");
-  static_assert(!MASK_A_K || T::PAIR, "k-masking of operand A is wired into the paired loop");
   if constexpr (T::PAIR) {
     // Paired loading for K-contiguous operands.  A stage takes 64 bytes of every operand row, half a 128-byte
     // cache line; when the second half is requested a stage later the line has already left the 32 KiB vector
@@ -315,15 +328,6 @@ __device__ __forceinline__ void mainloop(const bf16_t* __restrict__ A, int64_t l
     // Each pair is therefore issued two and a half stages before its first use.  An odd stage count is rounded up:
     // the extra stage is loaded as zeros.
     static_assert(!T::PAIR || (!A_KM && !B_KM && T::KK == 2), "paired loading is for K-contiguous operands");
-    unsigned voffA_last[MASK_A_K ? T::A_INSTR : 1];  // offsets of operand A in the last stage: chunks past K_a masked
-    if constexpr (MASK_A_K) {
-#pragma unroll
-      for (int c = 0; c < T::A_INSTR; ++c) {
-        const int row = (wave * T::A_INSTR + c) * T::RPI + lane / T::CPR;
-        const int ch = (lane % T::CPR) ^ ((row / T::RW) % T::CPR);
-        voffA_last[c] = (nk - 1) * T::BK + ch * 8 < K_a ? voffA[c] : OOB_OFFSET;
-      }
-    }
     auto issue_pair = [&](int stage0, int slot0, int slot1, int part) {
       const unsigned sb = part == 0 ? stage_bytes_a : stage_bytes_b;
       const unsigned k0 = stage0 < nk ? (unsigned)stage0 * sb : PAST_END_OFFSET;
