@@ -496,6 +496,12 @@ int l4q_export_packed(const l4q_desc* desc, const void* W0, const void* A, const
   (void)hipGetLastError();
   if (desc->dtype == L4Q_DTYPE_BF16) {
     l4q::MergeQuantOut<bf16_t> mq;
+    mq.packed = packed;
+    if (l4q::merge_quant_stream_supported(d, mq)) {  // packed by the pass itself; the workspace is not touched
+      l4q::launch_merge_quant_stream(d, (const bf16_t*)W0, (const bf16_t*)A, (const bf16_t*)B, scale, zero, mq, stream);
+      return launch_status();
+    }
+    mq.packed = nullptr;
     mq.codes = codes;
     l4q::launch_merge_quant<bf16_t>(d, (const bf16_t*)W0, (const bf16_t*)A, (const bf16_t*)B, scale, zero, mq, stream);
   } else {

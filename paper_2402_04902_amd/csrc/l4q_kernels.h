@@ -37,6 +37,12 @@ struct MergeQuantOut {
   int8_t* codes = nullptr;   // [o,i]
   float* wcomb = nullptr;    // [o,i] binary32 merged weight
   uint8_t* mask = nullptr;   // [o,i] 1 where Q_N <= w <= Q_P
+  // Streaming form only, each alone:
+  uint32_t* packed = nullptr;     // [o, bits i / 32] the codes as `bits`-wide fields of code - Q_N (i % 32 == 0)
+  float* errors = nullptr;        // pairs of partial sums of |Wc - Wq|, |Wc - (clamp(w) s + b)|, one per wavefront of the launch
+  float* init_scale = nullptr;    // [o,G] initialisation by method 0 .. 2 from the groups' extremes (g <= 256; no scale / zero read)
+  float* init_zero = nullptr;
+  int init_method = 0;
 };
 template <class T>
 void launch_merge_quant(const LayerDims& d, const T* W0, const T* A, const T* B, const float* scale,
@@ -47,9 +53,10 @@ void launch_merge_quant(const LayerDims& d, const T* W0, const T* A, const T* B,
 // fused-backward set (wqT + fgrad [+ bT]), rank a multiple of 8, group size >= 32.  launch_merge_quant uses it where
 // it applies.
 bool merge_quant_stream_supported(const LayerDims& d, const MergeQuantOut<bf16_t>& out);
-void launch_merge_quant_stream(const LayerDims& d, const bf16_t* W0, const bf16_t* A, const bf16_t* B,
-                               const float* scale, const float* zero, const MergeQuantOut<bf16_t>& out,
-                               hipStream_t stream);
+// returns the wavefronts of the launch (at most o * ceil(i / 256))
+int64_t launch_merge_quant_stream(const LayerDims& d, const bf16_t* W0, const bf16_t* A, const bf16_t* B,
+                                  const float* scale, const float* zero, const MergeQuantOut<bf16_t>& out,
+                                  hipStream_t stream);
 // Check of the streaming form's reciprocal-based quotient against the IEEE divide for `count` significands of the
 // scale starting at `first`; counts (device, zeroed by the caller): wrong reciprocals, wrong quotients, quotients compared.
 void launch_check_fast_divide(uint32_t first, uint32_t count, unsigned long long* counts, hipStream_t stream);

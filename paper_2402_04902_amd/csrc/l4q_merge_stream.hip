@@ -76,6 +76,14 @@ __device__ __forceinline__ float fast_quotient(float x, float s, float r, float 
   return fmaf(t, r, q);
 }
 
+// the value of another lane of the same 16 (DPP control word)
+template <int CTRL> __device__ __forceinline__ uint32_t lane_swap_u(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
+}
+template <int CTRL> __device__ __forceinline__ float lane_swap(float v) {
+  return __uint_as_float(lane_swap_u<CTRL>(__float_as_uint(v)));
+}
+
 // What one row block (32 rows x 64 columns) needs from memory.  The weight rows are requested a whole row block
 // ahead of their use (two register sets); the factors and the quantizer parameters of the next row block are
 // requested as soon as the current one has consumed its own (one set), before its streaming phase.
@@ -88,7 +96,8 @@ struct WeightLoads {
 };
 
 // MODE 1: forward (dequantized Wq, [ld_wq / 32][o][32]).  MODE 2: backward (Wq^T, [ld_wqT / 32][i][32]; optionally the
-// factor [o, i] and B^T).  MODE 3: export (any of int8 codes, binary32 merged weight, mask; all [o, i]).
+// factor [o, i] and B^T).  MODE 3: export (any of int8 codes, binary32 merged weight, mask; all [o, i]).  MODE 4: error
+// sums, one pair per wavefront.  MODE 5: scale / zero from the groups' extremes.  MODE 6: packed codes.
 // Grid: x = 256-column strips, y = partitions of the row blocks; wavefront w of a workgroup walks the row blocks
 // [nrb y / gridDim.y, nrb (y + 1) / gridDim.y) of its 64 columns (forward / export: one resident round of workgroups
 // covers the matrix; backward: four rounds' worth of shorter runs).
@@ -131,7 +140,12 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
       }
     }
   }
-  if (jw >= i) return;  // a whole wavefront past the last column (no workgroup barrier exists to miss)
+  double err_q = 0.0, err_c = 0.0;  // MODE 4: this lane's share of the wavefront's sums
+  float* const err_out = MODE == 4 ? out.errors + 2 * (((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 4 + wave) : nullptr;
+  if (jw >= i) {  // a whole wavefront past the last column (MODE 5's barriers count the wavefronts that are left)
+    if (MODE == 4 && lane < 2) err_out[lane] = 0.f;
+    return;
+  }
 
   // streaming role: 4 consecutive columns and 8 rows of the row block.  Forward: rows 4 rr + lane / 16, so that one
   // store instruction covers 4 consecutive rows (Wq is written in blocks of 32 columns, [j / 32][p][j % 32]: 4 rows of a
@@ -166,6 +180,15 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
   const __amdgpu_buffer_rsrc_t rsWc = __builtin_amdgcn_make_buffer_rsrc(out.wcomb, 0, o * i * 4, 0x00020000);
   const bool want_f = MODE == 2 && out.fgrad != nullptr;
 
+  // MODE 6: word t = lane % 8 of a run of 32 columns takes fields from lanes first .. first + pack_lanes - 1 of 8
+  const int pack_row = d.bits * (i / 32) * 4;  // bytes of a packed row
+  const int pack_t = c16 & 7, pack_first = 8 * pack_t / d.bits < 8 ? 8 * pack_t / d.bits : 7;
+  const int pack_src = (lane & ~7) + pack_first, pack_shift = 4 * d.bits * pack_first - 32 * pack_t;
+  const int pack_lanes = d.bits > 4 ? 3 : 4;
+  const bool pack_whole = d.bits == 2 || d.bits == 4 || d.bits == 8;
+  const bool pack_lane = pack_whole ? pack_t * d.bits % 8 == 0 : pack_t < d.bits;
+  const __amdgpu_buffer_rsrc_t rsPack = __builtin_amdgcn_make_buffer_rsrc(out.packed, 0, o * pack_row, 0x00020000);
+
   // A[k, jm] of the first ACH rank chunks, two bfloat16 per register: loaded once per wavefront
   uint32_t apk[8 * ACH];
   const unsigned voffA = jm < i ? (unsigned)(jm * 2) : OOB;
@@ -186,6 +209,7 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
     const unsigned voffB = row_m ? (unsigned)((p0 + l32) * r * 2) : OOB;
     F.bq0 = __builtin_amdgcn_raw_buffer_load_b128(rsB, (int)voffB, 0, 0);
     F.bq1 = __builtin_amdgcn_raw_buffer_load_b128(rsB, (int)(r > 8 ? voffB + 16u : voffB), 0, 0);
+    if (MODE == 5) return;
     const unsigned vt = tab_lane && row_m ? (unsigned)(((p0 + l32) * G + qtab) * 4) : OOB;
     F.s = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsS, (int)vt, 0, 0));
     F.b = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsZ, (int)vt, 0, 0));
@@ -265,9 +289,9 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
     }
 
     // ---- (row, group) table into the padding of the sums tile: s, b, RN(1 / s), 1024 s
-    const bool bad_scale = tab_lane && p0 + l32 < o && !scale_in_fast_range(F.s);
+    const bool bad_scale = MODE != 5 && tab_lane && p0 + l32 < o && !scale_in_fast_range(F.s);
     const bool slow = __builtin_amdgcn_ballot_w64(bad_scale) != 0;  // wave-uniform
-    if (tab_lane) {
+    if (MODE != 5 && tab_lane) {
       const float rc = exact_reciprocal(F.s);
       *reinterpret_cast<float4*>(S + l32 * MS_SPITCH + 64 + 4 * (lane >> 5)) = make_float4(F.s, F.b, rc, F.s * 1024.f);
     }
@@ -285,6 +309,12 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
     const unsigned vo_out = MODE == 1 ? (wq_col_off == OOB ? OOB : wq_col_off + (unsigned)((p0 + g16) * 64))
                             : rows_ok && j0 < ld_out ? (unsigned)(((p0 + 8 * g16) * ld_out + j0) * (MODE == 3 ? 1 : 2)) : OOB;
     const int row_bytes = MODE == 1 ? ROW_R * 64 : ld_out * (MODE == 3 ? 1 : 2);
+    float eq = 0.f, ec = 0.f;          // MODE 4
+    float lo[8], hi8[8];               // MODE 5: extremes of the lane's 4 columns, per row
+    const unsigned vo_pack = pack_lane && rows_ok && jw + 32 * (c16 >> 3) < i  // MODE 6
+                                 ? (unsigned)((p0 + 8 * g16) * pack_row + ((jw >> 5) + (c16 >> 3)) * 4 * d.bits +
+                                              (pack_whole ? pack_t * d.bits / 8 : pack_t) * 4)
+                                 : OOB;
     uint32_t wqpack[4][4];  // backward form: dequantized weights of the row block, [column][row pair]
     // (the padding columns are zeroed with a mask, not a select: a select over the whole quantizer chain is compiled
     // into a branch per row, which cuts the eight rows into pieces that cannot be scheduled together; for the same
@@ -308,11 +338,17 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
           wc[c] = GAMMA_POW2 ? fmaf(d.gamma, av[c], w0[c]) : w0[c] + d.gamma * av[c];
+          if constexpr (MODE == 5) continue;
           const float x = wc[c] - b;
           const float w = FAST ? fast_quotient(x, s, rc, hi) : __fdiv_rn(x, s);
           const float cl = __builtin_amdgcn_fmed3f(w, d.qn, d.qp);
           const float code = rintf(cl);
-          if (MODE != 3) wq[c] = fmaf(code, s, b);
+          if (MODE == 1 || MODE == 2 || MODE == 4) wq[c] = fmaf(code, s, b);
+          if (MODE == 4) {
+            eq += rows_ok && col_ok ? fabsf(wc[c] - wq[c]) : 0.f;
+            ec += rows_ok && col_ok ? fabsf(wc[c] - fmaf(cl, s, b)) : 0.f;
+          }
+          if (MODE == 6) cpack |= (uint32_t)(int)(code - d.qn) << (d.bits * c);
           if (MODE == 2) fg[c] = cl == w ? code - w : code;  // in range = the clamp changed nothing
           if (MODE == 3) {
             cpack |= ((uint32_t)(uint8_t)(int8_t)(int)code) << (8 * c);
@@ -336,7 +372,25 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
             if ((rr & 1) == 0) wqprev[c] = wq[c];
             else wqpack[c][rr >> 1] = rows_ok ? pack_bf16x2(wqprev[c], wq[c]) : 0u;
           }
-        } else {
+        } else if (MODE == 5) {
+          lo[rr] = col_ok ? fminf(fminf(wc[0], wc[1]), fminf(wc[2], wc[3])) : __builtin_huge_valf();
+          hi8[rr] = col_ok ? fmaxf(fmaxf(wc[0], wc[1]), fmaxf(wc[2], wc[3])) : -__builtin_huge_valf();
+        } else if (MODE == 6) {
+          // 8 lanes hold 32 columns, `bits` words.  2, 4, 8 bits: a word is the fields of 4, 2, 1 lanes, joined in the first
+          // of them; otherwise lane t gathers word t from the lanes whose fields reach into it (10 us more per 45 M weights)
+          uint32_t word = pack_whole ? cpack : 0;
+          if (pack_whole) {
+            if (d.bits < 8) word |= lane_swap_u<0xB1>(word) << (4 * d.bits & 31);
+            if (d.bits < 4) word |= lane_swap_u<0x4E>(word) << 16;
+          } else {
+            for (int q = 0; q < pack_lanes; ++q) {
+              const uint32_t v = (uint32_t)__shfl((int)cpack, pack_src + q, 64);
+              const int sh = pack_shift + 4 * d.bits * q;
+              word |= sh >= 32 ? 0u : sh >= 0 ? v << sh : v >> -sh;
+            }
+          }
+          __builtin_amdgcn_raw_buffer_store_b32(word, rsPack, (int)vo_pack, rr * pack_row, 0);
+        } else if (MODE == 3) {
           if (out.codes) __builtin_amdgcn_raw_buffer_store_b32(cpack, rsOut, (int)vo_out, rr * row_bytes, 0);
           if (out.mask) __builtin_amdgcn_raw_buffer_store_b32(mpack, rsMask, (int)vo_out, rr * row_bytes, 0);
           if (out.wcomb) {
@@ -356,6 +410,56 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();  // every lane's reads of the sums tile are done: it may be overwritten
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+
+    if constexpr (MODE == 4) {
+      err_q += (double)eq;
+      err_c += (double)ec;
+    }
+    if constexpr (MODE == 5) {
+      // ---- extremes over the 8 (g = 32) or 16 lanes of a row, then over the wavefronts that share a group: through the
+      //      padding of the sums tiles, two sets in turn, so that one barrier per row block is enough
+      const int set = 64 + 4 * ((rb - rb_begin) & 1);
+#pragma unroll
+      for (int rr = 0; rr < 8; ++rr) {
+        float a = lo[rr], z = hi8[rr];
+        a = fminf(a, lane_swap<0xB1>(a)); z = fmaxf(z, lane_swap<0xB1>(z));      // quad_perm: lane ^ 1
+        a = fminf(a, lane_swap<0x4E>(a)); z = fmaxf(z, lane_swap<0x4E>(z));      // quad_perm: lane ^ 2
+        a = fminf(a, lane_swap<0x141>(a)); z = fmaxf(z, lane_swap<0x141>(z));    // row_half_mirror
+        if (g > 32) {
+          a = fminf(a, lane_swap<0x140>(a)); z = fmaxf(z, lane_swap<0x140>(z));  // row_mirror
+        }
+        if ((c16 & 7) == 0)
+          *reinterpret_cast<float2*>(S + (8 * g16 + rr) * MS_SPITCH + set + 2 * (c16 >> 3)) = make_float2(a, z);
+      }
+      if (g > 64) __syncthreads();
+      else {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      }
+      const int span = g > 64 ? g / 64 : 1;  // wavefronts of a group; its first one finishes it
+      if (wave % span == 0 && tab_lane && p0 + l32 < o) {
+        const float* t = S + l32 * MS_SPITCH + set + 2 * (lane >> 5);
+        float a = t[0], z = t[1];
+        for (int w = 1; w < span; ++w) {
+          a = fminf(a, t[w * (MS_WAVE_LDS / 4)]);
+          z = fmaxf(z, t[w * (MS_WAVE_LDS / 4) + 1]);
+        }
+        float s0, b0 = 0.f;
+        if (out.init_method == 0) {         // asymmetric min / max
+          s0 = __fdiv_rn(z - a, d.qp - d.qn);
+          b0 = a - s0 * d.qn;
+        } else if (out.init_method == 1) {  // symmetric
+          s0 = __fdiv_rn(fmaxf(fabsf(a), fabsf(z)), -d.qn);
+        } else {                            // L4Q_init (Eq. l4q_quant_init)
+          s0 = fmaxf(fabsf(__fdiv_rn(a, d.qn)), fabsf(__fdiv_rn(z, d.qp)));
+        }
+        if (qtab < G) {
+          out.init_scale[(int64_t)(p0 + l32) * G + qtab] = s0;
+          out.init_zero[(int64_t)(p0 + l32) * G + qtab] = b0;
+        }
+      }
+    }
 
     if constexpr (MODE == 2) {
       // ---- Wq^T in blocks of 32 rows, [p / 32][j][p % 32]: this row block's 64 columns are 4 KiB of consecutive
@@ -398,6 +502,16 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
     compute(L1, rb);
     ++rb;
   }
+  if constexpr (MODE == 4) {
+    for (int off = 32; off > 0; off >>= 1) {
+      err_q += __shfl_xor(err_q, off, 64);
+      err_c += __shfl_xor(err_c, off, 64);
+    }
+    if (lane == 0) {
+      err_out[0] = (float)err_q;
+      err_out[1] = (float)err_c;
+    }
+  }
 #endif
 }
 
@@ -419,13 +533,14 @@ void merge_quant_stream_bwd_kernel(LayerDims d, const bf16_t* __restrict__ W0, c
   __shared__ __attribute__((aligned(16))) unsigned char lds_all[4 * ms_wave_lds<2>()];
   merge_quant_stream_body<2, GAMMA_POW2, 1>(d, W0, A, B, scale, zero, out, nrb, lds_all);
 }
-template <bool GAMMA_POW2>
+// MODE 3 .. 6: the export, statistics and packing forms, as the forward form 4 workgroups per compute unit
+template <bool GAMMA_POW2, int MODE>
 __global__ __launch_bounds__(MS_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void merge_quant_stream_export_kernel(LayerDims d, const bf16_t* __restrict__ W0, const bf16_t* __restrict__ A,
                                       const bf16_t* __restrict__ B, const float* __restrict__ scale,
                                       const float* __restrict__ zero, MergeQuantOut<bf16_t> out, int nrb) {
-  __shared__ __attribute__((aligned(16))) unsigned char lds_all[4 * ms_wave_lds<3>()];
-  merge_quant_stream_body<3, GAMMA_POW2, 1>(d, W0, A, B, scale, zero, out, nrb, lds_all);
+  __shared__ __attribute__((aligned(16))) unsigned char lds_all[4 * ms_wave_lds<MODE>()];
+  merge_quant_stream_body<MODE, GAMMA_POW2, 1>(d, W0, A, B, scale, zero, out, nrb, lds_all);
 }
 
 // ------------------------------------------------------------------ check of the reciprocal-based quotient
@@ -484,14 +599,16 @@ bool merge_quant_stream_supported(const LayerDims& d, const MergeQuantOut<bf16_t
   const bool fwd = out.wq && !out.wqT && !out.fgrad && !misc;
   const bool bwd = !out.wq && out.wqT && !misc;
   const bool exp = !out.wq && !out.wqT && !out.fgrad && misc;
+  if (out.packed || out.errors || out.init_scale)  // each of them alone
+    return d.r % 8 == 0 && d.g >= 32 && (!out.packed || d.i % 32 == 0) && (!out.init_scale || d.g <= 256);
   const bool blocks = (!out.wq || out.ld_wq % 32 == 0) && (!out.wqT || out.ld_wqT % 32 == 0);
   return (fwd || bwd || exp) && blocks && d.r % 8 == 0 && d.g >= 32;
 }
 
-void launch_merge_quant_stream(const LayerDims& d, const bf16_t* W0, const bf16_t* A, const bf16_t* B,
-                               const float* scale, const float* zero, const MergeQuantOut<bf16_t>& out,
-                               hipStream_t stream) {
-  const int mode = out.wq ? 1 : out.wqT ? 2 : 3;
+int64_t launch_merge_quant_stream(const LayerDims& d, const bf16_t* W0, const bf16_t* A, const bf16_t* B,
+                                  const float* scale, const float* zero, const MergeQuantOut<bf16_t>& out,
+                                  hipStream_t stream) {
+  const int mode = out.wq ? 1 : out.wqT ? 2 : out.errors ? 4 : out.init_scale ? 5 : out.packed ? 6 : 3;
   const int64_t rows = mode == 2 && out.ld_wqT > d.o ? out.ld_wqT : d.o;
   const int nrb = (int)((rows + 31) / 32);
   // one resident round: 4 (backward: 3) workgroups per compute unit, each wavefront walking a run of row blocks
@@ -515,8 +632,12 @@ void launch_merge_quant_stream(const LayerDims& d, const bf16_t* W0, const bf16_
   if (mode == 1 && wide) { if (pow2) L4Q_MS_LAUNCH(merge_quant_stream_fwd_kernel, true, 4); else L4Q_MS_LAUNCH(merge_quant_stream_fwd_kernel, false, 4); }
   else if (mode == 1) { if (pow2) L4Q_MS_LAUNCH(merge_quant_stream_fwd_kernel, true); else L4Q_MS_LAUNCH(merge_quant_stream_fwd_kernel, false); }
   else if (mode == 2) { if (pow2) L4Q_MS_LAUNCH(merge_quant_stream_bwd_kernel, true); else L4Q_MS_LAUNCH(merge_quant_stream_bwd_kernel, false); }
-  else { if (pow2) L4Q_MS_LAUNCH(merge_quant_stream_export_kernel, true); else L4Q_MS_LAUNCH(merge_quant_stream_export_kernel, false); }
+  else if (mode == 3) { if (pow2) L4Q_MS_LAUNCH(merge_quant_stream_export_kernel, true, 3); else L4Q_MS_LAUNCH(merge_quant_stream_export_kernel, false, 3); }
+  else if (mode == 4) { if (pow2) L4Q_MS_LAUNCH(merge_quant_stream_export_kernel, true, 4); else L4Q_MS_LAUNCH(merge_quant_stream_export_kernel, false, 4); }
+  else if (mode == 5) { if (pow2) L4Q_MS_LAUNCH(merge_quant_stream_export_kernel, true, 5); else L4Q_MS_LAUNCH(merge_quant_stream_export_kernel, false, 5); }
+  else { if (pow2) L4Q_MS_LAUNCH(merge_quant_stream_export_kernel, true, 6); else L4Q_MS_LAUNCH(merge_quant_stream_export_kernel, false, 6); }
 #undef L4Q_MS_LAUNCH
+  return (int64_t)strips * parts * 4;
 }
 
 void launch_check_fast_divide(uint32_t first, uint32_t count, unsigned long long* counts, hipStream_t stream) {

@@ -470,11 +470,11 @@ __global__ __launch_bounds__(MQ_THREADS) void weight_stats_tile_kernel(LayerDims
   }
 }
 
-// sums err_part [rows * 2] pairs into out[0] (E_quant) and out[1] (E_clip); one block, fixed order
-__global__ __launch_bounds__(256) void sum_error_pairs_kernel(const float* __restrict__ part, int64_t npairs,
-                                                               float* __restrict__ out) {
-  __shared__ double sh[2][256];
+// Sums of a run of pairs by one block of 256 threads, in binary64 and fixed order; the totals in sh[0][0], sh[1][0].
+template <class V>
+__device__ __forceinline__ void sum_pairs(const V* __restrict__ part, int64_t npairs, double (&sh)[2][256]) {
   double a = 0.0, b = 0.0;
+#pragma unroll 8
   for (int64_t e = threadIdx.x; e < npairs; e += 256) {
     a += part[2 * e];
     b += part[2 * e + 1];
@@ -488,6 +488,40 @@ __global__ __launch_bounds__(256) void sum_error_pairs_kernel(const float* __res
       sh[1][threadIdx.x] += sh[1][threadIdx.x + st];
     }
     __syncthreads();
+  }
+}
+
+// Many pairs: block b adds the pairs [b ERR_CHUNK, (b + 1) ERR_CHUNK), the last one what is left over too, and leaves the two
+// sums as binary64 in the place of its first two pairs (nobody else reads its run).  (45088 pairs of an 11008 x 4096 weight in
+// one block, the only form before, took 167 us.)
+constexpr int ERR_CHUNK = 2048;
+__global__ __launch_bounds__(256) void sum_error_chunks_kernel(float* __restrict__ part, int64_t npairs) {
+  __shared__ double sh[2][256];
+  const int64_t first = (int64_t)blockIdx.x * ERR_CHUNK;
+  const int64_t n = blockIdx.x + 1 == gridDim.x ? npairs - first : ERR_CHUNK;
+  sum_pairs(part + 2 * first, n, sh);
+  if (threadIdx.x < 2) reinterpret_cast<double*>(part + 2 * first)[threadIdx.x] = sh[threadIdx.x][0];
+}
+
+// sums npairs pairs into out[0] (E_quant) and out[1] (E_clip): binary32 pairs, or (chunks > 0) the binary64 sums the
+// kernel above has left every ERR_CHUNK pairs
+__global__ __launch_bounds__(256) void sum_error_pairs_kernel(const float* __restrict__ part, int64_t npairs, int chunks,
+                                                               float* __restrict__ out) {
+  __shared__ double sh[2][256];
+  if (chunks == 0) {
+    sum_pairs(part, npairs, sh);
+  } else {
+    double a = 0.0, b = 0.0;
+    for (int c = threadIdx.x; c < chunks; c += 256) {
+      const double* q = reinterpret_cast<const double*>(part + 2 * (int64_t)c * ERR_CHUNK);
+      a += q[0];
+      b += q[1];
+    }
+    __shared__ double tot[512];
+    tot[2 * threadIdx.x] = a;
+    tot[2 * threadIdx.x + 1] = b;
+    __syncthreads();
+    sum_pairs(tot, 256, sh);
   }
   if (threadIdx.x == 0) {
     out[0] = (float)sh[0][0];
@@ -572,6 +606,16 @@ void launch_merge_quant(const LayerDims& d, const T* W0, const T* A, const T* B,
 template <class T>
 void launch_init_qparams(const LayerDims& d, const T* W0, const T* A, const T* B, int method, float* scale,
                          float* zero, hipStream_t stream) {
+  if constexpr (std::is_same<T, bf16_t>::value) {
+    MergeQuantOut<bf16_t> out;
+    out.init_scale = scale;
+    out.init_zero = zero;
+    out.init_method = method;
+    if (method <= 2 && merge_quant_stream_supported(d, out)) {  // (LSQ+_init needs a second pass over the group)
+      launch_merge_quant_stream(d, W0, A, B, scale, zero, out, stream);
+      return;
+    }
+  }
   if (d.g <= 256) {
     dim3 grid((unsigned)((d.i + MQ_COLS - 1) / MQ_COLS), (unsigned)((d.o + MQ_ROWS - 1) / MQ_ROWS));
     hipLaunchKernelGGL(weight_stats_tile_kernel<T>, grid, dim3(MQ_THREADS), 0, stream, d, W0, A, B, method, scale,
@@ -586,12 +630,23 @@ void launch_init_qparams(const LayerDims& d, const T* W0, const T* A, const T* B
 template <class T>
 void launch_quant_errors(const LayerDims& d, const T* W0, const T* A, const T* B, const float* scale,
                          const float* zero, float* partial, float* out2, hipStream_t stream) {
-  dim3 grid((unsigned)((d.i + MQ_COLS - 1) / MQ_COLS), (unsigned)((d.o + MQ_ROWS - 1) / MQ_ROWS));
-  hipLaunchKernelGGL(weight_stats_tile_kernel<T>, grid, dim3(MQ_THREADS), 0, stream, d, W0, A, B, STAT_ERRORS,
-                     const_cast<float*>(scale), const_cast<float*>(zero), partial);
-  hipLaunchKernelGGL(sum_error_pairs_kernel, dim3(1), dim3(256), 0, stream, partial, d.o * (int64_t)grid.x, out2);
+  int64_t npairs = 0;
+  if constexpr (std::is_same<T, bf16_t>::value) {
+    MergeQuantOut<bf16_t> out;
+    out.errors = partial;
+    if (merge_quant_stream_supported(d, out)) npairs = launch_merge_quant_stream(d, W0, A, B, scale, zero, out, stream);
+  }
+  if (npairs == 0) {
+    dim3 grid((unsigned)((d.i + MQ_COLS - 1) / MQ_COLS), (unsigned)((d.o + MQ_ROWS - 1) / MQ_ROWS));
+    hipLaunchKernelGGL(weight_stats_tile_kernel<T>, grid, dim3(MQ_THREADS), 0, stream, d, W0, A, B, STAT_ERRORS,
+                       const_cast<float*>(scale), const_cast<float*>(zero), partial);
+    npairs = d.o * (int64_t)grid.x;
+  }
+  // one block adds up to 4 runs' worth of pairs itself
+  const int chunks = npairs > 4 * ERR_CHUNK ? (int)(npairs / ERR_CHUNK) : 0;
+  if (chunks > 0) hipLaunchKernelGGL(sum_error_chunks_kernel, dim3((unsigned)chunks), dim3(256), 0, stream, partial, npairs);
+  hipLaunchKernelGGL(sum_error_pairs_kernel, dim3(1), dim3(256), 0, stream, partial, npairs, chunks, out2);
 }
-
 
 template void launch_merge_quant<float>(const LayerDims&, const float*, const float*, const float*, const float*,
                                         const float*, const MergeQuantOut<float>&, hipStream_t);

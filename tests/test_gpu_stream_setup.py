@@ -1,0 +1,79 @@
+"""The streaming pass's set-up forms (ranks that are multiples of 8, groups of 32 and more): packed codes of every width,
+extremes across the wavefronts of a group, error sums with many and few partial pairs, at widths that end inside a strip
+of 256 columns and heights that end inside a row block of 32, against the oracle (words and scales bit for bit)."""
+import numpy as np
+import pytest
+
+from paper_2402_04902_amd import inputs
+from paper_2402_04902_amd.inputs import DTYPE_BF16, DTYPE_F32, LayerSpec
+
+from parity_util import host_qparams
+from test_gpu_quantized_path import packed_on_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4, 5, 6, 7, 8])
+@pytest.mark.parametrize("i,o,r,g", [(32, 8, 8, 32), (352, 72, 24, 32), (1152, 1032, 16, 128)])
+def test_packed(bits, i, o, r, g):
+    from oracle import l4q_oracle as O
+    from paper_2402_04902_amd import binding
+    spec = LayerSpec(f"pack{bits}_{o}x{i}", 8, i, o, r, 2.0 * r, bits, g, DTYPE_BF16)
+    print("case", spec.name, flush=True)
+    arrs = inputs.make_layer_inputs(spec, seed=bits + i)
+    s, b = host_qparams(spec, arrs, "asymm", 0.8)
+    s[0, 0] = 2.0 ** -70  # one scale outside the reciprocal's range: its row block takes the IEEE divide
+    layer = binding.upload(spec, arrs, s, b)
+    got = packed_on_gpu(spec, layer).cpu().numpy().view(np.uint32)
+    dec, _, _ = O.decide_f32(arrs["W0"], arrs["A"], arrs["B"], s, b, bits, g, spec.alpha)
+    assert np.array_equal(got, O.pack_codes(dec.codes, bits))
+
+
+@pytest.mark.parametrize("method,mid", [("asymm", 0), ("symm", 1), ("l4q", 2)])
+@pytest.mark.parametrize("i,o,g", [(96, 40, 32), (320, 8, 64), (640, 1032, 128), (768, 264, 256)])
+def test_init(method, mid, i, o, g):
+    import torch
+    from oracle import l4q_oracle as O
+    from paper_2402_04902_amd import binding
+    spec = LayerSpec(f"init_{method}_{o}x{i}_g{g}", 8, i, o, 16, 24.0, 3, g, DTYPE_BF16)  # gamma = 1.5: no power of two
+    print("case", spec.name, flush=True)
+    arrs = inputs.make_layer_inputs(spec, seed=g)
+    layer = binding.upload(spec, arrs)
+    binding.l4q_init_qparams(layer.desc, layer.W0, layer.A, layer.B, mid, layer.scale, layer.zero)
+    torch.cuda.synchronize()
+    s, b = O.init_qparams(O.merge_f32(arrs["W0"], arrs["A"], arrs["B"], spec.alpha), 3, g, method, dtype=np.float32)
+    assert np.array_equal(layer.scale.cpu().numpy().view(np.uint32), s.view(np.uint32))
+    assert np.array_equal(layer.zero.cpu().numpy().view(np.uint32), b.view(np.uint32))
+
+
+@pytest.mark.parametrize("i,o,r,g,dtype", [
+    (32, 8, 8, 32, DTYPE_BF16),         # four pairs, three of them of wavefronts past the last column
+    (352, 1032, 8, 32, DTYPE_BF16),
+    (1024, 72, 16, 1024, DTYPE_BF16),   # a group across strips
+    (2560, 1000, 4, 64, DTYPE_BF16),    # the general pass: 10000 pairs, added in runs of 2048, the last one longer
+    (512, 4097, 3, 64, DTYPE_F32),      # 8194 pairs: four runs
+    (256, 2049, 3, 64, DTYPE_F32),      # 2049 pairs: one block
+])
+def test_error_sums(i, o, r, g, dtype):
+    import torch
+    from oracle import l4q_oracle as O
+    from paper_2402_04902_amd import binding
+    spec = LayerSpec(f"err_{o}x{i}_r{r}", 8, i, o, r, 2.0 * r, 4, g, dtype)
+    print("case", spec.name, flush=True)
+    arrs = inputs.make_layer_inputs(spec, seed=i + o)
+    s, b = host_qparams(spec, arrs, "asymm", 0.7)
+    layer = binding.upload(spec, arrs, s, b)
+    errors = torch.zeros(8, dtype=torch.float32, device=layer.W0.device)
+    need = o * ((i + 255) // 256) * 8
+    ws = torch.full((need + 256,), 0x7F, dtype=torch.uint8, device=layer.W0.device)
+    binding.l4q_quant_errors(layer.desc, layer.W0, layer.A, layer.B, layer.scale, layer.zero, errors, ws[:need])
+    binding.l4q_quant_errors_static(layer.desc, layer.W0, layer.A, layer.B, layer.scale, layer.zero, errors[4:])
+    torch.cuda.synchronize()
+    assert (ws[need:] == 0x7F).all()  # nothing past the stated size
+    e = errors.cpu().numpy()
+    Wc = O.merge(arrs["W0"], arrs["A"], arrs["B"], spec.alpha)
+    want = np.array([O.quantization_error(Wc, s, b, 4, g), O.clipping_error(Wc, s, b, 4, g)])
+    # binary32 terms of |Wc| <= 2 with 2^-24 rounding each and decisions a rounding away from a tie, whose two codes are
+    # equally far: well below 1e-5 of sums that average a quarter of a step per weight
+    assert np.allclose(e[:2], want, rtol=1e-5, atol=0), (e, want)
+    assert np.array_equal(e[:2], e[4:6])
