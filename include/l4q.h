@@ -171,9 +171,9 @@ int l4q_export_packed(const l4q_desc* desc, const void* W0, const void* A, const
 
 /* Forward pass of the fully quantized layer from the packed codes alone (no W0, A, B):
  *   Y[T,o] = X[T,i] . (w~ scale + zero)^T        (Eq. l4q_forward with Eq. l4q_Wdequant)
- * BF16 only (X, Y bfloat16); bits in {2,3,4,8}; in_features % 64 == 0.  Meant for decode-sized T:
- * the packed weights are streamed once per pass of at most 64 tokens (32 or 48 for some shapes), so the
- * cost grows with T beyond that.
+ * BF16 only (X, Y bfloat16); bits in {2,3,4,8}; in_features % 64 == 0.  Decode sizes stream the packed
+ * weights once per pass of at most 64 tokens (32 or 48 for some shapes); prompts (groups of 64 and more,
+ * in_features % 128 == 0) run as one pass in two-dimensional tiles from where that is faster.
  * workspace (device memory, 256-byte aligned) is optional: NULL / 0 is always accepted.  Layers with few output
  * rows and long rows run faster from about 8 tokens on when given
  * l4q_quantized_forward_workspace_bytes() of it

@@ -4,8 +4,8 @@
 // Packed layout: the unsigned field u = w~ - Q_N of column j occupies bits [n j, n j + n) of the
 // row's little-endian bit string; rows are n * i / 32 words.
 //
-// Five kernels compute the product, chosen by launch_qgemm from the code width, the token count and the layer's
-// shape (each is described where it is defined): qgemm_wreg_kernel (2 / 3 / 4 / 8 bits, groups of 128 and more, one
+// Six kernels compute the product, chosen by launch_qgemm from the code width, the token count and the layer's
+// shape (each is described where it is defined): qgemm_prefill_kernel (l4q_prefill.hip: prompts), qgemm_wreg_kernel (2 / 3 / 4 / 8 bits, groups of 128 and more, one
 // token to a few token blocks: the packed codes resident in registers, the activations streamed),
 // qgemm_decode_kernel (2 / 4 / 8 bits, activations resident in LDS, the weights streamed through rings),
 // qgemm_stream_kernel (4 / 8 bits, up to 32 tokens per pass), qgemm_tile_kernel (3 / 4 / 8 bits, 64-row tiles, up to
@@ -21,6 +21,7 @@
 #include <type_traits>
 
 #include "l4q_device.h"
+#include "l4q_codes.h"
 #include "l4q_gemm_core.h"
 #include "l4q_kernels.h"
 
@@ -300,56 +301,6 @@ __global__ __launch_bounds__(QG_WAVES * 64) void qgemm_kernel(const bf16_t* __re
 // Ring of 4 stages per wave: three stages are in flight while one is consumed.  X fragments and scale /
 // zero are fetched one stage ahead into registers; every load is issued in a fixed order so that one
 // partial s_waitcnt covers the stage.
-// Operand fragment f (8 consecutive codes) of a 16-byte chunk of packed codes, as bf16 values without a convert.
-// 4 bits: byte r holds codes 2r (low nibble) and 2r + 1; times 0x1001 puts a copy of the byte 12 bits up, so one mask
-// leaves code 2r in bits 0..3 and code 2r + 1 in bits 16..19, and OR-ing 0x4300 into both halves makes the bf16 pair
-// 128 + u (the caller's K0 takes the 128 and the code offset out again).  8 bits: code - 128, converted.
-typedef uint32_t code_chunk_t __attribute__((ext_vector_type(4)));
-template <int BITS>
-__device__ __forceinline__ bf16x8_t code_fragment(const code_chunk_t& w, int f) {
-  code_chunk_t d;
-  if (BITS == 4) {
-    const uint32_t v = w[f];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const uint32_t spread = __builtin_amdgcn_ubfe(v, 8 * r, 8) * 0x1001u;
-      // ((x & mask) | bias as one v_and_or_b32: the constants are made opaque so that they stay in registers - the op
-      // takes no literals; the op itself is left to the compiler: as inline assembly it would hide that a vector op wrote
-      // the register, and the wait states a matrix op needs before it reads such a register would be missing)
-      uint32_t mask = 0x000F000Fu, bias = 0x43004300u;
-      asm("" : "+s"(mask));
-      asm("" : "+v"(bias));
-      d[r] = (spread & mask) | bias;
-    }
-  } else if (BITS == 2) {
-    // the chunk's first two dwords hold 32 codes; fragment f is the 16-bit half f % 2 of dword f / 2, its code pairs are
-    // 4-bit fields: times 0x4001 puts a copy 14 bits up, the mask leaves code 2r in bits 0..1 and code 2r + 1 in bits
-    // 16..17 (the caller's K0 is 128 + 2)
-    const uint32_t v = w[f >> 1];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const uint32_t spread = __builtin_amdgcn_ubfe(v, 16 * (f & 1) + 4 * r, 4) * 0x4001u;
-      d[r] = (spread & 0x00030003u) | 0x43004300u;
-    }
-  } else if (BITS == 3) {
-    // the chunk's first three dwords hold 32 codes; fragment f is the 24-bit window from bit 24 f, its code pairs are
-    // 6-bit fields: times 0x2001 puts a copy 13 bits up, the mask leaves code 2r in bits 0..2 and code 2r + 1 in bits
-    // 16..18 (the caller's K0 is 128 + 4)
-    const uint32_t win = f == 0 ? w[0] : f == 1 ? (w[0] >> 24) | (w[1] << 8) : f == 2 ? (w[1] >> 16) | (w[2] << 16) : w[2] >> 8;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const uint32_t spread = __builtin_amdgcn_ubfe(win, 6 * r, 6) * 0x2001u;
-      d[r] = (spread & 0x00070007u) | 0x43004300u;
-    }
-  } else {
-    const uint32_t v0 = w[(2 * f) & 3], v1 = w[(2 * f + 1) & 3];  // 4 + 4 codes
-    d[0] = pack_bf16x2((float)(v0 & 0xFFu) - 128.f, (float)((v0 >> 8) & 0xFFu) - 128.f);
-    d[1] = pack_bf16x2((float)((v0 >> 16) & 0xFFu) - 128.f, (float)(v0 >> 24) - 128.f);
-    d[2] = pack_bf16x2((float)(v1 & 0xFFu) - 128.f, (float)((v1 >> 8) & 0xFFu) - 128.f);
-    d[3] = pack_bf16x2((float)((v1 >> 16) & 0xFFu) - 128.f, (float)(v1 >> 24) - 128.f);
-  }
-  return __builtin_bit_cast(bf16x8_t, d);
-}
 
 constexpr int QS_NSW = 4;             // ring stages per wave
 
@@ -1628,8 +1579,33 @@ size_t qgemm_workspace_bytes(const LayerDims& d) {
   return tile_bytes > wreg_bytes ? tile_bytes : wreg_bytes;
 }
 
+namespace {
+
+// Estimated time (us) of the passes the kernels of this file would take above 64 tokens: full passes of 64 tokens in 64-row
+// tiles, 8 + 0.38 per million weights (4 bits, 64 tokens: [4096 x 4096] 14.2, [4096 x 11008] 25.3, [11008 x 4096] 28.1, [8192
+// x 8192] 31.5, [16384 x 4096] 29.6; the last pass by its token blocks; 3 and 8 bits 10 .. 30 % more); twice that where only
+// the general kernel or the k-split streaming form is left (2 bits [11008 x 4096] 54, [4096 x 11008] 55).
+double qgemm_passes_us(const LayerDims& d, bool have_workspace) {
+  const TilePlan plan = qgemm_tile_plan(d);
+  const bool tiles = plan.tb_max > 0 && (plan.slices == 1 || have_workspace);
+  const double pass = (8.0 + 0.38e-6 * (double)d.o * (double)d.i) * (d.bits == 4 ? 1.0 : 1.2) * (tiles ? 1.0 : 2.0);
+  const int64_t full = d.T / 64, blocks = (d.T % 64 + 15) / 16;
+  return pass * ((double)full + (blocks > 0 ? 0.45 + 0.1375 * (double)blocks : 0.0));
+}
+
+}  // namespace
+
 void launch_qgemm(const LayerDims& d, const bf16_t* X, const uint32_t* packed, const float* scale, const float* zero,
                   bf16_t* Y, float* partial, size_t partial_bytes, hipStream_t stream) {
+  // prompts: one pass in two-dimensional tiles, from where it is estimated to be faster than 64 tokens at a time
+  // (4 bits: [11008 x 4096] 65 tokens, 33 against 47 us; [4096 x 4096] 129, 32 against 40; [4096 x 11008] 177, 83 against 95)
+  if (d.T > 64) {
+    const PrefillPlan pf = qgemm_prefill_plan(d);
+    if (pf.form >= 0 && pf.us < qgemm_passes_us(d, partial != nullptr && partial_bytes >= qgemm_workspace_bytes(d))) {
+      launch_qgemm_prefill(pf, d, X, packed, scale, zero, Y, stream);
+      return;
+    }
+  }
   dim3 grid((unsigned)((d.o + 31) / 32));
   // a few token blocks at most, groups of 128 and more: the packed codes resident in registers
   if (L4Q_WREG_SWITCH) {

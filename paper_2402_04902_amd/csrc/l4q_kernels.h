@@ -149,6 +149,15 @@ size_t qgemm_workspace_bytes(const LayerDims& d);
 void launch_qgemm(const LayerDims& d, const bf16_t* X, const uint32_t* packed, const float* scale, const float* zero,
                   bf16_t* Y, float* partial, size_t partial_bytes, hipStream_t stream);
 
+// The same product at prompt sizes (l4q_prefill.hip; more than 64 tokens, groups of 64 and more, i % 128 == 0).
+struct PrefillPlan {
+  int form;   // tile shape, or -1: not covered
+  double us;  // estimated time
+};
+PrefillPlan qgemm_prefill_plan(const LayerDims& d);
+void launch_qgemm_prefill(const PrefillPlan& plan, const LayerDims& d, const bf16_t* X, const uint32_t* packed,
+                          const float* scale, const float* zero, bf16_t* Y, hipStream_t stream);
+
 // outa = scale * sum of nba partials of na elements, outb likewise, in one launch (na, nb multiples of 4)
 void launch_reduce_two_partials(const float* pa, int nba, int64_t na, float* outa, const float* pb, int nbb,
                                 int64_t nb, float* outb, float scale, bool accumulate, hipStream_t stream);

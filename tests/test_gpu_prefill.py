@@ -1,0 +1,50 @@
+"""Quantized forward at prompt sizes (two-dimensional tiles): every tile shape and code width, token and row counts that end
+inside a tile, one to nine sections of k (an odd count leaves half a zero-term pair), groups of half a section, one, two
+and four, against the oracle; a NaN token stays in its row."""
+import numpy as np
+import pytest
+
+from paper_2402_04902_amd import inputs
+from paper_2402_04902_amd.inputs import DTYPE_BF16, LayerSpec
+
+from parity_util import compare_tensor, host_qparams, rel_fro
+from test_gpu_quantized_path import packed_on_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4, 8])
+@pytest.mark.parametrize("T,i,o,g", [
+    (65, 128, 8, 128),       # 64 x 128 tiles: one section, the second tile one token, eight rows
+    (129, 640, 264, 128),    # five sections
+    (100, 1152, 392, 64),    # half sections (3 bits: the 64-token passes)
+    (130, 1536, 136, 512),   # groups of four sections
+    (401, 384, 5000, 128),   # 128 x 128 tiles, three sections, ragged rows
+    (385, 512, 5128, 256),   # ... groups of two sections
+    (385, 192, 5128, 64),    # ... i not a multiple of 128: the 64-token passes
+    (641, 256, 8200, 128),   # 128 x 256 tiles (8 bits: 64 x 128), one token in the last
+])
+def test_prefill(T, i, o, g, bits):
+    import torch
+    from oracle import l4q_oracle as O
+    from paper_2402_04902_amd import binding
+    spec = LayerSpec(f"prefill_{T}x{i}x{o}_{bits}b_g{g}", T, i, o, 8, 16.0, bits, g, DTYPE_BF16)
+    print("case", spec.name, flush=True)
+    arrs = inputs.make_layer_inputs(spec, seed=T + bits)
+    s, b = host_qparams(spec, arrs, "asymm", 0.9)
+    layer = binding.upload(spec, arrs, s, b)
+    packed = packed_on_gpu(spec, layer)
+    nan_row = T - 2
+    layer.X[nan_row, i // 2] = float("nan")
+    Y = torch.full_like(layer.Y, 7.0)
+    binding.l4q_quantized_forward(layer.desc, layer.X, packed, layer.scale, layer.zero, Y)
+    torch.cuda.synchronize()
+    dec, _, _ = O.decide_f32(arrs["W0"], arrs["A"], arrs["B"], s, b, bits, g, spec.alpha)
+    ref = O.quantized_forward(arrs["X"], O.pack_codes(dec.codes, bits), s, b, bits, g)
+    got = Y.double().cpu().numpy()
+    assert np.isnan(got[nan_row]).all()
+    keep = np.arange(T) != nan_row
+    compare_tensor(spec.name, got[keep], ref[keep], 2e-2, 2e-2)
+    # exact codes and binary32 sums: what is left is the rounding of Y to bfloat16, 2^-9 / sqrt(3) = 1.1e-3 rms of a value at
+    # the top of its binade and up to twice that at the bottom (mean 1.7e-3)
+    assert rel_fro(got[keep], ref[keep]) <= 2.2e-3
