@@ -39,7 +39,8 @@ __device__ __forceinline__ void store_out(const SgemmArgs& a, int64_t m, int64_t
 }
 
 // ------------------------------------------------------------------ tiled form
-// 4 waves (2 x 2); k in steps of 32, the next two steps' operands travelling to registers while the current one is
+// KG groups of 4 waves (2 x 2) on the same tile, group q taking the k-steps q, q + KG, ..., their sums added at the end; k in
+// steps of 32, the next two steps' operands travelling to registers while the current one is
 // multiplied out of LDS; two LDS buffers, one barrier per step.  K-contiguous operands lie in LDS as rows
 // of 32 k + 4 floats of padding (16-byte reads of 16 consecutive rows meet all banks once), K-major ones as they come.
 constexpr int SG_BK = 32;
@@ -101,15 +102,17 @@ struct SgemmOperand {
   }
 };
 
-template <int BM, int BN, bool A_KM, bool B_KM>
-__global__ __launch_bounds__(256, 2) void sgemm_tile_kernel(SgemmArgs a) {
+template <int BM, int BN, int KG, bool A_KM, bool B_KM>
+__global__ __launch_bounds__(256 * KG, KG == 2 ? 4 : 1) void sgemm_tile_kernel(SgemmArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)
   typedef SgemmOperand<BM, A_KM> OpA;
   typedef SgemmOperand<BN, B_KM> OpB;
   constexpr int STAGE = OpA::FLOATS + OpB::FLOATS;
   constexpr int TM = BM / 64, TN = BN / 64;  // 32 x 32 accumulator tiles per wave
-  __shared__ __align__(16) float lds[2 * STAGE];
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  static_assert(KG == 1 || (KG == 2 && BM == 64 && BN == 64), "the second group's sums fit its buffers");
+  __shared__ __align__(16) float lds[2 * KG * STAGE];
+  const int group = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+  const int tid = threadIdx.x & 255, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, half = lane >> 5;
   const int tiles_m = (int)((a.M + BM - 1) / BM), tiles_n = (int)((a.N + BN - 1) / BN);
   int tm, tn;
@@ -129,20 +132,20 @@ __global__ __launch_bounds__(256, 2) void sgemm_tile_kernel(SgemmArgs a) {
   OpB ob[2];
 #pragma unroll
   for (int p = 0; p < 2; ++p) {
-    oa[p].load(a.A, a.lda, m0, a.M, p * SG_BK, a.K, tid);
-    ob[p].load(a.B, a.ldb, n0, a.N, p * SG_BK, a.K, tid);
+    oa[p].load(a.A, a.lda, m0, a.M, (p * KG + group) * SG_BK, a.K, tid);
+    ob[p].load(a.B, a.ldb, n0, a.N, (p * KG + group) * SG_BK, a.K, tid);
   }
-  for (int64_t k0 = 0; k0 < a.K; k0 += 2 * SG_BK) {
+  for (int64_t k0 = 0; k0 < a.K; k0 += 2 * KG * SG_BK) {
 #pragma unroll
     for (int p = 0; p < 2; ++p) {  // steps of one buffer and register set each
-      if (p == 1 && k0 + SG_BK >= a.K) break;
-      float* la = lds + p * STAGE;
+      if (p == 1 && k0 + KG * SG_BK >= a.K) break;  // (the same for all groups: a step past K multiplies zeros)
+      float* la = lds + (group * 2 + p) * STAGE;
       float* lb = la + OpA::FLOATS;
       oa[p].store(la, tid);
       ob[p].store(lb, tid);
       __syncthreads();  // (the buffer's previous readers passed the barrier of the step between)
-      const int64_t next = k0 + (p + 2) * SG_BK;
-      if (next < a.K) {
+      const int64_t next = k0 + ((p + 2) * KG + group) * SG_BK;
+      if (k0 + (p + 2) * KG * SG_BK < a.K) {
         oa[p].load(a.A, a.lda, m0, a.M, next, a.K, tid);
         ob[p].load(a.B, a.ldb, n0, a.N, next, a.K, tid);
       }
@@ -162,6 +165,18 @@ __global__ __launch_bounds__(256, 2) void sgemm_tile_kernel(SgemmArgs a) {
               acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[x][j], fb[y][j], acc[x][y], 0, 0, 0);
       }
     }
+  }
+  if constexpr (KG == 2) {  // group 1's sums through LDS to group 0
+    __syncthreads();
+    float* sums = lds + tid * 17;  // (odd pitch: no bank conflicts)
+    if (group == 1) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) sums[e] = acc[0][0][e];
+    }
+    __syncthreads();
+    if (group == 1) return;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[0][0][e] += sums[e];
   }
   // accumulator: lane = column n, register e = row 8 (e / 4) + 4 half + e % 4
 #pragma unroll
@@ -247,28 +262,32 @@ __global__ __launch_bounds__(64 * SL_WAVES) void sgemm_sliced_kernel(SgemmArgs a
 #endif
 }
 
-// Which form, in us (K-contiguous operands; sliced / 64 x 64 / 128 x 128 tiles):
-//   64-wide tiles   16 (100 x 512 x 1024)   11 / 29 / 82        the vector kernel took 36 .. 44 us on a 4-tile product
-//                   80 (300 x 1024 x 1024)  21 / 30 / 82        of K = 256 (sliced form: 4.8) and 318 .. 363 us on
-//                  128 (512 x 1024 x 2048)  41 / 56 / 160       1000 x 2048 x 2048
-//                  160 (1000 x 600 x 2048)  63 / 57 / 159
-//                  256 (1000 x 1024 x 1024) 42 / 31 / 82
-//                  512 (1000 x 2048 x 2048) 152 / 89 / 158      (95 TFLOP/s; matrix peak 157)
-//                 1024 (2048 x 2048 x 1000) 144 / 88 / 85
-//                 2048 (2048 x 4096 x 2048) 606 / 322 / 284     (121 TFLOP/s)
-// A 64-wide tile occupies a compute unit for its whole k range with one wave per SIMD, so below 5/8 of the units' number
-// the sliced form, eight times as many waves on a quarter of the tile, is ahead; 128-wide tiles halve the operand
-// traffic and win once there are two of them per compute unit.
+// Which form, in us (K-contiguous operands; sliced / 64 x 64 tiles by one, by two groups of waves / 128 x 128 tiles):
+//   64-wide tiles   16 (100 x 512 x 1024)   11 / 30 / 25 / 82     the vector kernel took 36 .. 44 us on a 4-tile product
+//                   80 (300 x 1024 x 1024)  21 / 31 / 26 / 83     of K = 256 (sliced form: 4.8) and 318 .. 363 us on
+//                  128 (512 x 1024 x 2048)  41 / 59 / 49 / 161    1000 x 2048 x 2048
+//                  160 (1000 x 600 x 2048)  63 / 60 / 49 / 161
+//                  256 (1000 x 1024 x 1024) 42 / 32 / 28 / 84
+//                  512 (1000 x 2048 x 2048) 155 / 96 / 91 / 160   (93 TFLOP/s; matrix peak 157)
+//                  512 (1000 x 2048 x 16)   11 / 6.3 / 8.2 / 11
+//                 1024 (2048 x 2048 x 1000) 147 / 96 / 92 / 87
+//                 2048 (2048 x 4096 x 2048) 606 / 342 / 330 / 290 (118 TFLOP/s)
+// A 64-wide tile of one group occupies a compute unit for its whole k range with one wave per SIMD; a second group on the
+// other k-steps halves the steps a wave waits through.  Below 5/8 of the units' number the sliced form, eight times as many
+// waves on a quarter of the tile, is ahead; 128-wide tiles halve the operand traffic and win once there are two of them
+// per compute unit.
 template <bool A_KM, bool B_KM>
 void launch_sgemm_form(const SgemmArgs& a, hipStream_t stream) {
   auto tiles = [&](int64_t bm, int64_t bn) { return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
   const int64_t cus = device_compute_units();
   if (tiles(64, 64) * 8 < cus * 5)
     hipLaunchKernelGGL((sgemm_sliced_kernel<A_KM, B_KM>), dim3((unsigned)tiles(32, 32)), dim3(64 * SL_WAVES), 0, stream, a);
+  else if (tiles(128, 128) < 2 * cus && a.K <= 4 * SG_BK)  // (fewer than two steps for each group)
+    hipLaunchKernelGGL((sgemm_tile_kernel<64, 64, 1, A_KM, B_KM>), dim3((unsigned)tiles(64, 64)), dim3(256), 0, stream, a);
   else if (tiles(128, 128) < 2 * cus)
-    hipLaunchKernelGGL((sgemm_tile_kernel<64, 64, A_KM, B_KM>), dim3((unsigned)tiles(64, 64)), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL((sgemm_tile_kernel<64, 64, 2, A_KM, B_KM>), dim3((unsigned)tiles(64, 64)), dim3(512), 0, stream, a);
   else
-    hipLaunchKernelGGL((sgemm_tile_kernel<128, 128, A_KM, B_KM>), dim3((unsigned)tiles(128, 128)), dim3(256), 0, stream, a);
+    hipLaunchKernelGGL((sgemm_tile_kernel<128, 128, 1, A_KM, B_KM>), dim3((unsigned)tiles(128, 128)), dim3(256), 0, stream, a);
 }
 
 }  // namespace

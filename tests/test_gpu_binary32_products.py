@@ -15,6 +15,8 @@ pytestmark = pytest.mark.gpu
     (7, 260, 129, 8, 4),        # sliced form, K = 7 and K = 129
     (1037, 1028, 1031, 3, 4),   # 64-wide tiles in the forward product, dX and dWq; K = 1031, 1037
     (16, 2052, 2051, 2, 4),     # 64-wide tiles on one k-step of 16 (dWq)
+    (1057, 1060, 1025, 3, 4),   # 64-wide tiles, the k-steps dealt to two groups of waves: the last one to the first
+    (129, 2052, 2051, 2, 4),    # ... five steps, the last of one row (dWq)
     (35, 2948, 2949, 2, 4),     # 128-wide tiles (dWq: 24 x 24), K = 35
 ])
 def test_binary32_product_forms(T, i, o, r, g):
