@@ -115,9 +115,27 @@ def _ptr(t) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
-def _stream() -> int:
+_stream_query = None
+
+
+def _find_stream_query():
+    """A function that returns the current device's current stream of the calling thread as an integer handle.  Asked of
+    torch's C layer where it has the two calls: torch.cuda.current_stream() builds a Stream object, 2.7 us of the 8.7 us
+    the host spent on a call, more than some of the kernels take; these two take 0.2."""
     import torch
-    return torch.cuda.current_stream().cuda_stream
+    torch.cuda.current_stream()  # initialises the device, or says why that cannot be
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    device = getattr(torch._C, "_cuda_getDevice", None)
+    if raw is None or device is None:
+        return lambda: torch.cuda.current_stream().cuda_stream
+    return lambda: raw(device())
+
+
+def _stream() -> int:
+    global _stream_query
+    if _stream_query is None:
+        _stream_query = _find_stream_query()
+    return _stream_query()
 
 
 def _check(status: int, where: str) -> None:
