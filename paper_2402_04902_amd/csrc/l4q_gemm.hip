@@ -304,84 +304,107 @@ int device_compute_units() {
 
 namespace {
 
-// Macro tiles of the K-contiguous products.  Both load 32-k stages.
-//   NtFull   256 x 256, 8 waves (2 x 4, two per SIMD, 128 x 64 each): a second wave on the SIMD keeps the matrix pipe busy
-//            while the first waits for a barrier or for operands (1.5 % over 2 x 2); stages loaded in cache-line pairs
-//   NtHalf   128 x 256, 4 waves (64 x 128 each), ring of six stages: 4/7 of a full tile's time for half its work, for
-//            products whose full tiles leave compute units idle
+// Macro tiles of the K-contiguous products; all load 32-k stages.
+//   NtFull     256 x 256, 8 waves (2 x 4, two per SIMD, 128 x 64 each): a second wave on the SIMD keeps the matrix pipe busy
+//              while the first waits for a barrier or for operands (1.5 % over 2 x 2); stages loaded in cache-line pairs
+//   NtHalf     128 x 256, 4 waves (64 x 128 each), ring of six stages: 4/7 of a full tile's time for half its work
+//   NtQuarter  128 x 128, 4 waves (64 x 64 each), ring of eight stages: 2/5 of a full tile's time for a quarter of it
+// the smaller ones for products whose full tiles leave compute units idle.
 typedef gemm::Tile<256, 256, 32, 5, true, 4> NtFull;
 typedef gemm::Tile<128, 256, 32, 6, false, 2> NtHalf;
+typedef gemm::Tile<128, 128, 32, 8, false, 2> NtQuarter;
+enum NtForm { kNtFull, kNtHalf, kNtQuarter };
 
 template <class F> int64_t nt_tiles(int64_t M, int64_t N) {
   return ((M + F::BM - 1) / F::BM) * ((N + F::BN - 1) / F::BN);
 }
 
-// One pass over k: which tile.  In us (full / half; number of full, half tiles on 256 compute units; M x N x K):
-//    86,  172   73 / 45    512 x 11008 x 4096        172,  344   79 / 95    1024 x 11008 x 4096
-//   128,  256   74 / 57   2048 x  4096 x 4096        192,  384   84 / 95    3000 x  4096 x 4096
-//   128,  256  186 / 142  2048 x  4096 x 11008       256,  512  100 / 111   4096 x  4096 x 4096
-//   344,  688  169 / 152  2048 x 11008 x 4096        688, 1376  271 / 309   4096 x 11008 x 4096
-// i.e. rounds of tiles over the units, a round of half tiles counting 4/7.
-bool nt_use_half(int64_t M, int64_t N) {
+// One pass over k: which tile.  In us (full / half / quarter; their numbers on 256 compute units; M x N x K):
+//    32,   64,  128   72 /  41 / 29    512 x  4096 x 4096      172,  344,  688    80 /  94 /  92   1024 x 11008 x 4096
+//    32,   64,  128   39 /  23 / 15   1000 x  2048 x 2048      192,  384,  768    84 /  95 /   -   3000 x  4096 x 4096
+//    64,  128,  256   73 /  42 / 33   1024 x  4096 x 4096      240,  440,  880   118 / 123 / 156   1328 x 10224 x 5120
+//    86,  172,  344   73 /  45 / 60    512 x 11008 x 4096      256,  512, 1024   100 / 111 /   -   4096 x  4096 x 4096
+//   128,  256,  512   74 /  57 / 64   2048 x  4096 x 4096      344,  688, 1376   169 / 152 /   -   2048 x 11008 x 4096
+//    99,  198,  396  158 / 103 / 133  2179 x  2784 x 9216      688, 1376, 2752   271 / 309 /   -   4096 x 11008 x 4096
+// i.e. rounds of tiles over the units, a round of full / half / quarter tiles counting 70 : 40 : 29.
+NtForm nt_one_pass_form(int64_t M, int64_t N) {
   const int64_t cus = device_compute_units();
-  const int64_t full = (nt_tiles<NtFull>(M, N) + cus - 1) / cus, half = (nt_tiles<NtHalf>(M, N) + cus - 1) / cus;
-  return 4 * half < 7 * full;
+  auto rounds = [&](int64_t tiles) { return (tiles + cus - 1) / cus; };
+  const int64_t full = 70 * rounds(nt_tiles<NtFull>(M, N)), half = 40 * rounds(nt_tiles<NtHalf>(M, N));
+  const int64_t quarter = 29 * rounds(nt_tiles<NtQuarter>(M, N));
+  if (quarter < half && quarter < full) return kNtQuarter;
+  return half < full ? kNtHalf : kNtFull;
 }
 
-}  // namespace
-
-// Slices of the k range for a product of few tiles (full tiles on at most half of the compute units; always half tiles
-// then): at most one (tile, slice) per compute unit, each at least four stage pairs (256 k) long, at most 8, no more than
-// keep the partial tiles (slices x M x N x 4 bytes, written and read once) within the size of operand B (N x K x 2
-// bytes), nor more than fit the slices of full tiles; of those the number with the least estimated time: 9 us per 1024 k
-// of a slice, and beyond one slice 6 us for the second launch and the partial tiles at 5 TB/s.  Estimated, measured (us):
-//   301 x 4096 x 4096    4: 23, 25   5: 23, 25   1: 36, 40     512 x 4096 x 11008  4: 44, 52   3: 48, 53   1: 97, 103
-//   512 x 4096 x 4096    3: 28, 29   4: 28, 30   2: 31, 33    1024 x 4096 x 4096   1: 36, 42   2: 37, 42
-// (256 x 256 tiles in as many slices as fill the chip took 35, 63, 38 and 54.)
-int gemm_nt_splitk_slices(int64_t M, int64_t N, int64_t K) {
-  const int64_t full = nt_tiles<NtFull>(M, N), half = nt_tiles<NtHalf>(M, N);
-  const int64_t cus = device_compute_units();
-  if (full <= 0 || 2 * full > cus) return 1;
-  const int64_t pairs = ((K + NtHalf::BK - 1) / NtHalf::BK + 1) / 2;
+// Products of few tiles (full ones on at most half of the compute units): half or quarter tiles in k-slices, at most one
+// (tile, slice) per compute unit, each slice at least four stage pairs (256 k) long, at most 8, no more than keep the
+// partial tiles (slices x M x N x 4 bytes, written and read once) within the size of operand B (N x K x 2 bytes), nor more
+// than fit the slices of full tiles; of those the form with the least estimated time: 9 us (half) or 6.2 us (quarter
+// tiles) per 1024 k of a slice, and beyond one slice 6 us for the second launch and the partial tiles at 5 TB/s.
+// Estimated, measured (us):
+//   301 x 4096 x 4096    quarter x 2 22, 23   half x 4 23, 25     512 x 4096 x 11008  half x 4 44, 52   quarter x 2 46, 52
+//   512 x 4096 x 4096    quarter x 2 25, 26   half x 3 28, 29     100 x 4096 x 4096   quarter x 5 14, 15   half x 6 16, 19
+//   400 x 2048 x 2048    quarter x 1 12, 13   half x 3 19, 21    1024 x 4096 x 4096   quarter x 1 25, 33   half x 1 36, 42
+// (256 x 256 tiles in as many slices as fill the chip took 35, 63, 38, 22, 25 and 54.)
+struct NtPlan {
+  NtForm form;
+  int slices;
+};
+NtPlan nt_plan(int64_t M, int64_t N, int64_t K) {
+  const int64_t full = nt_tiles<NtFull>(M, N), cus = device_compute_units();
+  if (full <= 0 || 2 * full > cus) return {nt_one_pass_form(M, N), 1};
+  const int64_t pairs = ((K + 31) / 32 + 1) / 2;
   int64_t most = cus / full;
-  if (most > cus / half) most = cus / half;
   if (most > pairs / 4) most = pairs / 4;
   if (most > 8) most = 8;
   if (most > K / (2 * M)) most = K / (2 * M);
-  int best = 1;
-  double best_us = 9.0 * (double)K / 1024.0;
-  for (int s = 2; s <= most; ++s) {
-    const double us = 9.0 * (double)K / 1024.0 / s + 6.0 + (double)s * (double)M * (double)N * 8.0 / 5e6;
-    if (us < best_us) {
-      best = s;
-      best_us = us;
+  if (most < 1) most = 1;
+  NtPlan best = {nt_one_pass_form(M, N), 1};
+  double best_us = 1e30;
+  for (NtForm form : {kNtQuarter, kNtHalf}) {
+    const int64_t tiles = form == kNtHalf ? nt_tiles<NtHalf>(M, N) : nt_tiles<NtQuarter>(M, N);
+    const double pass_us = (form == kNtHalf ? 9.0 : 6.2) * (double)K / 1024.0 * (double)((tiles + cus - 1) / cus);
+    for (int s = 1; s <= most && (s == 1 || tiles * s <= cus); ++s) {
+      const double us = pass_us / s + (s > 1 ? 6.0 + (double)s * (double)M * (double)N * 8.0 / 5e6 : 0.0);
+      if (us < best_us) {
+        best = {form, s};
+        best_us = us;
+      }
     }
   }
   return best;
 }
 
+}  // namespace
+
+int gemm_nt_splitk_slices(int64_t M, int64_t N, int64_t K) { return nt_plan(M, N, K).slices; }
+
 namespace {
 
 // `f` with the tile type and whether rows of A need masking past K_a (an instance of its own, so that the usual shapes do
 // not pay for the selection)
-template <class Fn> void nt_dispatch(bool half, bool mask, Fn&& f) {
-  if (half && mask) f(NtHalf(), std::true_type());
-  else if (half) f(NtHalf(), std::false_type());
-  else if (mask) f(NtFull(), std::true_type());
-  else f(NtFull(), std::false_type());
+template <class Fn> void nt_dispatch(NtForm form, bool mask, Fn&& f) {
+  auto with_mask = [&](auto tile) {
+    if (mask) f(tile, std::true_type());
+    else f(tile, std::false_type());
+  };
+  if (form == kNtQuarter) with_mask(NtQuarter());
+  else if (form == kNtHalf) with_mask(NtHalf());
+  else with_mask(NtFull());
 }
 
 }  // namespace
 
 void launch_gemm_bf16_nt(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, int64_t M, int64_t N,
                          int64_t K, int64_t K_a, bf16_t* C, int64_t ldc, hipStream_t stream, float* partial) {
-  const int slices = partial ? gemm_nt_splitk_slices(M, N, K) : 1;
-  nt_dispatch(slices > 1 || nt_use_half(M, N), K_a != K, [&](auto tile, auto mask) {
+  const NtPlan plan = partial ? nt_plan(M, N, K) : NtPlan{nt_one_pass_form(M, N), 1};
+  const int slices = plan.slices;
+  nt_dispatch(plan.form, K_a != K, [&](auto tile, auto mask) {
     typedef decltype(tile) F;
     constexpr bool MASK = decltype(mask)::value;
     const int tiles_m = (int)((M + F::BM - 1) / F::BM), tiles_n = (int)((N + F::BN - 1) / F::BN);
     if (slices > 1) {
-      if constexpr (std::is_same<F, NtHalf>::value) {
+      if constexpr (!std::is_same<F, NtFull>::value) {
         hipLaunchKernelGGL((gemm_bf16_nt_splitk_kernel<F, MASK, true>),
                            dim3((unsigned)(tiles_m * tiles_n), (unsigned)slices), dim3(F::NT), 0, stream, A, lda, B, ldb,
                            (int)M, (int)N, (int)K, (int)K_a, partial, tiles_m, tiles_n);
@@ -399,7 +422,7 @@ void launch_gemm_bf16_nt(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t 
 
 void launch_gemm_bf16_nt_rank(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t M, int64_t N, int64_t K, int64_t K_a,
                               bf16_t* C, int64_t ldc, const RankTerm& term, hipStream_t stream) {
-  nt_dispatch(nt_use_half(M, N), K_a != K, [&](auto tile, auto mask) {
+  nt_dispatch(nt_one_pass_form(M, N), K_a != K, [&](auto tile, auto mask) {
     typedef decltype(tile) F;
     const int tiles_m = (int)((M + F::BM - 1) / F::BM), tiles_n = (int)((N + F::BN - 1) / F::BN);
     hipLaunchKernelGGL((gemm_bf16_nt_rank_kernel<F, decltype(mask)::value>), dim3((unsigned)(tiles_m * tiles_n)),
@@ -446,7 +469,7 @@ void launch_dw_masked_products(const LayerDims& d, const bf16_t* dWm, const bf16
     hipLaunchKernelGGL((gemm_bf16_nt_splitk_kernel<F, false, false>), dim3((unsigned)(tiles_m * tiles_n), (unsigned)sb),
                        dim3(F::NT), 0, stream, dWm, d.i, A, d.i, (int)d.o, d.r, (int)d.i, (int)d.i, rawB, tiles_m, tiles_n);
   };
-  if (d.r <= 128) thin_b(gemm::Tile<128, 128, 32, 8, false, 2>());
+  if (d.r <= 128) thin_b(NtQuarter());
   else thin_b(NtFull());
   // rawA [sa][r, i] = B [o, r]^T . dWm [o, i]: both K-major, k = o
   {

@@ -1,4 +1,4 @@
-"""Forward and dX products in 128 x 256 macro tiles (few or unevenly filled 256 x 256 ones): token counts one off a tile,
+"""Forward and dX products in 128 x 256 and 128 x 128 macro tiles (few or unevenly filled 256 x 256 ones): token counts one off a tile,
 rows that end inside a k-step (masked), one pass and k-slices, fewer stages than the ring holds, against the oracle."""
 import pytest
 
@@ -12,10 +12,12 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("T,i,o,g", [
     (1, 32, 8, 32),          # one stage of k
-    (129, 96, 264, 32),      # three stages, two tile rows, the second one token
+    (129, 96, 264, 32),      # three stages, two tile rows, the second one token (128 x 128 tiles, as the next)
     (127, 2056, 1096, 8),    # k-slices (forward), rows that end inside the last one's last stage
-    (300, 264, 16400, 8),    # one pass over 195 half tiles (forward, masked), k-slices in dX
+    (300, 264, 16400, 8),    # one pass over 195 128 x 256 tiles (forward, masked), k-slices of 128 x 128 tiles in dX
     (385, 16416, 264, 32),   # the same the other way round; four tile rows, the last one token
+    (1000, 2080, 2056, 32),  # one pass over 128 128 x 128 tiles, both ends ragged
+    (500, 11008, 4096, 128), # four k-slices of 128 x 256 tiles (forward)
 ])
 def test_half_tiles(T, i, o, g):
     # No outlier weights: in rows this short one outlier's rounding to bfloat16, up to 2^-9 * 1.6 * |x| with |x| to 4.5, is
@@ -24,6 +26,6 @@ def test_half_tiles(T, i, o, g):
     run_case(LayerSpec(f"half_{T}x{i}x{o}", T, i, o, 8, 16.0, 4, g, DTYPE_BF16, outliers=False), seed=T, shrink=0.8)
 
 
-@pytest.mark.parametrize("T,i,o,g", [(129, 1032, 264, 8), (300, 264, 16400, 8)])
+@pytest.mark.parametrize("T,i,o,g", [(129, 1032, 264, 8), (300, 264, 16400, 8), (641, 1024, 11000, 8)])
 def test_half_tiles_with_rank_term(T, i, o, g):
     _run(LayerSpec(f"half_ql_{T}x{i}x{o}", T, i, o, 20, 40.0, 4, g, DTYPE_BF16, outliers=False), seed=T)
