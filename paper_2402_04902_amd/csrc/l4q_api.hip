@@ -225,10 +225,10 @@ void gemm_nt(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, int64_t
   l4q::launch_gemm_bf16_nt(A, lda, B, ldb, M, N, K, K_algorithmic, C, ldc, stream, splitk);
 }
 
-// The same with the QAT-LoRA layer's LoRA term added to the product.
+// The same with the QAT-LoRA layer's LoRA term added to the product (not counted in the FLOPs).
 void gemm_nt_rank(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t M, int64_t N, int64_t K, int64_t K_algorithmic,
                   bf16_t* C, const l4q::RankTerm& term, hipStream_t stream) {
-  Timed t(stream, kKindGemm, 2.0 * (double)M * (double)N * (double)(K_algorithmic + term.r));
+  Timed t(stream, kKindGemm, 2.0 * (double)M * (double)N * (double)K_algorithmic);
   l4q::launch_gemm_bf16_nt_rank(A, lda, B, M, N, K, K_algorithmic, C, N, term, stream);
 }
 
