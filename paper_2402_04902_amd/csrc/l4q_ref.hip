@@ -250,8 +250,40 @@ __global__ __launch_bounds__(256) void adamw_kernel(AdamwArgs a) {
   }
 }
 
+// The same for tensors whose sizes are all multiples of 4 (every bfloat16 layer): 4 consecutive elements per thread,
+// 16-byte accesses.  Bound: memory and a launch (0.9 M elements, 27 MB, of a 4096 x 11008 layer at rank 16: 6.0
+// against 6.8 us).
+__global__ __launch_bounds__(256) void adamw_quad_kernel(AdamwArgs a) {
+  const int64_t e = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
+  int t = 0;
+  int64_t k = e;
+  while (t < 4 && k >= a.n[t]) { k -= a.n[t]; ++t; }
+  if (t == 4) return;
+  float g[4], p[4], m[4], v[4];
+  load4(a.grad[t] + k, g);
+  load4(a.param[t] + k, p);
+  load4(a.m + e, m);
+  load4(a.v + e, v);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    m[c] = a.beta1 * m[c] + (1.f - a.beta1) * g[c];
+    v[c] = a.beta2 * v[c] + (1.f - a.beta2) * g[c] * g[c];
+    const float mhat = m[c] / a.bias1, vhat = v[c] / a.bias2;
+    p[c] = p[c] - a.lr * a.weight_decay * p[c] - a.lr * mhat / (sqrtf(vhat) + a.eps);
+  }
+  store4(a.m + e, m);
+  store4(a.v + e, v);
+  store4(a.param[t] + k, p);
+  if (t < 2 && a.copy_bf16[t]) store4(a.copy_bf16[t] + k, p);
+}
+
 void launch_adamw(const AdamwArgs& a, hipStream_t stream) {
   const int64_t n = a.n[0] + a.n[1] + a.n[2] + a.n[3];
+  // (the moments are one array for all four tensors: a tensor of any other size would misalign the next one's)
+  if (((a.n[0] | a.n[1] | a.n[2] | a.n[3]) & 3) == 0 && n < (1ll << 33)) {  // (one launch's threads)
+    hipLaunchKernelGGL(adamw_quad_kernel, dim3((unsigned)((n / 4 + 255) / 256)), dim3(256), 0, stream, a);
+    return;
+  }
   int64_t blocks = (n + 255) / 256;
   if (blocks > 4096) blocks = 4096;
   hipLaunchKernelGGL(adamw_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, a);
