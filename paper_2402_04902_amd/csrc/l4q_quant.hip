@@ -51,34 +51,34 @@ __device__ __forceinline__ float bword_value(const bf16_t*, uint32_t w, int half
   return __uint_as_float(half ? (w & 0xFFFF0000u) : (w << 16));
 }
 
-template <class T>
+template <class T, int RPW>
 __device__ __forceinline__ void lora_rows(const LayerDims& d, const T* __restrict__ A, const T* __restrict__ B,
-                                          unsigned jc, int64_t pw, int lane, float (&acc)[MQ_RPW][4]) {
+                                          unsigned jc, int64_t pw, int lane, float (&acc)[RPW][4]) {
   typedef typename Raw4<T>::type raw4_t;
   constexpr int PER = BWord<T>::PER;
 #pragma unroll
-  for (int rr = 0; rr < MQ_RPW; ++rr)
+  for (int rr = 0; rr < RPW; ++rr)
 #pragma unroll
     for (int c = 0; c < 4; ++c) acc[rr][c] = 0.f;
   {  // rows of B are whole 32-bit words (binary32 storage; bfloat16 rows with an even rank): scalar path, any rank
     const int nw = d.r / PER;
     const uint32_t* Bw = reinterpret_cast<const uint32_t*>(B);
-    const uint32_t* brow[MQ_RPW];
+    const uint32_t* brow[RPW];
 #pragma unroll
-    for (int rr = 0; rr < MQ_RPW; ++rr) brow[rr] = Bw + (pw + rr < d.o ? pw + rr : d.o - 1) * nw;
+    for (int rr = 0; rr < RPW; ++rr) brow[rr] = Bw + (pw + rr < d.o ? pw + rr : d.o - 1) * nw;
     const T* ak = A + jc;
 #pragma unroll 2
     for (int w = 0; w < nw; ++w) {
-      uint32_t bw[MQ_RPW];
+      uint32_t bw[RPW];
 #pragma unroll
-      for (int rr = 0; rr < MQ_RPW; ++rr) bw[rr] = brow[rr][w];
+      for (int rr = 0; rr < RPW; ++rr) bw[rr] = brow[rr][w];
 #pragma unroll
       for (int h = 0; h < PER; ++h) {
         float a[4];
         unpack4(*reinterpret_cast<const raw4_t*>(ak), a);
         ak += d.i;
 #pragma unroll
-        for (int rr = 0; rr < MQ_RPW; ++rr) {
+        for (int rr = 0; rr < RPW; ++rr) {
           const float bk = bword_value((const T*)nullptr, bw[rr], h);
 #pragma unroll
           for (int c = 0; c < 4; ++c) acc[rr][c] = lora_mac<T>(acc[rr][c], bk, a[c]);
@@ -176,15 +176,15 @@ __device__ __forceinline__ void lora_rows_mfma(const LayerDims& d, const bf16_t*
 #endif
 }
 
-template <class T, class F>
+template <class T, int RPW, class F>
 __device__ __forceinline__ void lora_sums(const LayerDims& d, const T* __restrict__ A, const T* __restrict__ B,
                                           unsigned jc, int64_t jblk, int64_t pblk, int64_t pw, int lane, int wave,
-                                          unsigned char* lds, float (&acc)[MQ_RPW][4], F&& request_row_data) {
+                                          unsigned char* lds, float (&acc)[RPW][4], F&& request_row_data) {
   if constexpr (std::is_same<T, bf16_t>::value) {
     lora_rows_mfma(d, A, B, jblk, pblk, lane, wave, reinterpret_cast<float*>(lds), acc, request_row_data);
   } else {
     request_row_data();
-    lora_rows<T>(d, A, B, jc, pw, lane, acc);
+    lora_rows<T, RPW>(d, A, B, jc, pw, lane, acc);
   }
 }
 
@@ -206,7 +206,7 @@ __device__ __forceinline__ QuantFast quantize_fast(float wc, float s, float b, f
 // MODE 0: any combination of outputs.  MODE 1: the forward pass (dequantized Wq only).  MODE 2: the fused
 // backward pass (Wq^T and the d(Wq)/d(scale) factor only).  The specialisations drop the arithmetic of the
 // outputs they do not write; all three compute w, the code and the mask with the same instructions.
-template <class T, int MODE>
+template <class T, int MODE, int RPW = MQ_RPW>
 __global__ __launch_bounds__(MQ_THREADS) void merge_quant_tile_kernel(LayerDims d, const T* __restrict__ W0,
                                                                        const T* __restrict__ A,
                                                                        const T* __restrict__ B,
@@ -224,7 +224,7 @@ __global__ __launch_bounds__(MQ_THREADS) void merge_quant_tile_kernel(LayerDims 
   const bool col_ok = j0 < d.i;
   const unsigned jc = col_ok ? (unsigned)j0 : 0u;                      // clamped column for loads (32-bit lane offset)
   const unsigned j32 = (unsigned)j0;
-  const int64_t pw = (int64_t)blockIdx.y * MQ_ROWS + wave * MQ_RPW;    // first row of this wave
+  const int64_t pw = (int64_t)blockIdx.y * (RPW * (MQ_THREADS / 64)) + wave * RPW;  // first row of this wave
   const int64_t G = d.i / d.g;
   const unsigned q = jc / (unsigned)d.g;  // 4 consecutive columns lie in one group because g % 4 == 0
   const float zero4[4] = {0.f, 0.f, 0.f, 0.f};
@@ -243,11 +243,11 @@ __global__ __launch_bounds__(MQ_THREADS) void merge_quant_tile_kernel(LayerDims 
       const_cast<float*>(zero), 0, BUF ? (int)(d.o * G * 4) : 0, 0x00020000);
 
   // row data: every load is requested before the rank sums are consumed
-  raw4_t w0raw[MQ_RPW];
-  float sv[MQ_RPW], bv[MQ_RPW];
+  raw4_t w0raw[RPW];
+  float sv[RPW], bv[RPW];
   auto request_row_data = [&]() {
 #pragma unroll
-    for (int rr = 0; rr < MQ_RPW; ++rr) {
+    for (int rr = 0; rr < RPW; ++rr) {
       const int64_t pc = pw + rr < d.o ? pw + rr : d.o - 1;
       if constexpr (BUF) {
         const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(rsrcW0, (int)(jc * 2), (int)(pc * d.i * 2), 0);
@@ -263,12 +263,12 @@ __global__ __launch_bounds__(MQ_THREADS) void merge_quant_tile_kernel(LayerDims 
     }
   };
 
-  float acc[MQ_RPW][4];
-  lora_sums<T>(d, A, B, jc, jblk, (int64_t)blockIdx.y * MQ_ROWS, pw, lane, wave, tile, acc, request_row_data);
+  float acc[RPW][4];
+  lora_sums<T, RPW>(d, A, B, jc, jblk, (int64_t)blockIdx.y * MQ_ROWS, pw, lane, wave, tile, acc, request_row_data);
 
-  float wqkeep[want_t ? MQ_RPW : 1][4];  // dequantized values of all rows, for the transposed output
+  float wqkeep[want_t ? RPW : 1][4];  // dequantized values of all rows, for the transposed output
 #pragma unroll
-  for (int rr = 0; rr < MQ_RPW; ++rr) {
+  for (int rr = 0; rr < RPW; ++rr) {
     const int64_t p = pw + rr;
     const bool ok = col_ok && p < d.o;
     float w0[4], wc[4], fg[4], wqv[4];
@@ -339,14 +339,14 @@ __global__ __launch_bounds__(MQ_THREADS) void merge_quant_tile_kernel(LayerDims 
     }
   }
 
-  if (want_t && (MODE == 2 || out.wqT)) {  // uniform: transpose the 64 x 256 tile through LDS
+  if constexpr (want_t) if (MODE == 2 || out.wqT) {  // uniform: transpose the 64 x 256 tile through LDS
     // column c of this lane, rows of this wave: 8 bf16 = one 16-byte LDS write
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-      uint32_t tp[MQ_RPW / 2];
+      uint32_t tp[RPW / 2];
 #pragma unroll
-      for (int h = 0; h < MQ_RPW / 2; ++h) tp[h] = pack_bf16x2(wqkeep[want_t ? 2 * h : 0][c], wqkeep[want_t ? 2 * h + 1 : 0][c]);
-      unsigned char* dst = tile + (lane * 4 + c) * MQ_TROW + wave * (MQ_RPW * 2);
+      for (int h = 0; h < RPW / 2; ++h) tp[h] = pack_bf16x2(wqkeep[want_t ? 2 * h : 0][c], wqkeep[want_t ? 2 * h + 1 : 0][c]);
+      unsigned char* dst = tile + (lane * 4 + c) * MQ_TROW + wave * (RPW * 2);
       *reinterpret_cast<uint4*>(dst) = make_uint4(tp[0], tp[1], tp[2], tp[3]);
     }
     __syncthreads();
@@ -405,7 +405,7 @@ __global__ __launch_bounds__(MQ_THREADS) void weight_stats_tile_kernel(LayerDims
     }
   };
   float acc[MQ_RPW][4];
-  lora_sums<T>(d, A, B, jc, (int64_t)blockIdx.x * MQ_COLS, (int64_t)blockIdx.y * MQ_ROWS, pw, lane, wave, lds, acc,
+  lora_sums<T, MQ_RPW>(d, A, B, jc, (int64_t)blockIdx.x * MQ_COLS, (int64_t)blockIdx.y * MQ_ROWS, pw, lane, wave, lds, acc,
                request_row_data);
 
 #pragma unroll
@@ -595,12 +595,37 @@ void launch_merge_quant(const LayerDims& d, const T* W0, const T* A, const T* B,
   const int64_t rows = out.wqT && out.ld_wqT > d.o ? out.ld_wqT : d.o;
   dim3 grid((unsigned)((d.i + MQ_COLS - 1) / MQ_COLS), (unsigned)((rows + MQ_ROWS - 1) / MQ_ROWS));
   const bool misc = out.codes || out.wcomb || out.mask;
-  if (out.wq && !out.wqT && !out.fgrad && !misc)
-    hipLaunchKernelGGL((merge_quant_tile_kernel<T, 1>), grid, dim3(MQ_THREADS), 0, stream, d, W0, A, B, scale, zero, out);
-  else if (!out.wq && out.wqT && out.fgrad && !misc)
-    hipLaunchKernelGGL((merge_quant_tile_kernel<T, 2>), grid, dim3(MQ_THREADS), 0, stream, d, W0, A, B, scale, zero, out);
-  else
+  if constexpr (std::is_same<T, float>::value) {
+    // A wave walks its rows through one chain of loads, rank sums and divides, so fewer rows per wave end sooner until
+    // the chip is full; then they only read A more often.  A layer's two passes at rank 16 with 1 / 4 / 8 rows per wave, in
+    // us more than with 2 (8 was the only form before): 256 x 2048 (128 workgroups at 2 rows) -2 / +3 / +9; 2048 x 1024 (512)
+    // +2 / +2 / +7; 2048 x 2048 (1024, the most that are resident at once) +2 / +3 / +7; 2048 x 4096 (2048) +7 / -5 / -3;
+    // 4096 x 11008 +56 / -21 / -7.
+    if (out.wq && !out.wqT && !out.fgrad && !misc) {
+      const int64_t two = (int64_t)grid.x * ((d.o + 15) / 16), cus = device_compute_units();
+      const int rpw = two <= cus / 2 ? 1 : two <= 4 * cus ? 2 : 4;
+      const int64_t gy = (d.o + 8 * rpw - 1) / (8 * rpw);
+      if (gy <= 65535) {  // (a grid's second dimension; the general form below has half as many workgroups)
+        grid.y = (unsigned)gy;
+#define L4Q_MQ_LAUNCH(RPW) \
+  hipLaunchKernelGGL((merge_quant_tile_kernel<T, 1, RPW>), grid, dim3(MQ_THREADS), 0, stream, d, W0, A, B, scale, zero, out)
+        if (rpw == 1) L4Q_MQ_LAUNCH(1);
+        else if (rpw == 2) L4Q_MQ_LAUNCH(2);
+        else L4Q_MQ_LAUNCH(4);
+#undef L4Q_MQ_LAUNCH
+        return;
+      }
+    }
     hipLaunchKernelGGL((merge_quant_tile_kernel<T, 0>), grid, dim3(MQ_THREADS), 0, stream, d, W0, A, B, scale, zero, out);
+    return;
+  } else {
+    if (out.wq && !out.wqT && !out.fgrad && !misc)
+      hipLaunchKernelGGL((merge_quant_tile_kernel<T, 1>), grid, dim3(MQ_THREADS), 0, stream, d, W0, A, B, scale, zero, out);
+    else if (!out.wq && out.wqT && out.fgrad && !misc)
+      hipLaunchKernelGGL((merge_quant_tile_kernel<T, 2>), grid, dim3(MQ_THREADS), 0, stream, d, W0, A, B, scale, zero, out);
+    else
+      hipLaunchKernelGGL((merge_quant_tile_kernel<T, 0>), grid, dim3(MQ_THREADS), 0, stream, d, W0, A, B, scale, zero, out);
+  }
 }
 
 template <class T>
