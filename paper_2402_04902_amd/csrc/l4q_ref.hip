@@ -16,48 +16,51 @@ namespace {
 //   dB[p,k]     = gamma * sum_j (m * dWq)[p,j] A[k,j] (Eq. appen_l4q_b)
 //
 // Bound: memory (dWq and W0 read once; LORA: the masked dWq written), with the IEEE divide and the rank sums close behind.
-// A workgroup takes QG_ROWS weight rows and deals their columns out to its 4 waves in units of 256 (or a whole group where
-// groups are longer), a lane owning 4 consecutive columns of all the rows: A is read once per QG_ROWS rows, and QG_ROWS
-// independent loads per operand are in flight.  One wave per row with one row's loads in flight, the form this replaces,
-// took 137 us on 4096 x 4096 bf16 of the QAT-LoRA layer (now 29: 100 MB at 3.4 TB/s) and 66 us on 2048 x 2048 binary32 at
-// rank 16 (now 32; on 256 x 256, where it is one chain of loads, rank sums and reductions, 8.5 against 10.5).
+// A workgroup takes ROWS weight rows and deals their columns out to its 4 waves in units of 256 (or a whole group where
+// groups are longer), a lane owning 4 consecutive columns of all the rows: A is read once per ROWS rows, and ROWS
+// independent loads per operand are in flight.  One wave per row with one row's loads in flight, the first form, took
+// 137 us on 4096 x 4096 bf16 of the QAT-LoRA layer (now 28: 100 MB at 3.5 TB/s) and 66 us on 2048 x 2048 binary32 at rank
+// 16 (now 27; 4 rows per workgroup 32).
 constexpr int QG_KCHUNK = 16;
-constexpr int QG_ROWS = 4;
 
-// v[64] per lane -> the sum over the wave of v[lane]: each step halves the values held and adds the halves exchanged
-template <int OFF = 32>
-__device__ __forceinline__ float wave_sum_scatter(float (&v)[64], int lane) {
-  const bool upper = (lane & OFF) != 0;
+// v[N] per lane -> the sum over the wave of v[lane % N]: each step halves the values held and adds the halves exchanged
+template <int N, int OFF = N / 2>
+__device__ __forceinline__ float wave_sum_scatter(float (&v)[N], int lane) {
+  if constexpr (OFF > 0) {
+    const bool upper = (lane & OFF) != 0;
 #pragma unroll
-  for (int c = 0; c < OFF; ++c) {
-    const float keep = upper ? v[c + OFF] : v[c], give = upper ? v[c] : v[c + OFF];
-    v[c] = keep + __shfl_xor(give, OFF, 64);
+    for (int c = 0; c < OFF; ++c) {
+      const float keep = upper ? v[c + OFF] : v[c], give = upper ? v[c] : v[c + OFF];
+      v[c] = keep + __shfl_xor(give, OFF, 64);
+    }
+    return wave_sum_scatter<N, OFF / 2>(v, lane);
+  } else {
+    float sum = v[0];
+    for (int off = N; off < 64; off <<= 1) sum += __shfl_xor(sum, off, 64);
+    return sum;
   }
-  if constexpr (OFF > 1) return wave_sum_scatter<OFF / 2>(v, lane);
-  else return v[0];
 }
 
-template <class T, bool LORA>
+template <class T, bool LORA, int ROWS>
 __global__ __launch_bounds__(256, 2) void quant_grads_kernel(LayerDims d, const T* __restrict__ W0,
                                                            const T* __restrict__ A, const T* __restrict__ B,
                                                            const float* __restrict__ scale,
                                                            const float* __restrict__ zero, float* __restrict__ dW,
                                                            float* __restrict__ dscale, float* __restrict__ dzero,
                                                            float* __restrict__ dB) {
-  static_assert(QG_ROWS * QG_KCHUNK == 64, "wave_sum_scatter leaves one of the dB sums in every lane");
   __shared__ float dB_sums[4][64];
-  __shared__ float b_lds[QG_ROWS][LORA ? 256 : 1];  // the rows of B (rank <= 256)
+  __shared__ float b_lds[ROWS][LORA ? 256 : 1];  // the rows of B (rank <= 256)
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t p0 = (int64_t)blockIdx.x * QG_ROWS;
+  const int64_t p0 = (int64_t)blockIdx.x * ROWS;
   const int64_t G = d.i / d.g;
   const int width = d.g / 4 < 64 ? d.g / 4 : 64;  // lanes that share a group within a step of 256 columns
   const int64_t unit = d.g > 256 ? d.g : 256;
-  int64_t row[QG_ROWS];  // rows past the end repeat the last one and store nothing
+  int64_t row[ROWS];  // rows past the end repeat the last one and store nothing
 #pragma unroll
-  for (int q = 0; q < QG_ROWS; ++q) row[q] = p0 + q < d.o ? p0 + q : d.o - 1;
+  for (int q = 0; q < ROWS; ++q) row[q] = p0 + q < d.o ? p0 + q : d.o - 1;
 
   if (LORA) {
-    for (int q = 0; q < QG_ROWS; ++q)
+    for (int q = 0; q < ROWS; ++q)
       for (int k = threadIdx.x; k < d.r; k += 256) b_lds[q][k] = load1(B + row[q] * d.r + k);
     __syncthreads();
   }
@@ -66,23 +69,23 @@ __global__ __launch_bounds__(256, 2) void quant_grads_kernel(LayerDims d, const 
   // the already masked dW.
   for (int k0 = 0; k0 < (LORA ? d.r : 1); k0 += QG_KCHUNK) {
     const int kn = d.r - k0 < QG_KCHUNK ? d.r - k0 : QG_KCHUNK;
-    float dBacc[QG_ROWS * QG_KCHUNK];
+    float dBacc[ROWS * QG_KCHUNK];
 #pragma unroll
-    for (int k = 0; k < QG_ROWS * QG_KCHUNK; ++k) dBacc[k] = 0.f;
+    for (int k = 0; k < ROWS * QG_KCHUNK; ++k) dBacc[k] = 0.f;
     for (int64_t u0 = wave * unit; u0 < d.i; u0 += 4 * unit) {
-      float ds[QG_ROWS] = {}, db[QG_ROWS] = {};
+      float ds[ROWS] = {}, db[ROWS] = {};
       for (int64_t base = u0; base < u0 + unit && base < d.i; base += 256) {
         const int64_t j0 = base + lane * 4;
         const bool active = j0 < d.i;
         const int64_t jc = active ? j0 : 0;
-        float g4[QG_ROWS][4];
+        float g4[ROWS][4];
 #pragma unroll
-        for (int q = 0; q < QG_ROWS; ++q) load4(dW + row[q] * d.i + jc, g4[q]);
+        for (int q = 0; q < ROWS; ++q) load4(dW + row[q] * d.i + jc, g4[q]);
         if (k0 == 0) {
           const int64_t grp = jc / d.g;
-          float w0[QG_ROWS][4], s[QG_ROWS], b[QG_ROWS], acc[QG_ROWS][4];
+          float w0[ROWS][4], s[ROWS], b[ROWS], acc[ROWS][4];
 #pragma unroll
-          for (int q = 0; q < QG_ROWS; ++q) {
+          for (int q = 0; q < ROWS; ++q) {
             load4(W0 + row[q] * d.i + jc, w0[q]);
             s[q] = scale[row[q] * G + grp];
             b[q] = zero[row[q] * G + grp];
@@ -96,13 +99,13 @@ __global__ __launch_bounds__(256, 2) void quant_grads_kernel(LayerDims d, const 
               float a[4];
               load4(ap, a);
 #pragma unroll
-              for (int q = 0; q < QG_ROWS; ++q)
+              for (int q = 0; q < ROWS; ++q)
 #pragma unroll
                 for (int c = 0; c < 4; ++c) acc[q][c] = lora_mac<T>(acc[q][c], b_lds[q][k], a[c]);
             }
           }
 #pragma unroll
-          for (int q = 0; q < QG_ROWS; ++q) {
+          for (int q = 0; q < ROWS; ++q) {
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
               const float wc = LORA ? w0[q][c] + d.gamma * acc[q][c] : w0[q][c];
@@ -123,7 +126,7 @@ __global__ __launch_bounds__(256, 2) void quant_grads_kernel(LayerDims d, const 
             load4(ap, a);
             ap += k + 1 < kn ? d.i : 0;  // (ranks past the last repeat it: those sums are not stored)
 #pragma unroll
-            for (int q = 0; q < QG_ROWS; ++q)
+            for (int q = 0; q < ROWS; ++q)
 #pragma unroll
               for (int c = 0; c < 4; ++c)
                 dBacc[q * QG_KCHUNK + k] = fmaf(active ? g4[q][c] : 0.f, a[c], dBacc[q * QG_KCHUNK + k]);
@@ -131,7 +134,7 @@ __global__ __launch_bounds__(256, 2) void quant_grads_kernel(LayerDims d, const 
         }
         if (k0 == 0 && (d.g <= 256 || base + 256 >= u0 + unit)) {  // the end of the lanes' groups
 #pragma unroll
-          for (int q = 0; q < QG_ROWS; ++q) {
+          for (int q = 0; q < ROWS; ++q) {
             const float ds_sum = wave_sum_width(ds[q], width), db_sum = wave_sum_width(db[q], width);
             if (active && (lane & (width - 1)) == 0 && p0 + q < d.o) {
               const int64_t at = row[q] * G + j0 / d.g;
@@ -145,11 +148,11 @@ __global__ __launch_bounds__(256, 2) void quant_grads_kernel(LayerDims d, const 
       }
     }
     if (LORA) {
-      dB_sums[wave][lane] = wave_sum_scatter(dBacc, lane);
+      dB_sums[wave][lane] = wave_sum_scatter<ROWS * QG_KCHUNK>(dBacc, lane);
       __syncthreads();
       if (wave == 0) {
         const int q = lane / QG_KCHUNK, k = lane % QG_KCHUNK;
-        if (k < kn && p0 + q < d.o) {
+        if (q < ROWS && k < kn && p0 + q < d.o) {
           const float v = d.gamma * (((dB_sums[0][lane] + dB_sums[1][lane]) + dB_sums[2][lane]) + dB_sums[3][lane]);
           float* dst = dB + (p0 + q) * d.r + k0 + k;
           *dst = d.accumulate ? *dst + v : v;
@@ -293,13 +296,21 @@ template <class T>
 void launch_quant_grads(const LayerDims& d, const T* W0, const T* A, const T* B, const float* scale,
                         const float* zero, float* dWq_inout, float* dscale, float* dzero, float* dB,
                         hipStream_t stream) {
-  dim3 grid((unsigned)((d.o + QG_ROWS - 1) / QG_ROWS));
-  if (dB)
-    hipLaunchKernelGGL((quant_grads_kernel<T, true>), grid, dim3(256), 0, stream, d, W0, A, B, scale, zero, dWq_inout,
-                       dscale, dzero, dB);
-  else
-    hipLaunchKernelGGL((quant_grads_kernel<T, false>), grid, dim3(256), 0, stream, d, W0, A, B, scale, zero, dWq_inout,
-                       dscale, dzero, dB);
+  // Rows per workgroup: 2, and 1 where 2 leave compute units without a workgroup.  The rank sums and 16 dB sums per row take
+  // registers: 2 rows leave 3 waves per SIMD where 4 leave 2.  Forward + backward of a binary32 layer at rank 16, 1 / 2 / 4
+  // rows, in us: 4096 x 4096 293 / 275 / 305; 2048 x 2048 111 / 109 / 114; 2048 x 1024 78 / 76 / 88; 2048 x 256 56 / 59 / 68;
+  // 256 x 256 at rank 8 33.6 / 34.7 / 38.4.  Unfused backward of a bfloat16 one: 4096 x 4096 152 / 134 / 162, at rank 64
+  // 361 / 265 / 345.  Without LoRA terms (this kernel alone, 4096 x 4096): 28.7 / 28.4 / 31.1.
+  const int rows = (d.o + 1) / 2 > device_compute_units() ? 2 : 1;
+  dim3 grid((unsigned)((d.o + rows - 1) / rows));
+#define L4Q_QG_LAUNCH(LORA, ROWS)                                                                                    \
+  hipLaunchKernelGGL((quant_grads_kernel<T, LORA, ROWS>), grid, dim3(256), 0, stream, d, W0, A, B, scale, zero, dWq_inout, \
+                     dscale, dzero, dB)
+  if (dB && rows == 2) L4Q_QG_LAUNCH(true, 2);
+  else if (dB) L4Q_QG_LAUNCH(true, 1);
+  else if (rows == 2) L4Q_QG_LAUNCH(false, 2);
+  else L4Q_QG_LAUNCH(false, 1);
+#undef L4Q_QG_LAUNCH
 }
 
 template void launch_quant_grads<float>(const LayerDims&, const float*, const float*, const float*, const float*,
