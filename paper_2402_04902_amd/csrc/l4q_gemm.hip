@@ -75,9 +75,12 @@ __device__ __forceinline__ void store_tile(gemm::Accum<T>& acc, int M, int N, vo
   }
 }
 
-// Adds gamma U . M^T (see RankTerm) to the tile's accumulators, operands straight from memory: gamma U is binary32 and
-// goes through the bfloat16 matrix op as the exact sum of three bfloat16 parts (8 significand bits each), so the product
-// is what binary32 operands would give.  At most 3 r / 16 matrix ops per accumulator tile against K / 16 of the main loop.
+// Leaves gamma U . M^T (see RankTerm) in the tile's accumulators, zero on entry, operands straight from memory: U is
+// binary32 and goes through the bfloat16 matrix op as the exact sum of three bfloat16 parts (8 significand bits each, cut
+// off rather than rounded, so that no part of a finite value is infinite), so the product is what binary32 operands would
+// give.  A non-finite M meets the first part alone: the others may be zero or of either sign, and would make NaN of an
+// infinite sum.  gamma scales the sum, as in gamma (U . M^T): gamma U by itself may overflow.
+// At most 3 r / 16 matrix ops per accumulator tile against K / 16 of the main loop.
 template <class T>
 __device__ __forceinline__ void add_rank_term(gemm::Accum<T>& acc, const RankTerm& t, int M, int N, int m0, int n0) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -106,6 +109,17 @@ __device__ __forceinline__ void add_rank_term(gemm::Accum<T>& acc, const RankTer
         fb[b] = f.v;
       }
     }
+    bf16x8_t fin[T::TN];  // fb with its infinities and NaN taken out
+#pragma unroll
+    for (int b = 0; b < T::TN; ++b) {
+      union { uint32_t w[4]; bf16x8_t v; } f;
+      f.v = fb[b];
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        f.w[e] = ((f.w[e] & 0x7F80u) == 0x7F80u ? 0u : f.w[e] & 0xFFFFu) |
+                 ((f.w[e] & 0x7F800000u) == 0x7F800000u ? 0u : f.w[e] & 0xFFFF0000u);
+      fin[b] = f.v;
+    }
     float u[T::TM][8];  // all rows requested before the first is used
 #pragma unroll
     for (int a = 0; a < T::TM; ++a) {
@@ -124,22 +138,27 @@ __device__ __forceinline__ void add_rank_term(gemm::Accum<T>& acc, const RankTer
       union { bf16_t h[8]; bf16x8_t v; } part[3];
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        float x = kb + e < t.r ? t.gamma * u[a][e] : 0.f;
+        float x = kb + e < t.r ? u[a][e] : 0.f;
+        const bool finite = fabsf(x) <= 3.4028235e38f;
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
-          const bf16_t hi = f32_to_bf16(x);
-          part[q].h[e] = hi;
-          const float back = bf16_to_f32(hi);
-          x = fabsf(back) <= 3.4028235e38f ? x - back : 0.f;  // exact; an infinity has no remainder
+          part[q].h[e] = finite ? (bf16_t)(__float_as_uint(x) >> 16) : f32_to_bf16(x);
+          x = finite ? x - bf16_to_f32(part[q].h[e]) : 0.f;  // exact; an infinity has no remainder
         }
       }
 #pragma unroll
       for (int q = 2; q >= 0; --q)
 #pragma unroll
         for (int b = 0; b < T::TN; ++b)
-          acc.v[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[b], part[q].v, acc.v[a][b], 0, 0, 0);
+          acc.v[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(q == 0 ? fb[b] : fin[b], part[q].v, acc.v[a][b], 0, 0, 0);
     }
   }
+#pragma unroll
+  for (int a = 0; a < T::TM; ++a)
+#pragma unroll
+    for (int b = 0; b < T::TN; ++b)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc.v[a][b][e] *= t.gamma;
 #endif
 }
 
