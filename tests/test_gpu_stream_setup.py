@@ -77,3 +77,32 @@ def test_error_sums(i, o, r, g, dtype):
     # equally far: well below 1e-5 of sums that average a quarter of a step per weight
     assert np.allclose(e[:2], want, rtol=1e-5, atol=0), (e, want)
     assert np.array_equal(e[:2], e[4:6])
+
+
+@pytest.mark.parametrize("method", [0, 1, 2])
+@pytest.mark.parametrize("i,o,g", [(96, 40, 32), (320, 40, 64), (768, 40, 256)])
+def test_init_with_nan(method, i, o, g):
+    """Rank 8 takes the streaming pass, rank 4 the general one: the same weight (B = 0) has to come out the same, bit for
+    bit, also where a group is partly or wholly NaN."""
+    import torch
+    from paper_2402_04902_amd import binding
+    out = []
+    for r in (8, 4):
+        spec = LayerSpec(f"init_nan_{o}x{i}_g{g}_r{r}", 8, i, o, r, 2.0 * r, 3, g, DTYPE_BF16)
+        print("case", spec.name, method, flush=True)
+        arrs = inputs.make_layer_inputs(LayerSpec("w", 8, i, o, 8, 16.0, 3, g, DTYPE_BF16), seed=g)
+        layer = binding.upload(LayerSpec("w", 8, i, o, 8, 16.0, 3, g, DTYPE_BF16), arrs)
+        layer.W0[3, :g] = float("nan")              # a whole group
+        layer.W0[o - 1, g:2 * g - 1] = float("nan")  # all of a group but its last weight
+        layer.W0[5, 7] = float("nan")
+        layer.W0[9, 2] = float("inf")
+        layer.W0[10, 1] = -float("inf")
+        A = layer.A[:r].contiguous()
+        B = torch.zeros((o, r), dtype=torch.bfloat16, device=A.device)
+        scale, zero = torch.full_like(layer.scale, 7.0), torch.full_like(layer.zero, 7.0)
+        binding.l4q_init_qparams(binding.make_desc(spec), layer.W0, A, B, method, scale, zero)
+        torch.cuda.synchronize()
+        out.append(torch.stack([scale, zero]).cpu())
+    streamed, general = out
+    assert torch.equal(torch.isnan(streamed), torch.isnan(general))
+    assert torch.equal(torch.nan_to_num(streamed, nan=7.0), torch.nan_to_num(general, nan=7.0))
