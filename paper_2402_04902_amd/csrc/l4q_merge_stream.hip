@@ -600,6 +600,9 @@ bool merge_quant_stream_supported(const LayerDims& d, const MergeQuantOut<bf16_t
   const bool fwd = out.wq && !out.wqT && !out.fgrad && !misc;
   const bool bwd = !out.wq && out.wqT && !misc;
   const bool exp = !out.wq && !out.wqT && !out.fgrad && misc;
+  // A and B are addressed with byte offsets below 2^31 (W0 and the outputs stay below 2^30 by the library's size limits,
+  // but a factor of rank 256 next to a few rows or columns does not)
+  if ((d.i > d.o ? d.i : d.o) * d.r * 2 >= (1ll << 31)) return false;
   if (out.packed || out.errors || out.init_scale)  // each of them alone
     return d.r % 8 == 0 && d.g >= 32 && (!out.packed || d.i % 32 == 0) && (!out.init_scale || d.g <= 256);
   const bool blocks = (!out.wq || out.ld_wq % 32 == 0) && (!out.wqT || out.ld_wqT % 32 == 0);
