@@ -562,7 +562,8 @@ int l4q_qatlora_forward(const l4q_desc* desc, const void* X, const void* W0, con
   if (!aligned(workspace, kWsAlign)) return L4Q_ERR_ALIGN;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   const LayerDims d = dims_of(desc);
-  LayerDims dq = d;   // the quantizer sees the frozen weight alone
+  LayerDims dq = d;   // the quantizer sees the frozen weight alone: no rank term, A and B are not read for it
+  dq.r = 0;
   dq.gamma = 0.f;
   (void)hipGetLastError();
   if (desc->dtype == L4Q_DTYPE_BF16) {
@@ -602,6 +603,7 @@ int l4q_qatlora_backward(const l4q_desc* desc, const void* X, const void* dY, co
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   const LayerDims d = dims_of(desc);
   LayerDims dq = d;
+  dq.r = 0;
   dq.gamma = 0.f;
   (void)hipGetLastError();
   if (desc->dtype == L4Q_DTYPE_BF16) {

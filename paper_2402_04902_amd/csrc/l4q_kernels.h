@@ -12,7 +12,7 @@ typedef uint16_t bf16_t;
 
 struct LayerDims {
   int64_t T, i, o;
-  int r, bits, g;
+  int r, bits, g;  // r = 0 (merge pass only): no rank term, Wc = W0
   float gamma;   // (float)alpha / (float)r
   float qn, qp;  // Q_N, Q_P as floats
   bool accumulate = false;  // backward: add dA, dB, dscale, dzero to what the outputs hold instead of overwriting

@@ -108,7 +108,7 @@ static_assert(64 * MS_TPITCH <= MS_WAVE_LDS, "transposed tile aliases the sums t
 template <int MODE> constexpr int ms_wave_lds() { return MS_WAVE_LDS; }
 
 // ACH: 16-k chunks of the rank whose A values a wavefront keeps in registers for its whole run (1: ranks up to 16;
-// 4: ranks up to 64, further chunks are loaded where they are used).
+// 4: ranks up to 64, further chunks are loaded where they are used; 0: no rank term, Wc = W0, and A and B are not read).
 template <int MODE, bool GAMMA_POW2, int ACH>
 __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, const bf16_t* __restrict__ W0,
                                                         const bf16_t* __restrict__ A, const bf16_t* __restrict__ B,
@@ -190,7 +190,7 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
   const __amdgpu_buffer_rsrc_t rsPack = __builtin_amdgcn_make_buffer_rsrc(out.packed, 0, o * pack_row, 0x00020000);
 
   // A[k, jm] of the first ACH rank chunks, two bfloat16 per register: loaded once per wavefront
-  uint32_t apk[8 * ACH];
+  uint32_t apk[ACH > 0 ? 8 * ACH : 1];
   const unsigned voffA = jm < i ? (unsigned)(jm * 2) : OOB;
 #pragma unroll
   for (int c = 0; c < ACH; ++c) {
@@ -206,9 +206,11 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
   auto request_factors = [&](FactorLoads& F, int rb) {
     const int p0 = rb * 32;
     const bool row_m = rb < rb_end && p0 + l32 < o;
-    const unsigned voffB = row_m ? (unsigned)((p0 + l32) * r * 2) : OOB;
-    F.bq0 = __builtin_amdgcn_raw_buffer_load_b128(rsB, (int)voffB, 0, 0);
-    F.bq1 = __builtin_amdgcn_raw_buffer_load_b128(rsB, (int)(r > 8 ? voffB + 16u : voffB), 0, 0);
+    if constexpr (ACH > 0) {
+      const unsigned voffB = row_m ? (unsigned)((p0 + l32) * r * 2) : OOB;
+      F.bq0 = __builtin_amdgcn_raw_buffer_load_b128(rsB, (int)voffB, 0, 0);
+      F.bq1 = __builtin_amdgcn_raw_buffer_load_b128(rsB, (int)(r > 8 ? voffB + 16u : voffB), 0, 0);
+    }
     if (MODE == 5) return;
     const unsigned vt = tab_lane && row_m ? (unsigned)(((p0 + l32) * G + qtab) * 4) : OOB;
     F.s = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsS, (int)vt, 0, 0));
@@ -246,7 +248,7 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
         bx[c - 1][1] = __builtin_amdgcn_raw_buffer_load_b128(rsB, (int)(16 * c + 8 < r ? vb + 16u : vb), 0, 0);
       }
     }
-    {
+    if constexpr (ACH > 0) {
       const uint32_t bw[8] = {F.bq0[0], F.bq0[1], F.bq0[2], F.bq0[3], F.bq1[0], F.bq1[1], F.bq1[2], F.bq1[3]};
 #pragma unroll
       for (int k = 0; k < 16; ++k) {
@@ -271,7 +273,7 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
         }
       }
     }
-    for (int k0 = 16 * ACH; k0 < r; k0 += 16) {  // chunks beyond those in registers: loaded where they are used
+    for (int k0 = 16 * ACH; ACH > 0 && k0 < r; k0 += 16) {  // chunks beyond those in registers: loaded where they are used
       const unsigned voffB = p0 + l32 < o ? (unsigned)((p0 + l32) * r * 2 + 2 * k0) : OOB;
       const u32x4 q0 = __builtin_amdgcn_raw_buffer_load_b128(rsB, (int)voffB, 0, 0);
       const u32x4 q1 = __builtin_amdgcn_raw_buffer_load_b128(rsB, (int)(k0 + 8 < r ? voffB + 16u : voffB), 0, 0);
@@ -298,9 +300,11 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
     request_factors(F, rb + 1);  // this row block has consumed its own
     // ---- sums to the streaming layout: register e of lane l is row 8 ((e % 16) / 4) + 4 (l / 32) + e % 4,
     //      column 32 (e / 16) + l % 32
+    if constexpr (ACH > 0) {
 #pragma unroll
-    for (int e = 0; e < 32; ++e)
-      S[(8 * ((e & 15) >> 2) + 4 * (lane >> 5) + (e & 3)) * MS_SPITCH + 32 * (e >> 4) + l32] = sum[e];
+      for (int e = 0; e < 32; ++e)
+        S[(8 * ((e & 15) >> 2) + 4 * (lane >> 5) + (e & 3)) * MS_SPITCH + 32 * (e >> 4) + l32] = sum[e];
+    }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -327,7 +331,8 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
 #pragma unroll
       for (int rr = 0; rr < 8; ++rr) {
         const int row = ROW_G * g16 + ROW_R * rr;
-        const float4 acc = *reinterpret_cast<const float4*>(S + row * MS_SPITCH + 4 * c16);
+        const float4 acc = ACH > 0 ? *reinterpret_cast<const float4*>(S + row * MS_SPITCH + 4 * c16)
+                                   : make_float4(0.f, 0.f, 0.f, 0.f);
         const float4 tab = *reinterpret_cast<const float4*>(S + row * MS_SPITCH + 64 + 4 * grp_lane);
         const float s = tab.x, b = tab.y, rc = tab.z, hi = tab.w;
         const float av[4] = {acc.x, acc.y, acc.z, acc.w};
@@ -337,7 +342,8 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
         uint32_t cpack = 0, mpack = 0;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-          wc[c] = GAMMA_POW2 ? fmaf(d.gamma, av[c], w0[c]) : w0[c] + d.gamma * av[c];
+          wc[c] = ACH == 0 ? w0[c] + 0.f  // (as W0 + gamma 0: a weight of -0 becomes +0)
+                  : GAMMA_POW2 ? fmaf(d.gamma, av[c], w0[c]) : w0[c] + d.gamma * av[c];
           if constexpr (MODE == 5) continue;
           const float x = wc[c] - b;
           const float w = FAST ? fast_quotient(x, s, rc, hi) : __fdiv_rn(x, s);
@@ -519,20 +525,20 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
 // Forward and export: 4 workgroups (16 wavefronts, 144 KiB of LDS) per compute unit.  Backward: MS_BWD_WAVES (the
 // dequantized weights of a row block wait in registers for the transposition: 152 registers per lane).
 template <bool GAMMA_POW2, int ACH = 1>
-__global__ __launch_bounds__(MS_THREADS) __attribute__((amdgpu_waves_per_eu(ACH == 1 ? 4 : 3, ACH == 1 ? 4 : 3)))
+__global__ __launch_bounds__(MS_THREADS) __attribute__((amdgpu_waves_per_eu(ACH <= 1 ? 4 : 3, ACH <= 1 ? 4 : 3)))
 void merge_quant_stream_fwd_kernel(LayerDims d, const bf16_t* __restrict__ W0, const bf16_t* __restrict__ A,
                                    const bf16_t* __restrict__ B, const float* __restrict__ scale,
                                    const float* __restrict__ zero, MergeQuantOut<bf16_t> out, int nrb) {
   __shared__ __attribute__((aligned(16))) unsigned char lds_all[4 * ms_wave_lds<1>()];
   merge_quant_stream_body<1, GAMMA_POW2, ACH>(d, W0, A, B, scale, zero, out, nrb, lds_all);
 }
-template <bool GAMMA_POW2>
+template <bool GAMMA_POW2, int ACH = 1>
 __global__ __launch_bounds__(MS_THREADS) __attribute__((amdgpu_waves_per_eu(MS_BWD_WAVES, MS_BWD_WAVES)))
 void merge_quant_stream_bwd_kernel(LayerDims d, const bf16_t* __restrict__ W0, const bf16_t* __restrict__ A,
                                    const bf16_t* __restrict__ B, const float* __restrict__ scale,
                                    const float* __restrict__ zero, MergeQuantOut<bf16_t> out, int nrb) {
   __shared__ __attribute__((aligned(16))) unsigned char lds_all[4 * ms_wave_lds<2>()];
-  merge_quant_stream_body<2, GAMMA_POW2, 1>(d, W0, A, B, scale, zero, out, nrb, lds_all);
+  merge_quant_stream_body<2, GAMMA_POW2, ACH>(d, W0, A, B, scale, zero, out, nrb, lds_all);
 }
 // MODE 3 .. 6: the export, statistics and packing forms, as the forward form 4 workgroups per compute unit
 template <bool GAMMA_POW2, int MODE>
@@ -633,7 +639,11 @@ int64_t launch_merge_quant_stream(const LayerDims& d, const bf16_t* W0, const bf
   const bool pow2 = (gb & 0x807FFFFFu) == 0 && d.gamma >= 1.f && d.gamma <= 1048576.f;
 #define L4Q_MS_LAUNCH(K, ...) \
   hipLaunchKernelGGL((K<__VA_ARGS__>), grid, dim3(MS_THREADS), 0, stream, d, W0, A, B, scale, zero, out, nrb)
-  if (mode == 1 && wide) { if (pow2) L4Q_MS_LAUNCH(merge_quant_stream_fwd_kernel, true, 4); else L4Q_MS_LAUNCH(merge_quant_stream_fwd_kernel, false, 4); }
+  if (d.r == 0) {  // (the QAT-LoRA layer's forward and backward)
+    if (mode == 1) L4Q_MS_LAUNCH(merge_quant_stream_fwd_kernel, false, 0);
+    else L4Q_MS_LAUNCH(merge_quant_stream_bwd_kernel, false, 0);
+  }
+  else if (mode == 1 && wide) { if (pow2) L4Q_MS_LAUNCH(merge_quant_stream_fwd_kernel, true, 4); else L4Q_MS_LAUNCH(merge_quant_stream_fwd_kernel, false, 4); }
   else if (mode == 1) { if (pow2) L4Q_MS_LAUNCH(merge_quant_stream_fwd_kernel, true); else L4Q_MS_LAUNCH(merge_quant_stream_fwd_kernel, false); }
   else if (mode == 2) { if (pow2) L4Q_MS_LAUNCH(merge_quant_stream_bwd_kernel, true); else L4Q_MS_LAUNCH(merge_quant_stream_bwd_kernel, false); }
   else if (mode == 3) { if (pow2) L4Q_MS_LAUNCH(merge_quant_stream_export_kernel, true, 3); else L4Q_MS_LAUNCH(merge_quant_stream_export_kernel, false, 3); }

@@ -110,6 +110,14 @@ __device__ __forceinline__ void lora_rows_mfma(const LayerDims& d, const bf16_t*
 #if defined(__HIP_DEVICE_COMPILE__)
   typedef float f32x32_t __attribute__((ext_vector_type(32)));
   static_assert(MQ_ROWS == 64 && MQ_COLS == 256 && MQ_THREADS == 512, "8 waves = 2 row blocks x 4 column blocks");
+  if (d.r == 0) {  // no rank term (uniform)
+    after_first_loads();
+#pragma unroll
+    for (int rr = 0; rr < MQ_RPW; ++rr)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc[rr][c] = 0.f;
+    return;
+  }
   const int rb = wave >> 2, cb = wave & 3;
   const int64_t p = pblk + 32 * rb + (lane & 31);
   const bf16_t* brow = B + (p < d.o ? p : d.o - 1) * d.r;

@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 from paper_2402_04902_amd import inputs
-from paper_2402_04902_amd.inputs import DTYPE_BF16, LayerSpec
+from paper_2402_04902_amd.inputs import DTYPE_BF16, DTYPE_F32, LayerSpec
 
 from parity_util import host_qparams
 
@@ -75,3 +75,30 @@ def test_large_u(r, gamma, second):
     want = gamma * ((2.0 - 2.0 ** -7) * 2.0 ** 127 + second) * 2.0 ** -100  # (X Wq, below one, is lost in it)
     got = layer.Y.double().cpu().numpy()
     assert np.abs(got / want - 1.0).max() <= 2.0 ** -8, (got.min(), got.max(), want)  # one rounding to bfloat16
+
+
+@pytest.mark.parametrize("r,g,dtype", [(16, 64, DTYPE_BF16),   # streaming merge pass
+                                       (24, 64, DTYPE_BF16),   # ... ranks above one chunk
+                                       (16, 16, DTYPE_BF16),   # general merge pass
+                                       (5, 64, DTYPE_F32)])
+def test_quantizer_does_not_see_the_factors(r, g, dtype):
+    """The quantizer's input is W0 alone: two columns of A and two rows of B whose product overflows, while X A^T and dY B
+    cancel to zero over them, leave every output as it is with those factors zero, bit for bit."""
+    import torch
+    from paper_2402_04902_amd import binding
+    spec = LayerSpec(f"ql_w0_only_r{r}_g{g}", 70, 320, 136, r, 2.0 * r, 4, g, dtype)
+    print("case", spec.name, flush=True)
+    arrs = inputs.make_layer_inputs(spec, seed=r)
+    out = []
+    for big in (0.0, 2.0 ** 83):  # (a power of two: the products that cancel are exact)
+        layer = binding.upload(spec, arrs, *host_qparams(spec, arrs, "asymm", 0.9))
+        layer.X[:, 201] = layer.X[:, 200]
+        layer.dY[:, 78] = layer.dY[:, 77]
+        layer.A[1] = 0.0
+        layer.A[1, 200], layer.A[1, 201] = big, -big
+        layer.B[:, 1] = 0.0
+        layer.B[77, 1], layer.B[78, 1] = big, -big
+        _run(binding, layer)
+        out.append({n: getattr(layer, n).clone() for n in ("Y", "dX", "dA", "dB", "dscale", "dzero")})
+    for n, want in out[0].items():
+        assert torch.isfinite(want).all() and torch.equal(out[1][n], want), n
