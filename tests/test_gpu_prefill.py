@@ -48,3 +48,28 @@ def test_prefill(T, i, o, g, bits):
     # exact codes and binary32 sums: what is left is the rounding of Y to bfloat16, 2^-9 / sqrt(3) = 1.1e-3 rms of a value at
     # the top of its binade and up to twice that at the bottom (mean 1.7e-3)
     assert rel_fro(got[keep], ref[keep]) <= 2.2e-3
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4, 8])
+@pytest.mark.parametrize("T,o", [(129, 264), (401, 5000), (641, 8200)])  # 64 x 128, 128 x 128, 128 x 256 tiles
+@pytest.mark.parametrize("i,col", [(640, 133), (896, 389)])  # five and seven sections of 128
+def test_infinite_token_with_an_odd_section_count(i, col, T, o, bits):
+    """Every weight positive: a token with +Inf has +Inf in all its outputs, wherever its section's sums lie when the last
+    section's zero term, which has no partner, is added; no other token notices."""
+    import torch
+    from paper_2402_04902_amd import binding
+    spec = LayerSpec(f"prefill_inf_{T}x{i}x{o}_{bits}b", T, i, o, 8, 16.0, bits, 128, DTYPE_BF16)
+    print("case", spec.name, flush=True)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(bits)
+    X = torch.rand((T, i), generator=gen, device="cuda:0").bfloat16()
+    X[70, col] = float("inf")
+    packed = torch.randint(-2**31, 2**31 - 1, (o, i * bits // 32), generator=gen, dtype=torch.int32, device="cuda:0")
+    if bits == 8:
+        packed |= -0x7E7E7E7F  # (codes above zero: eight bits enter the product without an offset)
+    scale, zero = torch.full((o, i // 128), 0.01, device="cuda:0"), torch.full((o, i // 128), 10.0, device="cuda:0")
+    Y = torch.zeros((T, o), dtype=torch.bfloat16, device="cuda:0")
+    binding.l4q_quantized_forward(binding.make_desc(spec), X, packed, scale, zero, Y)
+    torch.cuda.synchronize()
+    assert (Y[70] == float("inf")).all()
+    assert torch.isfinite(Y[torch.arange(T, device=Y.device) != 70]).all()
