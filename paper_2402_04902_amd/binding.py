@@ -131,6 +131,16 @@ def _find_stream_query():
     return lambda: raw(device())
 
 
+def _forget_stream_query():
+    global _stream_query
+    _stream_query = None
+
+
+# A forked child cannot use its parent's device; the public call says so, the C layer's two do not: ask again there.
+if hasattr(os, "register_at_fork"):
+    os.register_at_fork(after_in_child=_forget_stream_query)
+
+
 def _stream() -> int:
     global _stream_query
     if _stream_query is None:
