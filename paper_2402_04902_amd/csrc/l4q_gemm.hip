@@ -338,6 +338,16 @@ template <class F> int64_t nt_tiles(int64_t M, int64_t N) {
   return ((M + F::BM - 1) / F::BM) * ((N + F::BN - 1) / F::BN);
 }
 
+// How far the layer's weight operand has left the memory-side cache (256 MB) by the time the product reads it: the merge
+// pass before it streams W0 and Wq, 4 N K bytes.  0 up to 62 M weights, 1 from 107 M on.  A stage's loads then take about
+// 2.6 us instead of 1.3, which a full tile's ring (four stages of 0.52 us ahead) nearly covers and the smaller tiles'
+// (0.28, 0.19 us a stage) do not: per 1024 k a full / half / quarter tile takes 16.6 / 9 / 6.2 us from the cache and
+// 20.6 / 17 / 12 from memory.
+double nt_uncached(int64_t N, int64_t K) {
+  const double c = ((double)N * (double)K - 62e6) / 45e6;
+  return c < 0.0 ? 0.0 : c > 1.0 ? 1.0 : c;
+}
+
 // One pass over k: which tile.  In us (full / half / quarter; their numbers on 256 compute units; M x N x K):
 //    32,   64,  128   72 /  41 / 29    512 x  4096 x 4096      172,  344,  688    80 /  94 /  92   1024 x 11008 x 4096
 //    32,   64,  128   39 /  23 / 15   1000 x  2048 x 2048      192,  384,  768    84 /  95 /   -   3000 x  4096 x 4096
@@ -345,12 +355,18 @@ template <class F> int64_t nt_tiles(int64_t M, int64_t N) {
 //    86,  172,  344   73 /  45 / 60    512 x 11008 x 4096      256,  512, 1024   100 / 111 /   -   4096 x  4096 x 4096
 //   128,  256,  512   74 /  57 / 64   2048 x  4096 x 4096      344,  688, 1376   169 / 152 /   -   2048 x 11008 x 4096
 //    99,  198,  396  158 / 103 / 133  2179 x  2784 x 9216      688, 1376, 2752   271 / 309 /   -   4096 x 11008 x 4096
-// i.e. rounds of tiles over the units, a round of full / half / quarter tiles counting 70 : 40 : 29.
-NtForm nt_one_pass_form(int64_t M, int64_t N) {
+// i.e. rounds of tiles over the units, a round of full / half / quarter tiles counting 70 : 40 : 29; short products, where
+// the fill of the ring and the store count for more, 22 : 16 : 13 (K = 1024, with the merge pass: 3000 x 8192 68 / 74,
+// 2048 x 11008 71 / 75, 4096 x 5120 63 / 66); weights out of the cache up to 87 : 60 : 44 (with the merge pass, 768 x
+// 28672 x 8192 574 / 628, 640 x 11008 x 11008 335 / 298, 1300 x 11008 x 11008 573 / 443, 2048 x 11008 x 11008 587 / 635).
+NtForm nt_one_pass_form(int64_t M, int64_t N, int64_t K) {
   const int64_t cus = device_compute_units();
-  auto rounds = [&](int64_t tiles) { return (tiles + cus - 1) / cus; };
-  const int64_t full = 70 * rounds(nt_tiles<NtFull>(M, N)), half = 40 * rounds(nt_tiles<NtHalf>(M, N));
-  const int64_t quarter = 29 * rounds(nt_tiles<NtQuarter>(M, N));
+  auto rounds = [&](int64_t tiles) { return (double)((tiles + cus - 1) / cus); };
+  const bool is_short = K < 1536;
+  const double c = nt_uncached(N, K);
+  const double full = ((is_short ? 22.0 : 70.0) + 17.0 * c) * rounds(nt_tiles<NtFull>(M, N));
+  const double half = ((is_short ? 16.0 : 40.0) + 20.0 * c) * rounds(nt_tiles<NtHalf>(M, N));
+  const double quarter = ((is_short ? 13.0 : 29.0) + 15.0 * c) * rounds(nt_tiles<NtQuarter>(M, N));
   if (quarter < half && quarter < full) return kNtQuarter;
   return half < full ? kNtHalf : kNtFull;
 }
@@ -365,24 +381,29 @@ NtForm nt_one_pass_form(int64_t M, int64_t N) {
 //   512 x 4096 x 4096    quarter x 2 25, 26   half x 3 28, 29     100 x 4096 x 4096   quarter x 5 14, 15   half x 6 16, 19
 //   400 x 2048 x 2048    quarter x 1 12, 13   half x 3 19, 21    1024 x 4096 x 4096   quarter x 1 25, 33   half x 1 36, 42
 // (256 x 256 tiles in as many slices as fill the chip took 35, 63, 38, 22, 25 and 54.)
+// Weights out of the cache take full tiles into account, at the times of nt_uncached.  Measured with the merge pass, full
+// tiles / the smaller ones as chosen from their cached times (us): 512 x 9600 x 9600 190 / 237, 256 x 11008 x 11008 191 / 234,
+// 640 x 7168 x 11008 183 / 212, 1024 x 5120 x 13824 210 / 244, 512 x 8192 x 11008 182 / 200; the other way round 64 x 4096 x
+// 28672 183 / 161, 300 x 7168 x 11008 158 / 144.
 struct NtPlan {
   NtForm form;
   int slices;
 };
 NtPlan nt_plan(int64_t M, int64_t N, int64_t K) {
+  const NtPlan one_pass = {nt_one_pass_form(M, N, K), 1};
   const int64_t full = nt_tiles<NtFull>(M, N), cus = device_compute_units();
-  if (full <= 0 || 2 * full > cus) return {nt_one_pass_form(M, N), 1};
+  if (full <= 0 || 2 * full > cus) return one_pass;
   const int64_t pairs = ((K + 31) / 32 + 1) / 2;
   int64_t most = cus / full;
   if (most > pairs / 4) most = pairs / 4;
   if (most > 8) most = 8;
   if (most > K / (2 * M)) most = K / (2 * M);
   if (most < 1) most = 1;
-  NtPlan best = {nt_one_pass_form(M, N), 1};
+  const double c = nt_uncached(N, K);
+  NtPlan best = one_pass;
   double best_us = 1e30;
-  for (NtForm form : {kNtQuarter, kNtHalf}) {
-    const int64_t tiles = form == kNtHalf ? nt_tiles<NtHalf>(M, N) : nt_tiles<NtQuarter>(M, N);
-    const double pass_us = (form == kNtHalf ? 9.0 : 6.2) * (double)K / 1024.0 * (double)((tiles + cus - 1) / cus);
+  auto consider = [&](NtForm form, int64_t tiles, double us_per_1024) {
+    const double pass_us = us_per_1024 * (double)K / 1024.0 * (double)((tiles + cus - 1) / cus);
     for (int s = 1; s <= most && (s == 1 || tiles * s <= cus); ++s) {
       const double us = pass_us / s + (s > 1 ? 6.0 + (double)s * (double)M * (double)N * 8.0 / 5e6 : 0.0);
       if (us < best_us) {
@@ -390,7 +411,10 @@ NtPlan nt_plan(int64_t M, int64_t N, int64_t K) {
         best_us = us;
       }
     }
-  }
+  };
+  consider(kNtQuarter, nt_tiles<NtQuarter>(M, N), 6.2 + 5.8 * c);
+  consider(kNtHalf, nt_tiles<NtHalf>(M, N), 9.0 + 7.8 * c);
+  if (c > 0.0) consider(kNtFull, full, 16.6 + 4.0 * c);
   return best;
 }
 
@@ -416,21 +440,19 @@ template <class Fn> void nt_dispatch(NtForm form, bool mask, Fn&& f) {
 
 void launch_gemm_bf16_nt(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, int64_t M, int64_t N,
                          int64_t K, int64_t K_a, bf16_t* C, int64_t ldc, hipStream_t stream, float* partial) {
-  const NtPlan plan = partial ? nt_plan(M, N, K) : NtPlan{nt_one_pass_form(M, N), 1};
+  NtPlan plan = nt_plan(M, N, K);
+  if (plan.slices > 1 && !partial) plan = {nt_one_pass_form(M, N, K), 1};
   const int slices = plan.slices;
   nt_dispatch(plan.form, K_a != K, [&](auto tile, auto mask) {
     typedef decltype(tile) F;
     constexpr bool MASK = decltype(mask)::value;
     const int tiles_m = (int)((M + F::BM - 1) / F::BM), tiles_n = (int)((N + F::BN - 1) / F::BN);
     if (slices > 1) {
-      if constexpr (!std::is_same<F, NtFull>::value) {
-        hipLaunchKernelGGL((gemm_bf16_nt_splitk_kernel<F, MASK, true>),
-                           dim3((unsigned)(tiles_m * tiles_n), (unsigned)slices), dim3(F::NT), 0, stream, A, lda, B, ldb,
-                           (int)M, (int)N, (int)K, (int)K_a, partial, tiles_m, tiles_n);
-        const int64_t quads = M * N / 4;
-        hipLaunchKernelGGL(splitk_sum_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream, partial,
-                           slices, M, N, C, ldc);
-      }
+      hipLaunchKernelGGL((gemm_bf16_nt_splitk_kernel<F, MASK, true>), dim3((unsigned)(tiles_m * tiles_n), (unsigned)slices),
+                         dim3(F::NT), 0, stream, A, lda, B, ldb, (int)M, (int)N, (int)K, (int)K_a, partial, tiles_m, tiles_n);
+      const int64_t quads = M * N / 4;
+      hipLaunchKernelGGL(splitk_sum_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream, partial, slices,
+                         M, N, C, ldc);
     } else {
       hipLaunchKernelGGL((gemm_bf16_nt_fast_kernel<F, true, false, false, MASK, true>),
                          dim3((unsigned)(tiles_m * tiles_n)), dim3(F::NT), 0, stream, A, lda, B, ldb, (int)M, (int)N,
@@ -441,7 +463,7 @@ void launch_gemm_bf16_nt(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t 
 
 void launch_gemm_bf16_nt_rank(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t M, int64_t N, int64_t K, int64_t K_a,
                               bf16_t* C, int64_t ldc, const RankTerm& term, hipStream_t stream) {
-  nt_dispatch(nt_one_pass_form(M, N), K_a != K, [&](auto tile, auto mask) {
+  nt_dispatch(nt_one_pass_form(M, N, K), K_a != K, [&](auto tile, auto mask) {
     typedef decltype(tile) F;
     const int tiles_m = (int)((M + F::BM - 1) / F::BM), tiles_n = (int)((N + F::BN - 1) / F::BN);
     hipLaunchKernelGGL((gemm_bf16_nt_rank_kernel<F, decltype(mask)::value>), dim3((unsigned)(tiles_m * tiles_n)),
