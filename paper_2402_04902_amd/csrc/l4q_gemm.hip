@@ -338,13 +338,16 @@ template <class F> int64_t nt_tiles(int64_t M, int64_t N) {
   return ((M + F::BM - 1) / F::BM) * ((N + F::BN - 1) / F::BN);
 }
 
-// How far the layer's weight operand has left the memory-side cache (256 MB) by the time the product reads it: the merge
-// pass before it streams W0 and Wq, 4 N K bytes.  0 up to 62 M weights, 1 from 107 M on.  A stage's loads then take about
-// 2.6 us instead of 1.3, which a full tile's ring (four stages of 0.52 us ahead) nearly covers and the smaller tiles'
-// (0.28, 0.19 us a stage) do not: per 1024 k a full / half / quarter tile takes 16.6 / 9 / 6.2 us from the cache and
-// 20.6 / 17 / 12 from memory.
-double nt_uncached(int64_t N, int64_t K) {
-  const double c = ((double)N * (double)K - 62e6) / 45e6;
+// How far the layer's weight operand has left the memory-side cache (256 MB) by the time the product reads it, 0 .. 1.
+// In a training step the merge pass reads W0 from memory and writes Wq right before the forward product (4 N K bytes):
+// felt from 40 M weights on, complete at 107 M.  Between it and the dX product (`late`) lie the weight-gradient kernel and
+// its factor array, another 4 N K bytes: from 30 M on, complete at 60 M.  A stage's loads then take about 2.6 us instead of
+// 1.3, which a full tile's ring (four stages of 0.52 us ahead) nearly covers and the smaller tiles' (0.28, 0.19 us a stage)
+// do not: per 1024 k a full / half / quarter tile takes 16.6 / 9 / 6.2 us from the cache and 20.6 / 15 .. 17 / 12 from memory
+// (late, quarter tiles come off better than that: 9).
+double nt_uncached(int64_t N, int64_t K, bool late) {
+  const double weights = (double)N * (double)K;
+  const double c = late ? (weights - 30e6) / 30e6 : (weights - 40e6) / 67e6;
   return c < 0.0 ? 0.0 : c > 1.0 ? 1.0 : c;
 }
 
@@ -359,11 +362,11 @@ double nt_uncached(int64_t N, int64_t K) {
 // the fill of the ring and the store count for more, 22 : 16 : 13 (K = 1024, with the merge pass: 3000 x 8192 68 / 74,
 // 2048 x 11008 71 / 75, 4096 x 5120 63 / 66); weights out of the cache up to 87 : 60 : 44 (with the merge pass, 768 x
 // 28672 x 8192 574 / 628, 640 x 11008 x 11008 335 / 298, 1300 x 11008 x 11008 573 / 443, 2048 x 11008 x 11008 587 / 635).
-NtForm nt_one_pass_form(int64_t M, int64_t N, int64_t K) {
+NtForm nt_one_pass_form(int64_t M, int64_t N, int64_t K, bool late) {
   const int64_t cus = device_compute_units();
   auto rounds = [&](int64_t tiles) { return (double)((tiles + cus - 1) / cus); };
   const bool is_short = K < 1536;
-  const double c = nt_uncached(N, K);
+  const double c = nt_uncached(N, K, late);
   const double full = ((is_short ? 22.0 : 70.0) + 17.0 * c) * rounds(nt_tiles<NtFull>(M, N));
   const double half = ((is_short ? 16.0 : 40.0) + 20.0 * c) * rounds(nt_tiles<NtHalf>(M, N));
   const double quarter = ((is_short ? 13.0 : 29.0) + 15.0 * c) * rounds(nt_tiles<NtQuarter>(M, N));
@@ -381,16 +384,17 @@ NtForm nt_one_pass_form(int64_t M, int64_t N, int64_t K) {
 //   512 x 4096 x 4096    quarter x 2 25, 26   half x 3 28, 29     100 x 4096 x 4096   quarter x 5 14, 15   half x 6 16, 19
 //   400 x 2048 x 2048    quarter x 1 12, 13   half x 3 19, 21    1024 x 4096 x 4096   quarter x 1 25, 33   half x 1 36, 42
 // (256 x 256 tiles in as many slices as fill the chip took 35, 63, 38, 22, 25 and 54.)
-// Weights out of the cache take full tiles into account, at the times of nt_uncached.  Measured with the merge pass, full
-// tiles / the smaller ones as chosen from their cached times (us): 512 x 9600 x 9600 190 / 237, 256 x 11008 x 11008 191 / 234,
-// 640 x 7168 x 11008 183 / 212, 1024 x 5120 x 13824 210 / 244, 512 x 8192 x 11008 182 / 200; the other way round 64 x 4096 x
-// 28672 183 / 161, 300 x 7168 x 11008 158 / 144.
+// Weights out of the cache take full tiles into account, at the times of nt_uncached.  Measured in us, full tiles / the
+// smaller ones as chosen from their cached times: merge pass and product 512 x 9600 x 9600 190 / 237, 256 x 11008 x 11008
+// 191 / 234, 640 x 7168 x 11008 183 / 212, 1024 x 5120 x 13824 210 / 244, 512 x 8192 x 11008 182 / 200, but 64 x 4096 x 28672
+// 183 / 161, 300 x 7168 x 11008 158 / 144; training steps with the dX product in either, 768 x 4096 x 11008 405 / 430,
+// 768 x 7168 x 7168 452 / 480, 1500 x 3072 x 11008 465 / 493.
 struct NtPlan {
   NtForm form;
   int slices;
 };
-NtPlan nt_plan(int64_t M, int64_t N, int64_t K) {
-  const NtPlan one_pass = {nt_one_pass_form(M, N, K), 1};
+NtPlan nt_plan(int64_t M, int64_t N, int64_t K, bool late) {
+  const NtPlan one_pass = {nt_one_pass_form(M, N, K, late), 1};
   const int64_t full = nt_tiles<NtFull>(M, N), cus = device_compute_units();
   if (full <= 0 || 2 * full > cus) return one_pass;
   const int64_t pairs = ((K + 31) / 32 + 1) / 2;
@@ -399,7 +403,7 @@ NtPlan nt_plan(int64_t M, int64_t N, int64_t K) {
   if (most > 8) most = 8;
   if (most > K / (2 * M)) most = K / (2 * M);
   if (most < 1) most = 1;
-  const double c = nt_uncached(N, K);
+  const double c = nt_uncached(N, K, late);
   NtPlan best = one_pass;
   double best_us = 1e30;
   auto consider = [&](NtForm form, int64_t tiles, double us_per_1024) {
@@ -412,15 +416,15 @@ NtPlan nt_plan(int64_t M, int64_t N, int64_t K) {
       }
     }
   };
-  consider(kNtQuarter, nt_tiles<NtQuarter>(M, N), 6.2 + 5.8 * c);
-  consider(kNtHalf, nt_tiles<NtHalf>(M, N), 9.0 + 7.8 * c);
+  consider(kNtQuarter, nt_tiles<NtQuarter>(M, N), 6.2 + (late ? 2.5 : 5.8) * c);
+  consider(kNtHalf, nt_tiles<NtHalf>(M, N), 9.0 + 6.5 * c);
   if (c > 0.0) consider(kNtFull, full, 16.6 + 4.0 * c);
   return best;
 }
 
 }  // namespace
 
-int gemm_nt_splitk_slices(int64_t M, int64_t N, int64_t K) { return nt_plan(M, N, K).slices; }
+int gemm_nt_splitk_slices(int64_t M, int64_t N, int64_t K, bool late) { return nt_plan(M, N, K, late).slices; }
 
 namespace {
 
@@ -439,9 +443,9 @@ template <class Fn> void nt_dispatch(NtForm form, bool mask, Fn&& f) {
 }  // namespace
 
 void launch_gemm_bf16_nt(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, int64_t M, int64_t N,
-                         int64_t K, int64_t K_a, bf16_t* C, int64_t ldc, hipStream_t stream, float* partial) {
-  NtPlan plan = nt_plan(M, N, K);
-  if (plan.slices > 1 && !partial) plan = {nt_one_pass_form(M, N, K), 1};
+                         int64_t K, int64_t K_a, bf16_t* C, int64_t ldc, hipStream_t stream, float* partial, bool late) {
+  NtPlan plan = nt_plan(M, N, K, late);
+  if (plan.slices > 1 && !partial) plan = {nt_one_pass_form(M, N, K, late), 1};
   const int slices = plan.slices;
   nt_dispatch(plan.form, K_a != K, [&](auto tile, auto mask) {
     typedef decltype(tile) F;
@@ -463,7 +467,7 @@ void launch_gemm_bf16_nt(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t 
 
 void launch_gemm_bf16_nt_rank(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t M, int64_t N, int64_t K, int64_t K_a,
                               bf16_t* C, int64_t ldc, const RankTerm& term, hipStream_t stream) {
-  nt_dispatch(nt_one_pass_form(M, N, K), K_a != K, [&](auto tile, auto mask) {
+  nt_dispatch(nt_one_pass_form(M, N, K, false), K_a != K, [&](auto tile, auto mask) {
     typedef decltype(tile) F;
     const int tiles_m = (int)((M + F::BM - 1) / F::BM), tiles_n = (int)((N + F::BN - 1) / F::BN);
     hipLaunchKernelGGL((gemm_bf16_nt_rank_kernel<F, decltype(mask)::value>), dim3((unsigned)(tiles_m * tiles_n)),
