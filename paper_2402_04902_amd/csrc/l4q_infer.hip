@@ -1343,11 +1343,12 @@ bool qgemm_decode_ok(const LayerDims& d) {
 // With fewer tiles, as many k-slices as fill the units, each at least four stages long.
 struct TilePlan {
   int tb_max, slices;
+  int64_t klen;  // k-values of the longest slice
   int pitch[5];
   int64_t lds[5];
 };
 TilePlan qgemm_tile_plan(const LayerDims& d) {
-  TilePlan plan = {0, 1, {1, 1, 1, 1, 1}, {0, 0, 0, 0, 0}};
+  TilePlan plan = {0, 1, 0, {1, 1, 1, 1, 1}, {0, 0, 0, 0, 0}};
   // 3 bits: activation stages of 256 k-values, weights in units of three 128-byte stages = four activation stages
   const bool w3 = d.bits == 3 && d.i % 256 == 0 && d.g % 128 == 0 && d.o * (d.i / 8 * 3) < (1ll << 31);
   if (!w3 && qgemm_stream_rows(d, 16) != 16) return plan;
@@ -1364,6 +1365,7 @@ TilePlan qgemm_tile_plan(const LayerDims& d) {
   }
   // stages of the longest slice (3 bits: slices are whole units of four stages)
   const int64_t stages = w3 ? 4 * (((nst + 3) / 4 + plan.slices - 1) / plan.slices) : (nst + plan.slices - 1) / plan.slices;
+  plan.klen = stages * ks;
   int64_t groups = (stages * ks - 1) / d.g + 2;                   // groups it can meet, wherever it starts
   if (groups > G) groups = G;
   if (groups > 4 * (QT_ROWQ * 256 / 64)) return plan;  // table rows longer than a thread's pieces cover
@@ -1581,30 +1583,59 @@ size_t qgemm_workspace_bytes(const LayerDims& d) {
 
 namespace {
 
-// Estimated time (us) of the passes the kernels of this file would take above 64 tokens: full passes of 64 tokens in 64-row
-// tiles, 8 + 0.38 per million weights (4 bits, 64 tokens: [4096 x 4096] 14.2, [4096 x 11008] 25.3, [11008 x 4096] 28.1, [8192
-// x 8192] 31.5, [16384 x 4096] 29.6; the last pass by its token blocks; 3 and 8 bits 10 .. 30 % more); twice that where only
-// the general kernel or the k-split streaming form is left (2 bits [11008 x 4096] 54, [4096 x 11008] 55).
+// Estimated time (us) of the passes the kernels of this file would take above 64 tokens, within 4 % on average (20 % at
+// most) of 6700 measured calls of the tile kernel and 6 % of 8000 of the general one:
+//  * tile kernel, per pass of tb token blocks: 4, the rounds of row tiles times the longest slice's k-values times a rate by
+//    tb, and with k-slices 1.5 and the partial sums (4 bits: [4096 x 4096] 64 tokens 14.2, [11008 x 4096] 28.1);
+//  * general kernel, one launch: rounds of 32-row workgroups; 64 tokens cost 19 per 4096 k-values, an odd run of 2048 at the
+//    end nearly as much (i = 2048 / 4096 / 6144 / 8192: 18 / 26 / 37 / 45), rows that are no multiple of 1 KiB a fifth less (no
+//    two of them start in the same memory channel); the tokens left over at least half of a pass of 64.
 double qgemm_passes_us(const LayerDims& d, bool have_workspace) {
   const TilePlan plan = qgemm_tile_plan(d);
-  const bool tiles = plan.tb_max > 0 && (plan.slices == 1 || have_workspace);
-  const double pass = (8.0 + 0.38e-6 * (double)d.o * (double)d.i) * (d.bits == 4 ? 1.0 : 1.2) * (tiles ? 1.0 : 2.0);
-  const int64_t full = d.T / 64, blocks = (d.T % 64 + 15) / 16;
-  return pass * ((double)full + (blocks > 0 ? 0.45 + 0.1375 * (double)blocks : 0.0));
+  const int64_t cus = device_compute_units();
+  if (plan.tb_max > 0 && (plan.slices == 1 || have_workspace)) {
+    static const double rate[3][4] = {{4.0, 4.8, 7.0, 6.5}, {3.55, 4.2, 5.6, 5.5}, {5.9, 6.1, 8.2, 7.25}};  // 3, 4, 8 bits
+    const int64_t rounds = ((d.o + 63) / 64 + cus - 1) / cus;
+    double us = 0.0;
+    for (int64_t t0 = 0; t0 < d.T; t0 += 16 * plan.tb_max) {
+      const int64_t n = d.T - t0 < 16 * plan.tb_max ? d.T - t0 : 16 * plan.tb_max;
+      int tb = (int)((n + 15) / 16);
+      while (plan.lds[tb] == 0) ++tb;
+      us += 4.0 + (double)rounds * (double)plan.klen / 1024.0 * rate[d.bits == 3 ? 0 : d.bits == 4 ? 1 : 2][tb - 1];
+      if (plan.slices > 1) us += 1.5 + 0.65 * (double)plan.slices * 16.0 * tb * (double)d.o * 4e-6;
+    }
+    return us;
+  }
+  const int64_t groups = (d.o + 31) / 32, runs = (d.i + 2047) / 2048, left = d.T % 64;
+  double pass = 19.3 * (double)(runs / 2) + (runs % 2 ? 18.2 : 6.0);
+  if (d.bits == 8) pass *= 1.17;
+  if (d.i % 512 != 0) pass *= 0.8;
+  else if (d.g >= 256) pass *= 0.95;
+  pass *= 0.96 + 0.1 * (groups < cus ? (double)groups / (double)cus : 1.0);  // (a full chip shares the memory)
+  return pass * (double)((groups + cus - 1) / cus) *
+         ((double)(d.T / 64) + (left > 0 ? (d.bits == 8 ? 0.62 : 0.56) + 0.0065 * (double)left : 0.0));
 }
 
 }  // namespace
 
+// Prompts: one pass in two-dimensional tiles, from where it is estimated to be faster than 64 tokens at a time (us, the
+// other / this one: 4 bits [11008 x 4096] 65 tokens, 47 / 33; [4096 x 4096] 129, 40 / 32; [4096 x 11008] 177, 95 / 83; the
+// passes stay ahead at 3 bits, groups of 256, [8192 x 8192] 96 tokens, 60 / 72, and at 2 bits, groups of 64, [8192 x 11008] 65
+// tokens, 88 / 107).
+PrefillPlan qgemm_prompt_plan(const LayerDims& d, bool have_workspace) {
+  PrefillPlan plan = {-1, 0.0};
+  if (d.T <= 64) return plan;
+  plan = qgemm_prefill_plan(d);
+  if (plan.form >= 0 && plan.us >= qgemm_passes_us(d, have_workspace)) plan.form = -1;
+  return plan;
+}
+
 void launch_qgemm(const LayerDims& d, const bf16_t* X, const uint32_t* packed, const float* scale, const float* zero,
                   bf16_t* Y, float* partial, size_t partial_bytes, hipStream_t stream) {
-  // prompts: one pass in two-dimensional tiles, from where it is estimated to be faster than 64 tokens at a time
-  // (4 bits: [11008 x 4096] 65 tokens, 33 against 47 us; [4096 x 4096] 129, 32 against 40; [4096 x 11008] 177, 83 against 95)
-  if (d.T > 64) {
-    const PrefillPlan pf = qgemm_prefill_plan(d);
-    if (pf.form >= 0 && pf.us < qgemm_passes_us(d, partial != nullptr && partial_bytes >= qgemm_workspace_bytes(d))) {
-      launch_qgemm_prefill(pf, d, X, packed, scale, zero, Y, stream);
-      return;
-    }
+  const PrefillPlan prompt = qgemm_prompt_plan(d, partial != nullptr && partial_bytes >= qgemm_workspace_bytes(d));
+  if (prompt.form >= 0) {
+    launch_qgemm_prefill(prompt, d, X, packed, scale, zero, Y, stream);
+    return;
   }
   dim3 grid((unsigned)((d.o + 31) / 32));
   // a few token blocks at most, groups of 128 and more: the packed codes resident in registers

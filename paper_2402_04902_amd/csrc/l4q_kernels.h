@@ -156,6 +156,8 @@ struct PrefillPlan {
   double us;  // estimated time
 };
 PrefillPlan qgemm_prefill_plan(const LayerDims& d);
+// ... where it is the faster way for this call; form -1: the passes of at most 64 tokens are
+PrefillPlan qgemm_prompt_plan(const LayerDims& d, bool have_workspace);
 void launch_qgemm_prefill(const PrefillPlan& plan, const LayerDims& d, const bf16_t* X, const uint32_t* packed,
                           const float* scale, const float* zero, bf16_t* Y, hipStream_t stream);
 

@@ -410,6 +410,9 @@ void launch_bits(int form, const LayerDims& d, const bf16_t* X, const uint32_t* 
 // 200, 4096 x 11008 83 / 120 / 165.  2 and 3 bits take 2 .. 20 % more, 8 bits 10 .. 40 %, groups of
 // 64 20 .. 35 % (twice the barriers and scalings).
 // (One pass of the decode kernels per 64 tokens: 512 tokens on 11008 x 4096 215, 256 on 4096 x 11008 106.)
+// The choice against those passes falls where 64 x 128 tiles are the best form, and needs their time closer than that: one
+// workgroup on a unit takes 0.885 us per section at 4 bits, two together 1.46 (2, 3, 8 bits: 0.97 and 1.6, 1.02 and 1.65, 1.13
+// and 2.37; groups of 64 28 % more, 23 % at 8 bits), within 3.5 % on average over 15000 measured calls.
 PrefillPlan qgemm_prefill_plan(const LayerDims& d) {
   PrefillPlan plan = {-1, 0.0};
   const bool g_ok = d.g >= 128 || (d.g == 64 && d.bits != 3);
@@ -429,6 +432,13 @@ PrefillPlan qgemm_prefill_plan(const LayerDims& d) {
       plan.form = f;
       plan.us = us;
     }
+  }
+  if (plan.form == 0) {
+    const double one[4] = {0.97, 1.02, 0.885, 1.13}, two[4] = {1.6, 1.65, 1.46, 2.37};
+    const int b = d.bits == 8 ? 3 : d.bits - 2;
+    const int64_t tiles = ((d.T + 63) / 64) * ((d.o + 127) / 128), left = tiles % (2 * cus);
+    const double rounds = (double)(tiles / (2 * cus)) * two[b] + (left > cus ? two[b] : left > 0 ? one[b] : 0.0);
+    plan.us = 3.3 + (double)d.i / 128.0 * rounds * (d.g != 64 ? 1.0 : d.bits == 8 ? 1.23 : 1.28);
   }
   return plan;
 }

@@ -1,0 +1,29 @@
+"""Where a quantized forward of more than 64 tokens takes the two-dimensional tiles and where the passes of 64 tokens, at sizes
+where both were measured (us, passes / tiles)."""
+import pytest
+
+from plan_util import PASSES, TILES_64x128, TILES_128x256, prompt_form
+
+
+@pytest.mark.parametrize("T,o,i,bits,g", [
+    (65, 8192, 11008, 2, 64),    # 88 / 107
+    (65, 8192, 8192, 4, 64),     # 72 / 79
+    (96, 8192, 8192, 3, 256),    # 60 / 72
+    (256, 2048, 8192, 3, 256),   # 61 / 71
+    (192, 4096, 8192, 4, 256),   # 59 / 64
+    (64, 4096, 4096, 4, 128),    # not a prompt
+    (300, 4096, 4096, 3, 64),    # no tiles for 3 bits in groups of 64
+])
+def test_passes(T, o, i, bits, g):
+    assert prompt_form(T, i, o, bits, g) == PASSES
+
+
+@pytest.mark.parametrize("T,o,i,bits,g,form", [
+    (65, 11008, 4096, 4, 128, TILES_64x128),    # 44 / 32
+    (129, 4096, 4096, 4, 128, TILES_64x128),    # 40 / 32
+    (128, 8192, 11008, 4, 64, TILES_64x128),    # 123 / 105
+    (300, 4096, 11008, 4, 128, TILES_64x128),   # 125 / 83
+    (512, 11008, 4096, 4, 128, TILES_128x256),  # 215 / 66
+])
+def test_tiles(T, o, i, bits, g, form):
+    assert prompt_form(T, i, o, bits, g) == form
