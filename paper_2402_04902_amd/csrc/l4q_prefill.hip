@@ -349,8 +349,8 @@ __global__ __launch_bounds__(P::NT) void qgemm_prefill_kernel(const bf16_t* __re
   __builtin_amdgcn_s_waitcnt(gemm::waitcnt_vm(0));
   // the last section of an odd count has no partner: the sums an earlier section has left in the partner's place are taken
   // out (its zero factor would make NaN of an infinite one).  No wave is behind the last barrier's section, and that reads
-  // the other two places.
-  if (nsec & 1)
+  // the other two places.  (Sections of 64, and of 128 with several to a group, come in even numbers.)
+  if constexpr (SEC == 128 && !P::WIDE) if (nsec & 1)
     for (int q = threadIdx.x; q < P::BM * 8; q += P::NT) sx[(nsec & 3) * P::BM * 8 + q] = 0.f;
   __syncthreads();  // the last pair's sums of X; every wave is done with the ring
   zero_term((nsec - 1) & 2, zpair);
