@@ -5,6 +5,7 @@ import pytest
 from paper_2402_04902_amd.inputs import DTYPE_F32, LayerSpec
 
 from test_gpu_parity import run_case
+from test_gpu_qatlora import _run
 
 pytestmark = pytest.mark.gpu
 
@@ -17,7 +18,19 @@ pytestmark = pytest.mark.gpu
     (16, 2052, 2051, 2, 4),     # 64-wide tiles on one k-step of 16 (dWq)
     (1057, 1060, 1025, 3, 4),   # 64-wide tiles, the k-steps dealt to two groups of waves: the last one to the first
     (129, 2052, 2051, 2, 4),    # ... five steps, the last of one row (dWq)
-    (35, 2948, 2949, 2, 4),     # 128-wide tiles (dWq: 24 x 24), K = 35
+    (35, 2948, 2949, 2, 4),     # 128-wide tiles (dWq: 24 x 24, both operands K-major), K = 35
+    (2945, 36, 2945, 2, 4),     # ... in the forward product (24 x 24, both K-contiguous), K = 36
+    (2945, 2948, 35, 2, 4),     # ... in dX (24 x 24, one of each), K = 35
 ])
 def test_binary32_product_forms(T, i, o, r, g):
     run_case(LayerSpec(f"f32_prod_{T}x{i}x{o}", T, i, o, r, 2.0 * r, 4, g, DTYPE_F32), seed=T + i, shrink=0.8)
+
+
+@pytest.mark.parametrize("T,i,o,r", [
+    (1037, 1028, 1031, 37),   # the rank term added to Y and dX in 64-wide tiles (17 x 17), one group of waves
+    (1037, 1028, 1031, 150),  # ... two groups, five k-steps
+    (2945, 36, 2945, 5),      # ... to Y in 128-wide tiles
+    (2945, 2948, 35, 5),      # ... to dX
+])
+def test_binary32_rank_terms(T, i, o, r):
+    _run(LayerSpec(f"f32_rank_{T}x{i}x{o}_r{r}", T, i, o, r, 2.0 * r, 4, 4, DTYPE_F32, outliers=False), seed=T + r)
