@@ -1,6 +1,6 @@
 """Quantized forward at prompt sizes (two-dimensional tiles): every tile shape and code width, token and row counts that end
-inside a tile, one to nine sections of k (an odd count leaves half a zero-term pair), groups of half a section, one, two
-and four, against the oracle; a NaN token stays in its row."""
+inside a tile, one to eighteen sections of k (an odd count leaves half a zero-term pair), groups of half a section, one, two
+and four in the shapes that have them, against the oracle; a NaN token stays in its row."""
 import numpy as np
 import pytest
 
@@ -8,22 +8,30 @@ from paper_2402_04902_amd import inputs
 from paper_2402_04902_amd.inputs import DTYPE_BF16, LayerSpec
 
 from parity_util import compare_tensor, host_qparams, rel_fro
+from plan_util import PASSES, TILES_128x128, TILES_128x256, TILES_64x128
 from test_gpu_quantized_path import packed_on_gpu
 
 pytestmark = pytest.mark.gpu
 
 
+# (T, in, out, group), the tile shape that 2, 3, 4 and 8 bits take (tests/test_prompt_route.py keeps the two together)
+CASES = [
+    ((65, 128, 8, 128), (TILES_64x128,) * 4),     # one section, the second tile one token, eight rows
+    ((129, 640, 264, 128), (TILES_64x128,) * 4),  # five sections
+    ((100, 1152, 392, 64), (TILES_64x128, PASSES, TILES_64x128, TILES_64x128)),       # half sections
+    ((130, 1536, 136, 512), (TILES_64x128,) * 4),    # groups of four sections
+    ((401, 384, 5000, 128), (TILES_128x128,) * 4),   # three sections, ragged rows
+    ((385, 512, 5128, 256), (TILES_128x128,) * 4),   # groups of two sections
+    ((385, 1536, 5128, 512), (TILES_128x128,) * 4),  # ... of four
+    ((385, 256, 5128, 64), (TILES_128x128, PASSES, TILES_128x128, TILES_128x128)),    # half sections, four of them
+    ((257, 1152, 7944, 64), (TILES_128x128, PASSES, TILES_128x128, TILES_128x128)),   # ... eighteen
+    ((385, 192, 5128, 64), (PASSES,) * 4),           # rows that are no multiple of 128
+    ((641, 256, 8200, 128), (TILES_128x256, TILES_128x256, TILES_128x256, TILES_64x128)),  # one token in the last tile
+]
+
+
 @pytest.mark.parametrize("bits", [2, 3, 4, 8])
-@pytest.mark.parametrize("T,i,o,g", [
-    (65, 128, 8, 128),       # 64 x 128 tiles: one section, the second tile one token, eight rows
-    (129, 640, 264, 128),    # five sections
-    (100, 1152, 392, 64),    # half sections (3 bits: the 64-token passes)
-    (130, 1536, 136, 512),   # groups of four sections
-    (401, 384, 5000, 128),   # 128 x 128 tiles, three sections, ragged rows
-    (385, 512, 5128, 256),   # ... groups of two sections
-    (385, 192, 5128, 64),    # ... i not a multiple of 128: the 64-token passes
-    (641, 256, 8200, 128),   # 128 x 256 tiles (8 bits: 64 x 128), one token in the last
-])
+@pytest.mark.parametrize("T,i,o,g", [c[0] for c in CASES])
 def test_prefill(T, i, o, g, bits):
     import torch
     from oracle import l4q_oracle as O

@@ -63,7 +63,8 @@ def test_quantized_forward_random_shapes(k, T, i, o, bits, g):
 def _random_tile_cases(count=18, seed=2402):
     """Seeded draw of problems for the 64-row tile kernel: wide layers (every compute unit gets a tile) and narrow
     ones with long rows (k-slices through the workspace), 3, 4 and 8 bits, groups of one to four sub-steps, 1 .. 100
-    tokens (every count of token blocks, several passes), ragged last row tiles."""
+    tokens (every count of token blocks; above 64 two passes where the two-dimensional tiles of prompts are not
+    faster), ragged last row tiles."""
     rng = np.random.default_rng(seed)
     cases = []
     for k in range(count):
@@ -172,7 +173,7 @@ def test_quantized_forward_weights_in_registers(T, i, o, bits, g):
     # wide layers (enough 64-row tiles for most compute units): tiles sharing the activation stage, 4, 3, 2 and 1
     # token blocks per pass, a ragged last row tile, odd stage count, 8-bit, groups of two sub-steps (4-bit g = 256,
     # 8-bit g = 128), long rows that leave LDS for two token blocks only, a small batch too long for the LDS-resident
-    # form
+    # form (70 tokens: a prompt, in two-dimensional tiles)
     (64, 4096, 11008, 4, 128), (70, 1024, 10248, 4, 128), (40, 896, 10312, 8, 128), (48, 11008, 10240, 4, 128),
     (24, 2048, 10304, 4, 256), (13, 4096, 10240, 4, 64), (30, 1024, 10240, 8, 64),
     # few row tiles and long rows with a workspace: k-slices over the compute units (4, 2 and 3 slices; a slice
@@ -185,9 +186,11 @@ def test_quantized_forward_weights_in_registers(T, i, o, bits, g):
     (16, 2048, 72, 3, 256), (3, 128, 40, 3, 128), (4, 11008, 4096, 3, 128),
     # 3 bits at larger batches (64-row tiles with weights in units of three stages where the in-register form does
     # not take the case): both projections (the narrow one in k-slices of whole units, the last one short), one to
-    # three token blocks per pass, two passes, a row of less than one unit, ragged last row tile, groups of 256
+    # three token blocks per pass, a row of less than one unit, ragged last row tile, groups of 256 (70 tokens: a prompt)
     (64, 4096, 11008, 3, 128), (40, 11008, 4096, 3, 128), (16, 4096, 10240, 3, 128), (33, 1024, 10312, 3, 256),
     (24, 2048, 10304, 3, 128), (70, 768, 10248, 3, 128),
+    # ... and two passes in k-slices, at 4 bits too
+    (100, 3072, 2048, 3, 512), (100, 3072, 2048, 4, 256),
     # ... and few tokens on narrow layers
     (16, 4096, 4096, 3, 128), (7, 11008, 4096, 3, 128),
     # 70B-class projections: the widest layer at a small batch, the longest rows (too many groups for the tile kernel's

@@ -3,6 +3,7 @@ where both were measured (us, passes / tiles)."""
 import pytest
 
 from plan_util import PASSES, TILES_64x128, TILES_128x256, prompt_form
+from test_gpu_prefill import CASES
 
 
 @pytest.mark.parametrize("T,o,i,bits,g", [
@@ -27,3 +28,14 @@ def test_passes(T, o, i, bits, g):
 ])
 def test_tiles(T, o, i, bits, g, form):
     assert prompt_form(T, i, o, bits, g) == form
+
+
+@pytest.mark.parametrize("case,forms", CASES)
+def test_gpu_cases_take_the_shapes_they_name(case, forms):
+    T, i, o, g = case
+    assert tuple(prompt_form(T, i, o, bits, g, False) for bits in (2, 3, 4, 8)) == forms
+
+
+@pytest.mark.parametrize("T,i,o,bits,g", [(80, 2304, 4104, 8, 128), (100, 3072, 2048, 3, 512), (100, 3072, 2048, 4, 256)])
+def test_two_pass_cases_of_the_quantized_path_are_passes(T, i, o, bits, g):
+    assert prompt_form(T, i, o, bits, g, True) == PASSES
