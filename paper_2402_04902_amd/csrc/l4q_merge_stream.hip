@@ -446,12 +446,14 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
       const int span = g > 64 ? g / 64 : 1;  // wavefronts of a group; its first one finishes it
       if (wave % span == 0 && tab_lane && p0 + l32 < o) {
         const float* t = S + l32 * MS_SPITCH + set + 2 * (lane >> 5);
-        // (from infinities: a group of nothing but NaN has the extremes of an empty one, as in the general pass)
-        float a = __builtin_huge_valf(), z = -__builtin_huge_valf();
-        for (int w = 0; w < span; ++w) {
+        float a = t[0], z = t[1];
+        for (int w = 1; w < span; ++w) {
           a = fminf(a, t[w * (MS_WAVE_LDS / 4)]);
           z = fmaxf(z, t[w * (MS_WAVE_LDS / 4) + 1]);
         }
+        // a group of nothing but NaN has the extremes of an empty one, as in the general pass
+        a = fminf(a, __builtin_huge_valf());
+        z = fmaxf(z, -__builtin_huge_valf());
         float s0, b0 = 0.f;
         if (out.init_method == 0) {         // asymmetric min / max
           s0 = __fdiv_rn(z - a, d.qp - d.qn);
