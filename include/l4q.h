@@ -140,8 +140,8 @@ int l4q_backward(const l4q_desc* desc, const void* X, const void* dY, const void
  *   the section names) and d(scale), d(zero) are taken from it with Eq. quant_lsq_s / quant_lsq_b;
  *   dA = gamma (dY B)^T X,  dB = gamma dY^T (X A^T)              (Eq. lora_backward).
  * Arguments, layouts, dtypes, flags (L4Q_FLAG_ACCUMULATE_GRADS) and error behaviour as l4q_forward / l4q_backward;
- * L4Q_FLAG_UNFUSED_BACKWARD has no effect.  The side products X A^T and dY B are binary32; in BF16 mode Y and dX
- * are rounded once by the main product and once more when the LoRA term is added.  Provided to measure the
+ * L4Q_FLAG_UNFUSED_BACKWARD has no effect.  The side products X A^T and dY B are binary32; in BF16 mode the LoRA term
+ * joins the main product's binary32 sums, and Y and dX are rounded once.  Provided to measure the
  * memory / time gap to the L4Q layer on the same device; it shares the L4Q kernels. */
 int l4q_qatlora_workspace_bytes(const l4q_desc* desc, size_t* forward_bytes, size_t* backward_bytes);
 int l4q_qatlora_forward(const l4q_desc* desc, const void* X, const void* W0, const void* A, const void* B,

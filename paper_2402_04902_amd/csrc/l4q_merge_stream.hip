@@ -5,7 +5,8 @@
 // Bound: HBM (2 bytes read + 2 written per weight forward, 2 + 4 backward) with a vector-ALU load close behind it,
 // so the kernel is built to keep both busy at once:
 //  * a wavefront is the unit of work and shares nothing with the other wavefronts of its workgroup (no workgroup
-//    barrier anywhere): four wavefronts per SIMD sit in different phases and overlap their loads, matrix ops, LDS
+//    barrier, but for the initialisation form in groups above 64, which joins the extremes of two or four wavefronts: all
+//    those of a workgroup that have columns walk the same row blocks, and the others have ended): four wavefronts per SIMD sit in different phases and overlap their loads, matrix ops, LDS
 //    round trips, vector arithmetic and stores.  A wavefront owns 64 columns of the weight and walks a run of row
 //    blocks of 32 down them (forward: one resident round of wavefronts covers the matrix), with the loads of the next row
 //    block in flight while it works on the current one; it has 9 KiB of LDS.

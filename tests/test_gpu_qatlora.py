@@ -42,7 +42,7 @@ def _run(spec, seed, shrink=0.8, accumulate=False):
     for name, got, ref in [("Y", layer.Y, Y), ("dX", layer.dX, gr.dX), ("dA", layer.dA, times * gr.dA),
                            ("dB", layer.dB, times * gr.dB), ("dscale", layer.dscale, times * gr.dscale),
                            ("dzero", layer.dzero, times * gr.dzero)]:
-        # Y and dX are rounded twice in bfloat16 mode (main product, then the LoRA term): the L4Q bounds hold
+        # Y and dX are rounded once in bfloat16 mode, the LoRA term included: the L4Q bounds hold
         fro_tol, elem_tol = BOUNDS[spec.dtype][name]
         compare_tensor(spec.name + " " + name, got.double().cpu().numpy(), ref, fro_tol, elem_tol)
     return fb, bb
