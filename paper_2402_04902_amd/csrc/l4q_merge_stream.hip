@@ -2,32 +2,51 @@
 // l4q_Wdequant; the backward form also leaves what the fused weight-gradient kernel needs: Wq^T, the
 // d(Wq)/d(scale) factor of Eq. quant_lsq_s with the straight-through mask of Eq. appen_ste in its magnitude, B^T).
 //
-// Bound: HBM (2 bytes read + 2 written per weight forward, 2 + 4 backward) with a vector-ALU load close behind it,
-// so the kernel is built to keep both busy at once:
-//  * a wavefront is the unit of work and shares nothing with the other wavefronts of its workgroup (no workgroup
-//    barrier, but for the initialisation form in groups above 64, which joins the extremes of two or four wavefronts: all
-//    those of a workgroup that have columns walk the same row blocks, and the others have ended): four wavefronts per SIMD sit in different phases and overlap their loads, matrix ops, LDS
-//    round trips, vector arithmetic and stores.  A wavefront owns 64 columns of the weight and walks a run of row
-//    blocks of 32 down them (forward: one resident round of wavefronts covers the matrix), with the loads of the next row
-//    block in flight while it works on the current one; it has 9 KiB of LDS.
-//  * rank sums sum_k B[p,k] A[k,j] on the matrix core as a chain of K = 1 binary32 ops, one per k in ascending order:
-//    each step is RN(acc + b a) with the bfloat16 product exact, i.e. the stated sequential order bit for bit.
-//    The accumulators come out one column per lane and pass through LDS once to become 4 consecutive columns of 8
-//    rows per lane: 16 lanes then cover 128 contiguous bytes of a weight row, a cache line, in every load.
-//  * Wq and Wq^T leave in the blocked layout the GEMM reads (32 k-values of all rows together): the forward form
-//    stores 256-byte runs, the backward form turns the row block over in LDS and stores 1 KiB runs.
-//  * the division w = (Wc - b) / s is not the 11-instruction IEEE expansion per weight.  One lane per (row, group)
-//    loads s and b, forms the correctly rounded reciprocal r = RN(1 / s) (hardware estimate, one Newton step, then the
-//    choice among the result and its two neighbours by the exact residual 1 - s r), and parks (s, b, r, 1024 s) in
-//    LDS; per weight the quotient is  q = x r;  t = fma(-s, q, x);  w = fma(t, r, q)  after clamping x to +-1024 s.
-//    With r correctly rounded, q is within one unit of x / s and the corrected w is the correctly rounded quotient
+// Bound: memory for the forward, statistics and packing forms, vector arithmetic for the backward and initialisation forms:
+// binary32 matrix ops and vector ops take turns (measured: a loop of each runs in the sum of their times, while bfloat16
+// matrix ops run beside vector ops), and 45 M weights x one vector op are 1.15 us of the chip.  A wavefront owns 64 columns of
+// the weight and walks a run of row blocks of 32 down them; it shares nothing with the others of its workgroup (but for the
+// initialisation form in groups above 64, which joins the extremes of two or four wavefronts).  One resident round of
+// workgroups covers the matrix; ids are dealt out so that an XCD works on whole rows (scale, zero and B are then fetched by
+// one L2 each: 49 -> 46 us at 11008 x 4096 forward).
+//  * A lane works on one row and 32 consecutive columns, one group: s, b and 1 / s are per-lane values, extremes and
+//    error sums need no exchange, 32 codes are `bits` whole words, and the matrix op's registers are the lane's columns in
+//    order (its M axis stands for the columns, see jm).  Only the 2-byte weights and results change lanes, through a 4 KiB
+//    tile of LDS, so that every load and store instruction covers whole cache lines.
+//  * Memory: the weights of the next row block are in flight while this one is worked on, its factors and parameters from the
+//    middle of this one on.  Loads and stores return in order of issue on one counter, so nothing may be waited for between
+//    a request and its use a row block later: no copies of requested registers at the loop's end, no request on a branch.
+//  * The stated rank sums sum_k B[p,k] A[k,j], k ascending, one rounding per step, are a chain of K = 1 binary32 matrix ops
+//    with the bfloat16 product exact: 64 cycles of the vector unit's time per k and 32 rows x 64 columns.  Forms whose result
+//    needs the codes alone (forward, packing) take near sums instead, from bfloat16 matrix ops (16 k at once, products
+//    exact, binary32 accumulation in the hardware's own order), and near quotients x (1/s), and settle what they cannot
+//    decide: a code is that of the stated arithmetic unless the near quotient w' lies within `tol` of a tie k + 1/2.
+//      tol = |gamma| D / s + 4 u |b| / s + 8 u R,   u = 2^-24, R = 2^(n-1) + 1 >= |w| wherever the code is not clear of the grid.
+//      D bounds the difference of the two sums: (r - 1) u S for the stated one (S = sum_k |B[p,k] A[k,j]|, products exact), and
+//      16 u S for each of the r / 16 matrix ops (17 terms cut to the largest one's 24 bits; measured on 12 M sums of 64 products
+//      with exponents up to 60 apart and nearly cancelling pairs: 7 u S for four ops): together below (2 r + 2) u S,
+//      S <= max |A| of the wavefront's columns x sum_k |B[p,k]|.
+//      The rest: Wc is rounded once on either side (u |Wc| each, |Wc| <= |b| + R s), the stated x and w once (u R each); near: 1 / s
+//      to one unit, 2 u, which multiplies Wc - b as a whole (2 u R), b / s rounded (u |b| / s), the sum rounded (u R).
+//    An infinity or NaN in A or B makes tol one, and nothing passes.  At 4 bits one row block in forty holds such a weight; the
+//    forward form then recomputes up to 8 of them alone from the operands in its registers, everything else repeats the row
+//    block by the stated arithmetic.  Forward 11008 x 4096, rank 16, inside a training step: 51 us (chain, sums through LDS) ->
+//    41; 4096 x 11008 at rank 64 105 -> 55; 4096 x 4096, groups of 64, 20.5 -> 14.4; packing 42 -> 27.  Error sums, which no
+//    single code decides, use the near values throughout: 45 -> 21.
+//  * Forms that need the quotient itself (backward: the factor; export) do not spend the 11-instruction IEEE expansion per
+//    weight: with the correctly rounded reciprocal r = RN(1 / s) (hardware estimate, one Newton step, then the
+//    choice among the result and its two neighbours by the exact residual 1 - s r),
+//    q = x r;  t = fma(-s, q, x);  w = fma(t, r, q)  after clamping x to +-1024 s.
+//    q is within one unit of x / s and the corrected w is the correctly rounded quotient
 //    (Markstein's theorem on division by multiplication with the reciprocal and one exact-remainder correction), so codes
 //    and mask are those of the stated arithmetic.  |x| > 1024 s lies beyond every code grid, where code, mask and
 //    factor depend on the sign of x alone.  Scales outside [2^-60, 2^60] take the IEEE divide instead (wave-uniform
 //    branch).  l4q_check_fast_divide compares the sequence with the IEEE divide on the GPU for every significand of s.
+//  * Wq and Wq^T leave in the blocked layout the GEMM reads (32 k-values of all rows together), 1 KiB per store instruction.
 //  * gamma a power of two (alpha = 2 r, the usual choice): gamma acc is exact, and W0 + gamma acc is one fused
 //    multiply-add with the same bits.
-// Shapes: bfloat16, rank a multiple of 8, group size >= 32; anything else runs merge_quant_tile_kernel.
+// Shapes: bfloat16, rank a multiple of 8, group size >= 32 (so rows are whole runs of 32); anything else runs
+// merge_quant_tile_kernel.
 #include <type_traits>
 
 #include "l4q_device.h"
@@ -39,15 +58,14 @@ namespace {
 
 constexpr int MS_COLS = 256;                     // columns per workgroup: 4 wavefronts x 64
 constexpr int MS_THREADS = 256;
-#ifndef MS_BWD_WAVES
-#define MS_BWD_WAVES 3                           // wavefronts per SIMD of the backward form
-#endif
-constexpr int MS_SPITCH = 72;                    // floats per row of the sums tile: 64 + 8, and 4 rows = 32 banks
-constexpr int MS_WAVE_LDS = 32 * MS_SPITCH * 4;  // 9216; the transposed tile of the backward form (5 KiB) aliases it
+constexpr int MS_BWD_WAVES = 3;                  // wavefronts per SIMD of the backward form
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef float f32x32_t __attribute__((ext_vector_type(32)));
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
 // RN(1 / s) for a normal s > 0 whose reciprocal is normal: the hardware estimate is within one unit in the last
 // place, a Newton step brings it to the correctly rounded value or a neighbour, and the exact residuals 1 - s r
@@ -78,39 +96,48 @@ __device__ __forceinline__ float fast_quotient(float x, float s, float r, float 
 }
 
 // the value of another lane of the same 16 (DPP control word)
-template <int CTRL> __device__ __forceinline__ uint32_t lane_swap_u(uint32_t v) {
+template <int CTRL> __device__ __forceinline__ uint32_t lane_swap(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
 }
-template <int CTRL> __device__ __forceinline__ float lane_swap(float v) {
-  return __uint_as_float(lane_swap_u<CTRL>(__float_as_uint(v)));
+// the values of lanes l % 32 and 32 + l % 32
+__device__ __forceinline__ uint2 both_halves(uint32_t v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const auto t = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return make_uint2(t[0], t[1]);
+#else
+  return make_uint2(v, v);
+#endif
+}
+__device__ __forceinline__ float2 both_halves(float v) {
+  const uint2 t = both_halves(__float_as_uint(v));
+  return make_float2(__uint_as_float(t.x), __uint_as_float(t.y));
+}
+__device__ __forceinline__ float half_sum(float v) {
+  const float2 t = both_halves(v);
+  return t.x + t.y;
 }
 
-// What one row block (32 rows x 64 columns) needs from memory.  The weight rows are requested a whole row block
-// ahead of their use (two register sets); the factors and the quantizer parameters of the next row block are
-// requested as soon as the current one has consumed its own (one set), before its streaming phase.
+// What one row block (32 rows x 64 columns) needs of the factors and the quantizer parameters.  Those of the next row block
+// are requested as soon as the current one has consumed its own, before its streaming phase.
+template <int ACH>
 struct FactorLoads {
-  u32x4 bq0, bq1;   // B[p0 + lane % 32, 0 .. 15] (first rank chunk)
-  float s, b;       // table role: scale / zero of (row lane % 32, group lane / 32)
+  u32x4 b[ACH > 0 ? ACH : 1];  // B[p, 16 c + 8 h .. + 7] of chunk c
+  float s, z;                  // scale / zero of row p = p0 + lane % 32, group of this lane's 32 columns
 };
-struct WeightLoads {
-  u32x2 w0[8];      // streaming role: W0[p0 + 8 (lane / 16) + rr, 4 columns]
-};
+
+// Bytes of LDS per wavefront: a tile of 32 rows x 128 bytes, in 16-byte pieces; backward: a second one for the factor;
+// export: 32 rows x 256 bytes (binary32); initialisation: two sets of 32 pairs behind the tile.
+template <int MODE> constexpr int ms_wave_lds() { return MODE == 2 || MODE == 3 ? 8192 : MODE == 5 ? 4096 + 512 : 4096; }
+template <int MODE> constexpr int ms_lds() { return 4 * ms_wave_lds<MODE>(); }
 
 // MODE 1: forward (dequantized Wq, [ld_wq / 32][o][32]).  MODE 2: backward (Wq^T, [ld_wqT / 32][i][32]; optionally the
 // factor [o, i] and B^T).  MODE 3: export (any of int8 codes, binary32 merged weight, mask; all [o, i]).  MODE 4: error
-// sums, one pair per wavefront.  MODE 5: scale / zero from the groups' extremes.  MODE 6: packed codes.
-// Grid: x = 256-column strips, y = partitions of the row blocks; wavefront w of a workgroup walks the row blocks
-// [nrb y / gridDim.y, nrb (y + 1) / gridDim.y) of its 64 columns (forward / export: one resident round of workgroups
-// covers the matrix; backward: four rounds' worth of shorter runs).
-// Transposed tile of the backward form (64 columns x 32 rows of bf16, column-major): pitch 80 bytes; it takes the place
-// of the sums tile once the row block has been streamed
-constexpr int MS_TPITCH = 80;
-static_assert(64 * MS_TPITCH <= MS_WAVE_LDS, "transposed tile aliases the sums tile");
-template <int MODE> constexpr int ms_wave_lds() { return MS_WAVE_LDS; }
-
+// sums, one pair per wavefront.  MODE 5: scale / zero from the groups' extremes.  MODE 6: packed codes of BITS bits.
+// Grid: 256-column strips x partitions of the row blocks; wavefront w of a workgroup walks the row blocks
+// [nrb part / parts, nrb (part + 1) / parts) of its 64 columns.
 // ACH: 16-k chunks of the rank whose A values a wavefront keeps in registers for its whole run (1: ranks up to 16;
 // 4: ranks up to 64, further chunks are loaded where they are used; 0: no rank term, Wc = W0, and A and B are not read).
-template <int MODE, bool GAMMA_POW2, int ACH>
+template <int MODE, bool GAMMA_POW2, int ACH, int BITS = 0>
 __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, const bf16_t* __restrict__ W0,
                                                         const bf16_t* __restrict__ A, const bf16_t* __restrict__ B,
                                                         const float* __restrict__ scale,
@@ -120,17 +147,20 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
 #if defined(__HIP_DEVICE_COMPILE__)
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  unsigned char* lds = lds_all + wave * ms_wave_lds<MODE>();
-  float* S = reinterpret_cast<float*>(lds);
-  unsigned char* Tt = lds;  // backward form: the transposed tile, in place of the sums tile
-  const int jw = blockIdx.x * MS_COLS + wave * 64;  // first column of this wavefront
+  [[maybe_unused]] unsigned char* tile = lds_all + wave * ms_wave_lds<MODE>();
+  // Workgroup ids go round-robin over the 8 XCDs: each XCD gets a contiguous run of row partitions with all their strips
+  const int strips = (int)((d.i + MS_COLS - 1) / MS_COLS), parts = (int)gridDim.x / strips;
+  const int total = (int)gridDim.x, xcd = (int)blockIdx.x & 7, at_xcd = (int)blockIdx.x >> 3;
+  const int id = xcd * (total >> 3) + (xcd < (total & 7) ? xcd : total & 7) + at_xcd;
+  const int strip = id % strips, part = id / strips;
+  const int jw = strip * MS_COLS + wave * 64;  // first column of this wavefront
   const int i = (int)d.i, o = (int)d.o, r = d.r, g = d.g;
   const int G = i / g;
-  const int rb_begin = (int)((int64_t)nrb * blockIdx.y / gridDim.y);
-  const int rb_end = (int)((int64_t)nrb * (blockIdx.y + 1) / gridDim.y);
+  const int rb_begin = (int)((int64_t)nrb * part / parts);
+  const int rb_end = (int)((int64_t)nrb * (part + 1) / parts);
   if constexpr (MODE == 2) {
     // the first column strip also leaves B^T for its rows (zeros from o to the padded width)
-    if (blockIdx.x == 0 && out.bT) {
+    if (strip == 0 && out.bT) {
       const int ld = (int)out.ld_wqT;
       const int pa = rb_begin * 32, pe = rb_end * 32 < ld ? rb_end * 32 : ld;
       const int np = pe - pa;
@@ -142,27 +172,21 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
     }
   }
   double err_q = 0.0, err_c = 0.0;  // MODE 4: this lane's share of the wavefront's sums
-  float* const err_out = MODE == 4 ? out.errors + 2 * (((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 4 + wave) : nullptr;
+  float* const err_out = MODE == 4 ? out.errors + 2 * ((int64_t)id * 4 + wave) : nullptr;
   if (jw >= i) {  // a whole wavefront past the last column (MODE 5's barriers count the wavefronts that are left)
     if (MODE == 4 && lane < 2) err_out[lane] = 0.f;
     return;
   }
 
-  // streaming role: 4 consecutive columns and 8 rows of the row block.  Forward: rows 4 rr + lane / 16, so that one
-  // store instruction covers 4 consecutive rows (Wq is written in blocks of 32 columns, [j / 32][p][j % 32]: 4 rows of a
-  // block are 256 contiguous bytes).  Backward / export: rows 8 (lane / 16) + rr, 8 consecutive rows per lane (a lane's
-  // column of the transposed tile is then 16 contiguous bytes).
-  constexpr int ROW_G = MODE == 1 ? 1 : 8, ROW_R = MODE == 1 ? 4 : 1;  // row = ROW_G (lane / 16) + ROW_R rr
-  const int g16 = lane >> 4, c16 = lane & 15;
-  const int j0 = jw + 4 * c16;
-  const bool col_ok = j0 < i;
-  const int grp_lane = g == 32 ? (c16 >> 3) : 0;  // group of the lane's columns within the wavefront's 64
-  // matrix role: lane = column jw + lane of the A operand, row p0 + lane % 32 of the B operand
-  const int jm = jw + lane;
-  const int l32 = lane & 31;
-  // table role: lane = (row lane % 32, group lane / 32) of the row block
-  const bool tab_lane = lane < (g == 32 ? 64 : 32);
-  const int qtab = jw / g + (lane >> 5);
+  // A lane works on row p0 + lane % 32 and the 32 consecutive columns from jl; i is a multiple of 32, so they are all
+  // inside or all outside, and of one group.
+  const int l32 = lane & 31, h = lane >> 5;
+  const int jl = jw + 32 * h;
+  const bool col_ok = jl < i;
+  const int qtab = jl / g;
+  // The matrix op's M axis is the columns: M index m = 8 q + 4 hh + e of column block b ends in register 4 q + e of half-wave
+  // hh.  With m standing for column 32 hh + 16 b + 4 q + e the registers of a lane are its 32 columns in order.
+  const int jm = jw + 32 * ((l32 >> 2) & 1) + 4 * (l32 >> 3) + (l32 & 3);  // + 16 b
 
   const __amdgpu_buffer_rsrc_t rsW0 = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(W0), 0, o * i * 2, 0x00020000);
   const __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(A), 0, r * i * 2, 0x00020000);
@@ -170,348 +194,529 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
   const __amdgpu_buffer_rsrc_t rsS = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(scale), 0, o * G * 4, 0x00020000);
   const __amdgpu_buffer_rsrc_t rsZ = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(zero), 0, o * G * 4, 0x00020000);
   constexpr unsigned OOB = 0x80000000u;
-  // outputs of the streaming layout
-  const int ld_out = MODE == 1 ? (int)out.ld_wq : i;
-  // forward: byte offset of the lane's 4 columns in row 0 of their 32-column block of Wq
-  const unsigned wq_col_off = j0 < ld_out ? (unsigned)((((jw >> 5) + (c16 >> 3)) * o * 32 + 4 * (c16 & 7)) * 2) : OOB;
-  const __amdgpu_buffer_rsrc_t rsOut = __builtin_amdgcn_make_buffer_rsrc(
-      MODE == 1 ? (void*)out.wq : MODE == 2 ? (void*)out.fgrad : (void*)out.codes, 0,
-      MODE == 3 ? o * i : o * ld_out * 2, 0x00020000);
-  const __amdgpu_buffer_rsrc_t rsMask = __builtin_amdgcn_make_buffer_rsrc(out.mask, 0, o * i, 0x00020000);
-  const __amdgpu_buffer_rsrc_t rsWc = __builtin_amdgcn_make_buffer_rsrc(out.wcomb, 0, o * i * 4, 0x00020000);
-  const bool want_f = MODE == 2 && out.fgrad != nullptr;
+  constexpr bool FILTER = MODE == 1 || MODE == 4 || MODE == 6, CHECKED = FILTER && MODE != 4;
+  constexpr bool FACTOR = MODE == 2 && ACH > 0;  // (the layers without a rank term take no factor)
 
-  // MODE 6: word t = lane % 8 of a run of 32 columns takes fields from lanes first .. first + pack_lanes - 1 of 8
-  const int pack_row = d.bits * (i / 32) * 4;  // bytes of a packed row
-  const int pack_t = c16 & 7, pack_first = 8 * pack_t / d.bits < 8 ? 8 * pack_t / d.bits : 7;
-  const int pack_src = (lane & ~7) + pack_first, pack_shift = 4 * d.bits * pack_first - 32 * pack_t;
-  const int pack_lanes = d.bits > 4 ? 3 : 4;
-  const bool pack_whole = d.bits == 2 || d.bits == 4 || d.bits == 8;
-  const bool pack_lane = pack_whole ? pack_t * d.bits % 8 == 0 : pack_t < d.bits;
-  const __amdgpu_buffer_rsrc_t rsPack = __builtin_amdgcn_make_buffer_rsrc(out.packed, 0, o * pack_row, 0x00020000);
-
-  // A[k, jm] of the first ACH rank chunks, two bfloat16 per register: loaded once per wavefront
-  uint32_t apk[ACH > 0 ? 8 * ACH : 1];
-  const unsigned voffA = jm < i ? (unsigned)(jm * 2) : OOB;
-#pragma unroll
-  for (int c = 0; c < ACH; ++c) {
-    uint32_t araw[16];
-#pragma unroll
-    for (int k = 0; k < 16; ++k)  // steps past the rank: a valid row is read; the B factor of that step is zero
-      araw[k] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rsA, (int)voffA, (16 * c + k < r ? 16 * c + k : r - 1) * i * 2, 0);
-#pragma unroll
-    for (int k = 0; k < 8; ++k) apk[8 * c + k] = araw[2 * k] | (araw[2 * k + 1] << 16);
-  }
+  // Memory role of a row-major tile: instruction t, lane = row 8 t + lane / 8, piece lane % 8 (whole 128-byte lines).  Piece
+  // c of row p lies at position c ^ (p % 8) of its row in LDS, so that 8 consecutive lanes meet all banks in either role.
+  const int mr = lane >> 3, mc = lane & 7;
+  const bool mcol_ok = jw + 8 * mc < i;
+  // LDS offsets of the two roles, recomputed from one base each per row block: left to itself the compiler keeps
+  // every address of the loop in a register of its own and spills the sums for them
+  uint32_t mem_base = (uint32_t)(wave * ms_wave_lds<MODE>() + mr * 128 + ((mc ^ mr) << 4));                     // + 1024 t
+  uint32_t row_base = (uint32_t)(wave * ms_wave_lds<MODE>() + l32 * 128 + (((4 * h) ^ (l32 & 7)) << 4));        // ^ 16 c
+  auto lds16 = [&](uint32_t at) -> u32x4& { return *reinterpret_cast<u32x4*>(lds_all + at); };
 
   // every load of row block rb; past the wavefront's range (or the matrix) the offsets are out of range: nothing moves
-  auto request_factors = [&](FactorLoads& F, int rb) {
-    const int p0 = rb * 32;
-    const bool row_m = rb < rb_end && p0 + l32 < o;
-    if constexpr (ACH > 0) {
-      const unsigned voffB = row_m ? (unsigned)((p0 + l32) * r * 2) : OOB;
-      F.bq0 = __builtin_amdgcn_raw_buffer_load_b128(rsB, (int)voffB, 0, 0);
-      F.bq1 = __builtin_amdgcn_raw_buffer_load_b128(rsB, (int)(r > 8 ? voffB + 16u : voffB), 0, 0);
-    }
+  FactorLoads<ACH> F;
+  auto load_b = [&](int p, bool row_ok, int k0) {  // (rank a multiple of 8: a lane's 8 values are all inside or all outside)
+    return __builtin_amdgcn_raw_buffer_load_b128(
+        rsB, (int)(row_ok & (k0 + 8 * h < r) ? (unsigned)((p * r + k0 + 8 * h) * 2) : OOB), 0, 0);
+  };
+  auto request_factors = [&](int rb) {
+    const int p = rb * 32 + l32;
+    const bool row_ok = (rb < rb_end) & (p < o);
+#pragma unroll
+    for (int c = 0; c < ACH; ++c) F.b[c] = load_b(p, row_ok, 16 * c);
     if (MODE == 5) return;
-    const unsigned vt = tab_lane && row_m ? (unsigned)(((p0 + l32) * G + qtab) * 4) : OOB;
+    const unsigned vt = row_ok & col_ok ? (unsigned)((p * G + qtab) * 4) : OOB;
     F.s = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsS, (int)vt, 0, 0));
-    F.b = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsZ, (int)vt, 0, 0));
+    F.z = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsZ, (int)vt, 0, 0));
   };
-  auto request_weights = [&](WeightLoads& L, int rb) {
-    const int p0 = rb * 32;
-    // rows are valid in blocks of 8 (o % 8 == 0).  Backward / export: this lane's 8 rows are all inside or all outside.
-    // Forward: rows 4 rr .. 4 rr + 3 of the block are inside or outside together (uniform in the wave): rows past o
-    // re-read the block's first rows, and nothing is stored for them.
-    const bool lane_rows_ok = MODE == 1 ? true : p0 + 8 * g16 < o;
-    const unsigned vw = rb < rb_end && lane_rows_ok && col_ok ? (unsigned)(((p0 + ROW_G * g16) * i + j0) * 2) : OOB;
+  u32x4 next_w[4];
+  auto request_weights = [&](int rb) {  // (rows from o on lie past the end of the buffer)
+    const unsigned vw = (rb < rb_end) & mcol_ok ? (unsigned)(((rb * 32 + mr) * i + jw + 8 * mc) * 2) : OOB;
 #pragma unroll
-    for (int rr = 0; rr < 8; ++rr) {
-      const int rsel = MODE == 1 && p0 + ROW_R * rr >= o ? 0 : ROW_R * rr;
-      L.w0[rr] = __builtin_amdgcn_raw_buffer_load_b64(rsW0, (int)vw, rsel * i * 2, 0);
-    }
+    for (int t = 0; t < 4; ++t) next_w[t] = __builtin_amdgcn_raw_buffer_load_b128(rsW0, (int)(vw + (unsigned)(t * 16 * i)), 0, 0);
   };
-
-  FactorLoads F;
-  auto compute = [&](WeightLoads& L, int rb) {
-    const int p0 = rb * 32;
-    const bool rows_ok = MODE == 1 ? true : p0 + 8 * g16 < o;  // (forward: decided per row, uniformly)
-    // ---- rank sums on the matrix core, k ascending
-    f32x32_t sum;
-#pragma unroll
-    for (int e = 0; e < 32; ++e) sum[e] = 0.f;
-    // B[p0 + lane % 32, 16 c .. 16 c + 15] of the chunks 1 .. ACH - 1, requested before the first chunk's matrix ops
-    u32x4 bx[ACH > 1 ? ACH - 1 : 1][2];
-    if constexpr (ACH > 1) {
-#pragma unroll
-      for (int c = 1; c < ACH; ++c) {
-        const unsigned vb = p0 + l32 < o && 16 * c < r ? (unsigned)((p0 + l32) * r * 2 + 32 * c) : OOB;
-        bx[c - 1][0] = __builtin_amdgcn_raw_buffer_load_b128(rsB, (int)vb, 0, 0);
-        bx[c - 1][1] = __builtin_amdgcn_raw_buffer_load_b128(rsB, (int)(16 * c + 8 < r ? vb + 16u : vb), 0, 0);
-      }
-    }
-    if constexpr (ACH > 0) {
-      const uint32_t bw[8] = {F.bq0[0], F.bq0[1], F.bq0[2], F.bq0[3], F.bq1[0], F.bq1[1], F.bq1[2], F.bq1[3]};
-#pragma unroll
-      for (int k = 0; k < 16; ++k) {
-        // a row of B ends at r: what follows in memory is the next row, not a zero
-        const float bk = k < r ? __uint_as_float(k & 1 ? bw[k >> 1] & 0xFFFF0000u : bw[k >> 1] << 16) : 0.f;
-        const float ak = __uint_as_float(k & 1 ? apk[k >> 1] & 0xFFFF0000u : apk[k >> 1] << 16);
-        sum = __builtin_amdgcn_mfma_f32_32x32x1f32(bk, ak, sum, 0, 0, 0);
-      }
-    }
-    if constexpr (ACH > 1) {
-#pragma unroll
-      for (int c = 1; c < ACH; ++c) {
-        if (16 * c < r) {  // (uniform)
-          const uint32_t bw[8] = {bx[c - 1][0][0], bx[c - 1][0][1], bx[c - 1][0][2], bx[c - 1][0][3],
-                                  bx[c - 1][1][0], bx[c - 1][1][1], bx[c - 1][1][2], bx[c - 1][1][3]};
-#pragma unroll
-          for (int k = 0; k < 16; ++k) {
-            const float bk = 16 * c + k < r ? __uint_as_float(k & 1 ? bw[k >> 1] & 0xFFFF0000u : bw[k >> 1] << 16) : 0.f;
-            const float ak = __uint_as_float(k & 1 ? apk[8 * c + (k >> 1)] & 0xFFFF0000u : apk[8 * c + (k >> 1)] << 16);
-            sum = __builtin_amdgcn_mfma_f32_32x32x1f32(bk, ak, sum, 0, 0, 0);
-          }
-        }
-      }
-    }
-    for (int k0 = 16 * ACH; ACH > 0 && k0 < r; k0 += 16) {  // chunks beyond those in registers: loaded where they are used
-      const unsigned voffB = p0 + l32 < o ? (unsigned)((p0 + l32) * r * 2 + 2 * k0) : OOB;
-      const u32x4 q0 = __builtin_amdgcn_raw_buffer_load_b128(rsB, (int)voffB, 0, 0);
-      const u32x4 q1 = __builtin_amdgcn_raw_buffer_load_b128(rsB, (int)(k0 + 8 < r ? voffB + 16u : voffB), 0, 0);
-      float af[16];
-#pragma unroll
-      for (int k = 0; k < 16; ++k)
-        af[k] = bf16_to_f32((uint16_t)__builtin_amdgcn_raw_buffer_load_b16(
-            rsA, (int)voffA, (k0 + k < r ? k0 + k : r - 1) * i * 2, 0));
-      const uint32_t bw[8] = {q0[0], q0[1], q0[2], q0[3], q1[0], q1[1], q1[2], q1[3]};
-#pragma unroll
-      for (int k = 0; k < 16; ++k) {
-        const float bk = k0 + k < r ? __uint_as_float(k & 1 ? bw[k >> 1] & 0xFFFF0000u : bw[k >> 1] << 16) : 0.f;
-        sum = __builtin_amdgcn_mfma_f32_32x32x1f32(bk, af[k], sum, 0, 0, 0);
-      }
-    }
-
-    // ---- (row, group) table into the padding of the sums tile: s, b, RN(1 / s), 1024 s
-    const bool bad_scale = MODE != 5 && tab_lane && p0 + l32 < o && !scale_in_fast_range(F.s);
-    const bool slow = __builtin_amdgcn_ballot_w64(bad_scale) != 0;  // wave-uniform
-    if (MODE != 5 && tab_lane) {
-      const float rc = exact_reciprocal(F.s);
-      *reinterpret_cast<float4*>(S + l32 * MS_SPITCH + 64 + 4 * (lane >> 5)) = make_float4(F.s, F.b, rc, F.s * 1024.f);
-    }
-    request_factors(F, rb + 1);  // this row block has consumed its own
-    // ---- sums to the streaming layout: register e of lane l is row 8 ((e % 16) / 4) + 4 (l / 32) + e % 4,
-    //      column 32 (e / 16) + l % 32
-    if constexpr (ACH > 0) {
-#pragma unroll
-      for (int e = 0; e < 32; ++e)
-        S[(8 * ((e & 15) >> 2) + 4 * (lane >> 5) + (e & 3)) * MS_SPITCH + 32 * (e >> 4) + l32] = sum[e];
-    }
+  auto lds_order = [&] {  // a wavefront's own LDS accesses stay in program order; the compiler has to keep it
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  request_weights(rb_begin);
+  request_factors(rb_begin);
 
-    // ---- stream: 8 rows x 4 columns per lane.  Forward: the padding columns i .. ld_wq - 1 are written as zeros.
-    const unsigned vo_out = MODE == 1 ? (wq_col_off == OOB ? OOB : wq_col_off + (unsigned)((p0 + g16) * 64))
-                            : rows_ok && j0 < ld_out ? (unsigned)(((p0 + 8 * g16) * ld_out + j0) * (MODE == 3 ? 1 : 2)) : OOB;
-    const int row_bytes = MODE == 1 ? ROW_R * 64 : ld_out * (MODE == 3 ? 1 : 2);
-    float eq = 0.f, ec = 0.f;          // MODE 4
-    float lo[8], hi8[8];               // MODE 5: extremes of the lane's 4 columns, per row
-    const unsigned vo_pack = pack_lane && rows_ok && jw + 32 * (c16 >> 3) < i  // MODE 6
-                                 ? (unsigned)((p0 + 8 * g16) * pack_row + ((jw >> 5) + (c16 >> 3)) * 4 * d.bits +
-                                              (pack_whole ? pack_t * d.bits / 8 : pack_t) * 4)
-                                 : OOB;
-    uint32_t wqpack[4][4];  // backward form: dequantized weights of the row block, [column][row pair]
-    // (the padding columns are zeroed with a mask, not a select: a select over the whole quantizer chain is compiled
-    // into a branch per row, which cuts the eight rows into pieces that cannot be scheduled together; for the same
-    // reason the row guard of the forward form exists only in the instance for the matrix's last, partial row block)
-    const uint32_t colmask = col_ok ? 0xFFFFFFFFu : 0u;
-    auto stream_rows = [&](auto fast_tag, auto guard_tag) {
-      constexpr bool FAST = decltype(fast_tag)::value;
-      constexpr bool GUARD_ROWS = decltype(guard_tag)::value;
-      float wqprev[4] = {0.f, 0.f, 0.f, 0.f};
+  // A of the first ACH rank chunks, two bfloat16 per register, loaded once per wavefront.  FILTER: operand fragments of the
+  // bfloat16 matrix op, A[16 c + 8 h + e, jm + 16 b] at [8 c + 4 b + e / 2].  Else A[16 c + k, jm + 16 h] at [8 c + k / 2].
+  uint32_t apk[ACH > 0 ? 8 * ACH : 1];
+  const unsigned voffA = jm + 16 * h < i ? (unsigned)((jm + 16 * h) * 2) : OOB;
+  // chunk k0 .. k0 + 15 as fragments
+  auto load_fragments = [&](int k0, uint32_t (&f)[8]) {
+    uint32_t raw[16];
 #pragma unroll
-      for (int rr = 0; rr < 8; ++rr) {
-        const int row = ROW_G * g16 + ROW_R * rr;
-        const float4 acc = ACH > 0 ? *reinterpret_cast<const float4*>(S + row * MS_SPITCH + 4 * c16)
-                                   : make_float4(0.f, 0.f, 0.f, 0.f);
-        const float4 tab = *reinterpret_cast<const float4*>(S + row * MS_SPITCH + 64 + 4 * grp_lane);
-        const float s = tab.x, b = tab.y, rc = tab.z, hi = tab.w;
-        const float av[4] = {acc.x, acc.y, acc.z, acc.w};
-        const float w0[4] = {__uint_as_float(L.w0[rr][0] << 16), __uint_as_float(L.w0[rr][0] & 0xFFFF0000u),
-                             __uint_as_float(L.w0[rr][1] << 16), __uint_as_float(L.w0[rr][1] & 0xFFFF0000u)};
-        float wc[4], wq[4], fg[4];
-        uint32_t cpack = 0, mpack = 0;
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          wc[c] = ACH == 0 ? w0[c] + 0.f  // (as W0 + gamma 0: a weight of -0 becomes +0)
-                  : GAMMA_POW2 ? fmaf(d.gamma, av[c], w0[c]) : w0[c] + d.gamma * av[c];
-          if constexpr (MODE == 5) continue;
-          const float x = wc[c] - b;
-          const float w = FAST ? fast_quotient(x, s, rc, hi) : __fdiv_rn(x, s);
-          const float cl = __builtin_amdgcn_fmed3f(w, d.qn, d.qp);
-          const float code = rintf(cl);
-          if (MODE == 1 || MODE == 2 || MODE == 4) wq[c] = fmaf(code, s, b);
-          if (MODE == 4) {
-            eq += rows_ok && col_ok ? fabsf(wc[c] - wq[c]) : 0.f;
-            ec += rows_ok && col_ok ? fabsf(wc[c] - fmaf(cl, s, b)) : 0.f;
-          }
-          if (MODE == 6) cpack |= (uint32_t)(int)(code - d.qn) << (d.bits * c);
-          if (MODE == 2) fg[c] = cl == w ? code - w : code;  // in range = the clamp changed nothing
-          if (MODE == 3) {
-            cpack |= ((uint32_t)(uint8_t)(int8_t)(int)code) << (8 * c);
-            mpack |= (cl == w ? 1u : 0u) << (8 * c);
-          }
-        }
-        if (MODE == 1) {
-          const u32x2 v = {pack_bf16x2(wq[0], wq[1]) & colmask, pack_bf16x2(wq[2], wq[3]) & colmask};
-          if (!GUARD_ROWS || p0 + ROW_R * rr < o)  // uniform
-            __builtin_amdgcn_raw_buffer_store_b64(v, rsOut, (int)vo_out, rr * row_bytes, 0);
-        } else if (MODE == 2) {
-          if (want_f) {
-            typedef _Float16 h4 __attribute__((ext_vector_type(4)));
-            const h4 h = {(_Float16)fg[0], (_Float16)fg[1], (_Float16)fg[2], (_Float16)fg[3]};
-            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, h), rsOut, (int)vo_out, rr * row_bytes, 0);
-          }
-          // rows 2 h, 2 h + 1 of this lane's 8 share a register per column; rows past o (the zero padding of Wq^T up
-          // to its leading dimension) are kept as zeros
+      for (int e = 0; e < 8; ++e)
+        raw[8 * b + e] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(
+            rsA, (int)(jm < i && k0 + 8 * h < r ? (unsigned)((8 * h * i + jm + 16 * b) * 2) : OOB), (k0 + e) * i * 2, 0);
 #pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            if ((rr & 1) == 0) wqprev[c] = wq[c];
-            else wqpack[c][rr >> 1] = rows_ok ? pack_bf16x2(wqprev[c], wq[c]) : 0u;
-          }
-        } else if (MODE == 5) {
-          lo[rr] = col_ok ? fminf(fminf(wc[0], wc[1]), fminf(wc[2], wc[3])) : __builtin_huge_valf();
-          hi8[rr] = col_ok ? fmaxf(fmaxf(wc[0], wc[1]), fmaxf(wc[2], wc[3])) : -__builtin_huge_valf();
-        } else if (MODE == 6) {
-          // 8 lanes hold 32 columns, `bits` words.  2, 4, 8 bits: a word is the fields of 4, 2, 1 lanes, joined in the first
-          // of them; otherwise lane t gathers word t from the lanes whose fields reach into it (10 us more per 45 M weights)
-          uint32_t word = pack_whole ? cpack : 0;
-          if (pack_whole) {
-            if (d.bits < 8) word |= lane_swap_u<0xB1>(word) << (4 * d.bits & 31);
-            if (d.bits < 4) word |= lane_swap_u<0x4E>(word) << 16;
-          } else {
-            for (int q = 0; q < pack_lanes; ++q) {
-              const uint32_t v = (uint32_t)__shfl((int)cpack, pack_src + q, 64);
-              const int sh = pack_shift + 4 * d.bits * q;
-              word |= sh >= 32 ? 0u : sh >= 0 ? v << sh : v >> -sh;
-            }
-          }
-          __builtin_amdgcn_raw_buffer_store_b32(word, rsPack, (int)vo_pack, rr * pack_row, 0);
-        } else if (MODE == 3) {
-          if (out.codes) __builtin_amdgcn_raw_buffer_store_b32(cpack, rsOut, (int)vo_out, rr * row_bytes, 0);
-          if (out.mask) __builtin_amdgcn_raw_buffer_store_b32(mpack, rsMask, (int)vo_out, rr * row_bytes, 0);
-          if (out.wcomb) {
-            const u32x4 v = {__float_as_uint(wc[0]), __float_as_uint(wc[1]), __float_as_uint(wc[2]), __float_as_uint(wc[3])};
-            __builtin_amdgcn_raw_buffer_store_b128(v, rsWc, (int)(vo_out == OOB ? OOB : vo_out * 4u), rr * row_bytes * 4, 0);
-          }
-        }
-      }
-    };
-    if (MODE == 1 && p0 + 32 > o) {  // last, partial row block of the forward form
-      if (!slow) stream_rows(std::true_type{}, std::true_type{});
-      else stream_rows(std::false_type{}, std::true_type{});
-    } else {
-      if (!slow) stream_rows(std::true_type{}, std::false_type{});
-      else stream_rows(std::false_type{}, std::false_type{});
+    for (int q = 0; q < 8; ++q) f[q] = raw[2 * q] | (raw[2 * q + 1] << 16);
+  };
+  if constexpr (FILTER) {
+#pragma unroll
+    for (int c = 0; c < ACH; ++c) {
+      uint32_t f[8] = {};
+      if (c == 0 || 16 * c < r) load_fragments(16 * c, f);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) apk[8 * c + q] = f[q];
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();  // every lane's reads of the sums tile are done: it may be overwritten
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  } else {
+#pragma unroll
+    for (int c = 0; c < ACH; ++c) {
+      uint32_t araw[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k)  // steps past the rank: a valid row is read; the B factor of that step is zero
+        araw[k] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rsA, (int)voffA, (16 * c + k < r ? 16 * c + k : r - 1) * i * 2, 0);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) apk[8 * c + k] = araw[2 * k] | (araw[2 * k + 1] << 16);
+    }
+  }
+  // CHECKED: what |sums' difference| / sum_k |B[p,k]| can come to, as a multiple of gamma max |A| of the wavefront's columns
+  float sum_tol = 0.f;
+  if constexpr (CHECKED && ACH > 0) {
+    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+    u16x2 m = {0, 0};
+    auto take = [&](uint32_t v) { m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, v & 0x7FFF7FFFu)); };
+#pragma unroll
+    for (int q = 0; q < 8 * ACH; ++q) take(apk[q]);
+    for (int k0 = 16 * ACH; k0 < r; k0 += 16) {
+      uint32_t f[8];
+      load_fragments(k0, f);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) take(f[q]);
+    }
+    uint32_t w = m[0] > m[1] ? m[0] : m[1];  // (magnitudes of bfloat16 order as integers, NaN above infinity)
+    auto take_lane = [&](uint32_t v) { w = w > v ? w : v; };
+    take_lane(lane_swap<0xB1>(w));   // quad_perm: lane ^ 1
+    take_lane(lane_swap<0x4E>(w));   // quad_perm: lane ^ 2
+    take_lane(lane_swap<0x141>(w));  // row_half_mirror
+    take_lane(lane_swap<0x140>(w));  // row_mirror
+    uint32_t top = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t v = (uint32_t)__builtin_amdgcn_readlane((int)w, 16 * q);
+      top = top > v ? top : v;
+    }
+    sum_tol = fabsf(d.gamma) * (float)(r + 2) * 0x1p-23f * __uint_as_float(top << 16);
+  }
 
-    if constexpr (MODE == 4) {
-      err_q += (double)eq;
-      err_c += (double)ec;
+  auto odd_even = [](uint32_t v, int k) { return __uint_as_float(k & 1 ? v & 0xFFFF0000u : v << 16); };
+  // one chunk of the stated sum: k ascending, RN(acc + b a) each; rank steps past r have a zero factor.  Each half-wave holds
+  // 8 of the 16 values of B, and both need all of them.
+  auto chain = [&](f32x32_t& sum, const u32x4& bq, const uint32_t* a) {
+    uint32_t bw[8];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint2 t = both_halves(bq[q]);
+      bw[q] = t.x;
+      bw[4 + q] = t.y;
     }
-    if constexpr (MODE == 5) {
-      // ---- extremes over the 8 (g = 32) or 16 lanes of a row, then over the wavefronts that share a group: through the
-      //      padding of the sums tiles, two sets in turn, so that one barrier per row block is enough
-      const int set = 64 + 4 * ((rb - rb_begin) & 1);
 #pragma unroll
-      for (int rr = 0; rr < 8; ++rr) {
-        float a = lo[rr], z = hi8[rr];
-        a = fminf(a, lane_swap<0xB1>(a)); z = fmaxf(z, lane_swap<0xB1>(z));      // quad_perm: lane ^ 1
-        a = fminf(a, lane_swap<0x4E>(a)); z = fmaxf(z, lane_swap<0x4E>(z));      // quad_perm: lane ^ 2
-        a = fminf(a, lane_swap<0x141>(a)); z = fmaxf(z, lane_swap<0x141>(z));    // row_half_mirror
-        if (g > 32) {
-          a = fminf(a, lane_swap<0x140>(a)); z = fmaxf(z, lane_swap<0x140>(z));  // row_mirror
-        }
-        if ((c16 & 7) == 0)
-          *reinterpret_cast<float2*>(S + (8 * g16 + rr) * MS_SPITCH + set + 2 * (c16 >> 3)) = make_float2(a, z);
-      }
-      if (g > 64) __syncthreads();
-      else {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      }
-      const int span = g > 64 ? g / 64 : 1;  // wavefronts of a group; its first one finishes it
-      if (wave % span == 0 && tab_lane && p0 + l32 < o) {
-        const float* t = S + l32 * MS_SPITCH + set + 2 * (lane >> 5);
-        float a = t[0], z = t[1];
-        for (int w = 1; w < span; ++w) {
-          a = fminf(a, t[w * (MS_WAVE_LDS / 4)]);
-          z = fmaxf(z, t[w * (MS_WAVE_LDS / 4) + 1]);
-        }
-        // a group of nothing but NaN has the extremes of an empty one, as in the general pass
-        a = fminf(a, __builtin_huge_valf());
-        z = fmaxf(z, -__builtin_huge_valf());
-        float s0, b0 = 0.f;
-        if (out.init_method == 0) {         // asymmetric min / max
-          s0 = __fdiv_rn(z - a, d.qp - d.qn);
-          b0 = a - s0 * d.qn;
-        } else if (out.init_method == 1) {  // symmetric
-          s0 = __fdiv_rn(fmaxf(fabsf(a), fabsf(z)), -d.qn);
-        } else {                            // L4Q_init (Eq. l4q_quant_init)
-          s0 = fmaxf(fabsf(__fdiv_rn(a, d.qn)), fabsf(__fdiv_rn(z, d.qp)));
-        }
-        if (qtab < G) {
-          out.init_scale[(int64_t)(p0 + l32) * G + qtab] = s0;
-          out.init_zero[(int64_t)(p0 + l32) * G + qtab] = b0;
-        }
-      }
-    }
-
-    if constexpr (MODE == 2) {
-      // ---- Wq^T in blocks of 32 rows, [p / 32][j][p % 32]: this row block's 64 columns are 4 KiB of consecutive
-      //      addresses.  Through LDS, column-major, then 16 bytes per lane, 1 KiB per store instruction.
+    for (int k = 0; k < 16; ++k)
+      sum = __builtin_amdgcn_mfma_f32_32x32x1f32(odd_even(a[k >> 1], k), odd_even(bw[k >> 1], k), sum, 0, 0, 0);
+  };
+  // chunks from k_first on, loaded where they are used
+  auto chain_rest = [&](f32x32_t& sum, int p, bool row_ok, int k_first) {
+    for (int k0 = k_first; k0 < r; k0 += 16) {
+      const u32x4 bq = load_b(p, row_ok, k0);
+      uint32_t araw[16], a[8];
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const u32x4 v = {wqpack[c][0], wqpack[c][1], wqpack[c][2], wqpack[c][3]};
-        *reinterpret_cast<u32x4*>(Tt + (4 * c16 + c) * MS_TPITCH + 16 * g16) = v;
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      const int ld = (int)out.ld_wqT;
-      const __amdgpu_buffer_rsrc_t rsT = __builtin_amdgcn_make_buffer_rsrc(out.wqT, 0, i * ld * 2, 0x00020000);
-      const int ch = lane & 3;
+      for (int k = 0; k < 16; ++k)
+        araw[k] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rsA, (int)voffA, (k0 + k < r ? k0 + k : r - 1) * i * 2, 0);
 #pragma unroll
-      for (int it = 0; it < 4; ++it) {
-        const int col = it * 16 + (lane >> 2);
-        const u32x4 v = *reinterpret_cast<const u32x4*>(Tt + col * MS_TPITCH + ch * 16);
-        const unsigned vo = jw + col < i ? (unsigned)(((rb * i + jw + col) * 32 + 8 * ch) * 2) : OOB;
-        __builtin_amdgcn_raw_buffer_store_b128(v, rsT, (int)vo, 0, 0);
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();  // the tile is read out: the next row block's sums may overwrite it
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      for (int k = 0; k < 8; ++k) a[k] = araw[2 * k] | (araw[2 * k + 1] << 16);
+      chain(sum, bq, a);
     }
   };
 
-  // Row blocks alternate between two register sets, so that the weight rows of the next row block are in flight while
-  // this one is worked on.
+  // nothing is outstanding where the loop is entered: else its waits are set for the entry's count of requests, which has no stores
+  // between, and each iteration waits for the last one's stores
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+  __builtin_amdgcn_sched_barrier(0);
+  uint32_t no_bits = 0;
+  asm volatile("" : "+s"(no_bits));
   int rb = rb_begin;
-  request_factors(F, rb);
-  WeightLoads L0, L1;
-  request_weights(L0, rb);
-  while (rb < rb_end) {
-    request_weights(L1, rb + 1);
-    compute(L0, rb);
-    if (++rb >= rb_end) break;
-    request_weights(L0, rb + 1);
-    compute(L1, rb);
-    ++rb;
-  }
+  do {  // (no partition is empty)
+    const int p0 = rb * 32, p = p0 + l32;
+    const bool row_ok = p < o;
+    asm volatile("" : "+v"(mem_base), "+v"(row_base));
+    if constexpr (ACH > 0) {  // (A stays packed: unpacked ahead of the loop it is spilled)
+#pragma unroll
+      for (int k = 0; k < 8 * ACH; ++k) asm volatile("" : "+v"(apk[k]));
+    }
+    // ---- this row block's weights: memory role -> one row per lane
+#pragma unroll
+    for (int t = 0; t < 4; ++t) lds16(mem_base + 1024 * t) = next_w[t];
+    if constexpr (FILTER) request_weights(rb + 1);
+    lds_order();
+    u32x4 w0[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) w0[c] = lds16(row_base ^ (16 * c));
+
+    // ---- rank sums
+    f32x16_t near[2];  // FILTER: near[b][e] of column 16 b + e
+    f32x32_t sum;
+    float bsum = 0.f;
+    if constexpr (FILTER) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) near[0][e] = near[1][e] = 0.f;
+      auto add_chunk = [&](const u32x4& bq, const uint32_t* a) {
+        const bf16x8_t fb = __builtin_bit_cast(bf16x8_t, bq);
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          const u32x4 fa = {a[4 * b], a[4 * b + 1], a[4 * b + 2], a[4 * b + 3]};
+          near[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, fa), fb, near[b], 0, 0, 0);
+        }
+        if constexpr (CHECKED) {
+          typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const uint32_t pair = bq[q] & 0x7FFF7FFFu;
+            bsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, pair),
+                                                   __builtin_bit_cast(bf16x2_t, 0x3F803F80u), bsum, false);
+          }
+        }
+      };
+#pragma unroll
+      for (int c = 0; c < ACH; ++c)
+        if (c == 0 || 16 * c < r) add_chunk(F.b[c], apk + 8 * c);  // (uniform)
+      for (int k0 = 16 * ACH; ACH > 0 && k0 < r; k0 += 16) {
+        uint32_t f[8];
+        load_fragments(k0, f);
+        add_chunk(load_b(p, row_ok, k0), f);
+      }
+    } else if constexpr (ACH > 0) {
+#pragma unroll
+      for (int e = 0; e < 32; ++e) sum[e] = 0.f;
+#pragma unroll
+      for (int c = 0; c < ACH; ++c)
+        if (c == 0 || 16 * c < r) chain(sum, F.b[c], apk + 8 * c);  // (uniform)
+      chain_rest(sum, p, row_ok, 16 * ACH);
+    }
+
+    // ---- this lane's group: s, b, 1 / s (RN(1 / s) unless the codes are checked), 1024 s
+    // (by an op, into registers of their own, so that the next row block's can be fetched into F's: otherwise the loop ends in
+    // copies that wait for that fetch)
+    const float s = __uint_as_float(__float_as_uint(F.s) ^ no_bits), b = __uint_as_float(__float_as_uint(F.z) ^ no_bits);
+    const bool bad_scale = MODE != 5 && row_ok && col_ok && !scale_in_fast_range(s);
+    const bool slow = __builtin_amdgcn_ballot_w64(bad_scale) != 0;  // wave-uniform
+    float rc = MODE == 5 ? 0.f : CHECKED ? __builtin_amdgcn_rcpf(s) : exact_reciprocal(s);
+    const float hi = s * 1024.f;
+    const float nbr = -(b * rc);                                   // FILTER
+    if constexpr (!FILTER) request_weights(rb + 1);  // (not before the rank sums: they need the registers)
+    request_factors(rb + 1);
+
+    // ---- stream: 32 columns per lane
+    float eq = 0.f, ec = 0.f;                                                   // MODE 4
+    float lo = __builtin_huge_valf(), top = -__builtin_huge_valf();             // MODE 5: extremes of the lane's columns
+    uint32_t words[BITS + 1];                                                   // MODE 6: the lane's columns are BITS whole words
+    const uint32_t row_mask = row_ok ? 0xFFFFFFFFu : 0u;                        // MODE 2: zeros below the last row
+    u32x4 code8[2], mask8[2], wc4;                                              // MODE 3
+    if (MODE == 3) lds_order();  // (its binary32 tile takes the place of the weights)
+    float off = 0.f;                                                            // CHECKED: largest |w - code| inside the grid
+    // Merged weights and quotients of columns 8 c .. 8 c + 7.  FORM 0: the stated sums, IEEE divide; 1: the stated sums, quotient
+    // by the reciprocal; 2: near sums and quotients.
+    auto stream_columns = [&](auto form_tag) {
+      constexpr int FORM = decltype(form_tag)::value;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        if (FORM == 0) __builtin_amdgcn_sched_barrier(0);
+        float wq[8], fg[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const int n = 8 * c + e;
+          const float wv = odd_even(w0[c][e >> 1], e);
+          float wc;
+          if constexpr (ACH == 0) wc = wv + 0.f;  // (as W0 + gamma 0: a weight of -0 becomes +0)
+          else if constexpr (FORM == 2) wc = fmaf(d.gamma, near[n / 16][n % 16], wv);
+          else wc = GAMMA_POW2 ? fmaf(d.gamma, sum[n], wv) : wv + d.gamma * sum[n];
+          if constexpr (MODE == 5) {
+            lo = fminf(lo, wc);
+            top = fmaxf(top, wc);
+            continue;
+          }
+          const float x = wc - b;
+          const float w = FORM == 2 ? fmaf(wc, rc, nbr) : FORM == 1 ? fast_quotient(x, s, rc, hi) : __fdiv_rn(x, s);
+          const float cl = __builtin_amdgcn_fmed3f(w, d.qn, d.qp);
+          if constexpr (MODE == 6) {
+            // cl + 1.5 2^23 rounds to an integer, ties to even, whose low bits are 0x4B400000 + code; field u = code - Q_N
+            constexpr uint32_t C = (1u << (BITS - 1)) - 0x4B400000u;
+            const float tf = cl + 12582912.f;
+            const uint32_t t = __float_as_uint(tf);
+            if (FORM == 2) off = fmaxf(off, fabsf(cl - (tf - 12582912.f)));
+            const int at = BITS * n, k = at / 32, sh = at % 32;
+            if (n == 0) {
+#pragma unroll
+              for (int q = 0; q <= BITS; ++q) words[q] = 0;
+            }
+            if (sh + BITS <= 32) words[k] += (t << sh) + (C << sh);  // (the constants of a word join at compile time)
+            else {
+              const uint32_t u = t + C;
+              words[k] += u << sh;
+              words[k + 1] += u >> (32 - sh);
+            }
+            continue;
+          }
+          const float code = rintf(cl);
+          if (CHECKED && FORM == 2) off = fmaxf(off, fabsf(cl - code));
+          if (MODE == 1 || MODE == 2) wq[e] = fmaf(code, s, b);
+          if (MODE == 4) {
+            if (FORM == 2) {  // (in units of s)
+              eq += fabsf(w - code);
+              ec += fabsf(w - cl);
+            } else {
+              eq += fabsf(wc - fmaf(code, s, b));
+              ec += fabsf(wc - fmaf(cl, s, b));
+            }
+          }
+          if (FACTOR) fg[e] = cl == w ? code - w : code;  // in range = the clamp changed nothing
+          if (MODE == 3) {
+            const uint32_t byte = (uint32_t)(uint8_t)(int8_t)(int)code, in = cl == w ? 1u : 0u;
+            if (n % 4 == 0) code8[n / 16][n / 4 % 4] = mask8[n / 16][n / 4 % 4] = 0;
+            code8[n / 16][n / 4 % 4] |= byte << (8 * (n % 4));
+            mask8[n / 16][n / 4 % 4] |= in << (8 * (n % 4));
+            wc4[n % 4] = __float_as_uint(wc);
+            if (n % 4 == 3 && out.wcomb)  // 16-byte piece q of row p of the binary32 tile: position q ^ (p % 16)
+              lds16(wave * ms_wave_lds<MODE>() + l32 * 256 + (((8 * h + n / 4) ^ (l32 & 15)) << 4)) = wc4;
+          }
+        }
+        // each piece goes back to LDS as it is finished (a lane's own row: nobody else reads or writes it), over the weights it
+        // was made from
+        if (FACTOR) {
+          typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+          typedef float f2 __attribute__((ext_vector_type(2)));
+          u32x4 v;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const f2 q = {fg[2 * e], fg[2 * e + 1]};
+            v[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(q, h2));
+          }
+          lds16((row_base ^ (16 * c)) + 4096) = v;
+        }
+        if (MODE == 1 || MODE == 2) {
+          u32x4 v;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            v[e] = pack_bf16x2(wq[2 * e], wq[2 * e + 1]);
+            if (MODE == 2) v[e] &= row_mask;
+          }
+          lds16(row_base ^ (16 * c)) = v;
+        }
+      }
+    };
+    // MODE 1: the elements of these lanes within reach of a tie, one after the other, by the stated arithmetic.  False (and
+    // nothing relied on) if they are many.
+    auto settle = [&](bool unsettled, float edge) {
+      uint32_t mine = 0;
+#pragma unroll
+      for (int n = 0; n < 32; ++n) {
+        const float wv = odd_even(w0[n / 8][n % 8 / 2], n);
+        const float wc = ACH == 0 ? wv + 0.f : fmaf(d.gamma, near[n / 16][n % 16], wv);
+        const float cl = __builtin_amdgcn_fmed3f(fmaf(wc, rc, nbr), d.qn, d.qp);
+        mine |= !(fabsf(cl - rintf(cl)) < edge) ? 1u << n : 0u;
+      }
+      if (!unsettled) mine = 0;
+      u32x4 bq[ACH > 0 ? ACH : 1];
+#pragma unroll
+      for (int c = 0; c < ACH; ++c) bq[c] = load_b(p, row_ok, 16 * c);
+      auto lane_of = [](uint32_t v, int l) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); };
+      for (int count = 0;; ++count) {
+        const uint64_t todo = __builtin_amdgcn_ballot_w64(mine != 0);
+        if (todo == 0) return true;
+        if (count == 8) return false;
+        const int at = __builtin_ctzll(todo), n = __builtin_ctz(lane_of(mine, at));  // (uniform from here on)
+        const int am = 8 * (n % 16 / 4) + 4 * (at >> 5) + n % 4;  // the M index of its column, in column block n / 16
+        float acc = 0.f;
+#pragma unroll
+        for (int c = 0; c < ACH; ++c)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) {
+            const int q = e % 8 / 2, side = e / 8 * 32;
+            const uint32_t av = n < 16 ? apk[8 * c + q] : apk[8 * c + 4 + q];
+            acc = fmaf(odd_even(lane_of(bq[c][q], (at & 31) + side), e), odd_even(lane_of(av, am + side), e), acc);
+          }
+        uint32_t wpair = w0[0][0];
+#pragma unroll
+        for (int q = 1; q < 16; ++q) wpair = n / 2 == q ? w0[q / 4][q % 4] : wpair;
+        wpair = lane_of(wpair, at);
+        const float wv = n & 1 ? odd_even(wpair, 1) : odd_even(wpair, 0);
+        const float sv = __uint_as_float(lane_of(__float_as_uint(s), at)), bv = __uint_as_float(lane_of(__float_as_uint(b), at));
+        const float wc = ACH == 0 ? wv + 0.f : wv + d.gamma * acc;
+        const float code = rintf(__builtin_amdgcn_fmed3f(__fdiv_rn(wc - bv, sv), d.qn, d.qp));
+        if (lane == at) {
+          *reinterpret_cast<bf16_t*>(lds_all + ((row_base ^ (16 * (n / 8))) + 2 * (n % 8))) = f32_to_bf16(fmaf(code, sv, bv));
+          mine &= mine - 1;
+        }
+      }
+    };
+    if constexpr (FILTER) {
+      bool exact = slow;
+      if (!exact) stream_columns(std::integral_constant<int, 2>{});
+      if constexpr (MODE == 4) {
+        eq *= s;
+        ec *= s;
+      }
+      if constexpr (CHECKED) {
+        // within tol of a tie the near quotient does not settle the code (see the top of the file)
+        bsum = ACH > 0 ? half_sum(bsum) : 0.f;
+        const float tol = fmaf(rc, fmaf(sum_tol, bsum, 0x1p-22f * fabsf(b)), 0x1p-21f * (1.f - d.qn));
+        const float edge = 0.5f - tol;
+        const bool unsettled = row_ok & col_ok & !(off < edge);
+        if (!exact && __builtin_amdgcn_ballot_w64(unsettled) != 0) {
+          if constexpr (MODE == 1) exact = r > 16 * ACH || !settle(unsettled, edge);  // (r > 16 ACH: A is not in registers)
+          else exact = true;
+        }
+      }
+      if (exact) {
+        if constexpr (ACH > 0) {
+#pragma unroll
+          for (int e = 0; e < 32; ++e) sum[e] = 0.f;
+          chain_rest(sum, p, row_ok, 0);
+        }
+        eq = ec = 0.f;
+        stream_columns(std::integral_constant<int, 0>{});
+      }
+    } else {
+      if (!slow) stream_columns(std::integral_constant<int, 1>{});
+      else stream_columns(std::integral_constant<int, 0>{});
+    }
+
+    if constexpr (MODE == 1) {
+      // ---- Wq in blocks of 32 columns, [j / 32][p][j % 32]: a half-wave's tile is 2 KiB of consecutive addresses; through
+      //      LDS, so that a store instruction covers 1 KiB (64 bytes per lane straight from the registers: 16-byte pieces
+      //      of lines, which took a bare copy from 29 to 35 us)
+      lds_order();
+      const __amdgpu_buffer_rsrc_t rsOut = __builtin_amdgcn_make_buffer_rsrc(out.wq, 0, o * i * 2, 0x00020000);
+      const int sr = lane >> 2, sc = lane & 3;  // instruction t: rows 16 (t % 2) + sr of column block t / 2
+      const uint32_t out_base = (uint32_t)(wave * ms_wave_lds<MODE>() + sr * 128 + ((sc ^ (sr & 7)) << 4));
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int row = 16 * (t & 1) + sr;
+        const u32x4 v = lds16((out_base ^ (64 * (t >> 1))) + 2048 * (t & 1));
+        const bool ok = p0 + row < o && jw + 32 * (t >> 1) < i;
+        const unsigned vo = ok ? (unsigned)((((jw >> 5) + (t >> 1)) * o + p0 + row) * 64 + sc * 16) : OOB;
+        __builtin_amdgcn_raw_buffer_store_b128(v, rsOut, (int)vo, 0, 0);
+      }
+      lds_order();
+    }
+    if constexpr (MODE == 2) {
+      // ---- the factor as it came, Wq^T in blocks of 32 rows, [p / 32][j][p % 32]: 64 columns are 4 KiB of consecutive
+      //      addresses.  The transposing read gives 16 lanes a column each of 4 rows (see l4q_gemm_core.h).
+      lds_order();
+      if (FACTOR && out.fgrad) {
+        const __amdgpu_buffer_rsrc_t rsF = __builtin_amdgcn_make_buffer_rsrc(out.fgrad, 0, o * i * 2, 0x00020000);
+        const unsigned vf = mcol_ok ? (unsigned)(((p0 + mr) * i + jw + 8 * mc) * 2) : OOB;
+#pragma unroll
+        for (int t = 0; t < 4; ++t)  // (rows from o on: past the end of the buffer)
+          __builtin_amdgcn_raw_buffer_store_b128(lds16(mem_base + 4096 + 1024 * t), rsF,
+                                                 (int)(vf + (unsigned)(t * 16 * i)), 0, 0);
+      }
+      typedef short s16x4_t __attribute__((ext_vector_type(4)));
+      typedef __attribute__((address_space(3))) s16x4_t* lds_s16x4_ptr_t;
+      const int ld = (int)out.ld_wqT;
+      const __amdgpu_buffer_rsrc_t rsT = __builtin_amdgcn_make_buffer_rsrc(out.wqT, 0, i * ld * 2, 0x00020000);
+      const int tg = lane >> 4, tj = lane & 15;  // rows 8 tg .. 8 tg + 7, column 16 t + tj
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        u32x2 v[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const int rowm = 4 * u + (tj >> 2);  // row % 8
+          unsigned char* q = tile + (8 * tg + rowm) * 128 + (((2 * t + ((tj >> 1) & 1)) ^ rowm) << 4) + (tj & 1) * 8;
+          v[u] = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr_t)q));
+        }
+        const bool ok = jw + 16 * t < i;  // (uniform)
+        const unsigned vo = ok ? (unsigned)(((rb * i + jw + 16 * t + tj) * 32 + 8 * tg) * 2) : OOB;
+        __builtin_amdgcn_raw_buffer_store_b128(u32x4{v[0][0], v[0][1], v[1][0], v[1][1]}, rsT, (int)vo, 0, 0);
+      }
+      lds_order();
+    }
+    if constexpr (MODE == 3) {
+      const unsigned at = row_ok && col_ok ? (unsigned)(p * i + jl) : OOB;
+      const __amdgpu_buffer_rsrc_t rsC = __builtin_amdgcn_make_buffer_rsrc(out.codes, 0, o * i, 0x00020000);
+      const __amdgpu_buffer_rsrc_t rsMask = __builtin_amdgcn_make_buffer_rsrc(out.mask, 0, o * i, 0x00020000);
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        if (out.codes) __builtin_amdgcn_raw_buffer_store_b128(code8[q], rsC, (int)(at + 16u * q), 0, 0);
+        if (out.mask) __builtin_amdgcn_raw_buffer_store_b128(mask8[q], rsMask, (int)(at + 16u * q), 0, 0);
+      }
+      if (out.wcomb) {
+        const __amdgpu_buffer_rsrc_t rsWc = __builtin_amdgcn_make_buffer_rsrc(out.wcomb, 0, o * i * 4, 0x00020000);
+        lds_order();
+        const int sr = lane >> 4, sc = lane & 15;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+          const int row = 4 * t + sr;
+          const u32x4 v = *reinterpret_cast<const u32x4*>(tile + row * 256 + ((sc ^ (row & 15)) << 4));
+          const unsigned vo = p0 + row < o && jw + 4 * sc < i ? (unsigned)(((p0 + row) * i + jw + 4 * sc) * 4) : OOB;
+          __builtin_amdgcn_raw_buffer_store_b128(v, rsWc, (int)vo, 0, 0);
+        }
+      }
+      lds_order();
+    }
+    if constexpr (MODE == 4) {
+      err_q += row_ok && col_ok ? (double)eq : 0.0;
+      err_c += row_ok && col_ok ? (double)ec : 0.0;
+    }
+    if constexpr (MODE == 5) {
+      // ---- extremes over the half-waves (groups above 32), then over the wavefronts that share a group: through LDS, two
+      //      sets in turn, so that one barrier per row block is enough
+      if (g > 32) {
+        const float2 l = both_halves(lo), t = both_halves(top);
+        lo = fminf(l.x, l.y);
+        top = fmaxf(t.x, t.y);
+      }
+      const int span = g > 64 ? g / 64 : 1;  // wavefronts of a group; its first one finishes it
+      if (g > 64) {
+        const int set = 4096 + 256 * ((rb - rb_begin) & 1);
+        if (h == 0) *reinterpret_cast<float2*>(tile + set + 8 * l32) = make_float2(lo, top);
+        __syncthreads();
+        if (wave % span == 0) {
+          for (int q = 1; q < span; ++q) {
+            const float2 t = *reinterpret_cast<const float2*>(tile + q * ms_wave_lds<MODE>() + set + 8 * l32);
+            lo = fminf(lo, t.x);
+            top = fmaxf(top, t.y);
+          }
+        }
+      }
+      if (wave % span == 0 && row_ok && col_ok && (g == 32 || h == 0)) {
+        // (a group of nothing but NaN has the extremes of an empty one, as in the general pass)
+        float s0, b0 = 0.f;
+        if (out.init_method == 0) {         // asymmetric min / max
+          s0 = __fdiv_rn(top - lo, d.qp - d.qn);
+          b0 = lo - s0 * d.qn;
+        } else if (out.init_method == 1) {  // symmetric
+          s0 = __fdiv_rn(fmaxf(fabsf(lo), fabsf(top)), -d.qn);
+        } else {                            // L4Q_init (Eq. l4q_quant_init)
+          s0 = fmaxf(fabsf(__fdiv_rn(lo, d.qn)), fabsf(__fdiv_rn(top, d.qp)));
+        }
+        out.init_scale[(int64_t)p * G + qtab] = s0;
+        out.init_zero[(int64_t)p * G + qtab] = b0;
+      }
+      lds_order();
+    }
+    if constexpr (MODE == 6) {
+      const int pack_row = BITS * (i / 32) * 4;  // bytes of a packed row
+      const __amdgpu_buffer_rsrc_t rsPack = __builtin_amdgcn_make_buffer_rsrc(out.packed, 0, o * pack_row, 0x00020000);
+      const unsigned vo = row_ok && col_ok ? (unsigned)(p * pack_row + (jl >> 5) * (4 * BITS)) : OOB;
+      constexpr int QUADS = BITS / 4;
+#pragma unroll
+      for (int q = 0; q < QUADS; ++q)
+        __builtin_amdgcn_raw_buffer_store_b128(u32x4{words[4 * q], words[4 * q + 1], words[4 * q + 2], words[4 * q + 3]}, rsPack,
+                                               (int)(vo + 16u * q), 0, 0);
+      if constexpr (BITS % 4 == 1)
+        __builtin_amdgcn_raw_buffer_store_b32(words[4 * QUADS], rsPack, (int)(vo + 16u * QUADS), 0, 0);
+      if constexpr (BITS % 4 == 2)
+        __builtin_amdgcn_raw_buffer_store_b64(u32x2{words[4 * QUADS], words[4 * QUADS + 1]}, rsPack, (int)(vo + 16u * QUADS), 0, 0);
+      if constexpr (BITS % 4 == 3)
+        __builtin_amdgcn_raw_buffer_store_b96(u32x3{words[4 * QUADS], words[4 * QUADS + 1], words[4 * QUADS + 2]}, rsPack,
+                                              (int)(vo + 16u * QUADS), 0, 0);
+      lds_order();
+    }
+    if constexpr (MODE == 4) lds_order();
+  } while (++rb < rb_end);
   if constexpr (MODE == 4) {
     for (int off = 32; off > 0; off >>= 1) {
       err_q += __shfl_xor(err_q, off, 64);
@@ -525,32 +730,32 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
 #endif
 }
 
-// Forward and export: 4 workgroups (16 wavefronts, 144 KiB of LDS) per compute unit.  Backward: MS_BWD_WAVES (the
-// dequantized weights of a row block wait in registers for the transposition: 152 registers per lane).
-template <bool GAMMA_POW2, int ACH = 1>
+// Forward and export: 4 workgroups (16 wavefronts) per compute unit, 3 with A of ranks above 16 in registers.  Backward:
+// MS_BWD_WAVES.
+template <int ACH>
 __global__ __launch_bounds__(MS_THREADS) __attribute__((amdgpu_waves_per_eu(ACH <= 1 ? 4 : 3, ACH <= 1 ? 4 : 3)))
 void merge_quant_stream_fwd_kernel(LayerDims d, const bf16_t* __restrict__ W0, const bf16_t* __restrict__ A,
                                    const bf16_t* __restrict__ B, const float* __restrict__ scale,
                                    const float* __restrict__ zero, MergeQuantOut<bf16_t> out, int nrb) {
-  __shared__ __attribute__((aligned(16))) unsigned char lds_all[4 * ms_wave_lds<1>()];
-  merge_quant_stream_body<1, GAMMA_POW2, ACH>(d, W0, A, B, scale, zero, out, nrb, lds_all);
+  __shared__ __attribute__((aligned(16))) unsigned char lds_all[ms_lds<1>()];
+  merge_quant_stream_body<1, false, ACH>(d, W0, A, B, scale, zero, out, nrb, lds_all);
 }
-template <bool GAMMA_POW2, int ACH = 1>
+template <bool GAMMA_POW2, int ACH>
 __global__ __launch_bounds__(MS_THREADS) __attribute__((amdgpu_waves_per_eu(MS_BWD_WAVES, MS_BWD_WAVES)))
 void merge_quant_stream_bwd_kernel(LayerDims d, const bf16_t* __restrict__ W0, const bf16_t* __restrict__ A,
                                    const bf16_t* __restrict__ B, const float* __restrict__ scale,
                                    const float* __restrict__ zero, MergeQuantOut<bf16_t> out, int nrb) {
-  __shared__ __attribute__((aligned(16))) unsigned char lds_all[4 * ms_wave_lds<2>()];
+  __shared__ __attribute__((aligned(16))) unsigned char lds_all[ms_lds<2>()];
   merge_quant_stream_body<2, GAMMA_POW2, ACH>(d, W0, A, B, scale, zero, out, nrb, lds_all);
 }
 // MODE 3 .. 6: the export, statistics and packing forms, as the forward form 4 workgroups per compute unit
-template <bool GAMMA_POW2, int MODE>
+template <bool GAMMA_POW2, int MODE, int BITS = 0>
 __global__ __launch_bounds__(MS_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void merge_quant_stream_export_kernel(LayerDims d, const bf16_t* __restrict__ W0, const bf16_t* __restrict__ A,
                                       const bf16_t* __restrict__ B, const float* __restrict__ scale,
                                       const float* __restrict__ zero, MergeQuantOut<bf16_t> out, int nrb) {
-  __shared__ __attribute__((aligned(16))) unsigned char lds_all[4 * ms_wave_lds<MODE>()];
-  merge_quant_stream_body<MODE, GAMMA_POW2, 1>(d, W0, A, B, scale, zero, out, nrb, lds_all);
+  __shared__ __attribute__((aligned(16))) unsigned char lds_all[ms_lds<MODE>()];
+  merge_quant_stream_body<MODE, GAMMA_POW2, 1, BITS>(d, W0, A, B, scale, zero, out, nrb, lds_all);
 }
 
 // ------------------------------------------------------------------ check of the reciprocal-based quotient
@@ -614,6 +819,7 @@ bool merge_quant_stream_supported(const LayerDims& d, const MergeQuantOut<bf16_t
   if ((d.i > d.o ? d.i : d.o) * d.r * 2 >= (1ll << 31)) return false;
   if (out.packed || out.errors || out.init_scale)  // each of them alone
     return d.r % 8 == 0 && d.g >= 32 && (!out.packed || d.i % 32 == 0) && (!out.init_scale || d.g <= 256);
+  if (d.r == 0 && out.fgrad) return false;  // (the instance without a rank term takes no factor)
   const bool blocks = (!out.wq || out.ld_wq % 32 == 0) && (!out.wqT || out.ld_wqT % 32 == 0);
   return (fwd || bwd || exp) && blocks && d.r % 8 == 0 && d.g >= 32;
 }
@@ -626,33 +832,39 @@ int64_t launch_merge_quant_stream(const LayerDims& d, const bf16_t* W0, const bf
   const int nrb = (int)((rows + 31) / 32);
   // one resident round: 4 (backward: 3) workgroups per compute unit, each wavefront walking a run of row blocks
   const int strips = (int)((d.i + MS_COLS - 1) / MS_COLS);
-  // Forward form at ranks above 16: A for four chunks in registers, 3 wavefronts per SIMD (rank 64: 111 against 134 us;
-  // the backward form, which would be down to 2 wavefronts per SIMD, does not gain: 124 against 120 us)
-  const bool wide = d.r > 16 && mode == 1;
+  const bool wide = d.r > 16 && (mode == 1 || mode == 2);
   int parts = (mode == 2 ? MS_BWD_WAVES : wide ? 3 : 4) * device_compute_units() / strips;
-  // backward: four times as many, shorter runs (about two row blocks each), handed out as workgroups finish: its
-  // wavefronts are fewer and their phases longer, and one round of 5-or-6-block runs ends ragged (stand-alone 62-65
-  // against 68-75 us; inside a training step 65 against 66)
-  if (mode == 2) parts *= 4;
+  // (two or four times as many, shorter runs, each with its own fetch of A: forward and packing 2 .. 17 % slower, backward the
+  // same at 11008 x 4096, 22 -> 25 us at 4096 x 4096; forward above rank 16, 3 workgroups per unit: 65 -> 60 with two, 63 with four)
+  if (wide && mode == 1) parts *= 2;
   if (parts < 1) parts = 1;
   if (parts > nrb) parts = nrb;
-  dim3 grid((unsigned)strips, (unsigned)parts);
+  dim3 grid((unsigned)(strips * parts));
   // gamma acc is exact when gamma is a power of two >= 1 (no underflow of the product)
   const uint32_t gb = __builtin_bit_cast(uint32_t, d.gamma);
   const bool pow2 = (gb & 0x807FFFFFu) == 0 && d.gamma >= 1.f && d.gamma <= 1048576.f;
 #define L4Q_MS_LAUNCH(K, ...) \
   hipLaunchKernelGGL((K<__VA_ARGS__>), grid, dim3(MS_THREADS), 0, stream, d, W0, A, B, scale, zero, out, nrb)
-  if (d.r == 0) {  // (the QAT-LoRA layer's forward and backward)
-    if (mode == 1) L4Q_MS_LAUNCH(merge_quant_stream_fwd_kernel, false, 0);
-    else L4Q_MS_LAUNCH(merge_quant_stream_bwd_kernel, false, 0);
-  }
-  else if (mode == 1 && wide) { if (pow2) L4Q_MS_LAUNCH(merge_quant_stream_fwd_kernel, true, 4); else L4Q_MS_LAUNCH(merge_quant_stream_fwd_kernel, false, 4); }
-  else if (mode == 1) { if (pow2) L4Q_MS_LAUNCH(merge_quant_stream_fwd_kernel, true); else L4Q_MS_LAUNCH(merge_quant_stream_fwd_kernel, false); }
-  else if (mode == 2) { if (pow2) L4Q_MS_LAUNCH(merge_quant_stream_bwd_kernel, true); else L4Q_MS_LAUNCH(merge_quant_stream_bwd_kernel, false); }
-  else if (mode == 3) { if (pow2) L4Q_MS_LAUNCH(merge_quant_stream_export_kernel, true, 3); else L4Q_MS_LAUNCH(merge_quant_stream_export_kernel, false, 3); }
-  else if (mode == 4) { if (pow2) L4Q_MS_LAUNCH(merge_quant_stream_export_kernel, true, 4); else L4Q_MS_LAUNCH(merge_quant_stream_export_kernel, false, 4); }
-  else if (mode == 5) { if (pow2) L4Q_MS_LAUNCH(merge_quant_stream_export_kernel, true, 5); else L4Q_MS_LAUNCH(merge_quant_stream_export_kernel, false, 5); }
-  else { if (pow2) L4Q_MS_LAUNCH(merge_quant_stream_export_kernel, true, 6); else L4Q_MS_LAUNCH(merge_quant_stream_export_kernel, false, 6); }
+#define L4Q_MS_POW2(K, ...) do { if (pow2) L4Q_MS_LAUNCH(K, true, __VA_ARGS__); else L4Q_MS_LAUNCH(K, false, __VA_ARGS__); } while (0)
+#define L4Q_MS_PACK(BITS) L4Q_MS_LAUNCH(merge_quant_stream_export_kernel, false, 6, BITS)
+  if (mode == 1 && d.r == 0) L4Q_MS_LAUNCH(merge_quant_stream_fwd_kernel, 0);  // (r = 0: the QAT-LoRA layer's passes)
+  else if (mode == 1 && wide) L4Q_MS_LAUNCH(merge_quant_stream_fwd_kernel, 4);
+  else if (mode == 1) L4Q_MS_LAUNCH(merge_quant_stream_fwd_kernel, 1);
+  else if (mode == 2 && d.r == 0) L4Q_MS_LAUNCH(merge_quant_stream_bwd_kernel, false, 0);
+  else if (mode == 2 && wide) L4Q_MS_POW2(merge_quant_stream_bwd_kernel, 4);
+  else if (mode == 2) L4Q_MS_POW2(merge_quant_stream_bwd_kernel, 1);
+  else if (mode == 3) L4Q_MS_POW2(merge_quant_stream_export_kernel, 3);
+  else if (mode == 4) L4Q_MS_LAUNCH(merge_quant_stream_export_kernel, false, 4);
+  else if (mode == 5) L4Q_MS_POW2(merge_quant_stream_export_kernel, 5);
+  else if (d.bits == 2) L4Q_MS_PACK(2);
+  else if (d.bits == 3) L4Q_MS_PACK(3);
+  else if (d.bits == 4) L4Q_MS_PACK(4);
+  else if (d.bits == 5) L4Q_MS_PACK(5);
+  else if (d.bits == 6) L4Q_MS_PACK(6);
+  else if (d.bits == 7) L4Q_MS_PACK(7);
+  else L4Q_MS_PACK(8);
+#undef L4Q_MS_PACK
+#undef L4Q_MS_POW2
 #undef L4Q_MS_LAUNCH
   return (int64_t)strips * parts * 4;
 }
