@@ -41,7 +41,8 @@ __device__ __forceinline__ void store_out(const SgemmArgs& a, int64_t m, int64_t
 // ------------------------------------------------------------------ tiled form
 // KG groups of 4 waves (2 x 2) on the same tile, group q taking the k-steps q, q + KG, ..., their sums added at the end; k in
 // steps of 32, the next two steps' operands travelling to registers while the current one is
-// multiplied out of LDS; two LDS buffers, one barrier per step.  K-contiguous operands lie in LDS as rows
+// multiplied out of LDS; two LDS buffers, one barrier per step.  For operands that are not whole 16-byte pieces, and for
+// products of few steps.  K-contiguous operands lie in LDS as rows
 // of 32 k + 4 floats of padding (16-byte reads of 16 consecutive rows meet all banks once), K-major ones as they come.
 constexpr int SG_BK = 32;
 constexpr int SG_KPITCH = SG_BK + 4;
@@ -101,6 +102,37 @@ struct SgemmOperand {
     }
   }
 };
+
+// The waves' accumulators to C: with two groups, group 1's sums through LDS to group 0 first.
+template <int TM, int TN, int KG>
+__device__ __forceinline__ void store_tile(const SgemmArgs& a, f32x16_t (&acc)[TM][TN], float* lds, int64_t mw, int64_t nw, int group,
+                                           int tid, int l32, int half) {
+  if constexpr (KG == 2) {
+    __syncthreads();
+    float* sums = lds + tid * 17;  // (odd pitch: no bank conflicts)
+    if (group == 1) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) sums[e] = acc[0][0][e];
+    }
+    __syncthreads();
+    if (group == 1) return;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[0][0][e] += sums[e];
+  }
+  // accumulator: lane = column n, register e = row 8 (e / 4) + 4 half + e % 4
+#pragma unroll
+  for (int x = 0; x < TM; ++x)
+#pragma unroll
+    for (int y = 0; y < TN; ++y) {
+      const int64_t n = nw + y * 32 + l32;
+      if (n >= a.N) continue;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int64_t m = mw + x * 32 + 8 * (e / 4) + 4 * half + (e % 4);
+        if (m < a.M) store_out(a, m, n, acc[x][y][e]);
+      }
+    }
+}
 
 template <int BM, int BN, int KG, bool A_KM, bool B_KM>
 __global__ __launch_bounds__(256 * KG, KG == 2 ? 4 : 1) void sgemm_tile_kernel(SgemmArgs a) {
@@ -166,31 +198,138 @@ __global__ __launch_bounds__(256 * KG, KG == 2 ? 4 : 1) void sgemm_tile_kernel(S
       }
     }
   }
-  if constexpr (KG == 2) {  // group 1's sums through LDS to group 0
-    __syncthreads();
-    float* sums = lds + tid * 17;  // (odd pitch: no bank conflicts)
-    if (group == 1) {
+  store_tile<TM, TN, KG>(a, acc, lds, m0 + wm, n0 + wn, group, tid, l32, half);
+#endif
+}
+
+// ------------------------------------------------------------------ tiled form, operands straight to LDS
+// The tiled form for operands of whole 16-byte pieces.  Binary32 matrix ops take the vector unit's time (a loop of each runs
+// in the sum of their times), so what the form above spends on bounds, addresses and copies through registers, about 50
+// vector ops and 8 branches per step beside 16 matrix ops, comes off its rate.  Here a step's operands travel memory -> LDS
+// (buffer_load ... lds) at offsets that a lane computes once, into the buffer that the previous step has left, one barrier
+// per step; the loop has no vector ops but the matrix ops.  1000 x 2048 x 2048 inside a training step, the three
+// orientations: 103 / 102 / 102 us -> 85 / 81 / 89; 512 x 2048 x 1024 28.4 -> 24.4; 2048 x 4096 x 2048 in 128-wide tiles 307 -> 288,
+// 4096 x 2048 x 2048 with both K-major 322 -> 277, 2048 x 2048 x 4096 in 64-wide ones 348 -> 287.  The sums and their order are the
+// same.  (The line to the sliced form stays where it is: 96 tiles, K = 1024 23.0 / 22.1 here / sliced, 128 tiles, K = 2048 41.8 / 41.6,
+// 64 tiles, K = 1024 22.4 / 13.9.)  K-contiguous rows: 8 pieces, piece p of row m at
+// position p ^ (m % 8) (8 consecutive lanes meet all banks); K-major rows: pieces of rows with bit 2 of k set are moved by 32
+// columns, so that the two half-waves of a read, 4 rows apart, meet different banks.
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+template <int ROWS, bool KMAJOR>
+struct SgemmPieces {
+  static constexpr int NV = ROWS / 32;           // loads per wave and step: 1 KiB each
+  static constexpr int BYTES = ROWS * SG_BK * 4;
+  __amdgpu_buffer_rsrc_t rs;
+  unsigned voff[NV];
+  int kpos[NV];      // this lane's k within the step
+  unsigned step_bytes;
+
+  __device__ void init(const float* P, int64_t ld, int64_t r0, int64_t extent, int wave, int lane) {
+    rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(P + (KMAJOR ? r0 : r0 * ld)), 0, 0x7FFFFFFF, 0x00020000);
+    step_bytes = (unsigned)(KMAJOR ? SG_BK * ld * 4 : SG_BK * 4);
 #pragma unroll
-      for (int e = 0; e < 16; ++e) sums[e] = acc[0][0][e];
+    for (int e = 0; e < NV; ++e) {
+      const int idx = (wave * NV + e) * 64 + lane;
+      constexpr int PER = KMAJOR ? ROWS / 4 : SG_BK / 4;
+      const int outer = idx / PER;
+      const int piece = (idx % PER) ^ (KMAJOR ? 8 * ((outer >> 2) & 1) : outer & 7);
+      const int64_t row = r0 + (KMAJOR ? 4 * piece : outer);  // (K-major: extents are whole pieces)
+      kpos[e] = KMAJOR ? outer : 4 * piece;
+      voff[e] = row < extent ? (unsigned)(((int64_t)outer * ld + 4 * piece) * 4) : gemm::OOB_OFFSET;
     }
-    __syncthreads();
-    if (group == 1) return;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) acc[0][0][e] += sums[e];
   }
-  // accumulator: lane = column n, register e = row 8 (e / 4) + 4 half + e % 4
+  // step `step` of the operand's K values into lds; what lies from K on comes as zeros
+  __device__ __forceinline__ void load(unsigned char* lds, int step, int64_t K, int wave) const {
+    const int left = (int)(K - (int64_t)step * SG_BK);
+    if (left >= SG_BK) {
+#pragma unroll
+      for (int e = 0; e < NV; ++e)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (gemm::lds_ptr_t)(lds + (wave * NV + e) * 1024), 16, voff[e],
+                                                 (int)(step * step_bytes), 0, 0);
+    } else {
+#pragma unroll
+      for (int e = 0; e < NV; ++e)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (gemm::lds_ptr_t)(lds + (wave * NV + e) * 1024), 16,
+                                                 kpos[e] < left ? voff[e] + step * step_bytes : gemm::OOB_OFFSET, 0, 0, 0);
+    }
+  }
+  // the 4 k-values of run kk (8 k-values) this lane feeds to the 4 matrix ops, for row `row` of the tile
+  __device__ static __forceinline__ f32x4_t fragment(const unsigned char* lds, int row, int kk, int half) {
+    f32x4_t f;
+    if constexpr (KMAJOR) {
+      const float* p = reinterpret_cast<const float*>(lds) + (kk * 8 + half * 4) * ROWS + (row ^ (32 * half));
+#pragma unroll
+      for (int j = 0; j < 4; ++j) f[j] = p[j * ROWS];
+    } else {
+      f = *reinterpret_cast<const f32x4_t*>(lds + row * 128 + (((2 * kk + half) ^ (row & 7)) << 4));
+    }
+    return f;
+  }
+};
+
+template <int BM, int BN, int KG, bool A_KM, bool B_KM>
+__global__ __launch_bounds__(256 * KG, KG == 2 ? 4 : 2) void sgemm_dma_kernel(SgemmArgs a) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  typedef SgemmPieces<BM, A_KM> OpA;
+  typedef SgemmPieces<BN, B_KM> OpB;
+  constexpr int STAGE = OpA::BYTES + OpB::BYTES;
+  constexpr int TM = BM / 64, TN = BN / 64;  // 32 x 32 accumulator tiles per wave
+  static_assert(KG == 1 || (KG == 2 && BM == 64 && BN == 64), "the second group's sums fit its buffers");
+  __shared__ __align__(1024) unsigned char lds[2 * KG * STAGE];
+  const int group = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+  const int tid = threadIdx.x & 255, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, half = lane >> 5;
+  const int tiles_m = (int)((a.M + BM - 1) / BM), tiles_n = (int)((a.N + BN - 1) / BN);
+  int tm, tn;
+  gemm::tile_of_block((int)blockIdx.x, tiles_m, tiles_n, tm, tn);
+  const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
+  const int wm = (wave >> 1) * (BM / 2), wn = (wave & 1) * (BN / 2);
+
+  f32x16_t acc[TM][TN];
 #pragma unroll
   for (int x = 0; x < TM; ++x)
 #pragma unroll
-    for (int y = 0; y < TN; ++y) {
-      const int64_t n = n0 + wn + y * 32 + l32;
-      if (n >= a.N) continue;
+    for (int y = 0; y < TN; ++y)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int64_t m = m0 + wm + x * 32 + 8 * (e / 4) + 4 * half + (e % 4);
-        if (m < a.M) store_out(a, m, n, acc[x][y][e]);
-      }
+      for (int e = 0; e < 16; ++e) acc[x][y][e] = 0.f;
+
+  OpA oa;
+  OpB ob;
+  oa.init(a.A, a.lda, m0, a.M, wave, lane);
+  ob.init(a.B, a.ldb, n0, a.N, wave, lane);
+  const int steps = (int)((a.K + SG_BK - 1) / SG_BK), turns = (steps + KG - 1) / KG;
+  auto buffer = [&](int t) { return lds + (group * 2 + (t & 1)) * STAGE; };
+  oa.load(buffer(0), group, a.K, wave);
+  ob.load(buffer(0) + OpA::BYTES, group, a.K, wave);
+  for (int t = 0; t < turns; ++t) {
+    __builtin_amdgcn_s_waitcnt(gemm::waitcnt_vm(0));  // this wave's share of the step has landed
+    __builtin_amdgcn_s_waitcnt(gemm::waitcnt_lgkm0());
+    __builtin_amdgcn_s_barrier();                     // everyone's has, and everyone has read the other buffer
+    __builtin_amdgcn_sched_barrier(0);
+    if (t + 1 < turns) {
+      oa.load(buffer(t + 1), (t + 1) * KG + group, a.K, wave);
+      ob.load(buffer(t + 1) + OpA::BYTES, (t + 1) * KG + group, a.K, wave);
     }
+    const unsigned char* la = buffer(t);
+    const unsigned char* lb = la + OpA::BYTES;
+#pragma unroll
+    for (int kk = 0; kk < SG_BK / 8; ++kk) {
+      f32x4_t fa[TM], fb[TN];
+#pragma unroll
+      for (int x = 0; x < TM; ++x) fa[x] = OpA::fragment(la, wm + x * 32 + l32, kk, half);
+#pragma unroll
+      for (int y = 0; y < TN; ++y) fb[y] = OpB::fragment(lb, wn + y * 32 + l32, kk, half);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int x = 0; x < TM; ++x)
+#pragma unroll
+          for (int y = 0; y < TN; ++y)
+            acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[x][j], fb[y][j], acc[x][y], 0, 0, 0);
+    }
+  }
+  store_tile<TM, TN, KG>(a, acc, reinterpret_cast<float*>(lds), m0 + wm, n0 + wn, group, tid, l32, half);
 #endif
 }
 
@@ -277,16 +416,29 @@ __global__ __launch_bounds__(64 * SL_WAVES) void sgemm_sliced_kernel(SgemmArgs a
 // waves on a quarter of the tile, is ahead.  128-wide tiles halve the operand traffic; the line at two of them per compute
 // unit leaves them out at one per unit, where they are 5 % ahead at K = 1000 (92 / 87) but add up k in one chain instead of
 // two of half the length (a layer of 1000 x 2048 x 2048 is 5.8e-7 off its value in 64 bits with two groups, 8.1e-7 with one).
+// operand of whole 16-byte pieces, every offset from a tile's first row within 31 bits
+template <bool KMAJOR>
+bool whole_pieces(const float* P, int64_t ld, int64_t extent, int64_t K) {
+  if ((reinterpret_cast<uintptr_t>(P) & 15) != 0 || ld % 4 != 0) return false;
+  if (KMAJOR) return extent % 4 == 0 && (K + SG_BK) * ld < (1ll << 29);
+  return K % 4 == 0 && 128 * ld + K + SG_BK < (1ll << 29);
+}
+
 template <bool A_KM, bool B_KM>
 void launch_sgemm_form(const SgemmArgs& a, hipStream_t stream) {
   auto tiles = [&](int64_t bm, int64_t bn) { return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
   const int64_t cus = device_compute_units();
+  const bool whole = whole_pieces<A_KM>(a.A, a.lda, a.M, a.K) && whole_pieces<B_KM>(a.B, a.ldb, a.N, a.K);
   if (tiles(64, 64) * 8 < cus * 5)
     hipLaunchKernelGGL((sgemm_sliced_kernel<A_KM, B_KM>), dim3((unsigned)tiles(32, 32)), dim3(64 * SL_WAVES), 0, stream, a);
   else if (tiles(128, 128) < 2 * cus && a.K <= 4 * SG_BK)  // (fewer than two steps for each group)
     hipLaunchKernelGGL((sgemm_tile_kernel<64, 64, 1, A_KM, B_KM>), dim3((unsigned)tiles(64, 64)), dim3(256), 0, stream, a);
+  else if (tiles(128, 128) < 2 * cus && whole)
+    hipLaunchKernelGGL((sgemm_dma_kernel<64, 64, 2, A_KM, B_KM>), dim3((unsigned)tiles(64, 64)), dim3(512), 0, stream, a);
   else if (tiles(128, 128) < 2 * cus)
     hipLaunchKernelGGL((sgemm_tile_kernel<64, 64, 2, A_KM, B_KM>), dim3((unsigned)tiles(64, 64)), dim3(512), 0, stream, a);
+  else if (whole)
+    hipLaunchKernelGGL((sgemm_dma_kernel<128, 128, 1, A_KM, B_KM>), dim3((unsigned)tiles(128, 128)), dim3(256), 0, stream, a);
   else
     hipLaunchKernelGGL((sgemm_tile_kernel<128, 128, 1, A_KM, B_KM>), dim3((unsigned)tiles(128, 128)), dim3(256), 0, stream, a);
 }

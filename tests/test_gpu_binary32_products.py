@@ -21,6 +21,12 @@ pytestmark = pytest.mark.gpu
     (35, 2948, 2949, 2, 4),     # 128-wide tiles (dWq: 24 x 24, both operands K-major), K = 35
     (2945, 36, 2945, 2, 4),     # ... in the forward product (24 x 24, both K-contiguous), K = 36
     (2945, 2948, 35, 2, 4),     # ... in dX (24 x 24, one of each), K = 35
+    # operands of whole 16-byte pieces, straight to LDS:
+    (1037, 1028, 1028, 3, 4),   # 64-wide tiles, ragged everywhere, K = 1028 (33 steps, the last of 4) and 1037 (of 13)
+    (1025, 1088, 1056, 3, 4),   # whole steps, an even and an odd number of them; K = 1025: the last step of one row
+    (2945, 2948, 36, 2, 4),     # 128-wide tiles in dX (one operand of each kind), K = 36
+    (132, 2948, 2948, 2, 4),    # ... in dWq (both K-major, 2948 = 23 tiles and 4 columns), K = 132
+    (2945, 260, 2948, 2, 4),    # ... in the forward product (both K-contiguous), K = 260
 ])
 def test_binary32_product_forms(T, i, o, r, g):
     run_case(LayerSpec(f"f32_prod_{T}x{i}x{o}", T, i, o, r, 2.0 * r, 4, g, DTYPE_F32), seed=T + i, shrink=0.8)
