@@ -156,6 +156,7 @@ struct PrefillPlan {
   double us;  // estimated time
 };
 PrefillPlan qgemm_prefill_plan(const LayerDims& d);
+int qgemm_prompt_wide_rows(const LayerDims& d);  // weight rows of a wide tile (form 2): 256 or 192
 // ... where it is the faster way for this call; form -1: the passes of at most 64 tokens are
 PrefillPlan qgemm_prompt_plan(const LayerDims& d, bool have_workspace);
 void launch_qgemm_prefill(const PrefillPlan& plan, const LayerDims& d, const bf16_t* X, const uint32_t* packed,

@@ -2,9 +2,9 @@
 //
 // Bound: the matrix cores, with the vector unit close behind (the codes are turned into operands where they are used, and
 // the affine part of every section of k is applied to its sums): per section of a 128 x 256 tile a wave has 1152 cycles of
-// matrix ops and 1100 of vector ops.  The decode kernels read and convert the whole weight once per 64 tokens: 8 passes of
-// 27 us at 512 tokens on [11008 x 4096]; this kernel takes 69 us.  A workgroup of 8 waves (2 x 4, two per SIMD) owns a tile of
-// 64 TM tokens x 128 TN weight rows, so a converted code is used for 32 TM tokens of a wave and the weight is read once per
+// matrix ops and 950 of vector ops.  The decode kernels read and convert the whole weight once per 64 tokens: 8 passes of
+// 27 us at 512 tokens on [11008 x 4096]; this kernel takes 58 us.  A workgroup of 8 waves (2 x 4, two per SIMD; for 192 rows
+// 2 x 6, three) owns a tile of 64 TM tokens x 32 WN TN weight rows, so a converted code is used for 32 TM tokens of a wave and the weight is read once per
 // tile row.  Arithmetic as in the decode kernels: the matrix cores multiply X with the exact integers w~ + K0, and
 //   sum_k X (w~ s + b) = s sum_k X (w~ + K0) + (b - K0 s) sum_k X   per section of SEC k-values (128, or groups of 64),
 // in binary32.
@@ -13,12 +13,13 @@
 //    consecutive codes each: section sub-stage jj, matrix op d contracts k = 64 jj + 32 half + 8 d + 0 .. 7.
 //  * scale and zero: every lane loads its own rows' values for four sections at a time into registers.
 //  * within a section everything is one matrix-op step ahead: reads, conversions, sums of X and the next loads are dealt
-//    out between the matrix ops (ahead of them in a lump they cost 93 against 69 us: both waves of a SIMD come out of
+//    out between the matrix ops (ahead of them in a lump they cost 93 against 69 us in 128 x 256 tiles: both waves of a SIMD come out of
 //    the barrier together and do the same thing at the same time).
 //  * sums of X per (token, section): dot products with ones by the four waves that hold the token, a quarter of the
 //    section each; the partial sums meet in LDS, and the zero term of two sections is one K = 2 binary32 matrix op.
-//  * 4 bits: the codes of a dword are paired (j, j + 4), one shift and one mask-or per pair, and the X fragments are
-//    permuted to match.
+//  * 4 bits: a byte's two codes by one multiplication with the byte picked by the op, one mask-or per pair, in the order in
+//    which X lies.  (Pairs (j, j + 4) take a shift less but X fragments permuted to match, by each of the four waves that
+//    hold the tokens: 75 us against 70 in 128 x 256 tiles, 56 against 49 in 128 x 128.)
 #include <type_traits>
 #include <utility>
 
@@ -44,15 +45,16 @@ __device__ __forceinline__ void static_for(F&& f) {
   static_for_impl<N>(static_cast<F&&>(f), std::make_integer_sequence<int, N>());
 }
 
-template <int BITS, int TM_, int TN_, int SEC_, bool WIDE_ = false>
+template <int BITS, int TM_, int TN_, int SEC_, bool WIDE_ = false, int WN_ = 4>
 struct Prefill {
   static constexpr int TM = TM_, TN = TN_, SEC = SEC_;
   static constexpr bool WIDE = WIDE_;                  // groups of more than a section
-  static constexpr int WN = 4, NT = 512;               // 2 x 4 waves, two per SIMD
+  static constexpr int WN = WN_, NT = 128 * WN;        // 2 x 4 waves, two per SIMD; or 2 x 6, three
   static constexpr int BM = 64 * TM, BN = 32 * WN * TN;
   static constexpr int NJ = SEC / 64;                  // 64-k sub-stages: 128-byte rows of X
   static constexpr int PPR = SEC * BITS / 128;         // 16-byte pieces of a weight row's section
-  static constexpr int X_INSTR = BM * SEC * 2 / (16 * NT);  // loads per wave and section
+  static constexpr int X_TOTAL = BM * SEC * 2 / 1024;  // loads of X per section, and per wave (the last ones of nothing)
+  static constexpr int X_INSTR = (X_TOTAL + 2 * WN - 1) / (2 * WN);
   static constexpr int W_INSTR = (BN * PPR + NT - 1) / NT;
   static constexpr int LOADS = X_INSTR + W_INSTR;
   static constexpr int X_BYTES = BM * SEC * 2;
@@ -60,7 +62,8 @@ struct Prefill {
   static constexpr int RING = 3;
   static constexpr int SX = RING * SLOT;               // [4 sections][BM tokens][8 partial sums]
   static constexpr int EP_ROW = 32 * TN * 2 + 16;      // bytes of a token's row in a wave's output block
-  static constexpr int LDS = SX + 4 * BM * 32;
+  static constexpr int IDLE = SX + 4 * BM * 32;        // where loads of nothing go
+  static constexpr int LDS = IDLE + (X_INSTR * 2 * WN > X_TOTAL ? 1024 : 0);
   static_assert(SEC * BITS % 128 == 0, "a row's section is whole 16-byte pieces");
   static_assert(2 * WN * 32 * TM * EP_ROW <= SX, "the output blocks take the ring's place");
   static_assert(LDS <= 160 * 1024, "LDS");
@@ -102,7 +105,7 @@ __global__ __launch_bounds__(P::NT) void qgemm_prefill_kernel(const bf16_t* __re
   for (int c = 0; c < P::X_INSTR; ++c) {  // instruction q of the slot: 8 token rows of sub-stage q / (BM / 8)
     const int q = wave * P::X_INSTR + c, jj = q / (P::BM / 8), row = (q % (P::BM / 8)) * 8 + (lane >> 3);
     const int ch = (lane & 7) ^ ((row >> 1) & 7);
-    voffX[c] = t0 + row < T ? (unsigned)(((t0 + row) * i + jj * 64 + ch * 8) * 2) : gemm::OOB_OFFSET;
+    voffX[c] = t0 + row < T && q < P::X_TOTAL ? (unsigned)(((t0 + row) * i + jj * 64 + ch * 8) * 2) : gemm::OOB_OFFSET;
   }
 #pragma unroll
   for (int c = 0; c < P::W_INSTR; ++c) {
@@ -115,7 +118,8 @@ __global__ __launch_bounds__(P::NT) void qgemm_prefill_kernel(const bf16_t* __re
     unsigned char* base = plds + slot * P::SLOT;
     if constexpr (c < P::X_INSTR) {
       const unsigned kx = sec < nsec ? (unsigned)sec * (SEC * 2) : gemm::PAST_END_OFFSET;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsX, (gemm::lds_ptr_t)(base + (wave * P::X_INSTR + c) * 1024), 16,
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsX, (gemm::lds_ptr_t)(wave * P::X_INSTR + c < P::X_TOTAL ? base + (wave * P::X_INSTR + c) * 1024
+                                                                                              : plds + P::IDLE), 16,
                                                voffX[c] + kx, 0, 0, 0);
     } else {
       constexpr int cw = c - P::X_INSTR;
@@ -209,9 +213,9 @@ __global__ __launch_bounds__(P::NT) void qgemm_prefill_kernel(const bf16_t* __re
     auto convert = [&](int b, int ks) {
       const int jj = ks >> 2, d = ks & 3;
       if constexpr (BITS == 4) {
-        u32x4_t f;
+        u32x4_t f;  // (a byte's two codes by one multiplication, see code_fragment; the byte is picked by the op itself)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) f[e] = ((w[b][jj][0][d] >> (4 * e)) & pair_mask) | pair_bias;
+        for (int e = 0; e < 4; ++e) f[e] = ((((w[b][jj][0][d] >> (8 * e)) & 0xFFu) * 0x1001u) & pair_mask) | pair_bias;
         return __builtin_bit_cast(bf16x8_t, f);
       } else if constexpr (BITS == 8) {
         return code_fragment<8>(w[b][jj][d >> 1], d & 1);
@@ -219,19 +223,9 @@ __global__ __launch_bounds__(P::NT) void qgemm_prefill_kernel(const bf16_t* __re
         return code_fragment<BITS>(w[b][jj][0], d);
       }
     };
-    auto permute = [&](const bf16x8_t& v) {
-      if constexpr (BITS == 4) {
-        const u32x4_t x = __builtin_bit_cast(u32x4_t, v);
-        const u32x4_t y = {__builtin_amdgcn_perm(x[2], x[0], 0x05040100u), __builtin_amdgcn_perm(x[2], x[0], 0x07060302u),
-                           __builtin_amdgcn_perm(x[3], x[1], 0x05040100u), __builtin_amdgcn_perm(x[3], x[1], 0x07060302u)};
-        return __builtin_bit_cast(bf16x8_t, y);
-      } else {
-        return v;
-      }
-    };
     const bf16x2_t ones = __builtin_bit_cast(bf16x2_t, 0x3F803F80u);
-    constexpr int VALU_PER = (TM * 4 + TN * 8 + TM * TN - 1) / (TM * TN);
-    bf16x8_t xr[3][TM], xp[2][TM], wf[2][TN], xq[TM];
+    constexpr int VALU_PER = TN == 1 ? 8 / TM : 6;  // (8 TN conversions a step, sums of X; 6 where 4 took 73 us for 70)
+    bf16x8_t xr[3][TM], wf[2][TN], xq[TM];
     float part[TM];
     f32x16_t tw[TM][TN];
 #pragma unroll
@@ -246,8 +240,6 @@ __global__ __launch_bounds__(P::NT) void qgemm_prefill_kernel(const bf16_t* __re
     }
 #pragma unroll
     for (int b = 0; b < TN; ++b) wf[0][b] = convert(b, 0);
-#pragma unroll
-    for (int a = 0; a < TM; ++a) xp[0][a] = permute(xr[0][a]);
     static_for<K>([&](auto kt) {
       constexpr int ks = decltype(kt)::value;
       if constexpr (ks + 2 < K) {
@@ -263,8 +255,6 @@ __global__ __launch_bounds__(P::NT) void qgemm_prefill_kernel(const bf16_t* __re
       if constexpr (ks + 1 < K) {
 #pragma unroll
         for (int b = 0; b < TN; ++b) wf[(ks + 1) & 1][b] = convert(b, ks + 1);
-#pragma unroll
-        for (int a = 0; a < TM; ++a) xp[(ks + 1) & 1][a] = permute(xr[(ks + 1) % 3][a]);
       }
       // sums of X: the steps of this wave's quarter, read a step ahead
       if constexpr (ks > 0 && ks <= NJ) {
@@ -279,7 +269,7 @@ __global__ __launch_bounds__(P::NT) void qgemm_prefill_kernel(const bf16_t* __re
         }
       }
       if constexpr (ks < NJ) {
-        const int kq = wn * NJ + ks;
+        const int kq = (wn & 3) * NJ + ks;  // (waves past the fourth: as the first ones, and not stored)
 #pragma unroll
         for (int a = 0; a < TM; ++a)
           xq[a] = *reinterpret_cast<const bf16x8_t*>(xrow[a] + (kq >> 2) * (P::BM * 128) + (((4 * h + (kq & 3)) ^ xsw[a]) << 4));
@@ -288,7 +278,7 @@ __global__ __launch_bounds__(P::NT) void qgemm_prefill_kernel(const bf16_t* __re
       for (int a = 0; a < TM; ++a)
 #pragma unroll
         for (int b = 0; b < TN; ++b)
-          tw[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xp[ks & 1][a], wf[ks & 1][b], tw[a][b], 0, 0, 0);
+          tw[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xr[ks % 3][a], wf[ks & 1][b], tw[a][b], 0, 0, 0);
       // matrix ops one by one, the vector ops, reads and loads of the step between them: issued back to back they would
       // hold up the wave's vector ops until the last has started
 #pragma unroll
@@ -299,8 +289,10 @@ __global__ __launch_bounds__(P::NT) void qgemm_prefill_kernel(const bf16_t* __re
         if (q == 0) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
       }
     });
+    if (wn < 4) {
 #pragma unroll
-    for (int a = 0; a < TM; ++a) sx[(j * P::BM + (wm * TM + a) * 32 + l32) * 8 + 2 * wn + h] = part[a];
+      for (int a = 0; a < TM; ++a) sx[(j * P::BM + (wm * TM + a) * 32 + l32) * 8 + 2 * wn + h] = part[a];
+    }
 #pragma unroll
     for (int a = 0; a < TM; ++a)
 #pragma unroll
@@ -391,14 +383,31 @@ void launch_form(const LayerDims& d, const bf16_t* X, const uint32_t* packed, co
                      packed, scale, zero, Y, (int)d.T, (int)d.o, (int)d.i, d.g, tiles_m, tiles_n);
 }
 
-// Forms: 0 = 64 x 128 tiles (two workgroups per compute unit), 1 = 128 x 128, 2 = 128 x 256 (groups of 128, not 8 bits).
+// 128-token tiles of 256 weight rows (8 waves of 64 x 64) or of 192 (12 waves of 64 x 32): a section of a round takes 1.95 and
+// 1.72 us, so 192 wherever it needs no more rounds, which leaves fewer units idle in the last one (4 bits, 256 / 192, us:
+// 512, 11008 x 4096 74 / 64;  1000, 11008 x 4096 147 / 139;  700, 6144 x 5120 87 / 74;  3 and 2 bits, 512, 11008 x 4096 87 / 72
+// and 80 / 69).
+struct WideTiles {
+  int rows;
+  double section_us;  // of all rounds
+};
+WideTiles wide_tiles(const LayerDims& d) {
+  const int64_t cus = device_compute_units(), tiles_m = (d.T + 127) / 128;
+  const double r256 = (double)((tiles_m * ((d.o + 255) / 256) + cus - 1) / cus) * 1.95;
+  const double r192 = (double)((tiles_m * ((d.o + 191) / 192) + cus - 1) / cus) * 1.72;
+  return r192 < r256 ? WideTiles{192, r192} : WideTiles{256, r256};
+}
+
+// Forms: 0 = 64 x 128 tiles (two workgroups per compute unit), 1 = 128 x 128, 2 = wide tiles (groups of 128, not 8 bits).
 template <int BITS, int SEC, bool WIDE>
 void launch_bits(int form, const LayerDims& d, const bf16_t* X, const uint32_t* packed, const float* scale,
                  const float* zero, bf16_t* Y, hipStream_t stream) {
   if (form == 0) launch_form<BITS, Prefill<BITS, 1, 1, SEC, WIDE>>(d, X, packed, scale, zero, Y, stream);
   else if (form == 1) launch_form<BITS, Prefill<BITS, 2, 1, SEC, WIDE>>(d, X, packed, scale, zero, Y, stream);
-  else if constexpr (BITS != 8 && SEC == 128 && !WIDE)
-    launch_form<BITS, Prefill<BITS, 2, 2, SEC, WIDE>>(d, X, packed, scale, zero, Y, stream);
+  else if constexpr (BITS != 8 && SEC == 128 && !WIDE) {
+    if (wide_tiles(d).rows == 256) launch_form<BITS, Prefill<BITS, 2, 2, SEC, WIDE>>(d, X, packed, scale, zero, Y, stream);
+    else launch_form<BITS, Prefill<BITS, 2, 1, SEC, WIDE, 6>>(d, X, packed, scale, zero, Y, stream);
+  }
 }
 
 }  // namespace
@@ -413,6 +422,8 @@ void launch_bits(int form, const LayerDims& d, const bf16_t* X, const uint32_t* 
 // The choice against those passes falls where 64 x 128 tiles are the best form, and needs their time closer than that: one
 // workgroup on a unit takes 0.885 us per section at 4 bits, two together 1.46 (2, 3, 8 bits: 0.97 and 1.6, 1.02 and 1.65, 1.13
 // and 2.37; groups of 64 28 % more, 23 % at 8 bits), within 3.5 % on average over 15000 measured calls.
+int qgemm_prompt_wide_rows(const LayerDims& d) { return wide_tiles(d).rows; }
+
 PrefillPlan qgemm_prefill_plan(const LayerDims& d) {
   PrefillPlan plan = {-1, 0.0};
   const bool g_ok = d.g >= 128 || (d.g == 64 && d.bits != 3);
@@ -420,14 +431,19 @@ PrefillPlan qgemm_prefill_plan(const LayerDims& d) {
       d.o * (d.i / d.g) >= (1ll << 28))
     return plan;
   const int64_t cus = device_compute_units();
-  const int64_t bm[3] = {64, 128, 128}, bn[3] = {128, 128, 256};
-  const double per_section[3] = {0.8, 1.35, 1.95};
+  const int64_t bm[2] = {64, 128}, bn[2] = {128, 128};
+  const double per_section[2] = {0.8, 1.35};
   const double bits_factor = (d.bits == 4 ? 1.0 : d.bits == 8 ? 1.25 : 1.12) * (d.g == 64 ? 1.25 : 1.0);
   for (int f = 0; f < (d.g == 128 && d.bits != 8 ? 3 : 2); ++f) {
-    const int64_t tiles = ((d.T + bm[f] - 1) / bm[f]) * ((d.o + bn[f] - 1) / bn[f]);
-    double rounds = (double)((tiles + cus - 1) / cus);
-    if (f == 0 && rounds < 1.1) rounds = 1.1;  // (two workgroups share a unit: one alone is not twice as fast)
-    const double us = 5.0 + rounds * (double)d.i / 128.0 * per_section[f] * bits_factor;
+    double section_us;  // of all rounds
+    if (f == 2) section_us = wide_tiles(d).section_us;
+    else {
+      const int64_t tiles = ((d.T + bm[f] - 1) / bm[f]) * ((d.o + bn[f] - 1) / bn[f]);
+      double rounds = (double)((tiles + cus - 1) / cus);
+      if (f == 0 && rounds < 1.1) rounds = 1.1;  // (two workgroups share a unit: one alone is not twice as fast)
+      section_us = rounds * per_section[f];
+    }
+    const double us = 5.0 + (double)d.i / 128.0 * section_us * bits_factor;
     if (plan.form < 0 || us < plan.us) {
       plan.form = f;
       plan.us = us;

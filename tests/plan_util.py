@@ -23,3 +23,11 @@ def prompt_form(T, i, o, bits, g, workspace=True):
     f.restype, f.argtypes = _PrefillPlan, [ctypes.POINTER(_LayerDims), ctypes.c_bool]
     q = float(1 << (bits - 1))
     return f(ctypes.byref(_LayerDims(T, i, o, 8, bits, g, 2.0, -q, q - 1.0, False)), workspace).form
+
+
+def wide_tile_rows(T, i, o, bits, g):
+    """l4q::qgemm_prompt_wide_rows: the weight rows of a 128-token wide tile for this call (what TILES_128x256 stands for)."""
+    f = getattr(binding.load_library(), "_ZN3l4q22qgemm_prompt_wide_rowsERKNS_9LayerDimsE")
+    f.restype, f.argtypes = ctypes.c_int, [ctypes.POINTER(_LayerDims)]
+    q = float(1 << (bits - 1))
+    return f(ctypes.byref(_LayerDims(T, i, o, 8, bits, g, 2.0, -q, q - 1.0, False)))

@@ -27,6 +27,8 @@ CASES = [
     ((257, 1152, 7944, 64), (TILES_128x128, PASSES, TILES_128x128, TILES_128x128)),   # ... eighteen
     ((385, 192, 5128, 64), (PASSES,) * 4),           # rows that are no multiple of 128
     ((641, 256, 8200, 128), (TILES_128x256, TILES_128x256, TILES_128x256, TILES_64x128)),  # one token in the last tile
+    ((513, 640, 7496, 128), (TILES_128x256, TILES_128x256, TILES_128x256, TILES_64x128)),  # wide tiles of 192 rows, the last of 8 rows
+    ((641, 384, 5896, 128), (TILES_128x256, TILES_128x256, TILES_128x256, TILES_64x128)),  # ... an odd count of sections, 136 rows in the last
 ]
 
 

@@ -2,7 +2,7 @@
 where both were measured (us, passes / tiles)."""
 import pytest
 
-from plan_util import PASSES, TILES_64x128, TILES_128x256, prompt_form
+from plan_util import PASSES, TILES_64x128, TILES_128x256, prompt_form, wide_tile_rows
 from test_gpu_prefill import CASES
 
 
@@ -39,3 +39,13 @@ def test_gpu_cases_take_the_shapes_they_name(case, forms):
 @pytest.mark.parametrize("T,i,o,bits,g", [(80, 2304, 4104, 8, 128), (100, 3072, 2048, 3, 512), (100, 3072, 2048, 4, 256)])
 def test_two_pass_cases_of_the_quantized_path_are_passes(T, i, o, bits, g):
     assert prompt_form(T, i, o, bits, g, True) == PASSES
+
+
+@pytest.mark.parametrize("T,o,rows", [
+    (512, 11008, 192),   # 172 tiles of 256 rows, 232 of 192: one round either way
+    (641, 8200, 256),    # 198 and 258: a second round
+    (513, 7496, 192),
+    (512, 16384, 256),   # 256 and 344
+])
+def test_wide_tile_rows(T, o, rows):
+    assert wide_tile_rows(T, 4096, o, 4, 128) == rows
