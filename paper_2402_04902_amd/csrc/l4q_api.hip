@@ -418,10 +418,7 @@ int l4q_backward(const l4q_desc* desc, const void* X, const void* dY, const void
     mq.wq = wq;
     mq.ld_wq = d.i;
     l4q::launch_merge_quant<float>(d, W0f, Af, Bf, scale, zero, mq, stream);
-    // dX[t,j] = sum_p dY[t,p] Wq[p,j]
-    l4q::launch_sgemm((const float*)dY, d.o, 1, wq, d.i, 1, (float*)dX, d.i, d.T, d.i, d.o, 1.f, stream);
-    // dWq[p,j] = sum_t dY[t,p] X[t,j]
-    l4q::launch_sgemm((const float*)dY, 1, d.o, (const float*)X, d.i, 1, w.dwq, d.i, d.o, d.i, d.T, 1.f, stream);
+    l4q::launch_sgemm_dx_dw((const float*)dY, (const float*)X, wq, d.T, d.i, d.o, (float*)dX, w.dwq, stream);
     l4q::launch_quant_grads<float>(d, W0f, Af, Bf, scale, zero, w.dwq, dscale, dzero, dB, stream);
     l4q::launch_tn<float, float>(Bf, w.dwq, d.o, d.i, d.r, false, w.dA_part, d.gamma, dA, d.accumulate, stream);
   }
@@ -631,10 +628,9 @@ int l4q_qatlora_backward(const l4q_desc* desc, const void* X, const void* dY, co
     mq.wq = w.wq32;
     mq.ld_wq = d.i;
     l4q::launch_merge_quant<float>(dq, W0f, Af, Bf, scale, zero, mq, stream);
-    l4q::launch_sgemm(dYf, d.o, 1, w.wq32, d.i, 1, (float*)dX, d.i, d.T, d.i, d.o, 1.f, stream);
+    l4q::launch_sgemm_dx_dw(dYf, Xf, w.wq32, d.T, d.i, d.o, (float*)dX, w.dwq, stream);
     l4q::launch_sgemm(dYf, d.o, 1, Bf, d.r, 1, w.dyb, d.r, d.T, d.r, d.o, 1.f, stream);
     l4q::launch_sgemm(w.dyb, d.r, 1, Af, d.i, 1, (float*)dX, d.i, d.T, d.i, d.r, d.gamma, stream, true);
-    l4q::launch_sgemm(dYf, 1, d.o, Xf, d.i, 1, w.dwq, d.i, d.o, d.i, d.T, 1.f, stream);
     l4q::launch_quant_grads<float>(dq, W0f, Af, Bf, scale, zero, w.dwq, dscale, dzero, nullptr, stream);
     l4q::launch_sgemm(Xf, d.i, 1, Af, 1, d.i, w.xa, d.r, d.T, d.r, d.i, 1.f, stream);
     l4q::launch_tn<float, float>(w.dyb, Xf, d.T, d.i, d.r, false, w.part, d.gamma, dA, d.accumulate, stream);

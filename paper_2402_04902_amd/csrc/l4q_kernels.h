@@ -116,6 +116,10 @@ void launch_sgemm(const float* A, int64_t a_rs, int64_t a_cs, const float* B, in
                   float* C, int64_t ldc, int64_t M, int64_t N, int64_t K, float scale, hipStream_t stream,
                   bool accumulate = false);
 
+// dX [T,i] = dY [T,o] . Wq [o,i] and dWq [o,i] = dY^T . X [T,i], binary32 row-major, in one launch where both are small
+void launch_sgemm_dx_dw(const float* dY, const float* X, const float* Wq, int64_t T, int64_t i, int64_t o, float* dX, float* dWq,
+                        hipStream_t stream);
+
 // ---- unfused quantizer gradients: reads dWq [o,i] (binary32), recomputes w, code, mask; writes
 // dscale, dzero [o,G], dB [o,r], and overwrites dWq with mask * dWq.  dB == nullptr (QAT-LoRA): the weight
 // is W0 alone (gamma, A and B are not looked at), only dscale and dzero are written ----
@@ -194,8 +198,8 @@ void launch_dw_masked_products(const LayerDims& d, const bf16_t* dWm, const bf16
 void launch_lora_down(const bf16_t* Xs, int64_t T, int64_t n, const bf16_t* M, int r, float* U, hipStream_t stream);
 // out [r, n] = in [n, r]^T
 void launch_transpose_small(const bf16_t* in, int64_t n, int r, bf16_t* out, hipStream_t stream);
-// out = gamma * sum_t U[t,:]^T Xs[t,:] (U [T, r]) as [r, n], or as [n, r] with out_n_by_r, in two passes of fixed summation
-// order; partial: lora_tn_blocks(T) * r * n floats.  Also dA = gamma * B^T . (m * dWq) of the unfused backward.
+// out = gamma * sum_t U[t,:]^T Xs[t,:] (U [T, r]) as [r, n], or as [n, r] with out_n_by_r, in fixed summation order, in one
+// pass for few rows, else in two; partial: lora_tn_blocks(T) * r * n floats.  Also dA = gamma * B^T . (m * dWq) of the unfused backward.
 int64_t lora_tn_blocks(int64_t T);  // row blocks of the partial sums
 template <class S, class UT>
 void launch_tn(const UT* U, const S* Xs, int64_t T, int64_t n, int r, bool out_n_by_r, float* partial, float gamma,

@@ -124,20 +124,23 @@ template <> struct Row4<bf16_t> {  // (rows are whole 16-byte pieces)
   }
 };
 
-template <class S, class UT, bool NR>
-__global__ __launch_bounds__(256) void tn_partial_kernel(const UT* __restrict__ U, const S* __restrict__ Xs, int64_t T,
-                                                          int64_t n, int r, float* __restrict__ part) {
+//
+// WHOLE (up to 4 row blocks): a workgroup has 4 waves for each row block, and the blocks' sums, formed as above, are added in
+// block order as the second pass would add them, scaled and stored: one launch instead of two, the same bits.
+template <class S, class UT, bool NR, bool WHOLE>
+__global__ __launch_bounds__(WHOLE ? 1024 : 256) void tn_partial_kernel(const UT* __restrict__ U, const S* __restrict__ Xs, int64_t T,
+                                                          int64_t n, int r, float* __restrict__ part, float gamma, bool accumulate) {
 #if defined(__HIP_DEVICE_COMPILE__)
   typedef Row4<float>::vec_t vec_t;
   constexpr int STEPS = LR_TB / 4 / 4;  // groups of 4 rows per wave
-  __shared__ __align__(16) float sums[4][LR_KC][64];
+  __shared__ __align__(16) float sums[WHOLE ? 16 : 4][LR_KC][64];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int h = lane >> 4, c16 = lane & 15;
+  const int h = lane >> 4, c16 = lane & 15, waves = WHOLE ? (int)blockDim.x >> 6 : 4;
   // the last workgroup of a row takes the last 64 columns, some of them its neighbour's (same sums, written twice);
   // rows of 4 to 63 columns end in lanes that repeat the last 4
   const int64_t j0 = n < 64 ? 0 : (int64_t)blockIdx.x * 64 < n - 64 ? (int64_t)blockIdx.x * 64 : n - 64;
   const int jl = n < 4 ? 0 : j0 + c16 * 4 < n - 4 ? c16 * 4 : (int)(n - 4 - j0);  // this lane's first column, from j0
-  const int64_t tb = blockIdx.y, t0 = tb * LR_TB + wave * (LR_TB / 4) + h;
+  const int64_t tb = WHOLE ? 0 : blockIdx.y, t0 = tb * LR_TB + wave * (LR_TB / 4) + h;
   typename Row4<S>::raw_t x[STEPS];
 #pragma unroll
   for (int q = 0; q < STEPS; ++q) {
@@ -175,8 +178,24 @@ __global__ __launch_bounds__(256) void tn_partial_kernel(const UT* __restrict__ 
     for (int e = 0; e < 4; ++e)  // accumulator: rank 4 h + e, column c16 of op c
       *reinterpret_cast<vec_t*>(&sums[wave][4 * h + e][jl]) = vec_t{acc[0][e], acc[1][e], acc[2][e], acc[3][e]};
     __syncthreads();
-    auto total = [&](int k, int j) { return ((sums[0][k][j] + sums[1][k][j]) + sums[2][k][j]) + sums[3][k][j]; };
-    if constexpr (NR) {
+    auto total = [&](int k, int j) {
+      auto block = [&](int w) { return ((sums[w][k][j] + sums[w + 1][k][j]) + sums[w + 2][k][j]) + sums[w + 3][k][j]; };
+      float v = 0.f + block(0);  // (as the second pass starts: no negative zero)
+      if constexpr (WHOLE) {
+        for (int w = 4; w < waves; w += 4) v += block(w);
+      }
+      return v;
+    };
+    if constexpr (WHOLE) {  // one output per thread and turn
+      for (int q = tid; q < LR_KC * 64; q += waves * 64) {
+        const int k = NR ? q % LR_KC : q / 64, j = NR ? q / LR_KC : q % 64;
+        if (j0 + j < n && k0 + k < r && j0 + j >= (int64_t)blockIdx.x * 64) {  // (columns below are the neighbour's: added to once)
+          float* p = part + (NR ? (j0 + j) * r + k0 + k : (int64_t)(k0 + k) * n + j0 + j);
+          const float v = gamma * total(k, j);
+          *p = accumulate ? *p + v : v;
+        }
+      }
+    } else if constexpr (NR) {
       const int j = tid >> 2, k = (tid & 3) * 4;
       if (j0 + j < n) {
         float* q = dst + (j0 + j) * r + k0 + k;
@@ -219,9 +238,17 @@ template <class S, class UT>
 void launch_tn(const UT* U, const S* Xs, int64_t T, int64_t n, int r, bool out_n_by_r, float* partial, float gamma,
                float* out, bool accumulate, hipStream_t stream) {
   const int64_t nb = lora_tn_blocks(T);
-  dim3 grid((unsigned)((n + 63) / 64), (unsigned)nb);
-  if (out_n_by_r) hipLaunchKernelGGL((tn_partial_kernel<S, UT, true>), grid, dim3(256), 0, stream, U, Xs, T, n, r, partial);
-  else hipLaunchKernelGGL((tn_partial_kernel<S, UT, false>), grid, dim3(256), 0, stream, U, Xs, T, n, r, partial);
+#define L4Q_TN(NR, WHOLE, GRID, THREADS, OUT) \
+  hipLaunchKernelGGL((tn_partial_kernel<S, UT, NR, WHOLE>), GRID, dim3(THREADS), 0, stream, U, Xs, T, n, r, OUT, gamma, accumulate)
+  const unsigned cols = (unsigned)((n + 63) / 64);
+  if (nb <= 4) {
+    if (out_n_by_r) L4Q_TN(true, true, dim3(cols), (unsigned)(256 * nb), out);
+    else L4Q_TN(false, true, dim3(cols), (unsigned)(256 * nb), out);
+    return;
+  }
+  if (out_n_by_r) L4Q_TN(true, false, dim3(cols, (unsigned)nb), 256u, partial);
+  else L4Q_TN(false, false, dim3(cols, (unsigned)nb), 256u, partial);
+#undef L4Q_TN
   launch_reduce_partials(partial, nb, (int64_t)r * n, gamma, out, accumulate, stream);
 }
 

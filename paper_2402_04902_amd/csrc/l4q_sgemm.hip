@@ -363,14 +363,15 @@ __device__ __forceinline__ void sliced_fragment(const float* __restrict__ P, int
 constexpr int SL_WAVES = 8;
 constexpr int SL_UNROLL = 4;  // runs of 8 k-values in flight per wave
 
+typedef float SlicedSums[SL_WAVES][32][33];
+
 template <bool A_KM, bool B_KM>
-__global__ __launch_bounds__(64 * SL_WAVES) void sgemm_sliced_kernel(SgemmArgs a) {
+__device__ __forceinline__ void sliced_tile(const SgemmArgs& a, int tile, SlicedSums& part) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  __shared__ float part[SL_WAVES][32][33];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, half = lane >> 5;
   const int tiles_n = (int)((a.N + 31) / 32);
-  const int64_t m0 = (int64_t)(blockIdx.x / tiles_n) * 32, n0 = (int64_t)(blockIdx.x % tiles_n) * 32;
+  const int64_t m0 = (int64_t)(tile / tiles_n) * 32, n0 = (int64_t)(tile % tiles_n) * 32;
   const bool m_ok = m0 + l32 < a.M, n_ok = n0 + l32 < a.N;
   f32x16_t acc;
 #pragma unroll
@@ -399,6 +400,21 @@ __global__ __launch_bounds__(64 * SL_WAVES) void sgemm_sliced_kernel(SgemmArgs a
     if (m0 + r < a.M && n0 + c < a.N) store_out(a, m0 + r, n0 + c, v);
   }
 #endif
+}
+
+template <bool A_KM, bool B_KM>
+__global__ __launch_bounds__(64 * SL_WAVES) void sgemm_sliced_kernel(SgemmArgs a) {
+  __shared__ SlicedSums part;
+  sliced_tile<A_KM, B_KM>(a, (int)blockIdx.x, part);
+}
+
+// Two products that do not need each other in one launch (dX and dWq of a small layer): the first `tiles` workgroups take
+// a, the others b.  Each is a single chain of loads, matrix ops and stores of about 5 us.
+template <bool A1, bool B1, bool A2, bool B2>
+__global__ __launch_bounds__(64 * SL_WAVES) void sgemm_sliced_pair_kernel(SgemmArgs a, SgemmArgs b, int tiles) {
+  __shared__ SlicedSums part;
+  if ((int)blockIdx.x < tiles) sliced_tile<A1, B1>(a, (int)blockIdx.x, part);
+  else sliced_tile<A2, B2>(b, (int)blockIdx.x - tiles, part);
 }
 
 // Which form, in us (K-contiguous operands; sliced / 64 x 64 tiles by one, by two groups of waves / 128 x 128 tiles):
@@ -445,21 +461,47 @@ void launch_sgemm_form(const SgemmArgs& a, hipStream_t stream) {
 
 }  // namespace
 
-void launch_sgemm(const float* A, int64_t a_rs, int64_t a_cs, const float* B, int64_t b_rs, int64_t b_cs, float* C,
-                  int64_t ldc, int64_t M, int64_t N, int64_t K, float scale, hipStream_t stream, bool accumulate) {
+namespace {
+SgemmArgs sgemm_args(const float* A, int64_t a_rs, int64_t a_cs, const float* B, int64_t b_rs, int64_t b_cs, float* C,
+                     int64_t ldc, int64_t M, int64_t N, int64_t K, float scale, bool accumulate) {
   SgemmArgs a;
   a.A = A; a.B = B; a.C = C;
   a.M = M; a.N = N; a.K = K;
   a.ldc = ldc;
   a.scale = scale;
   a.accumulate = accumulate;
-  const bool a_km = a_cs != 1, b_km = b_rs != 1;  // (one of an operand's strides is 1)
-  a.lda = a_km ? a_cs : a_rs;
-  a.ldb = b_km ? b_rs : b_cs;
+  a.lda = a_cs != 1 ? a_cs : a_rs;  // (one of an operand's strides is 1)
+  a.ldb = b_rs != 1 ? b_rs : b_cs;
+  return a;
+}
+}  // namespace
+
+void launch_sgemm(const float* A, int64_t a_rs, int64_t a_cs, const float* B, int64_t b_rs, int64_t b_cs, float* C,
+                  int64_t ldc, int64_t M, int64_t N, int64_t K, float scale, hipStream_t stream, bool accumulate) {
+  const SgemmArgs a = sgemm_args(A, a_rs, a_cs, B, b_rs, b_cs, C, ldc, M, N, K, scale, accumulate);
+  const bool a_km = a_cs != 1, b_km = b_rs != 1;
   if (a_km && b_km) launch_sgemm_form<true, true>(a, stream);
   else if (a_km) launch_sgemm_form<true, false>(a, stream);
   else if (b_km) launch_sgemm_form<false, true>(a, stream);
   else launch_sgemm_form<false, false>(a, stream);
+}
+
+void launch_sgemm_dx_dw(const float* dY, const float* X, const float* Wq, int64_t T, int64_t i, int64_t o, float* dX, float* dWq,
+                        hipStream_t stream) {
+  // dX[t,j] = sum_p dY[t,p] Wq[p,j];  dWq[p,j] = sum_t dY[t,p] X[t,j]
+  auto tiles = [](int64_t m, int64_t n, int64_t b) { return ((m + b - 1) / b) * ((n + b - 1) / b); };
+  const int64_t few = device_compute_units() * 5;
+  // both of few tiles (the line of launch_sgemm_form), and in forms whose operands' unit strides are where they are expected
+  if (tiles(T, i, 64) * 8 < few && tiles(o, i, 64) * 8 < few && i != 1 && o != 1) {
+    const SgemmArgs a = sgemm_args(dY, o, 1, Wq, i, 1, dX, i, T, i, o, 1.f, false);
+    const SgemmArgs b = sgemm_args(dY, 1, o, X, i, 1, dWq, i, o, i, T, 1.f, false);
+    const int first = (int)tiles(T, i, 32);
+    hipLaunchKernelGGL((sgemm_sliced_pair_kernel<false, true, true, true>), dim3((unsigned)(first + tiles(o, i, 32))),
+                       dim3(64 * SL_WAVES), 0, stream, a, b, first);
+    return;
+  }
+  launch_sgemm(dY, o, 1, Wq, i, 1, dX, i, T, i, o, 1.f, stream);
+  launch_sgemm(dY, 1, o, X, i, 1, dWq, i, o, i, T, 1.f, stream);
 }
 
 }  // namespace l4q
