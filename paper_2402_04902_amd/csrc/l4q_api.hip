@@ -383,6 +383,8 @@ int l4q_backward(const l4q_desc* desc, const void* X, const void* dY, const void
     mq.ld_wqT = w.opad;
     mq.fgrad = w.fgrad;  // null when unfused
     mq.bT = w.fused ? w.bT : nullptr;  // (the masked form reads B as it lies)
+    mq.bT_rank = d.r;
+    mq.ld_bT = w.opad;
     merge_quant_bf16(d, W0b, Ab, Bb, scale, zero, mq, stream);
     // dWq = dY^T . X, both operands read as they lie in memory.  The fused kernel goes first: the factor array the
     // merge pass has just written is then still in the memory-side cache when the epilogues ask for it.
@@ -570,7 +572,8 @@ int l4q_qatlora_forward(const l4q_desc* desc, const void* X, const void* W0, con
     mq.wq = wq;
     mq.ld_wq = w.ipad;
     l4q::launch_merge_quant<bf16_t>(dq, (const bf16_t*)W0, (const bf16_t*)A, (const bf16_t*)B, scale, zero, mq, stream);
-    l4q::launch_lora_down((const bf16_t*)X, d.T, d.i, (const bf16_t*)A, d.r, w.xa, stream);
+    const l4q::LoraDown down = {(const bf16_t*)X, d.i, (const bf16_t*)A, d.i, w.xa};
+    l4q::launch_lora_down(&down, 1, d.T, d.r, stream);
     gemm_nt_rank((const bf16_t*)X, d.i, wq, d.T, d.o, w.ipad, d.i, (bf16_t*)Y, {w.xa, (const bf16_t*)B, d.r, d.gamma, true},
                  stream);
   } else {
@@ -610,17 +613,23 @@ int l4q_qatlora_backward(const l4q_desc* desc, const void* X, const void* dY, co
     l4q::MergeQuantOut<bf16_t> mq;
     mq.wqT = w.wqT;
     mq.ld_wqT = w.opad;
-    l4q::launch_merge_quant<bf16_t>(dq, W0b, Ab, Bb, scale, zero, mq, stream);
     bf16_t* bT = (bf16_t*)w.part;  // B^T [r, o]: `part` (at least 4 r o bytes) is not in use yet
-    l4q::launch_transpose_small(Bb, d.o, d.r, bT, stream);
-    l4q::launch_lora_down(dYb, d.T, d.o, bT, d.r, w.dyb, stream);
+    mq.bT = bT;
+    mq.bT_rank = d.r;
+    mq.ld_bT = d.o;
+    l4q::launch_merge_quant<bf16_t>(dq, W0b, Ab, Bb, scale, zero, mq, stream);
+    const l4q::LoraDown down[2] = {{dYb, d.o, bT, d.o, w.dyb}, {Xb, d.i, Ab, d.i, w.xa}};
+    l4q::launch_lora_down(down, 2, d.T, d.r, stream);
     gemm_nt_rank(dYb, d.o, w.wqT, d.T, d.i, w.opad, d.o, (bf16_t*)dX, {w.dyb, Ab, d.r, d.gamma, false}, stream);
     // the weight gradient is materialised: scale and zero are updated from it
     l4q::launch_gemm_bf16_kmajor_f32(dYb, d.o, Xb, d.i, d.o, d.i, d.T, w.dwq, d.i, stream);
     l4q::launch_quant_grads<bf16_t>(dq, W0b, Ab, Bb, scale, zero, w.dwq, dscale, dzero, nullptr, stream);
-    l4q::launch_lora_down(Xb, d.T, d.i, Ab, d.r, w.xa, stream);
-    l4q::launch_tn<bf16_t, float>(w.dyb, Xb, d.T, d.i, d.r, false, w.part, d.gamma, dA, d.accumulate, stream);
-    l4q::launch_tn<bf16_t, float>(w.xa, dYb, d.T, d.o, d.r, true, w.part, d.gamma, dB, d.accumulate, stream);
+    if (l4q::lora_tn_blocks(d.T) * d.r <= d.i) {  // the weight gradient has been used: its place takes dB's partial sums
+      l4q::launch_tn_pair(w.dyb, Xb, d.i, dA, w.part, w.xa, dYb, d.o, dB, w.dwq, d.T, d.r, d.gamma, d.accumulate, stream);
+    } else {
+      l4q::launch_tn<bf16_t, float>(w.dyb, Xb, d.T, d.i, d.r, false, w.part, d.gamma, dA, d.accumulate, stream);
+      l4q::launch_tn<bf16_t, float>(w.xa, dYb, d.T, d.o, d.r, true, w.part, d.gamma, dB, d.accumulate, stream);
+    }
   } else {
     const float *Xf = (const float*)X, *dYf = (const float*)dY, *W0f = (const float*)W0, *Af = (const float*)A,
                 *Bf = (const float*)B;

@@ -31,7 +31,9 @@ struct MergeQuantOut {
   int64_t ld_wq = 0;         // multiple of 32 (bfloat16)
   bf16_t* wqT = nullptr;
   int64_t ld_wqT = 0;        // multiple of 32
-  bf16_t* bT = nullptr;      // B^T [r, ld_wqT] bf16 for the fused backward; columns o..ld_wqT-1 zeros (bf16 mode only)
+  bf16_t* bT = nullptr;      // B^T [bT_rank, ld_bT] bf16 beside wqT; columns o..ld_bT-1 zeros (bf16 mode only)
+  int bT_rank = 0;           // rank of B, also where the pass itself has none (LayerDims::r == 0)
+  int64_t ld_bT = 0;         // o .. ld_wqT
   uint16_t* fgrad = nullptr; // [o,i] binary16: d(Wq)/d(scale) = code - w in range, code (= Q_N or Q_P) when clipped;
                              // |value| <= 1/2 exactly when the element is in range
   int8_t* codes = nullptr;   // [o,i]
@@ -194,15 +196,23 @@ void launch_dw_masked_products(const LayerDims& d, const bf16_t* dWm, const bf16
                                float* rawB, hipStream_t stream);
 
 // ---- rank-r side products of the QAT-LoRA layer (Sec. 3.1) ----
-// U [T, r] (binary32) = Xs [T, n] . M [r, n]^T, n % 8 == 0
-void launch_lora_down(const bf16_t* Xs, int64_t T, int64_t n, const bf16_t* M, int r, float* U, hipStream_t stream);
-// out [r, n] = in [n, r]^T
-void launch_transpose_small(const bf16_t* in, int64_t n, int r, bf16_t* out, hipStream_t stream);
+// U [T, r] (binary32) = Xs [T, n] . M [r, n]^T, n % 8 == 0, rows of M ldm % 8 == 0 elements apart; one or two in a launch
+struct LoraDown {
+  const bf16_t* Xs;
+  int64_t n;
+  const bf16_t* M;
+  int64_t ldm;
+  float* U;
+};
+void launch_lora_down(const LoraDown* jobs, int njobs, int64_t T, int r, hipStream_t stream);
 // out = gamma * sum_t U[t,:]^T Xs[t,:] (U [T, r]) as [r, n], or as [n, r] with out_n_by_r, in fixed summation order, in one
 // pass for few rows, else in two; partial: lora_tn_blocks(T) * r * n floats.  Also dA = gamma * B^T . (m * dWq) of the unfused backward.
 int64_t lora_tn_blocks(int64_t T);  // row blocks of the partial sums
 template <class S, class UT>
 void launch_tn(const UT* U, const S* Xs, int64_t T, int64_t n, int r, bool out_n_by_r, float* partial, float gamma,
                float* out, bool accumulate, hipStream_t stream);
+// outa [r, na] = gamma Ua^T . Xa and outb [nb, r] = gamma (Ub^T . Xb)^T together; parta, partb: lora_tn_blocks(T) * r * na / nb floats
+void launch_tn_pair(const float* Ua, const bf16_t* Xa, int64_t na, float* outa, float* parta, const float* Ub, const bf16_t* Xb,
+                    int64_t nb, float* outb, float* partb, int64_t T, int r, float gamma, bool accumulate, hipStream_t stream);
 
 }  // namespace l4q

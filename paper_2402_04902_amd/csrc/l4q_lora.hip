@@ -27,11 +27,16 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 constexpr int LD_WAVES = 16;
 constexpr int LD_AHEAD = 4;
 
+// Two products of the same T and r (the backward pass's) share a launch: 2048 tokens are 128 workgroups each, half of the
+// compute units (2 x 9.2 us apart, 10.9 together).
 template <int NC>
-__global__ __launch_bounds__(64 * LD_WAVES) void lora_down_kernel(const bf16_t* __restrict__ Xs, int64_t T, int64_t n,
-                                                                  const bf16_t* __restrict__ M, int r,
-                                                                  float* __restrict__ U) {
+__global__ __launch_bounds__(64 * LD_WAVES) void lora_down_kernel(LoraDown job0, LoraDown job1, int64_t T, int r) {
 #if defined(__HIP_DEVICE_COMPILE__)
+  const LoraDown& job = blockIdx.z == 0 ? job0 : job1;
+  const bf16_t* __restrict__ Xs = job.Xs;
+  const bf16_t* __restrict__ M = job.M;
+  float* __restrict__ U = job.U;
+  const int64_t n = job.n;
   __shared__ float sums[LD_WAVES][16][16 * NC + 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c16 = lane & 15, h = lane >> 4;
@@ -41,7 +46,7 @@ __global__ __launch_bounds__(64 * LD_WAVES) void lora_down_kernel(const bf16_t* 
   const bf16_t* xp = Xs + (t0 + c16 < T ? t0 + c16 : T - 1) * n;
   const bf16_t* mp[NC];
 #pragma unroll
-  for (int c = 0; c < NC; ++c) mp[c] = M + (int64_t)(k0 + c * 16 + c16 < r ? k0 + c * 16 + c16 : r - 1) * n;
+  for (int c = 0; c < NC; ++c) mp[c] = M + (int64_t)(k0 + c * 16 + c16 < r ? k0 + c * 16 + c16 : r - 1) * job.ldm;
   f32x4_t acc[NC];
 #pragma unroll
   for (int c = 0; c < NC; ++c) acc[c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -80,19 +85,6 @@ __global__ __launch_bounds__(64 * LD_WAVES) void lora_down_kernel(const bf16_t* 
 #endif
 }
 
-// out[k][j] = in[j][k]: 64 rows of `in` per workgroup through LDS
-__global__ __launch_bounds__(256) void transpose_small_kernel(const bf16_t* __restrict__ in, int64_t n, int r,
-                                                               bf16_t* __restrict__ out) {
-  __shared__ bf16_t tile[64][256 + 2];  // (rank <= 256)
-  const int64_t j0 = (int64_t)blockIdx.x * 64;
-  const int rows = n - j0 < 64 ? (int)(n - j0) : 64;
-  for (int q = threadIdx.x; q < rows * r; q += 256) tile[q / r][q % r] = in[j0 * r + q];
-  __syncthreads();
-  const int lane = threadIdx.x & 63;
-  if (lane < rows)
-    for (int k = threadIdx.x >> 6; k < r; k += 4) out[(int64_t)k * n + j0 + lane] = tile[lane][k];
-}
-
 // part[tb][k][j] (or [tb][j][k] when NR) = sum over the 128 rows of block tb of U[t, k] Xs[t, j].
 // Bound: Xs read once.  v_mfma_f32_16x16x4_f32 takes 16 ranks x 4 rows x 16 columns in binary32: lane (h = lane / 16,
 // c = lane % 16) holds row h of four and 4 consecutive columns, one per op, so its loads are 8 or 16 consecutive bytes, 16
@@ -127,18 +119,19 @@ template <> struct Row4<bf16_t> {  // (rows are whole 16-byte pieces)
 //
 // WHOLE (up to 4 row blocks): a workgroup has 4 waves for each row block, and the blocks' sums, formed as above, are added in
 // block order as the second pass would add them, scaled and stored: one launch instead of two, the same bits.
+typedef float TnSums[LR_KC][64];
+
 template <class S, class UT, bool NR, bool WHOLE>
-__global__ __launch_bounds__(WHOLE ? 1024 : 256) void tn_partial_kernel(const UT* __restrict__ U, const S* __restrict__ Xs, int64_t T,
-                                                          int64_t n, int r, float* __restrict__ part, float gamma, bool accumulate) {
+__device__ __forceinline__ void tn_columns(int block, TnSums* sums, const UT* __restrict__ U, const S* __restrict__ Xs, int64_t T,
+                                           int64_t n, int r, float* __restrict__ part, float gamma, bool accumulate) {
 #if defined(__HIP_DEVICE_COMPILE__)
   typedef Row4<float>::vec_t vec_t;
   constexpr int STEPS = LR_TB / 4 / 4;  // groups of 4 rows per wave
-  __shared__ __align__(16) float sums[WHOLE ? 16 : 4][LR_KC][64];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = lane >> 4, c16 = lane & 15, waves = WHOLE ? (int)blockDim.x >> 6 : 4;
   // the last workgroup of a row takes the last 64 columns, some of them its neighbour's (same sums, written twice);
   // rows of 4 to 63 columns end in lanes that repeat the last 4
-  const int64_t j0 = n < 64 ? 0 : (int64_t)blockIdx.x * 64 < n - 64 ? (int64_t)blockIdx.x * 64 : n - 64;
+  const int64_t j0 = n < 64 ? 0 : (int64_t)block * 64 < n - 64 ? (int64_t)block * 64 : n - 64;
   const int jl = n < 4 ? 0 : j0 + c16 * 4 < n - 4 ? c16 * 4 : (int)(n - 4 - j0);  // this lane's first column, from j0
   const int64_t tb = WHOLE ? 0 : blockIdx.y, t0 = tb * LR_TB + wave * (LR_TB / 4) + h;
   typename Row4<S>::raw_t x[STEPS];
@@ -189,7 +182,7 @@ __global__ __launch_bounds__(WHOLE ? 1024 : 256) void tn_partial_kernel(const UT
     if constexpr (WHOLE) {  // one output per thread and turn
       for (int q = tid; q < LR_KC * 64; q += waves * 64) {
         const int k = NR ? q % LR_KC : q / 64, j = NR ? q / LR_KC : q % 64;
-        if (j0 + j < n && k0 + k < r && j0 + j >= (int64_t)blockIdx.x * 64) {  // (columns below are the neighbour's: added to once)
+        if (j0 + j < n && k0 + k < r && j0 + j >= (int64_t)block * 64) {  // (columns below are the neighbour's: added to once)
           float* p = part + (NR ? (j0 + j) * r + k0 + k : (int64_t)(k0 + k) * n + j0 + j);
           const float v = gamma * total(k, j);
           *p = accumulate ? *p + v : v;
@@ -215,21 +208,40 @@ __global__ __launch_bounds__(WHOLE ? 1024 : 256) void tn_partial_kernel(const UT
 #endif
 }
 
-}  // namespace
-
-void launch_lora_down(const bf16_t* Xs, int64_t T, int64_t n, const bf16_t* M, int r, float* U, hipStream_t stream) {
-  const unsigned tiles = (unsigned)((T + 15) / 16);
-  if (r <= 16)
-    hipLaunchKernelGGL(lora_down_kernel<1>, dim3(tiles), dim3(64 * LD_WAVES), 0, stream, Xs, T, n, M, r, U);
-  else if (r <= 32)
-    hipLaunchKernelGGL(lora_down_kernel<2>, dim3(tiles), dim3(64 * LD_WAVES), 0, stream, Xs, T, n, M, r, U);
-  else
-    hipLaunchKernelGGL(lora_down_kernel<4>, dim3(tiles, (unsigned)((r + 63) / 64)), dim3(64 * LD_WAVES), 0, stream, Xs, T, n,
-                       M, r, U);
+template <class S, class UT, bool NR, bool WHOLE>
+__global__ __launch_bounds__(WHOLE ? 1024 : 256) void tn_partial_kernel(const UT* __restrict__ U, const S* __restrict__ Xs, int64_t T,
+                                                          int64_t n, int r, float* __restrict__ part, float gamma, bool accumulate) {
+  __shared__ __align__(16) TnSums sums[WHOLE ? 16 : 4];
+  tn_columns<S, UT, NR, WHOLE>((int)blockIdx.x, sums, U, Xs, T, n, r, part, gamma, accumulate);
 }
 
-void launch_transpose_small(const bf16_t* in, int64_t n, int r, bf16_t* out, hipStream_t stream) {
-  hipLaunchKernelGGL(transpose_small_kernel, dim3((unsigned)((n + 63) / 64)), dim3(256), 0, stream, in, n, r, out);
+// dA and dB of the QAT-LoRA layer in one launch (2048 tokens, 4096 x 4096, rank 16: 9.7 + 10.6 us apart, 17.5 together, and one
+// second pass instead of two): the first `cols` workgroups of a row take a as [r, n], the others b as [n, r].
+struct TnJob {
+  const float* U;
+  const bf16_t* Xs;
+  int64_t n;
+  float* out;  // partial sums, or the result (WHOLE)
+};
+template <bool WHOLE>
+__global__ __launch_bounds__(WHOLE ? 1024 : 256) void tn_pair_kernel(TnJob a, TnJob b, int cols, int64_t T, int r, float gamma,
+                                                                     bool accumulate) {
+  __shared__ __align__(16) TnSums sums[WHOLE ? 16 : 4];
+  if ((int)blockIdx.x < cols)
+    tn_columns<bf16_t, float, false, WHOLE>((int)blockIdx.x, sums, a.U, a.Xs, T, a.n, r, a.out, gamma, accumulate);
+  else
+    tn_columns<bf16_t, float, true, WHOLE>((int)blockIdx.x - cols, sums, b.U, b.Xs, T, b.n, r, b.out, gamma, accumulate);
+}
+
+}  // namespace
+
+void launch_lora_down(const LoraDown* jobs, int njobs, int64_t T, int r, hipStream_t stream) {
+  const unsigned tiles = (unsigned)((T + 15) / 16), z = (unsigned)njobs;
+  const LoraDown &a = jobs[0], &b = jobs[njobs - 1];
+  if (r <= 16) hipLaunchKernelGGL(lora_down_kernel<1>, dim3(tiles, 1, z), dim3(64 * LD_WAVES), 0, stream, a, b, T, r);
+  else if (r <= 32) hipLaunchKernelGGL(lora_down_kernel<2>, dim3(tiles, 1, z), dim3(64 * LD_WAVES), 0, stream, a, b, T, r);
+  else
+    hipLaunchKernelGGL(lora_down_kernel<4>, dim3(tiles, (unsigned)((r + 63) / 64), z), dim3(64 * LD_WAVES), 0, stream, a, b, T, r);
 }
 
 int64_t lora_tn_blocks(int64_t T) { return (T + LR_TB - 1) / LR_TB; }
@@ -250,6 +262,21 @@ void launch_tn(const UT* U, const S* Xs, int64_t T, int64_t n, int r, bool out_n
   else L4Q_TN(false, false, dim3(cols, (unsigned)nb), 256u, partial);
 #undef L4Q_TN
   launch_reduce_partials(partial, nb, (int64_t)r * n, gamma, out, accumulate, stream);
+}
+
+void launch_tn_pair(const float* Ua, const bf16_t* Xa, int64_t na, float* outa, float* parta, const float* Ub, const bf16_t* Xb,
+                    int64_t nb, float* outb, float* partb, int64_t T, int r, float gamma, bool accumulate, hipStream_t stream) {
+  const int64_t blocks = lora_tn_blocks(T);
+  const int cols = (int)((na + 63) / 64), all = cols + (int)((nb + 63) / 64);
+  if (blocks <= 4) {
+    hipLaunchKernelGGL(tn_pair_kernel<true>, dim3((unsigned)all), dim3((unsigned)(256 * blocks)), 0, stream, TnJob{Ua, Xa, na, outa},
+                       TnJob{Ub, Xb, nb, outb}, cols, T, r, gamma, accumulate);
+    return;
+  }
+  hipLaunchKernelGGL(tn_pair_kernel<false>, dim3((unsigned)all, (unsigned)blocks), dim3(256), 0, stream, TnJob{Ua, Xa, na, parta},
+                     TnJob{Ub, Xb, nb, partb}, cols, T, r, gamma, accumulate);
+  launch_reduce_two_partials(parta, (int)blocks, (int64_t)r * na, outa, partb, (int)blocks, (int64_t)r * nb, outb, gamma, accumulate,
+                             stream);
 }
 
 template void launch_tn<float, float>(const float*, const float*, int64_t, int64_t, int, bool, float*, float, float*, bool,

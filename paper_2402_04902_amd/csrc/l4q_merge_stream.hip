@@ -159,15 +159,15 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
   const int rb_begin = (int)((int64_t)nrb * part / parts);
   const int rb_end = (int)((int64_t)nrb * (part + 1) / parts);
   if constexpr (MODE == 2) {
-    // the first column strip also leaves B^T for its rows (zeros from o to the padded width)
+    // the first column strip also leaves B^T for its rows (zeros from o to its leading dimension)
     if (strip == 0 && out.bT) {
-      const int ld = (int)out.ld_wqT;
+      const int ld = (int)out.ld_bT, rank = out.bT_rank;
       const int pa = rb_begin * 32, pe = rb_end * 32 < ld ? rb_end * 32 : ld;
       const int np = pe - pa;
-      for (int idx = threadIdx.x; idx < r * np; idx += MS_THREADS) {
+      for (int idx = threadIdx.x; idx < rank * np; idx += MS_THREADS) {
         const int k = idx / np;
         const int p2 = pa + idx % np;
-        out.bT[(int64_t)k * ld + p2] = p2 < o ? B[(int64_t)p2 * r + k] : (bf16_t)0;
+        out.bT[(int64_t)k * ld + p2] = p2 < o ? B[(int64_t)p2 * rank + k] : (bf16_t)0;
       }
     }
   }
@@ -565,7 +565,7 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
         const float edge = 0.5f - tol;
         const bool unsettled = row_ok & col_ok & !(off < edge);
         if (!exact && __builtin_amdgcn_ballot_w64(unsettled) != 0) {
-          if constexpr (MODE == 1) exact = r > 16 * ACH || !settle(unsettled, edge);  // (r > 16 ACH: A is not in registers)
+          if constexpr (MODE == 1 && ACH > 0) exact = r > 16 * ACH || !settle(unsettled, edge);  // (r > 16 ACH: A is not in registers)
           else exact = true;
         }
       }

@@ -334,15 +334,15 @@ __global__ __launch_bounds__(MQ_THREADS) void merge_quant_tile_kernel(LayerDims 
     }
   }
 
-  if constexpr (MODE == 2 && std::is_same<T, bf16_t>::value) {
-    // The first column tile of every row block also leaves B^T for its 64 rows (the fused weight-gradient kernel's
-    // dA product reads B that way): r x 64 elements, zeros past o up to the padded width.
+  if constexpr (MODE != 1 && std::is_same<T, bf16_t>::value) {
+    // The first column tile of every row block also leaves B^T for its 64 rows (the dA product of the fused weight-gradient
+    // kernel and dY . B of the QAT-LoRA layer read B that way): rank x 64 elements, zeros past o up to the leading dimension.
     if (blockIdx.x == 0 && out.bT) {
       const int64_t pblk = (int64_t)blockIdx.y * MQ_ROWS;
-      for (int idx = threadIdx.x; idx < d.r * MQ_ROWS; idx += MQ_THREADS) {
+      for (int idx = threadIdx.x; idx < out.bT_rank * MQ_ROWS; idx += MQ_THREADS) {
         const int k = idx / MQ_ROWS;
         const int64_t p = pblk + idx % MQ_ROWS;
-        if (p < out.ld_wqT) out.bT[(int64_t)k * out.ld_wqT + p] = p < d.o ? B[p * d.r + k] : (bf16_t)0;
+        if (p < out.ld_bT) out.bT[(int64_t)k * out.ld_bT + p] = p < d.o ? B[p * out.bT_rank + k] : (bf16_t)0;
       }
     }
   }
