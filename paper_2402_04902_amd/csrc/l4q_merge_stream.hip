@@ -31,8 +31,8 @@
 //    An infinity or NaN in A or B makes tol one, and nothing passes.  At 4 bits one row block in forty holds such a weight; the
 //    forward form then recomputes up to 8 of them alone from the operands in its registers, everything else repeats the row
 //    block by the stated arithmetic.  Forward 11008 x 4096, rank 16, inside a training step: 51 us (chain, sums through LDS) ->
-//    41; 4096 x 11008 at rank 64 105 -> 55; 4096 x 4096, groups of 64, 20.5 -> 14.4; packing 42 -> 27.  Error sums, which no
-//    single code decides, use the near values throughout: 45 -> 21.
+//    41; 4096 x 11008 at rank 64 105 -> 54; 4096 x 4096, groups of 64, 20.5 -> 13.9; packing 42 -> 26.5.  Error sums, which no
+//    single code decides, use the near values throughout: 45 -> 18.
 //  * Forms that need the quotient itself (backward: the factor; export) do not spend the 11-instruction IEEE expansion per
 //    weight: with the correctly rounded reciprocal r = RN(1 / s) (hardware estimate, one Newton step, then the
 //    choice among the result and its two neighbours by the exact residual 1 - s r),
@@ -58,7 +58,13 @@ namespace {
 
 constexpr int MS_COLS = 256;                     // columns per workgroup: 4 wavefronts x 64
 constexpr int MS_THREADS = 256;
-constexpr int MS_BWD_WAVES = 3;                  // wavefronts per SIMD of the backward form
+// Wavefronts per SIMD, and workgroups per compute unit of the one resident round, of a form.  As few as keep the memory busy: a
+// wavefront starts with a fetch of A and of its first row block that nothing hides, and more registers mean no spills.  us at 4 / 3 /
+// 2: forward 11008 x 4096 42.7 / 41.6 / 42.4, 4096 x 4096 14.1 / 13.9 / 14.1, rank 64 4096 x 11008 - / 56.5 / 53.9; error sums 21.1 /
+// 19.6 / 18.3 (the second launch has half the pairs to add); packing 26.6 / 26.4 / 27.3; initialisation 26.6 / 27.4 (5: 26.4).
+template <int MODE, int ACH> constexpr int ms_waves() {
+  return MODE == 5 ? 4 : MODE == 4 || (MODE == 1 && ACH > 1) ? 2 : 3;
+}
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
@@ -730,10 +736,8 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
 #endif
 }
 
-// Forward and export: 4 workgroups (16 wavefronts) per compute unit, 3 with A of ranks above 16 in registers.  Backward:
-// MS_BWD_WAVES.
 template <int ACH>
-__global__ __launch_bounds__(MS_THREADS) __attribute__((amdgpu_waves_per_eu(ACH <= 1 ? 4 : 3, ACH <= 1 ? 4 : 3)))
+__global__ __launch_bounds__(MS_THREADS) __attribute__((amdgpu_waves_per_eu(ms_waves<1, ACH>(), ms_waves<1, ACH>())))
 void merge_quant_stream_fwd_kernel(LayerDims d, const bf16_t* __restrict__ W0, const bf16_t* __restrict__ A,
                                    const bf16_t* __restrict__ B, const float* __restrict__ scale,
                                    const float* __restrict__ zero, MergeQuantOut<bf16_t> out, int nrb) {
@@ -741,16 +745,16 @@ void merge_quant_stream_fwd_kernel(LayerDims d, const bf16_t* __restrict__ W0, c
   merge_quant_stream_body<1, false, ACH>(d, W0, A, B, scale, zero, out, nrb, lds_all);
 }
 template <bool GAMMA_POW2, int ACH>
-__global__ __launch_bounds__(MS_THREADS) __attribute__((amdgpu_waves_per_eu(MS_BWD_WAVES, MS_BWD_WAVES)))
+__global__ __launch_bounds__(MS_THREADS) __attribute__((amdgpu_waves_per_eu(ms_waves<2, ACH>(), ms_waves<2, ACH>())))
 void merge_quant_stream_bwd_kernel(LayerDims d, const bf16_t* __restrict__ W0, const bf16_t* __restrict__ A,
                                    const bf16_t* __restrict__ B, const float* __restrict__ scale,
                                    const float* __restrict__ zero, MergeQuantOut<bf16_t> out, int nrb) {
   __shared__ __attribute__((aligned(16))) unsigned char lds_all[ms_lds<2>()];
   merge_quant_stream_body<2, GAMMA_POW2, ACH>(d, W0, A, B, scale, zero, out, nrb, lds_all);
 }
-// MODE 3 .. 6: the export, statistics and packing forms, as the forward form 4 workgroups per compute unit
+// MODE 3 .. 6: the export, statistics and packing forms
 template <bool GAMMA_POW2, int MODE, int BITS = 0>
-__global__ __launch_bounds__(MS_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4)))
+__global__ __launch_bounds__(MS_THREADS) __attribute__((amdgpu_waves_per_eu(ms_waves<MODE, 1>(), ms_waves<MODE, 1>())))
 void merge_quant_stream_export_kernel(LayerDims d, const bf16_t* __restrict__ W0, const bf16_t* __restrict__ A,
                                       const bf16_t* __restrict__ B, const float* __restrict__ scale,
                                       const float* __restrict__ zero, MergeQuantOut<bf16_t> out, int nrb) {
@@ -830,13 +834,14 @@ int64_t launch_merge_quant_stream(const LayerDims& d, const bf16_t* W0, const bf
   const int mode = out.wq ? 1 : out.wqT ? 2 : out.errors ? 4 : out.init_scale ? 5 : out.packed ? 6 : 3;
   const int64_t rows = mode == 2 && out.ld_wqT > d.o ? out.ld_wqT : d.o;
   const int nrb = (int)((rows + 31) / 32);
-  // one resident round: 4 (backward: 3) workgroups per compute unit, each wavefront walking a run of row blocks
   const int strips = (int)((d.i + MS_COLS - 1) / MS_COLS);
   const bool wide = d.r > 16 && (mode == 1 || mode == 2);
-  int parts = (mode == 2 ? MS_BWD_WAVES : wide ? 3 : 4) * device_compute_units() / strips;
+  const int waves = mode == 1 ? (d.r == 0 ? ms_waves<1, 0>() : wide ? ms_waves<1, 4>() : ms_waves<1, 1>())
+                  : mode == 2 ? (d.r == 0 ? ms_waves<2, 0>() : ms_waves<2, 1>())
+                  : mode == 4 ? ms_waves<4, 1>() : mode == 5 ? ms_waves<5, 1>() : mode == 6 ? ms_waves<6, 1>() : ms_waves<3, 1>();
+  int parts = waves * device_compute_units() / strips;
   // (two or four times as many, shorter runs, each with its own fetch of A: forward and packing 2 .. 17 % slower, backward the
-  // same at 11008 x 4096, 22 -> 25 us at 4096 x 4096; forward above rank 16, 3 workgroups per unit: 65 -> 60 with two, 63 with four)
-  if (wide && mode == 1) parts *= 2;
+  // same at 11008 x 4096, 22 -> 25 us at 4096 x 4096)
   if (parts < 1) parts = 1;
   if (parts > nrb) parts = nrb;
   dim3 grid((unsigned)(strips * parts));
