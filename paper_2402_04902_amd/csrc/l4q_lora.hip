@@ -117,7 +117,8 @@ template <> struct Row4<bf16_t> {  // (rows are whole 16-byte pieces)
 };
 
 //
-// WHOLE (up to 4 row blocks): a workgroup has 4 waves for each row block, and the blocks' sums, formed as above, are added in
+// WHOLE (up to 2 row blocks; with 4, 1024 threads on a quarter of the workgroups, a 495 x 1568 binary32 step took 68.2 us against
+// 67.3 in two passes): a workgroup has 4 waves for each row block, and the blocks' sums, formed as above, are added in
 // block order as the second pass would add them, scaled and stored: one launch instead of two, the same bits.
 typedef float TnSums[LR_KC][64];
 
@@ -209,9 +210,9 @@ __device__ __forceinline__ void tn_columns(int block, TnSums* sums, const UT* __
 }
 
 template <class S, class UT, bool NR, bool WHOLE>
-__global__ __launch_bounds__(WHOLE ? 1024 : 256) void tn_partial_kernel(const UT* __restrict__ U, const S* __restrict__ Xs, int64_t T,
+__global__ __launch_bounds__(WHOLE ? 512 : 256) void tn_partial_kernel(const UT* __restrict__ U, const S* __restrict__ Xs, int64_t T,
                                                           int64_t n, int r, float* __restrict__ part, float gamma, bool accumulate) {
-  __shared__ __align__(16) TnSums sums[WHOLE ? 16 : 4];
+  __shared__ __align__(16) TnSums sums[WHOLE ? 8 : 4];
   tn_columns<S, UT, NR, WHOLE>((int)blockIdx.x, sums, U, Xs, T, n, r, part, gamma, accumulate);
 }
 
@@ -224,9 +225,9 @@ struct TnJob {
   float* out;  // partial sums, or the result (WHOLE)
 };
 template <bool WHOLE>
-__global__ __launch_bounds__(WHOLE ? 1024 : 256) void tn_pair_kernel(TnJob a, TnJob b, int cols, int64_t T, int r, float gamma,
+__global__ __launch_bounds__(WHOLE ? 512 : 256) void tn_pair_kernel(TnJob a, TnJob b, int cols, int64_t T, int r, float gamma,
                                                                      bool accumulate) {
-  __shared__ __align__(16) TnSums sums[WHOLE ? 16 : 4];
+  __shared__ __align__(16) TnSums sums[WHOLE ? 8 : 4];
   if ((int)blockIdx.x < cols)
     tn_columns<bf16_t, float, false, WHOLE>((int)blockIdx.x, sums, a.U, a.Xs, T, a.n, r, a.out, gamma, accumulate);
   else
@@ -253,7 +254,7 @@ void launch_tn(const UT* U, const S* Xs, int64_t T, int64_t n, int r, bool out_n
 #define L4Q_TN(NR, WHOLE, GRID, THREADS, OUT) \
   hipLaunchKernelGGL((tn_partial_kernel<S, UT, NR, WHOLE>), GRID, dim3(THREADS), 0, stream, U, Xs, T, n, r, OUT, gamma, accumulate)
   const unsigned cols = (unsigned)((n + 63) / 64);
-  if (nb <= 4) {
+  if (nb <= 2) {
     if (out_n_by_r) L4Q_TN(true, true, dim3(cols), (unsigned)(256 * nb), out);
     else L4Q_TN(false, true, dim3(cols), (unsigned)(256 * nb), out);
     return;
@@ -268,7 +269,7 @@ void launch_tn_pair(const float* Ua, const bf16_t* Xa, int64_t na, float* outa, 
                     int64_t nb, float* outb, float* partb, int64_t T, int r, float gamma, bool accumulate, hipStream_t stream) {
   const int64_t blocks = lora_tn_blocks(T);
   const int cols = (int)((na + 63) / 64), all = cols + (int)((nb + 63) / 64);
-  if (blocks <= 4) {
+  if (blocks <= 2) {
     hipLaunchKernelGGL(tn_pair_kernel<true>, dim3((unsigned)all), dim3((unsigned)(256 * blocks)), 0, stream, TnJob{Ua, Xa, na, outa},
                        TnJob{Ub, Xb, nb, outb}, cols, T, r, gamma, accumulate);
     return;

@@ -55,6 +55,7 @@ struct Prefill {
   static constexpr int PPR = SEC * BITS / 128;         // 16-byte pieces of a weight row's section
   static constexpr int X_TOTAL = BM * SEC * 2 / 1024;  // loads of X per section, and per wave (the last ones of nothing)
   static constexpr int X_INSTR = (X_TOTAL + 2 * WN - 1) / (2 * WN);
+  static constexpr bool X_EVEN = X_INSTR * 2 * WN == X_TOTAL;
   static constexpr int W_INSTR = (BN * PPR + NT - 1) / NT;
   static constexpr int LOADS = X_INSTR + W_INSTR;
   static constexpr int X_BYTES = BM * SEC * 2;
@@ -63,7 +64,7 @@ struct Prefill {
   static constexpr int SX = RING * SLOT;               // [4 sections][BM tokens][8 partial sums]
   static constexpr int EP_ROW = 32 * TN * 2 + 16;      // bytes of a token's row in a wave's output block
   static constexpr int IDLE = SX + 4 * BM * 32;        // where loads of nothing go
-  static constexpr int LDS = IDLE + (X_INSTR * 2 * WN > X_TOTAL ? 1024 : 0);
+  static constexpr int LDS = IDLE + (X_EVEN ? 0 : 1024);
   static_assert(SEC * BITS % 128 == 0, "a row's section is whole 16-byte pieces");
   static_assert(2 * WN * 32 * TM * EP_ROW <= SX, "the output blocks take the ring's place");
   static_assert(LDS <= 160 * 1024, "LDS");
@@ -105,7 +106,7 @@ __global__ __launch_bounds__(P::NT) void qgemm_prefill_kernel(const bf16_t* __re
   for (int c = 0; c < P::X_INSTR; ++c) {  // instruction q of the slot: 8 token rows of sub-stage q / (BM / 8)
     const int q = wave * P::X_INSTR + c, jj = q / (P::BM / 8), row = (q % (P::BM / 8)) * 8 + (lane >> 3);
     const int ch = (lane & 7) ^ ((row >> 1) & 7);
-    voffX[c] = t0 + row < T && q < P::X_TOTAL ? (unsigned)(((t0 + row) * i + jj * 64 + ch * 8) * 2) : gemm::OOB_OFFSET;
+    voffX[c] = t0 + row < T && (P::X_EVEN || q < P::X_TOTAL) ? (unsigned)(((t0 + row) * i + jj * 64 + ch * 8) * 2) : gemm::OOB_OFFSET;
   }
 #pragma unroll
   for (int c = 0; c < P::W_INSTR; ++c) {
@@ -118,7 +119,7 @@ __global__ __launch_bounds__(P::NT) void qgemm_prefill_kernel(const bf16_t* __re
     unsigned char* base = plds + slot * P::SLOT;
     if constexpr (c < P::X_INSTR) {
       const unsigned kx = sec < nsec ? (unsigned)sec * (SEC * 2) : gemm::PAST_END_OFFSET;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsX, (gemm::lds_ptr_t)(wave * P::X_INSTR + c < P::X_TOTAL ? base + (wave * P::X_INSTR + c) * 1024
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsX, (gemm::lds_ptr_t)(P::X_EVEN || wave * P::X_INSTR + c < P::X_TOTAL ? base + (wave * P::X_INSTR + c) * 1024
                                                                                               : plds + P::IDLE), 16,
                                                voffX[c] + kx, 0, 0, 0);
     } else {
@@ -224,7 +225,9 @@ __global__ __launch_bounds__(P::NT) void qgemm_prefill_kernel(const bf16_t* __re
       }
     };
     const bf16x2_t ones = __builtin_bit_cast(bf16x2_t, 0x3F803F80u);
-    constexpr int VALU_PER = TN == 1 ? 8 / TM : 6;  // (8 TN conversions a step, sums of X; 6 where 4 took 73 us for 70)
+    // vector ops dealt to a matrix op: 4 bits 8 TN conversions a step and sums of X (128 x 256 tiles 6: 70 us, 4: 73); the other
+    // widths convert in 12 to 16
+    constexpr int VALU_PER = BITS == 4 ? (TN == 1 ? 8 / TM : 6) : P::WN == 6 ? 4 : (TM * 4 + TN * 8 + TM * TN - 1) / (TM * TN);
     bf16x8_t xr[3][TM], wf[2][TN], xq[TM];
     float part[TM];
     f32x16_t tw[TM][TN];
@@ -269,7 +272,7 @@ __global__ __launch_bounds__(P::NT) void qgemm_prefill_kernel(const bf16_t* __re
         }
       }
       if constexpr (ks < NJ) {
-        const int kq = (wn & 3) * NJ + ks;  // (waves past the fourth: as the first ones, and not stored)
+        const int kq = (P::WN == 4 ? wn : wn & 3) * NJ + ks;  // (waves past the fourth: as the first ones, and not stored)
 #pragma unroll
         for (int a = 0; a < TM; ++a)
           xq[a] = *reinterpret_cast<const bf16x8_t*>(xrow[a] + (kq >> 2) * (P::BM * 128) + (((4 * h + (kq & 3)) ^ xsw[a]) << 4));
@@ -289,7 +292,7 @@ __global__ __launch_bounds__(P::NT) void qgemm_prefill_kernel(const bf16_t* __re
         if (q == 0) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
       }
     });
-    if (wn < 4) {
+    if (P::WN == 4 || wn < 4) {
 #pragma unroll
       for (int a = 0; a < TM; ++a) sx[(j * P::BM + (wm * TM + a) * 32 + l32) * 8 + 2 * wn + h] = part[a];
     }

@@ -17,11 +17,11 @@ pytestmark = pytest.mark.gpu
     (127, 1032, 1048, 24, 8, DTYPE_BF16),
     (255, 320, 136, 70, 64, DTYPE_BF16),
     (300, 576, 264, 200, 64, DTYPE_BF16),   # dA and dB apart: three row blocks of rank 200 do not fit the weight gradient's place
-    (511, 264, 72, 17, 8, DTYPE_BF16),      # both in one launch, four row blocks added there (the general merge pass leaves B^T)
-    (513, 264, 136, 17, 8, DTYPE_BF16),     # five row blocks: a second pass for both
+    (256, 264, 72, 17, 8, DTYPE_BF16),      # both in one launch, two row blocks added there (the general merge pass leaves B^T)
+    (257, 264, 136, 17, 8, DTYPE_BF16),     # three row blocks: a second pass for both
     (641, 352, 1000, 48, 32, DTYPE_BF16),   # ... (the streaming pass leaves B^T), columns that end inside 64 in both
-    (512, 68, 67, 20, 4, DTYPE_F32),        # four row blocks
-    (513, 68, 3, 20, 4, DTYPE_F32),
+    (256, 68, 67, 20, 4, DTYPE_F32),        # two row blocks, and one
+    (257, 68, 3, 20, 4, DTYPE_F32),
     (1, 4, 1, 1, 4, DTYPE_F32),
     (129, 68, 3, 17, 4, DTYPE_F32),
     (257, 132, 67, 33, 4, DTYPE_F32),
