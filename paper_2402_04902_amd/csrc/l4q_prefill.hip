@@ -3,7 +3,7 @@
 // Bound: the matrix cores, with the vector unit close behind (the codes are turned into operands where they are used, and
 // the affine part of every section of k is applied to its sums): per section of a 128 x 256 tile a wave has 1152 cycles of
 // matrix ops and 950 of vector ops.  The decode kernels read and convert the whole weight once per 64 tokens: 8 passes of
-// 27 us at 512 tokens on [11008 x 4096]; this kernel takes 58 us.  A workgroup of 8 waves (2 x 4, two per SIMD; for 192 rows
+// 27 us at 512 tokens on [11008 x 4096]; this kernel takes 56 us.  A workgroup of 8 waves (2 x 4, two per SIMD; for 192 rows
 // 2 x 6, three) owns a tile of 64 TM tokens x 32 WN TN weight rows, so a converted code is used for 32 TM tokens of a wave and the weight is read once per
 // tile row.  Arithmetic as in the decode kernels: the matrix cores multiply X with the exact integers w~ + K0, and
 //   sum_k X (w~ s + b) = s sum_k X (w~ + K0) + (b - K0 s) sum_k X   per section of SEC k-values (128, or groups of 64),
