@@ -32,7 +32,7 @@
 //    forward form then recomputes up to 8 of them alone from the operands in its registers, everything else repeats the row
 //    block by the stated arithmetic.  Forward 11008 x 4096, rank 16, inside a training step: 51 us (chain, sums through LDS) ->
 //    41; 4096 x 11008 at rank 64 105 -> 54; 4096 x 4096, groups of 64, 20.5 -> 13.9; packing 42 -> 26.5.  Error sums, which no
-//    single code decides, use the near values throughout: 45 -> 18.
+//    single code decides, use the near values (but where a quotient overflows): 45 -> 18.
 //  * Forms that need the quotient itself (backward: the factor; export) do not spend the 11-instruction IEEE expansion per
 //    weight: with the correctly rounded reciprocal r = RN(1 / s) (hardware estimate, one Newton step, then the
 //    choice among the result and its two neighbours by the exact residual 1 - s r),
@@ -563,6 +563,8 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
       if constexpr (MODE == 4) {
         eq *= s;
         ec *= s;
+        // a quotient has overflowed, W / s or b / s alone, where the errors themselves need not: the stated form
+        if (!exact) exact = __builtin_amdgcn_ballot_w64(row_ok & col_ok & !(eq + ec < __builtin_huge_valf())) != 0;
       }
       if constexpr (CHECKED) {
         // within tol of a tie the near quotient does not settle the code (see the top of the file)

@@ -79,6 +79,35 @@ def test_error_sums(i, o, r, g, dtype):
     assert np.array_equal(e[:2], e[4:6])
 
 
+@pytest.mark.parametrize("what", ["weight", "zero", "both"])
+@pytest.mark.parametrize("i,o,r,g", [(96, 40, 16, 32), (512, 72, 64, 128)])
+def test_error_sums_beyond_the_quotients_range(i, o, r, g, what):
+    """W / s or zero / s past the largest binary32 number, with the scale inside the reciprocal's range: the errors are
+    finite, of the size of W or zero."""
+    import torch
+    from oracle import l4q_oracle as O
+    from paper_2402_04902_amd import binding
+    spec = LayerSpec(f"err_range_{what}_{o}x{i}_r{r}", 8, i, o, r, 2.0 * r, 4, g, DTYPE_BF16)
+    print("case", spec.name, flush=True)
+    arrs = inputs.make_layer_inputs(spec, seed=i)
+    s, b = host_qparams(spec, arrs, "asymm", 0.7)
+    s[5, 1] = 2.0 ** -50
+    W0 = np.asarray(arrs["W0"]).copy()
+    if what != "zero":
+        W0[5, g + 3], W0[5, g + 9] = 2.0 ** 100, -(2.0 ** 101)
+    if what != "weight":
+        b[5, 1] = 2.0 ** 100
+    arrs["W0"] = W0
+    layer = binding.upload(spec, arrs, s, b)
+    errors = torch.zeros(4, dtype=torch.float32, device=layer.W0.device)
+    ws = torch.zeros(o * ((i + 255) // 256) * 8, dtype=torch.uint8, device=layer.W0.device)
+    binding.l4q_quant_errors(layer.desc, layer.W0, layer.A, layer.B, layer.scale, layer.zero, errors, ws)
+    torch.cuda.synchronize()
+    Wc = O.merge(arrs["W0"], arrs["A"], arrs["B"], spec.alpha)
+    want = np.array([O.quantization_error(Wc, s, b, 4, g), O.clipping_error(Wc, s, b, 4, g)])
+    assert np.allclose(errors[:2].cpu().numpy(), want, rtol=1e-5, atol=0), (errors, want)
+
+
 @pytest.mark.parametrize("method", [0, 1, 2])
 @pytest.mark.parametrize("i,o,g", [(96, 40, 32), (320, 40, 64), (768, 40, 256)])
 def test_init_with_nan(method, i, o, g):
