@@ -22,10 +22,13 @@
 //    exact, binary32 accumulation in the hardware's own order), and near quotients x (1/s), and settle what they cannot
 //    decide: a code is that of the stated arithmetic unless the near quotient w' lies within `tol` of a tie k + 1/2.
 //      tol = |gamma| D / s + 4 u |b| / s + 8 u R,   u = 2^-24, R = 2^(n-1) + 1 >= |w| wherever the code is not clear of the grid.
-//      D bounds the difference of the two sums: (r - 1) u S for the stated one (S = sum_k |B[p,k] A[k,j]|, products exact), and
-//      16 u S for each of the r / 16 matrix ops (17 terms cut to the largest one's 24 bits; measured on 12 M sums of 64 products
-//      with exponents up to 60 apart and nearly cancelling pairs: 7 u S for four ops): together below (2 r + 2) u S,
-//      S <= max |A| of the wavefront's columns x sum_k |B[p,k]|.
+//      D = 4 r u S bounds the difference of the two sums, S = sum_k |B[p,k] A[k,j]| <= max |A| of the wavefront's columns x
+//      sum_k |B[p,k]|.  The stated sum is (r - 1) u S off at most (products exact).  A matrix op adds in an order and width of
+//      its own; taken for granted is that it forms exact products and adds them to the accumulator in steps of 4 or more, a
+//      step's terms aligned to the largest and cut to 24 bits or more, below 2 u S lost of each, the step's result rounded or
+//      cut, 2 u S more: 2 r u S, and 2 u S for each of at most r / 4 steps (+ 2 where half of the last op's products are zeros).
+//      Measured: 7.8 u S at ranks 8 to 32, 15.6 at 64, 63 at 256, one large product beside others just below its last place; on
+//      random ones 1 to 4 u S, 11 at rank 256 with exponents 60 apart.  Subnormal factors are not lost.
 //      The rest: Wc is rounded once on either side (u |Wc| each, |Wc| <= |b| + R s), the stated x and w once (u R each); near: 1 / s
 //      to one unit, 2 u, which multiplies Wc - b as a whole (2 u R), b / s rounded (u |b| / s), the sum rounded (u R).
 //    An infinity or NaN in A or B makes tol one, and nothing passes.  At 4 bits one row block in forty holds such a weight; the
@@ -278,8 +281,8 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
       for (int k = 0; k < 8; ++k) apk[8 * c + k] = araw[2 * k] | (araw[2 * k + 1] << 16);
     }
   }
-  // CHECKED: what |sums' difference| / sum_k |B[p,k]| can come to, as a multiple of gamma max |A| of the wavefront's columns
-  float sum_tol = 0.f;
+  [[maybe_unused]] const float sum_tol = fabsf(d.gamma) * (float)r * 0x1p-22f;  // CHECKED: |gamma| D / S
+  float top_a = 0.f;                                                            // max |A| of the wavefront's columns
   if constexpr (CHECKED && ACH > 0) {
     typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
     u16x2 m = {0, 0};
@@ -304,7 +307,7 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
       const uint32_t v = (uint32_t)__builtin_amdgcn_readlane((int)w, 16 * q);
       top = top > v ? top : v;
     }
-    sum_tol = fabsf(d.gamma) * (float)(r + 2) * 0x1p-23f * __uint_as_float(top << 16);
+    top_a = __uint_as_float(top << 16);
   }
 
   auto odd_even = [](uint32_t v, int k) { return __uint_as_float(k & 1 ? v & 0xFFFF0000u : v << 16); };
@@ -364,7 +367,7 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
     // ---- rank sums
     f32x16_t near[2];  // FILTER: near[b][e] of column 16 b + e
     f32x32_t sum;
-    float bsum = 0.f;
+    float bsum = 0x1p-118f;  // CHECKED: sum_k |B[p,k]| of this lane's k; above what subnormal ones come to, which the op drops
     if constexpr (FILTER) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) near[0][e] = near[1][e] = 0.f;
@@ -569,7 +572,7 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
       if constexpr (CHECKED) {
         // within tol of a tie the near quotient does not settle the code (see the top of the file)
         bsum = ACH > 0 ? half_sum(bsum) : 0.f;
-        const float tol = fmaf(rc, fmaf(sum_tol, bsum, 0x1p-22f * fabsf(b)), 0x1p-21f * (1.f - d.qn));
+        const float tol = fmaf(rc, fmaf(top_a * bsum, sum_tol, 0x1p-22f * fabsf(b)), 0x1p-21f * (1.f - d.qn));
         const float edge = 0.5f - tol;
         const bool unsettled = row_ok & col_ok & !(off < edge);
         if (!exact && __builtin_amdgcn_ballot_w64(unsettled) != 0) {

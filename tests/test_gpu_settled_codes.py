@@ -71,3 +71,32 @@ def test_infinite_factor():
     got = packed_on_gpu(spec, layer).cpu().numpy().view(np.uint32)
     torch.cuda.synchronize()
     assert np.array_equal(got, O.pack_codes(dec.codes, bits))
+
+
+@pytest.mark.parametrize("where,value", [("A", np.inf), ("B", -np.inf), ("B", np.nan)])
+@pytest.mark.parametrize("r", [8, 16, 24, 64])
+def test_weights_beside_a_nonfinite_factor(r, where, value):
+    """The weights whose sums are finite, in the row block of one whose sum is not: forward and packing."""
+    import torch
+    from paper_2402_04902_amd import binding
+    i, o, g, bits = 256, 72, 64, 4
+    spec = LayerSpec(f"beside_r{r}_{where}{value}", 8, i, o, r, 2.0 * r, bits, g, DTYPE_BF16)
+    print("case", spec.name, flush=True)
+    arrs = inputs.make_layer_inputs(spec, seed=r)
+    v = np.asarray(arrs[where]).copy()
+    v[3, 7] = value  # (a column of the weight, or a row)
+    arrs[where] = v
+    s, b = np.full((o, i // g), 0.01, np.float32), np.full((o, i // g), 0.002, np.float32)
+    layer = binding.upload(spec, arrs, s, b)
+    with np.errstate(invalid="ignore"):
+        dec, Wc, _ = O.decide_f32(arrs["W0"], arrs["A"], arrs["B"], s, b, bits, g, spec.alpha)
+    finite = np.isfinite(Wc)
+    assert finite.sum() >= o * i - max(o, i)
+    got = O.unpack_codes(packed_on_gpu(spec, layer).cpu().numpy().view(np.uint32), bits, i)
+    assert np.array_equal(got[finite], dec.codes[finite])
+    layer.forward()
+    torch.cuda.synchronize()
+    wq = layer.ws[: o * i * 2].view(torch.int16).reshape(i // 32, o, 32).cpu().numpy().view(np.uint16)
+    wq = np.ascontiguousarray(wq.transpose(1, 0, 2)).reshape(o, i)
+    want = (dec.codes.astype(np.float64) * np.float64(s[0, 0]) + np.float64(b[0, 0])).astype(np.float32)
+    assert np.array_equal(wq[finite], inputs.bf16_bits(inputs.round_to_bf16(want))[finite])
