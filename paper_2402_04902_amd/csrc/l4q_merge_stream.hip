@@ -29,13 +29,24 @@
 //      cut, 2 u S more: 2 r u S, and 2 u S for each of at most r / 4 steps (+ 2 where half of the last op's products are zeros).
 //      Measured: 7.8 u S at ranks 8 to 32, 15.6 at 64, 63 at 256, one large product beside others just below its last place; on
 //      random ones 1 to 4 u S, 11 at rank 256 with exponents 60 apart.  Subnormal factors are not lost.
-//      The rest: Wc is rounded once on either side (u |Wc| each, |Wc| <= |b| + R s), the stated x and w once (u R each); near: 1 / s
-//      to one unit, 2 u, which multiplies Wc - b as a whole (2 u R), b / s rounded (u |b| / s), the sum rounded (u R).
-//    An infinity or NaN in A or B makes tol one, and nothing passes.  At 4 bits one row block in forty holds such a weight; the
-//    forward form then recomputes up to 8 of them alone from the operands in its registers, everything else repeats the row
-//    block by the stated arithmetic.  Forward 11008 x 4096, rank 16, inside a training step: 51 us (chain, sums through LDS) ->
-//    41; 4096 x 11008 at rank 64 105 -> 54; 4096 x 4096, groups of 64, 20.5 -> 13.9; packing 42 -> 26.5.  Error sums, which no
-//    single code decides, use the near values (but where a quotient overflows): 45 -> 18.
+//      The rest: Wc is rounded once on either side (u |Wc| each, |Wc| <= |b| + R s), gamma acc where gamma is no power of two (in
+//      D), the stated x and w once (u R each); near: 1 / s, which multiplies Wc - b as a whole (u R), b / s (u |b| / s), the sum
+//      (u R): 3 u |b| / s + 6 u R.
+//    An infinity or NaN in A or B makes tol one, and nothing passes.  What is undecided depends on the layer's state.  In the
+//    middle of a run (B moved, scales no simple fractions of the weights) 2 % of the row blocks hold such a weight at 4 bits,
+//    24 % at 8 (counted, groups of 128).  At the start, B = 0 and min / max scales of bfloat16 weights, 2 to 7 weights of a row
+//    block, and some in 80 to 99 % of them, lie exactly on ties; but sums of nothing are not near, they are the stated ones, so a row block whose rows of B are all
+//    zero (or whose A is) takes W0 and the stated quotient and leaves nothing undecided, as the layers without a rank term do.
+//    Undecided weights are settled by the stated sum, one of every lane at a time, from the operands in registers (ranks above
+//    what they hold: from memory); a row block with more than 3 in a lane is repeated by the stated arithmetic, and
+//    the next 3 go there directly.  (Most in a lane 1 / 3 / 8, packing 11008 x 4096: 16 a row block 61 / 48 / 48 us, 128 61 / 61 /
+//    69; A in memory, rank 64: 120 / 122 / 124, 124 / 123 / 293.  Every weight on a tie: 61, going there directly 48.)
+//    us, weights from HBM; chain with sums through LDS / here: forward 11008 x 4096, rank 16, in the middle of a run 46 / 37, at
+//    the start 46 / 37, 8 bits 45 / 39; 4096 x 11008 at rank 64 100 / 50; 4096 x 4096, groups of 64, 20.4 / 14.0; packing
+//    11008 x 4096 49 / 32, at the start 47 / 32, 8 bits 45 / 39.  (Every undecided row block repeated, ties of the start
+//    included: forward 86 at the start, packing 63 and at 8 bits 50.)  Slower than the chain, 0.7 to 0.9 times: weights held on
+//    ties by a B that is not zero but too small to move them.
+//    Error sums, which no single code decides, use the near values (but where a quotient overflows): 45 / 18.
 //  * Forms that need the quotient itself (backward: the factor; export) do not spend the 11-instruction IEEE expansion per
 //    weight: with the correctly rounded reciprocal r = RN(1 / s) (hardware estimate, one Newton step, then the
 //    choice among the result and its two neighbours by the exact residual 1 - s r),
@@ -347,6 +358,7 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
   uint32_t no_bits = 0;
   asm volatile("" : "+s"(no_bits));
   int rb = rb_begin;
+  [[maybe_unused]] int direct = 0;  // CHECKED: row blocks ahead that go straight to the stated sums
   do {  // (no partition is empty)
     const int p0 = rb * 32, p = p0 + l32;
     const bool row_ok = p < o;
@@ -368,6 +380,7 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
     f32x16_t near[2];  // FILTER: near[b][e] of column 16 b + e
     f32x32_t sum;
     float bsum = 0x1p-118f;  // CHECKED: sum_k |B[p,k]| of this lane's k; above what subnormal ones come to, which the op drops
+    uint32_t bany = 0;       // CHECKED: any bit of their magnitudes
     if constexpr (FILTER) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) near[0][e] = near[1][e] = 0.f;
@@ -385,6 +398,7 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
             const uint32_t pair = bq[q] & 0x7FFF7FFFu;
             bsum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, pair),
                                                    __builtin_bit_cast(bf16x2_t, 0x3F803F80u), bsum, false);
+            bany |= pair;
           }
         }
       };
@@ -405,13 +419,18 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
       chain_rest(sum, p, row_ok, 16 * ACH);
     }
 
-    // ---- this lane's group: s, b, 1 / s (RN(1 / s) unless the codes are checked), 1024 s
+    // ---- this lane's group: s, b, RN(1 / s), 1024 s
     // (by an op, into registers of their own, so that the next row block's can be fetched into F's: otherwise the loop ends in
     // copies that wait for that fetch)
     const float s = __uint_as_float(__float_as_uint(F.s) ^ no_bits), b = __uint_as_float(__float_as_uint(F.z) ^ no_bits);
+    [[maybe_unused]] u32x4 b_now[ACH > 0 ? ACH : 1];
+    if constexpr (CHECKED) {
+#pragma unroll
+      for (int c = 0; c < ACH; ++c) b_now[c] = F.b[c] ^ no_bits;
+    }
     const bool bad_scale = MODE != 5 && row_ok && col_ok && !scale_in_fast_range(s);
     const bool slow = __builtin_amdgcn_ballot_w64(bad_scale) != 0;  // wave-uniform
-    float rc = MODE == 5 ? 0.f : CHECKED ? __builtin_amdgcn_rcpf(s) : exact_reciprocal(s);
+    const float rc = MODE == 5 ? 0.f : exact_reciprocal(s);
     const float hi = s * 1024.f;
     const float nbr = -(b * rc);                                   // FILTER
     if constexpr (!FILTER) request_weights(rb + 1);  // (not before the rank sums: they need the registers)
@@ -424,9 +443,9 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
     const uint32_t row_mask = row_ok ? 0xFFFFFFFFu : 0u;                        // MODE 2: zeros below the last row
     u32x4 code8[2], mask8[2], wc4;                                              // MODE 3
     if (MODE == 3) lds_order();  // (its binary32 tile takes the place of the weights)
-    float off = 0.f;                                                            // CHECKED: largest |w - code| inside the grid
+    float off[4] = {};                                                          // CHECKED: largest |w - code| of 8 columns
     // Merged weights and quotients of columns 8 c .. 8 c + 7.  FORM 0: the stated sums, IEEE divide; 1: the stated sums, quotient
-    // by the reciprocal; 2: near sums and quotients.
+    // by the reciprocal; 2: near sums and quotients; 3: no rank term, quotient by the reciprocal.
     auto stream_columns = [&](auto form_tag) {
       constexpr int FORM = decltype(form_tag)::value;
 #pragma unroll
@@ -438,7 +457,7 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
           const int n = 8 * c + e;
           const float wv = odd_even(w0[c][e >> 1], e);
           float wc;
-          if constexpr (ACH == 0) wc = wv + 0.f;  // (as W0 + gamma 0: a weight of -0 becomes +0)
+          if constexpr (ACH == 0 || FORM == 3) wc = wv + 0.f;  // (as W0 + gamma 0: a weight of -0 becomes +0)
           else if constexpr (FORM == 2) wc = fmaf(d.gamma, near[n / 16][n % 16], wv);
           else wc = GAMMA_POW2 ? fmaf(d.gamma, sum[n], wv) : wv + d.gamma * sum[n];
           if constexpr (MODE == 5) {
@@ -447,14 +466,14 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
             continue;
           }
           const float x = wc - b;
-          const float w = FORM == 2 ? fmaf(wc, rc, nbr) : FORM == 1 ? fast_quotient(x, s, rc, hi) : __fdiv_rn(x, s);
+          const float w = FORM == 2 ? fmaf(wc, rc, nbr) : FORM == 0 ? __fdiv_rn(x, s) : fast_quotient(x, s, rc, hi);
           const float cl = __builtin_amdgcn_fmed3f(w, d.qn, d.qp);
           if constexpr (MODE == 6) {
             // cl + 1.5 2^23 rounds to an integer, ties to even, whose low bits are 0x4B400000 + code; field u = code - Q_N
             constexpr uint32_t C = (1u << (BITS - 1)) - 0x4B400000u;
             const float tf = cl + 12582912.f;
             const uint32_t t = __float_as_uint(tf);
-            if (FORM == 2) off = fmaxf(off, fabsf(cl - (tf - 12582912.f)));
+            if (FORM == 2 && ACH > 0) off[c] = fmaxf(off[c], fabsf(cl - (tf - 12582912.f)));
             const int at = BITS * n, k = at / 32, sh = at % 32;
             if (n == 0) {
 #pragma unroll
@@ -469,7 +488,7 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
             continue;
           }
           const float code = rintf(cl);
-          if (CHECKED && FORM == 2) off = fmaxf(off, fabsf(cl - code));
+          if (CHECKED && FORM == 2 && ACH > 0) off[c] = fmaxf(off[c], fabsf(cl - code));
           if (MODE == 1 || MODE == 2) wq[e] = fmaf(code, s, b);
           if (MODE == 4) {
             if (FORM == 2) {  // (in units of s)
@@ -515,70 +534,109 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
         }
       }
     };
-    // MODE 1: the elements of these lanes within reach of a tie, one after the other, by the stated arithmetic.  False (and
-    // nothing relied on) if they are many.
+    // CHECKED: the elements of these lanes within reach of a tie by the stated arithmetic, one of every lane at a time: from
+    // registers alone where they hold all of A (a fetch waits for everything the wavefront has in flight: 8 bits, packing
+    // 44.6 us against 38.8).  False (and nothing relied on) where a lane has many.
     auto settle = [&](bool unsettled, float edge) {
       uint32_t mine = 0;
 #pragma unroll
-      for (int n = 0; n < 32; ++n) {
-        const float wv = odd_even(w0[n / 8][n % 8 / 2], n);
-        const float wc = ACH == 0 ? wv + 0.f : fmaf(d.gamma, near[n / 16][n % 16], wv);
-        const float cl = __builtin_amdgcn_fmed3f(fmaf(wc, rc, nbr), d.qn, d.qp);
-        mine |= !(fabsf(cl - rintf(cl)) < edge) ? 1u << n : 0u;
-      }
-      if (!unsettled) mine = 0;
-      u32x4 bq[ACH > 0 ? ACH : 1];
+      for (int c = 0; c < 4; ++c) {
+        if (__builtin_amdgcn_ballot_w64(unsettled && !(off[c] < edge)) == 0) continue;
 #pragma unroll
-      for (int c = 0; c < ACH; ++c) bq[c] = load_b(p, row_ok, 16 * c);
-      auto lane_of = [](uint32_t v, int l) { return (uint32_t)__builtin_amdgcn_readlane((int)v, l); };
-      for (int count = 0;; ++count) {
-        const uint64_t todo = __builtin_amdgcn_ballot_w64(mine != 0);
-        if (todo == 0) return true;
-        if (count == 8) return false;
-        const int at = __builtin_ctzll(todo), n = __builtin_ctz(lane_of(mine, at));  // (uniform from here on)
-        const int am = 8 * (n % 16 / 4) + 4 * (at >> 5) + n % 4;  // the M index of its column, in column block n / 16
-        float acc = 0.f;
-#pragma unroll
-        for (int c = 0; c < ACH; ++c)
-#pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            const int q = e % 8 / 2, side = e / 8 * 32;
-            const uint32_t av = n < 16 ? apk[8 * c + q] : apk[8 * c + 4 + q];
-            acc = fmaf(odd_even(lane_of(bq[c][q], (at & 31) + side), e), odd_even(lane_of(av, am + side), e), acc);
-          }
-        uint32_t wpair = w0[0][0];
-#pragma unroll
-        for (int q = 1; q < 16; ++q) wpair = n / 2 == q ? w0[q / 4][q % 4] : wpair;
-        wpair = lane_of(wpair, at);
-        const float wv = n & 1 ? odd_even(wpair, 1) : odd_even(wpair, 0);
-        const float sv = __uint_as_float(lane_of(__float_as_uint(s), at)), bv = __uint_as_float(lane_of(__float_as_uint(b), at));
-        const float wc = ACH == 0 ? wv + 0.f : wv + d.gamma * acc;
-        const float code = rintf(__builtin_amdgcn_fmed3f(__fdiv_rn(wc - bv, sv), d.qn, d.qp));
-        if (lane == at) {
-          *reinterpret_cast<bf16_t*>(lds_all + ((row_base ^ (16 * (n / 8))) + 2 * (n % 8))) = f32_to_bf16(fmaf(code, sv, bv));
-          mine &= mine - 1;
+        for (int n = 8 * c; n < 8 * c + 8; ++n) {
+          const float wc = fmaf(d.gamma, near[n / 16][n % 16], odd_even(w0[n / 8][n % 8 / 2], n));
+          const float cl = __builtin_amdgcn_fmed3f(fmaf(wc, rc, nbr), d.qn, d.qp);
+          mine |= !(fabsf(cl - rintf(cl)) < edge) ? 1u << n : 0u;
         }
       }
+      if (!unsettled) mine = 0;
+      if (__builtin_amdgcn_ballot_w64(__builtin_popcount(mine) > 3) != 0) return false;
+      while (__builtin_amdgcn_ballot_w64(mine != 0) != 0) {
+        const bool live = mine != 0;
+        const int n = live ? __builtin_ctz(mine) : 0;
+        float acc = 0.f;
+        if (r <= 16 * ACH) {
+          const int from = 4 * (8 * (n % 16 / 4) + 4 * h + n % 4);  // the lane of its column's M index, times 4
+#pragma unroll
+          for (int c = 0; c < ACH; ++c) {
+            uint32_t bw[8], aw[8];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const uint2 v = both_halves(b_now[c][q]);
+              bw[q] = v.x;
+              bw[4 + q] = v.y;
+#pragma unroll
+              for (int side = 0; side < 2; ++side) {
+                const int lo16 = __builtin_amdgcn_ds_bpermute(from + 128 * side, (int)apk[8 * c + q]);
+                const int hi16 = __builtin_amdgcn_ds_bpermute(from + 128 * side, (int)apk[8 * c + 4 + q]);
+                aw[4 * side + q] = (uint32_t)(n < 16 ? lo16 : hi16);
+              }
+            }
+#pragma unroll
+            for (int k = 0; k < 16; ++k) acc = fmaf(odd_even(bw[k / 2], k), odd_even(aw[k / 2], k), acc);
+          }
+        } else {
+          for (int k0 = 0; k0 < r; k0 += 8) {
+            const u32x4 bq = __builtin_amdgcn_raw_buffer_load_b128(rsB, (int)(live ? (unsigned)((p * r + k0) * 2) : OOB), 0, 0);
+            uint32_t av[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+              av[k] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rsA, (int)(live ? (unsigned)((jl + n) * 2) : OOB), (k0 + k) * i * 2, 0);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) acc = fmaf(odd_even(bq[k / 2], k), odd_even(av[k], 0), acc);
+          }
+        }
+        uint32_t pick[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) pick[q] = w0[q / 4][q % 4];
+#pragma unroll
+        for (int half = 8; half > 0; half /= 2)
+#pragma unroll
+          for (int q = 0; q < half; ++q) pick[q] = n & (2 * half) ? pick[q + half] : pick[q];
+        const float wv = __uint_as_float(n & 1 ? pick[0] & 0xFFFF0000u : pick[0] << 16);
+        const float code = rintf(__builtin_amdgcn_fmed3f(fast_quotient(wv + d.gamma * acc - b, s, rc, hi), d.qn, d.qp));
+        if constexpr (MODE == 1) {
+          if (live) *reinterpret_cast<bf16_t*>(lds_all + ((row_base ^ (16 * (n / 8))) + 2 * (n % 8))) = f32_to_bf16(fmaf(code, s, b));
+        }
+        if constexpr (MODE == 6) {
+          const uint64_t field = live ? (uint64_t)((1u << BITS) - 1u) << (BITS * n % 32) : 0;
+          const uint64_t u = (uint64_t)(uint32_t)((int)code + (1 << (BITS - 1))) << (BITS * n % 32);
+          const int k = BITS * n / 32;
+#pragma unroll
+          for (int q = 0; q < BITS; ++q) {
+            const uint32_t f = q == k ? (uint32_t)field : q == k + 1 ? (uint32_t)(field >> 32) : 0u;
+            words[q] = (words[q] & ~f) | ((q == k ? (uint32_t)u : (uint32_t)(u >> 32)) & f);
+          }
+        }
+        mine &= mine - 1;
+      }
+      return true;
     };
     if constexpr (FILTER) {
-      bool exact = slow;
-      if (!exact) stream_columns(std::integral_constant<int, 2>{});
+      bool exact = slow || direct > 0;
+      direct = direct > 0 ? direct - 1 : 0;
+      // (uniform) no rank term in this row block: its sums are zeros, and W0 and the stated quotient leave nothing undecided
+      const bool no_term = CHECKED && (ACH == 0 || top_a == 0.f || __builtin_amdgcn_ballot_w64(bany != 0) == 0);
+      if constexpr (CHECKED) {
+        if (!exact && no_term) stream_columns(std::integral_constant<int, 3>{});
+      }
+      if constexpr (ACH > 0) {
+        if (!exact && !no_term) stream_columns(std::integral_constant<int, 2>{});
+      }
       if constexpr (MODE == 4) {
         eq *= s;
         ec *= s;
         // a quotient has overflowed, W / s or b / s alone, where the errors themselves need not: the stated form
         if (!exact) exact = __builtin_amdgcn_ballot_w64(row_ok & col_ok & !(eq + ec < __builtin_huge_valf())) != 0;
       }
-      if constexpr (CHECKED) {
-        // within tol of a tie the near quotient does not settle the code (see the top of the file)
-        bsum = ACH > 0 ? half_sum(bsum) : 0.f;
-        const float tol = fmaf(rc, fmaf(top_a * bsum, sum_tol, 0x1p-22f * fabsf(b)), 0x1p-21f * (1.f - d.qn));
+      if constexpr (CHECKED && ACH > 0) {
+        // within tol of a tie the near sum does not settle the code (see the top of the file)
+        const float tol = fmaf(rc, fmaf(top_a * half_sum(bsum), sum_tol, 0x1p-22f * fabsf(b)), 0x1p-21f * (1.f - d.qn));
         const float edge = 0.5f - tol;
-        const bool unsettled = row_ok & col_ok & !(off < edge);
-        if (!exact && __builtin_amdgcn_ballot_w64(unsettled) != 0) {
-          if constexpr (MODE == 1 && ACH > 0) exact = r > 16 * ACH || !settle(unsettled, edge);  // (r > 16 ACH: A is not in registers)
-          else exact = true;
-        }
+        const bool unsettled = row_ok & col_ok & !(fmaxf(fmaxf(off[0], off[1]), fmaxf(off[2], off[3])) < edge);
+        if (!exact && !no_term && __builtin_amdgcn_ballot_w64(unsettled) != 0)
+          direct = __builtin_amdgcn_ballot_w64(unsettled && !(edge > 0.f)) != 0 || !settle(unsettled, edge) ? 3 : 0;
+        exact |= direct == 3;  // (set just now)
       }
       if (exact) {
         if constexpr (ACH > 0) {
@@ -587,7 +645,8 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
           chain_rest(sum, p, row_ok, 0);
         }
         eq = ec = 0.f;
-        stream_columns(std::integral_constant<int, 0>{});
+        if (!slow) stream_columns(std::integral_constant<int, 1>{});
+        else stream_columns(std::integral_constant<int, 0>{});
       }
     } else {
       if (!slow) stream_columns(std::integral_constant<int, 1>{});

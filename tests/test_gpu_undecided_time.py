@@ -1,0 +1,96 @@
+"""Time of the passes whose codes come from near sums, by the state of the layer.  At its initial state (B = 0, min / max
+scales of bfloat16 weights) a layer has several weights exactly on rounding ties in nearly every row block of 32 x 64, and at
+8 bits one row block in four has a weight within reach of one whatever its state; either once cost up to twice the time of a
+layer that has none.  Compared with that layer (all quotients a quarter of a step off), in turn, medians."""
+import statistics
+
+import pytest
+
+from paper_2402_04902_amd.inputs import DTYPE_BF16, LayerSpec
+
+pytestmark = pytest.mark.gpu
+
+COPIES = 4  # of the weight, in turn: 360 MB, more than the memory-side cache holds
+
+
+def layer_state(i, o, r, bits, g, state):
+    import torch
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(bits)
+    A = ((torch.rand((r, i), generator=gen, device=dev) * 2 - 1) * i ** -0.5).bfloat16()
+    B = (torch.randn((o, r), generator=gen, device=dev) * 1e-3).bfloat16()
+    qn, qp, G = -(1 << (bits - 1)), (1 << (bits - 1)) - 1, i // g
+    if state == "clear":
+        k = torch.randint(qn // 2, qp // 2 + 1, (o, i), generator=gen, device=dev)
+        W0 = ((k + 0.25) * 2.0 ** -6).bfloat16()
+        s = torch.full((o, G), 2.0 ** -6, device=dev)
+        return W0, A, B, s, torch.zeros_like(s)
+    W0 = (torch.randn((o, i), generator=gen, device=dev) * 0.02).bfloat16()
+    lo, hi = W0.view(o, G, g).amin(2).float(), W0.view(o, G, g).amax(2).float()
+    if state == "l4q":
+        s = torch.maximum((lo / qn).abs(), (hi / qp).abs())
+        z = torch.zeros_like(s)
+    else:
+        s = (hi - lo) / (qp - qn)
+        z = lo - s * qn
+    if state == "moved":
+        s = s * (torch.rand((o, G), generator=gen, device=dev) * 0.2 + 0.8)
+        z = lo - s * qn + s * (torch.rand((o, G), generator=gen, device=dev) - 0.5)
+    else:
+        B.zero_()
+    return W0, A, B, s, z
+
+
+@pytest.mark.parametrize("call,i,o,r,bits,state,most", [
+    ("packed", 4096, 11008, 16, 4, "asymm", 1.2), ("packed", 4096, 11008, 16, 4, "l4q", 1.2), ("packed", 4096, 11008, 16, 8, "moved", 1.2),
+    ("forward", 4096, 11008, 16, 4, "l4q", 1.2), ("forward", 4096, 11008, 16, 8, "asymm", 1.2), ("forward", 11008, 4096, 64, 4, "asymm", 1.2),
+    ("qatlora", 4096, 4096, 16, 4, "l4q", 1.08)])
+def test_time_by_state(call, i, o, r, bits, state, most):
+    import torch
+    from paper_2402_04902_amd import binding
+    g, T = 128, 8
+    desc = binding.make_desc(LayerSpec("state", T, i, o, r, 2.0 * r, bits, g, DTYPE_BF16))
+    print("case", call, o, i, r, bits, state, flush=True)
+    dev = torch.device("cuda:0")
+    X, Y = torch.randn((T, i), device=dev).bfloat16(), torch.empty((T, o), dtype=torch.bfloat16, device=dev)
+    packed = torch.empty((o, bits * i // 32), dtype=torch.int32, device=dev)
+    ws = torch.empty(max(o * i, *binding.l4q_workspace_bytes(desc), *binding.l4q_qatlora_workspace_bytes(desc)), dtype=torch.uint8, device=dev)
+    runs = {}
+    for which in ("clear", state):
+        W0, *rest = layer_state(i, o, r, bits, g, which)
+        runs[which] = ([W0.clone() for _ in range(COPIES)], rest)
+
+    def run(which, n):
+        weights, rest = runs[which]
+        for q in range(n):
+            w = (weights[q % COPIES], *rest)
+            if call == "packed":
+                binding.l4q_export_packed(desc, *w, packed, ws)
+            elif call == "forward":
+                binding.l4q_forward(desc, X, *w, Y, ws)
+            else:
+                binding.l4q_qatlora_forward(desc, X, *w, Y, ws)
+
+    def us(which, n=16):
+        run(which, COPIES)
+        if call == "forward":  # the merge + quantize pass alone
+            binding.l4q_profile_gemm(True)
+            run(which, n)
+            ms, launches, _ = binding.l4q_profile_read(binding.PROFILE_MERGE_FORWARD)
+            binding.l4q_profile_gemm(False)
+            return 1e3 * ms / launches
+        t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        t0.record()
+        run(which, n)
+        t1.record()
+        t1.synchronize()
+        return 1e3 * t0.elapsed_time(t1) / n
+
+    times = {"clear": [], state: []}
+    for _ in range(9):
+        for which in times:
+            times[which].append(us(which))
+    clear, other = statistics.median(times["clear"]), statistics.median(times[state])
+    print(f"{clear:.1f} us, {state}: {other:.1f} us")
+    assert other < most * clear
