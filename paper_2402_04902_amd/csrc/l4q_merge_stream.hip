@@ -179,15 +179,26 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
   const int rb_begin = (int)((int64_t)nrb * part / parts);
   const int rb_end = (int)((int64_t)nrb * (part + 1) / parts);
   if constexpr (MODE == 2) {
-    // the first column strip also leaves B^T for its rows (zeros from o to its leading dimension)
-    if (strip == 0 && out.bT) {
+    // B^T for this partition's rows (zeros from o to its leading dimension), dealt out over the strips; where rows are whole
+    // 16-byte pieces, 8 ranks of a row per thread.  (All of it on the first strip's workgroups, by elements: an 11008 x
+    // 4096 weight at rank 16 67 us, here 60; rank 256 without a rank term of the pass's own 128, here 35.)
+    if (out.bT) {
       const int ld = (int)out.ld_bT, rank = out.bT_rank;
       const int pa = rb_begin * 32, pe = rb_end * 32 < ld ? rb_end * 32 : ld;
-      const int np = pe - pa;
-      for (int idx = threadIdx.x; idx < rank * np; idx += MS_THREADS) {
-        const int k = idx / np;
-        const int p2 = pa + idx % np;
-        out.bT[(int64_t)k * ld + p2] = p2 < o ? B[(int64_t)p2 * rank + k] : (bf16_t)0;
+      const int np = pe - pa, step = strips * MS_THREADS;
+      if (rank % 8 == 0) {
+        for (int idx = strip * MS_THREADS + (int)threadIdx.x; idx < rank / 8 * np; idx += step) {
+          const int k = idx / np * 8, p2 = pa + idx % np;
+          u32x4 v = {0u, 0u, 0u, 0u};
+          if (p2 < o) v = *reinterpret_cast<const u32x4*>(B + (int64_t)p2 * rank + k);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) out.bT[(int64_t)(k + e) * ld + p2] = (bf16_t)(e & 1 ? v[e / 2] >> 16 : v[e / 2]);
+        }
+      } else {
+        for (int idx = strip * MS_THREADS + (int)threadIdx.x; idx < rank * np; idx += step) {
+          const int k = idx / np, p2 = pa + idx % np;
+          out.bT[(int64_t)k * ld + p2] = p2 < o ? B[(int64_t)p2 * rank + k] : (bf16_t)0;
+        }
       }
     }
   }

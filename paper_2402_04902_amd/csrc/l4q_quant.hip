@@ -335,14 +335,13 @@ __global__ __launch_bounds__(MQ_THREADS) void merge_quant_tile_kernel(LayerDims 
   }
 
   if constexpr (MODE != 1 && std::is_same<T, bf16_t>::value) {
-    // The first column tile of every row block also leaves B^T for its 64 rows (the dA product of the fused weight-gradient
+    // The workgroups of a row block also leave B^T for its 64 rows, each a share (the dA product of the fused weight-gradient
     // kernel and dY . B of the QAT-LoRA layer read B that way): rank x 64 elements, zeros past o up to the leading dimension.
-    if (blockIdx.x == 0 && out.bT) {
+    if (out.bT) {
       const int64_t pblk = (int64_t)blockIdx.y * MQ_ROWS;
-      for (int idx = threadIdx.x; idx < out.bT_rank * MQ_ROWS; idx += MQ_THREADS) {
-        const int k = idx / MQ_ROWS;
-        const int64_t p = pblk + idx % MQ_ROWS;
-        if (p < out.ld_bT) out.bT[(int64_t)k * out.ld_bT + p] = p < d.o ? B[p * out.bT_rank + k] : (bf16_t)0;
+      for (int64_t idx = (int64_t)blockIdx.x * MQ_THREADS + threadIdx.x; idx < out.bT_rank * MQ_ROWS; idx += (int64_t)gridDim.x * MQ_THREADS) {
+        const int64_t k = idx / MQ_ROWS, p = pblk + idx % MQ_ROWS;
+        if (p < out.ld_bT) out.bT[k * out.ld_bT + p] = p < d.o ? B[p * out.bT_rank + k] : (bf16_t)0;
       }
     }
   }

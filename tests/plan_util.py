@@ -31,3 +31,51 @@ def wide_tile_rows(T, i, o, bits, g):
     f.restype, f.argtypes = ctypes.c_int, [ctypes.POINTER(_LayerDims)]
     q = float(1 << (bits - 1))
     return f(ctypes.byref(_LayerDims(T, i, o, 8, bits, g, 2.0, -q, q - 1.0, False)))
+
+
+class _MergeQuantOut(ctypes.Structure):  # MergeQuantOut<bf16_t> of csrc/l4q_kernels.h
+    _fields_ = [("wq", ctypes.c_void_p), ("ld_wq", ctypes.c_int64), ("wqT", ctypes.c_void_p), ("ld_wqT", ctypes.c_int64),
+                ("bT", ctypes.c_void_p), ("bT_rank", ctypes.c_int), ("ld_bT", ctypes.c_int64), ("fgrad", ctypes.c_void_p),
+                ("codes", ctypes.c_void_p), ("wcomb", ctypes.c_void_p), ("mask", ctypes.c_void_p), ("packed", ctypes.c_void_p),
+                ("errors", ctypes.c_void_p), ("init_scale", ctypes.c_void_p), ("init_zero", ctypes.c_void_p),
+                ("init_method", ctypes.c_int)]
+
+
+def merge_quant_transposed(W0, B, scale, zero, bits, g, wqT, bT):
+    """l4q::launch_merge_quant<bf16> without a rank term: Wq^T [i, o32] and, where bT [rank, o] is given, B^T."""
+    import torch
+    f = getattr(binding.load_library(), "_ZN3l4q18launch_merge_quantItEEvRKNS_9LayerDimsEPKT_S6_S6_PKfS8_RKNS_13MergeQuantOutIS4_EEP12ihipStream_t")
+    f.restype, f.argtypes = None, [ctypes.c_void_p] * 8
+    o, i = W0.shape
+    q = float(1 << (bits - 1))
+    dims = _LayerDims(1, i, o, 0, bits, g, 1.0, -q, q - 1.0, False)
+    out = _MergeQuantOut(wqT=wqT.data_ptr(), ld_wqT=(o + 31) // 32 * 32)
+    if bT is not None:
+        out.bT, out.bT_rank, out.ld_bT = bT.data_ptr(), B.shape[1], bT.shape[1]
+    f(ctypes.byref(dims), W0.data_ptr(), None, B.data_ptr(), scale.data_ptr(), zero.data_ptr(), ctypes.byref(out),
+      torch.cuda.current_stream().cuda_stream)
+
+
+def transposed_rank_product(U, Xs, n_by_r, partial, out):
+    """l4q::launch_tn<float, float>: out = U^T Xs [r, n], or its transpose; U [T, r], Xs [T, n], partial ceil(T / 128) r n floats."""
+    import torch
+    f = getattr(binding.load_library(), "_ZN3l4q9launch_tnIffEEvPKT0_PKT_llibPffS7_bP12ihipStream_t")
+    f.restype = None
+    f.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_bool, ctypes.c_void_p,
+                  ctypes.c_float, ctypes.c_void_p, ctypes.c_bool, ctypes.c_void_p]
+    f(U.data_ptr(), Xs.data_ptr(), U.shape[0], Xs.shape[1], U.shape[1], n_by_r, partial.data_ptr(), 1.0, out.data_ptr(), False,
+      torch.cuda.current_stream().cuda_stream)
+
+
+def gpu_us(call, n=30):
+    """Time of one call among n, on the GPU."""
+    import torch
+    t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    for _ in range(5):
+        call()
+    t0.record()
+    for _ in range(n):
+        call()
+    t1.record()
+    t1.synchronize()
+    return 1e3 * t0.elapsed_time(t1) / n
