@@ -116,7 +116,6 @@ template <> struct Row4<bf16_t> {  // (rows are whole 16-byte pieces)
   }
 };
 
-//
 // WHOLE (up to 2 row blocks; with 4, 1024 threads on a quarter of the workgroups, a 495 x 1568 binary32 step took 68.2 us against
 // 67.3 in two passes): a workgroup has 4 waves for each row block, and the blocks' sums, formed as above, are added in
 // block order as the second pass would add them, scaled and stored: one launch instead of two, the same bits.
@@ -180,14 +179,31 @@ __device__ __forceinline__ void tn_columns(int block, TnSums* sums, const UT* __
       }
       return v;
     };
-    if constexpr (WHOLE) {  // one output per thread and turn
-      for (int q = tid; q < LR_KC * 64; q += waves * 64) {
-        const int k = NR ? q % LR_KC : q / 64, j = NR ? q / LR_KC : q % 64;
-        if (j0 + j < n && k0 + k < r && j0 + j >= (int64_t)block * 64) {  // (columns below are the neighbour's: added to once)
-          float* p = part + (NR ? (j0 + j) * r + k0 + k : (int64_t)(k0 + k) * n + j0 + j);
-          const float v = gamma * total(k, j);
-          *p = accumulate ? *p + v : v;
+    if constexpr (WHOLE) {
+      auto mine = [&](int j) { return j0 + j < n && j0 + j >= (int64_t)block * 64; };  // (columns below are the neighbour's: added to once)
+      if constexpr (NR) {  // 4 consecutive ranks per thread: 16 lanes read 16 columns (a rank per lane: one bank for all of them)
+        const int j = tid >> 2, k = (tid & 3) * 4;
+        if (tid < 256 && mine(j)) {
+          float* q = part + (j0 + j) * r + k0 + k;
+          if (k0 + k + 3 < r) {
+            vec_t v = {gamma * total(k, j), gamma * total(k + 1, j), gamma * total(k + 2, j), gamma * total(k + 3, j)};
+            if (accumulate) v = *reinterpret_cast<const vec_t*>(q) + v;
+            *reinterpret_cast<vec_t*>(q) = v;
+          } else {
+            for (int c = 0; c < 3; ++c)
+              if (k0 + k + c < r) {
+                const float v = gamma * total(k + c, j);
+                q[c] = accumulate ? q[c] + v : v;
+              }
+          }
         }
+      } else if (mine(lane)) {
+        for (int k = wave; k < LR_KC; k += waves)
+          if (k0 + k < r) {
+            float* p = part + (int64_t)(k0 + k) * n + j0 + lane;
+            const float v = gamma * total(k, lane);
+            *p = accumulate ? *p + v : v;
+          }
       }
     } else if constexpr (NR) {
       const int j = tid >> 2, k = (tid & 3) * 4;
