@@ -116,8 +116,7 @@ template <> struct Row4<bf16_t> {  // (rows are whole 16-byte pieces)
   }
 };
 
-// WHOLE (up to 2 row blocks; with 4, 1024 threads on a quarter of the workgroups, a 495 x 1568 binary32 step took 68.2 us against
-// 67.3 in two passes): a workgroup has 4 waves for each row block, and the blocks' sums, formed as above, are added in
+// WHOLE (see tn_whole): a workgroup has 4 waves for each row block, and the blocks' sums, formed as above, are added in
 // block order as the second pass would add them, scaled and stored: one launch instead of two, the same bits.
 typedef float TnSums[LR_KC][64];
 
@@ -261,6 +260,12 @@ void launch_lora_down(const LoraDown* jobs, int njobs, int64_t T, int r, hipStre
     hipLaunchKernelGGL(lora_down_kernel<4>, dim3(tiles, (unsigned)((r + 63) / 64), z), dim3(64 * LD_WAVES), 0, stream, a, b, T, r);
 }
 
+// One pass or two (WHOLE): a workgroup of one pass takes all row blocks, so with two of them and high ranks, whose steps of 16 it
+// goes through one after the other, its waves meet at barriers twice as often for the launch it saves.  Binary32, us in two passes /
+// one, [r, n], n = 1024: 128 rows 10.2 / 7.8 at ranks up to 16, 10.7 / 7.8 at 64, 28 / 23 at 256; 200 rows 10.5 / 7.9 at 16, 10.8 /
+// 10.4 at 64 (as [n, r] 10.3 / 11.2), 29 / 34 at 256.  Four blocks (1024 threads), 495 columns: 67.3 / 68.2 for a whole step.
+static bool tn_whole(int64_t row_blocks, int r) { return row_blocks == 1 || (row_blocks == 2 && r <= 32); }
+
 int64_t lora_tn_blocks(int64_t T) { return (T + LR_TB - 1) / LR_TB; }
 
 template <class S, class UT>
@@ -270,7 +275,7 @@ void launch_tn(const UT* U, const S* Xs, int64_t T, int64_t n, int r, bool out_n
 #define L4Q_TN(NR, WHOLE, GRID, THREADS, OUT) \
   hipLaunchKernelGGL((tn_partial_kernel<S, UT, NR, WHOLE>), GRID, dim3(THREADS), 0, stream, U, Xs, T, n, r, OUT, gamma, accumulate)
   const unsigned cols = (unsigned)((n + 63) / 64);
-  if (nb <= 2) {
+  if (tn_whole(nb, r)) {
     if (out_n_by_r) L4Q_TN(true, true, dim3(cols), (unsigned)(256 * nb), out);
     else L4Q_TN(false, true, dim3(cols), (unsigned)(256 * nb), out);
     return;
@@ -285,7 +290,7 @@ void launch_tn_pair(const float* Ua, const bf16_t* Xa, int64_t na, float* outa, 
                     int64_t nb, float* outb, float* partb, int64_t T, int r, float gamma, bool accumulate, hipStream_t stream) {
   const int64_t blocks = lora_tn_blocks(T);
   const int cols = (int)((na + 63) / 64), all = cols + (int)((nb + 63) / 64);
-  if (blocks <= 2) {
+  if (tn_whole(blocks, r)) {
     hipLaunchKernelGGL(tn_pair_kernel<true>, dim3((unsigned)all), dim3((unsigned)(256 * blocks)), 0, stream, TnJob{Ua, Xa, na, outa},
                        TnJob{Ub, Xb, nb, outb}, cols, T, r, gamma, accumulate);
     return;
