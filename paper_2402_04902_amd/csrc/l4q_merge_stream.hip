@@ -35,12 +35,13 @@
 //    An infinity or NaN in A or B makes tol one, and nothing passes.  What is undecided depends on the layer's state.  In the
 //    middle of a run (B moved, scales no simple fractions of the weights) 2 % of the row blocks hold such a weight at 4 bits,
 //    24 % at 8 (counted, groups of 128).  At the start, B = 0 and min / max scales of bfloat16 weights, 2 to 7 weights of a row
-//    block, and some in 80 to 99 % of them, lie exactly on ties; but sums of nothing are not near, they are the stated ones, so a row block whose rows of B are all
-//    zero (or whose A is) takes W0 and the stated quotient and leaves nothing undecided, as the layers without a rank term do.
+//    block, and some in 80 to 99 % of them, lie exactly on ties; but sums of nothing are not near, they are the stated ones:
+//    a row block whose rows of B are all zero (or whose A is) takes W0 and the stated quotient and leaves nothing undecided, as
+//    the layers without a rank term do.
 //    Undecided weights are settled by the stated sum, one of every lane at a time, from the operands in registers (ranks above
-//    what they hold: from memory); a row block with more than 3 in a lane is repeated by the stated arithmetic, and
+//    what they hold: one at a time, from memory); a row block with more than 3 in a lane is repeated by the stated arithmetic, and
 //    the next 3 go there directly.  (Most in a lane 1 / 3 / 8, packing 11008 x 4096: 16 a row block 61 / 48 / 48 us, 128 61 / 61 /
-//    69; A in memory, rank 64: 120 / 122 / 124, 124 / 123 / 293.  Every weight on a tie: 61, going there directly 48.)
+//    69.  Every weight on a tie: 61, going there directly 48.)
 //    us, weights from HBM; chain with sums through LDS / here: forward 11008 x 4096, rank 16, in the middle of a run 46 / 37, at
 //    the start 46 / 37, 8 bits 45 / 39; 4096 x 11008 at rank 64 100 / 50; 4096 x 4096, groups of 64, 20.4 / 14.0; packing
 //    11008 x 4096 49 / 32, at the start 47 / 32, 8 bits 45 / 39.  (Every undecided row block repeated, ties of the start
@@ -226,6 +227,7 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
   const __amdgpu_buffer_rsrc_t rsZ = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(zero), 0, o * G * 4, 0x00020000);
   constexpr unsigned OOB = 0x80000000u;
   constexpr bool FILTER = MODE == 1 || MODE == 4 || MODE == 6, CHECKED = FILTER && MODE != 4;
+  constexpr bool REST = ACH > 0 && !(MODE <= 2 && ACH == 1);  // ranks above 16 ACH (the forward and backward forms have ACH = 4 for them)
   constexpr bool FACTOR = MODE == 2 && ACH > 0;  // (the layers without a rank term take no factor)
 
   // Memory role of a row-major tile: instruction t, lane = row 8 t + lane / 8, piece lane % 8 (whole 128-byte lines).  Piece
@@ -305,19 +307,11 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
   }
   [[maybe_unused]] const float sum_tol = fabsf(d.gamma) * (float)r * 0x1p-22f;  // CHECKED: |gamma| D / S
   float top_a = 0.f;                                                            // max |A| of the wavefront's columns
-  if constexpr (CHECKED && ACH > 0) {
-    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
-    u16x2 m = {0, 0};
-    auto take = [&](uint32_t v) { m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, v & 0x7FFF7FFFu)); };
-#pragma unroll
-    for (int q = 0; q < 8 * ACH; ++q) take(apk[q]);
-    for (int k0 = 16 * ACH; k0 < r; k0 += 16) {
-      uint32_t f[8];
-      load_fragments(k0, f);
-#pragma unroll
-      for (int q = 0; q < 8; ++q) take(f[q]);
-    }
-    uint32_t w = m[0] > m[1] ? m[0] : m[1];  // (magnitudes of bfloat16 order as integers, NaN above infinity)
+  typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+  [[maybe_unused]] u16x2 a_max = {0, 0};  // of this lane's part of it (magnitudes of bfloat16 order as integers, NaN above infinity)
+  auto take_max = [](u16x2& m, uint32_t v) { m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, v & 0x7FFF7FFFu)); };
+  auto all_max = [&](const u16x2& m) {
+    uint32_t w = m[0] > m[1] ? m[0] : m[1];
     auto take_lane = [&](uint32_t v) { w = w > v ? w : v; };
     take_lane(lane_swap<0xB1>(w));   // quad_perm: lane ^ 1
     take_lane(lane_swap<0x4E>(w));   // quad_perm: lane ^ 2
@@ -329,7 +323,12 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
       const uint32_t v = (uint32_t)__builtin_amdgcn_readlane((int)w, 16 * q);
       top = top > v ? top : v;
     }
-    top_a = __uint_as_float(top << 16);
+    return __uint_as_float(top << 16);
+  };
+  if constexpr (CHECKED && ACH > 0) {
+#pragma unroll
+    for (int q = 0; q < 8 * ACH; ++q) take_max(a_max, apk[q]);
+    top_a = all_max(a_max);
   }
 
   auto odd_even = [](uint32_t v, int k) { return __uint_as_float(k & 1 ? v & 0xFFFF0000u : v << 16); };
@@ -369,7 +368,11 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
   uint32_t no_bits = 0;
   asm volatile("" : "+s"(no_bits));
   int rb = rb_begin;
-  [[maybe_unused]] int direct = 0;  // CHECKED: row blocks ahead that go straight to the stated sums
+  // CHECKED: row blocks ahead that go straight to the stated sums.  From the start where nothing hides the settling of one, which
+  // takes 2 us at rank 256, in a launch that leaves units idle (chain / near sums, 1024 x 1024, in the middle of a run, at the
+  // start: forward at rank 256 20 / 26 and 20 / 13 us, at 128 15.4 / 15.7 and 15.2 / 10.0; packing 17 / 25 and 17 / 9, 10.8 / 13.2
+  // and 10.6 / 6.5, at 72 9.3 / 7.0; 2048 x 2048, rank 256, forward 34 / 29).
+  [[maybe_unused]] int direct = CHECKED && REST && r >= (MODE == 1 ? 136 : 128) && (int)gridDim.x <= 256 && rb_end - rb_begin == 1;
   do {  // (no partition is empty)
     const int p0 = rb * 32, p = p0 + l32;
     const bool row_ok = p < o;
@@ -416,10 +419,18 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
 #pragma unroll
       for (int c = 0; c < ACH; ++c)
         if (c == 0 || 16 * c < r) add_chunk(F.b[c], apk + 8 * c);  // (uniform)
-      for (int k0 = 16 * ACH; ACH > 0 && k0 < r; k0 += 16) {
+      [[maybe_unused]] u16x2 m = a_max;
+      for (int k0 = 16 * ACH; REST && k0 < r && (!CHECKED || direct == 0); k0 += 16) {
         uint32_t f[8];
         load_fragments(k0, f);
         add_chunk(load_b(p, row_ok, k0), f);
+        if constexpr (CHECKED) {  // (here and not ahead of the row blocks: another fetch of A, 14.1 us against 10.3 at 256 x 256, rank 72)
+#pragma unroll
+          for (int q = 0; q < 8; ++q) take_max(m, f[q]);
+        }
+      }
+      if constexpr (CHECKED && REST) {
+        if (r > 16 * ACH) top_a = all_max(m);
       }
     } else if constexpr (ACH > 0) {
 #pragma unroll
@@ -427,7 +438,7 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
 #pragma unroll
       for (int c = 0; c < ACH; ++c)
         if (c == 0 || 16 * c < r) chain(sum, F.b[c], apk + 8 * c);  // (uniform)
-      chain_rest(sum, p, row_ok, 16 * ACH);
+      if constexpr (REST) chain_rest(sum, p, row_ok, 16 * ACH);
     }
 
     // ---- this lane's group: s, b, RN(1 / s), 1024 s
@@ -547,7 +558,9 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
     };
     // CHECKED: the elements of these lanes within reach of a tie by the stated arithmetic, one of every lane at a time: from
     // registers alone where they hold all of A (a fetch waits for everything the wavefront has in flight: 8 bits, packing
-    // 44.6 us against 38.8).  False (and nothing relied on) where a lane has many.
+    // 44.6 us against 38.8), else one of one lane.  (All lanes' there, from memory, 8 or 32 ranks at a time: packing 11008 x 4096
+    // at rank 64, 8 bits, 76 us against 73, forward 5120 x 5120 at rank 256 115 / 102; four lanes' at a time 77.)  False (and
+    // nothing relied on) where a lane has many.
     auto settle = [&](bool unsettled, float edge) {
       uint32_t mine = 0;
 #pragma unroll
@@ -562,11 +575,13 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
       }
       if (!unsettled) mine = 0;
       if (__builtin_amdgcn_ballot_w64(__builtin_popcount(mine) > 3) != 0) return false;
-      while (__builtin_amdgcn_ballot_w64(mine != 0) != 0) {
-        const bool live = mine != 0;
+      for (;;) {
+        const uint64_t todo = __builtin_amdgcn_ballot_w64(mine != 0);
+        if (todo == 0) return true;
+        bool live = mine != 0;
         const int n = live ? __builtin_ctz(mine) : 0;
         float acc = 0.f;
-        if (r <= 16 * ACH) {
+        if (!REST || r <= 16 * ACH) {
           const int from = 4 * (8 * (n % 16 / 4) + 4 * h + n % 4);  // the lane of its column's M index, times 4
 #pragma unroll
           for (int c = 0; c < ACH; ++c) {
@@ -586,16 +601,26 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
 #pragma unroll
             for (int k = 0; k < 16; ++k) acc = fmaf(odd_even(bw[k / 2], k), odd_even(aw[k / 2], k), acc);
           }
-        } else {
-          for (int k0 = 0; k0 < r; k0 += 8) {
-            const u32x4 bq = __builtin_amdgcn_raw_buffer_load_b128(rsB, (int)(live ? (unsigned)((p * r + k0) * 2) : OOB), 0, 0);
-            uint32_t av[8];
+        } else if constexpr (REST) {
+          // of the first lane alone, lane = k: one round trip for up to 256 products (exact, but for some below 2^-126, on which no
+          // code depends), added in order
+          const int at = __builtin_ctzll(todo), col = jw + 32 * (at >> 5) + __builtin_amdgcn_readlane(n, at);
+          live = lane == at;
+          float prod[4];
 #pragma unroll
-            for (int k = 0; k < 8; ++k)
-              av[k] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rsA, (int)(live ? (unsigned)((jl + n) * 2) : OOB), (k0 + k) * i * 2, 0);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) acc = fmaf(odd_even(bq[k / 2], k), odd_even(av[k], 0), acc);
+          for (int c = 0; c < 4; ++c) {
+            const int k = 64 * c + lane;
+            const uint32_t bv = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rsB, (int)(k < r ? (unsigned)(((p0 + (at & 31)) * r + k) * 2) : OOB), 0, 0);
+            const uint32_t av = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rsA, (int)(k < r ? (unsigned)((k * i + col) * 2) : OOB), 0, 0);
+            prod[c] = odd_even(bv, 0) * odd_even(av, 0);
           }
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            for (int k0 = 0; 64 * c + k0 < r && k0 < 64; k0 += 8) {
+#pragma unroll
+              for (int k = 0; k < 8; ++k)
+                acc += __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(prod[c]), k0 + k));
+            }
         }
         uint32_t pick[16];
 #pragma unroll
@@ -619,9 +644,8 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
             words[q] = (words[q] & ~f) | ((q == k ? (uint32_t)u : (uint32_t)(u >> 32)) & f);
           }
         }
-        mine &= mine - 1;
+        if (live) mine &= mine - 1;
       }
-      return true;
     };
     if constexpr (FILTER) {
       bool exact = slow || direct > 0;

@@ -94,3 +94,31 @@ def test_time_by_state(call, i, o, r, bits, state, most):
     clear, other = statistics.median(times["clear"]), statistics.median(times[state])
     print(f"{clear:.1f} us, {state}: {other:.1f} us")
     assert other < most * clear
+
+
+@pytest.mark.parametrize("i,o,r", [(256, 256, 72), (1024, 1024, 72), (1024, 1024, 256)])
+def test_high_ranks_of_small_layers(i, o, r):
+    """The forward pass against the backward one, which forms the stated sums and twice the output: where a launch has one row block
+    a wavefront, A's chunks past the registers come from memory once.  (Once more for their largest element: 1.3 to 1.4 times.)"""
+    import torch
+    from paper_2402_04902_amd import binding
+    dev, T, bits, g = torch.device("cuda:0"), 8, 4, 128
+    desc = binding.make_desc(LayerSpec("small", T, i, o, r, 2.0 * r, bits, g, DTYPE_BF16))
+    w = layer_state(i, o, r, bits, g, "moved")
+    X, dY = torch.randn((T, i), device=dev).bfloat16(), torch.randn((T, o), device=dev).bfloat16()
+    Y, dX = torch.empty_like(dY), torch.empty_like(X)
+    grads = [torch.empty(s, device=dev) for s in ((r, i), (o, r), (o, i // g), (o, i // g))]
+    ws = torch.empty(max(binding.l4q_workspace_bytes(desc)), dtype=torch.uint8, device=dev)
+    times = {binding.PROFILE_MERGE_FORWARD: [], binding.PROFILE_MERGE_BACKWARD: []}
+    for rep in range(9):
+        binding.l4q_profile_gemm(True)
+        for _ in range(16):
+            binding.l4q_forward(desc, X, *w, Y, ws)
+            binding.l4q_backward(desc, X, dY, *w, dX, *grads, ws)
+        for kind in times:
+            ms, launches, _ = binding.l4q_profile_read(kind)
+            times[kind].append(1e3 * ms / launches)
+        binding.l4q_profile_gemm(False)
+    forward, backward = (statistics.median(t[1:]) for t in times.values())
+    print(f"{o}x{i} rank {r}: forward {forward:.1f} us, backward {backward:.1f} us")
+    assert forward < 1.15 * backward
