@@ -74,9 +74,11 @@ namespace {
 constexpr int MS_COLS = 256;                     // columns per workgroup: 4 wavefronts x 64
 constexpr int MS_THREADS = 256;
 // Wavefronts per SIMD, and workgroups per compute unit of the one resident round, of a form.  As few as keep the memory busy: a
-// wavefront starts with a fetch of A and of its first row block that nothing hides, and more registers mean no spills.  us at 4 / 3 /
-// 2: forward 11008 x 4096 42.7 / 41.6 / 42.4, 4096 x 4096 14.1 / 13.9 / 14.1, rank 64 4096 x 11008 - / 56.5 / 53.9; error sums 21.1 /
-// 19.6 / 18.3 (the second launch has half the pairs to add); packing 26.6 / 26.4 / 27.3; initialisation 26.6 / 27.4 (5: 26.4).
+// wavefront starts with a fetch of A and of its first row block that nothing hides, and more registers mean no spills.  us at 2 / 3 /
+// 4, weights from HBM, 11008 x 4096 and 13824 x 5120: forward 39 / 39 / 42 and 64 / 63 / 67, rank 64 48 / 140 / 183 and 76 / 216 /
+// 292; backward 57 / 56 / 59 and 97 / 92 / 100, rank 64 92 / 91 / 135; codes 43 / 42 / 50 and 70 / 69 / 79; error sums 23 / 24 / 23
+// and 39 / 38 / 39 (and fewer pairs to add); initialisation 30 / 29 / 27 and 44 / 41 / 40; packing 32 / 32 / 65 and 51 / 51 / 103.
+// 4096 x 4096 and 2048 x 2048 within 1 us of the best.
 template <int MODE, int ACH> constexpr int ms_waves() {
   return MODE == 5 ? 4 : MODE == 4 || (MODE == 1 && ACH > 1) ? 2 : 3;
 }

@@ -3,7 +3,7 @@
 // Bound: the matrix cores, with the vector unit close behind (the codes are turned into operands where they are used, and
 // the affine part of every section of k is applied to its sums): per section of a 128 x 256 tile a wave has 1152 cycles of
 // matrix ops and 950 of vector ops.  The decode kernels read and convert the whole weight once per 64 tokens: 8 passes of
-// 27 us at 512 tokens on [11008 x 4096]; this kernel takes 56 us.  A workgroup of 8 waves (2 x 4, two per SIMD; for 192 rows
+// 27 us at 512 tokens on [11008 x 4096]; this kernel takes 58 us (calls one after the other; 64 under a kernel trace).  A workgroup of 8 waves (2 x 4, two per SIMD; for 192 rows
 // 2 x 6, three) owns a tile of 64 TM tokens x 32 WN TN weight rows, so a converted code is used for 32 TM tokens of a wave and the weight is read once per
 // tile row.  Arithmetic as in the decode kernels: the matrix cores multiply X with the exact integers w~ + K0, and
 //   sum_k X (w~ s + b) = s sum_k X (w~ + K0) + (b - K0 s) sum_k X   per section of SEC k-values (128, or groups of 64),
@@ -13,13 +13,13 @@
 //    consecutive codes each: section sub-stage jj, matrix op d contracts k = 64 jj + 32 half + 8 d + 0 .. 7.
 //  * scale and zero: every lane loads its own rows' values for four sections at a time into registers.
 //  * within a section everything is one matrix-op step ahead: reads, conversions, sums of X and the next loads are dealt
-//    out between the matrix ops (ahead of them in a lump they cost 93 against 69 us in 128 x 256 tiles: both waves of a SIMD come out of
-//    the barrier together and do the same thing at the same time).
+//    out between the matrix ops (ahead of them in a lump they cost a third more, 93 us against 69 before the codes were taken in
+//    X's order: both waves of a SIMD come out of the barrier together and do the same thing at the same time).
 //  * sums of X per (token, section): dot products with ones by the four waves that hold the token, a quarter of the
 //    section each; the partial sums meet in LDS, and the zero term of two sections is one K = 2 binary32 matrix op.
 //  * 4 bits: a byte's two codes by one multiplication with the byte picked by the op, one mask-or per pair, in the order in
 //    which X lies.  (Pairs (j, j + 4) take a shift less but X fragments permuted to match, by each of the four waves that
-//    hold the tokens: 75 us against 70 in 128 x 256 tiles, 56 against 49 in 128 x 128.)
+//    hold the tokens: 7 % more time in 128 x 256 tiles, 14 % in 128 x 128.)
 #include <type_traits>
 #include <utility>
 
@@ -386,10 +386,10 @@ void launch_form(const LayerDims& d, const bf16_t* X, const uint32_t* packed, co
                      packed, scale, zero, Y, (int)d.T, (int)d.o, (int)d.i, d.g, tiles_m, tiles_n);
 }
 
-// 128-token tiles of 256 weight rows (8 waves of 64 x 64) or of 192 (12 waves of 64 x 32): a section of a round takes 1.95 and
-// 1.72 us, so 192 wherever it needs no more rounds, which leaves fewer units idle in the last one (4 bits, 256 / 192, us:
-// 512, 11008 x 4096 74 / 64;  1000, 11008 x 4096 147 / 139;  700, 6144 x 5120 87 / 74;  3 and 2 bits, 512, 11008 x 4096 87 / 72
-// and 80 / 69).
+// 128-token tiles of 256 weight rows (8 waves of 64 x 64) or of 192 (12 waves of 64 x 32): a section of a round is put at 1.95 and
+// 1.72 us, and the smaller sum of rounds is taken, so 192 wherever it needs no more rounds (it leaves fewer units idle in the
+// last one), or 9 for 8.  us at 4, 3, 2 bits, 256 / 192: 512, 11008 x 4096 62 / 59, 77 / 63, 73 / 62;  1000, 11008 x 4096 126 / 114,
+// 154 / 127, 147 / 122;  700, 6144 x 5120 73 / 65, 92 / 74, 88 / 71;  512, 4096 x 4096 59 / 52, 74 / 59, 71 / 57.
 struct WideTiles {
   int rows;
   double section_us;  // of all rounds
@@ -415,18 +415,20 @@ void launch_bits(int form, const LayerDims& d, const bf16_t* X, const uint32_t* 
 
 }  // namespace
 
-// Time of the three forms in us: rounds of tiles over the compute units, times sections of 128 k-values, times what a section
-// of a round takes, plus 5 for the launch, the first loads and the store.  Measured at 4 bits (64 x 128 / 128 x 128 /
-// 128 x 256; T, o x i): 200, 4096 x 4096 31 / 44 / 62;  512, 4096 x 4096 34 / 47 / 64;  1024, 4096 x 4096 55 / 50 / 64;
-// 256, 11008 x 4096 51 / 49 / 65;  512, 11008 x 4096 80 / 94 / 69;  1000, 11008 x 4096 152 / 141 / 136;
-// 200, 4096 x 11008 83 / 120 / 165.  2 and 3 bits take 2 .. 20 % more, 8 bits 10 .. 40 %, groups of
-// 64 20 .. 35 % (twice the barriers and scalings).
-// (One pass of the decode kernels per 64 tokens: 512 tokens on 11008 x 4096 215, 256 on 4096 x 11008 106.)
-// The choice against those passes falls where 64 x 128 tiles are the best form, and needs their time closer than that: one
-// workgroup on a unit takes 0.885 us per section at 4 bits, two together 1.46 (2, 3, 8 bits: 0.97 and 1.6, 1.02 and 1.65, 1.13
-// and 2.37; groups of 64 28 % more, 23 % at 8 bits), within 3.5 % on average over 15000 measured calls.
 int qgemm_prompt_wide_rows(const LayerDims& d) { return wide_tiles(d).rows; }
 
+// Time of the three forms in us: rounds of tiles over the compute units, times sections of 128 k-values, times what a section
+// of a round takes, plus 5 for the launch, the first loads and the store.  Measured at 4 bits (64 x 128 / 128 x 128 / wide
+// tiles, here all of 192 rows; T, o x i): 200, 4096 x 4096 29 / 38 / 50;  512, 4096 x 4096 31 / 41 / 52;  1024, 4096 x 4096
+// 51 / 47 / 56;  256, 11008 x 4096 46 / 41 / 52;  512, 11008 x 4096 75 / 84 / 58;  1000, 11008 x 4096 143 / 132 / 115;
+// 200, 4096 x 11008 75 / 102 / 134.  2 and 3 bits take 2 .. 20 % more, 8 bits 10 .. 40 %, groups of
+// 64 20 .. 35 % (twice the barriers and scalings).
+// (One pass of the decode kernels per 64 tokens: 512 tokens on 11008 x 4096 214, 256 on 4096 x 11008 103.)
+// The choice against those passes falls where 64 x 128 tiles are the best form, and needs their time closer than that: one
+// workgroup on a unit is put at 0.885 us per section at 4 bits, two together at 1.46 (2, 3, 8 bits: 0.97 and 1.6, 1.02 and 1.65,
+// 1.13 and 2.37; groups of 64 28 % more, 23 % at 8 bits).  On 470 drawn calls of 65 to 1024 tokens that is 2 to 3 % off on
+// average, but 10 % above the time at 4 bits in groups of 128, whose conversion has become faster since: of 260 such calls
+// 8, of 84 to 290 tokens, go through the passes and would be 5 to 19 % faster here; the mean loss of all is 0.4 %.
 PrefillPlan qgemm_prefill_plan(const LayerDims& d) {
   PrefillPlan plan = {-1, 0.0};
   const bool g_ok = d.g >= 128 || (d.g == 64 && d.bits != 3);

@@ -417,6 +417,14 @@ __global__ __launch_bounds__(64 * SL_WAVES) void sgemm_sliced_pair_kernel(SgemmA
   else sliced_tile<A2, B2>(b, (int)blockIdx.x - tiles, part);
 }
 
+// operand of whole 16-byte pieces, every offset from a tile's first row within 31 bits
+template <bool KMAJOR>
+bool whole_pieces(const float* P, int64_t ld, int64_t extent, int64_t K) {
+  if ((reinterpret_cast<uintptr_t>(P) & 15) != 0 || ld % 4 != 0) return false;
+  if (KMAJOR) return extent % 4 == 0 && (K + SG_BK) * ld < (1ll << 29);
+  return K % 4 == 0 && 128 * ld + K + SG_BK < (1ll << 29);
+}
+
 // Which form, in us (K-contiguous operands; sliced / 64 x 64 tiles by one, by two groups of waves / 128 x 128 tiles):
 //   64-wide tiles   16 (100 x 512 x 1024)   11 / 30 / 25 / 82     the vector kernel took 36 .. 44 us on a 4-tile product
 //                   80 (300 x 1024 x 1024)  21 / 31 / 26 / 83     of K = 256 (sliced form: 4.8) and 318 .. 363 us on
@@ -432,14 +440,6 @@ __global__ __launch_bounds__(64 * SL_WAVES) void sgemm_sliced_pair_kernel(SgemmA
 // waves on a quarter of the tile, is ahead.  128-wide tiles halve the operand traffic; the line at two of them per compute
 // unit leaves them out at one per unit, where they are 5 % ahead at K = 1000 (92 / 87) but add up k in one chain instead of
 // two of half the length (a layer of 1000 x 2048 x 2048 is 5.8e-7 off its value in 64 bits with two groups, 8.1e-7 with one).
-// operand of whole 16-byte pieces, every offset from a tile's first row within 31 bits
-template <bool KMAJOR>
-bool whole_pieces(const float* P, int64_t ld, int64_t extent, int64_t K) {
-  if ((reinterpret_cast<uintptr_t>(P) & 15) != 0 || ld % 4 != 0) return false;
-  if (KMAJOR) return extent % 4 == 0 && (K + SG_BK) * ld < (1ll << 29);
-  return K % 4 == 0 && 128 * ld + K + SG_BK < (1ll << 29);
-}
-
 template <bool A_KM, bool B_KM>
 void launch_sgemm_form(const SgemmArgs& a, hipStream_t stream) {
   auto tiles = [&](int64_t bm, int64_t bn) { return ((a.M + bm - 1) / bm) * ((a.N + bn - 1) / bn); };
