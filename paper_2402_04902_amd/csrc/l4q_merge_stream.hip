@@ -47,7 +47,8 @@
 //    11008 x 4096 49 / 32, at the start 47 / 32, 8 bits 45 / 39.  (Every undecided row block repeated, ties of the start
 //    included: forward 86 at the start, packing 63 and at 8 bits 50.)  Slower than the chain, 0.7 to 0.9 times: weights held on
 //    ties by a B that is not zero but too small to move them.
-//    Error sums, which no single code decides, use the near values (but where a quotient overflows): 45 / 18.
+//    Error sums, which no single code decides, use the near values (but where a quotient overflows): 45 / 18 with
+//    much of the weight in the memory-side cache, 23 from HBM.
 //  * Forms that need the quotient itself (backward: the factor; export) do not spend the 11-instruction IEEE expansion per
 //    weight: with the correctly rounded reciprocal r = RN(1 / s) (hardware estimate, one Newton step, then the
 //    choice among the result and its two neighbours by the exact residual 1 - s r),
