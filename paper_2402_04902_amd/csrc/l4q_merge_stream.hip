@@ -371,11 +371,18 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
   uint32_t no_bits = 0;
   asm volatile("" : "+s"(no_bits));
   int rb = rb_begin;
-  // CHECKED: row blocks ahead that go straight to the stated sums.  From the start where nothing hides the settling of one, which
-  // takes 2 us at rank 256, in a launch that leaves units idle (chain / near sums, 1024 x 1024, in the middle of a run, at the
-  // start: forward at rank 256 20 / 26 and 20 / 13 us, at 128 15.4 / 15.7 and 15.2 / 10.0; packing 17 / 25 and 17 / 9, 10.8 / 13.2
-  // and 10.6 / 6.5, at 72 9.3 / 7.0; 2048 x 2048, rank 256, forward 34 / 29).
-  [[maybe_unused]] int direct = CHECKED && REST && r >= (MODE == 1 ? 136 : 128) && (int)gridDim.x <= 256 && rb_end - rb_begin == 1;
+  // CHECKED: row blocks ahead that go straight to the stated sums.  From the start where A is not in registers, a wavefront has one
+  // or two row blocks, so that little hides the settling (1 us a weight at rank 64, 2 at 256), and the weights to settle are many:
+  // at 8 bits, or at high ranks in a launch that leaves units idle.  us, stated / near sums, in the middle of a run (at the start of
+  // one the near sums would have been faster, as their last figure says): packing, 8 bits, 1024 x 1024 rank 24 5.9 / 7.8, 64 7.6 /
+  // 12.7 (5.2), 2048 x 2048 rank 64 11.8 / 14.9 (7.6), 4 bits, 1024 x 1024 rank 256 17 / 25 (9), 72 9.3 / 7.0; forward, 8 bits, 1024 x
+  // 1024 rank 72 12.3 / 13.7 (8.3), 1536 x 1536 rank 72 18.3 / 15.0, 128 22.3 / 26.0, 4 bits, 1024 x 1024 rank 256 20 / 26 (13),
+  // 128 15.4 / 15.7 (10), 2048 x 2048 rank 256 34 / 29; two row blocks, 8 bits, 4096 x 2048: packing rank 64 20.1 / 21.5 (12), 96
+  // 25 / 28 (14), 128 30 / 43, forward rank 72 28 / 21, 128 37 / 39.
+  const bool idle_units = (int)gridDim.x <= 256, high_rank = r >= (MODE == 1 ? 136 : 128);
+  const bool many = d.bits == 8 ? (2 * parts >= nrb && r >= (MODE == 1 ? 128 : 96)) || (parts >= nrb && (MODE != 1 || idle_units))
+                                : parts >= nrb && high_rank && idle_units;
+  [[maybe_unused]] int direct = CHECKED && REST && r > 16 * ACH && many ? rb_end - rb_begin : 0;
   do {  // (no partition is empty)
     const int p0 = rb * 32, p = p0 + l32;
     const bool row_ok = p < o;
@@ -655,6 +662,18 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
       direct = direct > 0 ? direct - 1 : 0;
       // (uniform) no rank term in this row block: its sums are zeros, and W0 and the stated quotient leave nothing undecided
       const bool no_term = CHECKED && (ACH == 0 || top_a == 0.f || __builtin_amdgcn_ballot_w64(bany != 0) == 0);
+      // within tol of a tie the near sum does not settle the code (see the top of the file)
+      const float tol = fmaf(rc, fmaf(top_a * half_sum(bsum), sum_tol, 0x1p-22f * fabsf(b)), 0x1p-21f * (1.f - d.qn));
+      const float edge = 0.5f - tol;
+      if constexpr (CHECKED && REST) {
+        // more than 2 weights of a row block within reach (2 tol of its 2048) take longer, one after the other, than its stated sums:
+        // the rest of the run goes there (8 bits, 4096 x 4096, packing / forward at rank 256 161 / 168 us without, chain 90 / 98; at
+        // rank 128, 1.6 a row block, 51 / 51 without, chain 52 / 58)
+        if (r > 16 * ACH && !exact && !no_term && __builtin_popcountll(__builtin_amdgcn_ballot_w64(tol > 0x1.2p-11f)) >= 32) {
+          exact = true;
+          direct = 1 << 30;
+        }
+      }
       if constexpr (CHECKED) {
         if (!exact && no_term) stream_columns(std::integral_constant<int, 3>{});
       }
@@ -668,9 +687,6 @@ __device__ __forceinline__ void merge_quant_stream_body(const LayerDims& d, cons
         if (!exact) exact = __builtin_amdgcn_ballot_w64(row_ok & col_ok & !(eq + ec < __builtin_huge_valf())) != 0;
       }
       if constexpr (CHECKED && ACH > 0) {
-        // within tol of a tie the near sum does not settle the code (see the top of the file)
-        const float tol = fmaf(rc, fmaf(top_a * half_sum(bsum), sum_tol, 0x1p-22f * fabsf(b)), 0x1p-21f * (1.f - d.qn));
-        const float edge = 0.5f - tol;
         const bool unsettled = row_ok & col_ok & !(fmaxf(fmaxf(off[0], off[1]), fmaxf(off[2], off[3])) < edge);
         if (!exact && !no_term && __builtin_amdgcn_ballot_w64(unsettled) != 0)
           direct = __builtin_amdgcn_ballot_w64(unsettled && !(edge > 0.f)) != 0 || !settle(unsettled, edge) ? 3 : 0;

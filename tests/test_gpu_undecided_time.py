@@ -122,3 +122,26 @@ def test_high_ranks_of_small_layers(i, o, r):
     forward, backward = (statistics.median(t[1:]) for t in times.values())
     print(f"{o}x{i} rank {r}: forward {forward:.1f} us, backward {backward:.1f} us")
     assert forward < 1.15 * backward
+
+
+@pytest.mark.parametrize("i,o,r,most", [(256, 256, 64, 1.4), (1024, 1024, 64, 1.4), (1024, 1024, 128, 1.4), (4096, 512, 96, 1.4)])
+def test_packing_small_layers_at_8_bits(i, o, r, most):
+    """Packing at 8 bits against 4 where A is not in registers and every row block has a weight or two to settle, with nothing beside it
+    in its wavefront: twice the output and the sums in the stated order, but no weight after weight (1.6 to 2.4 times)."""
+    import torch
+    from paper_2402_04902_amd import binding
+    from plan_util import gpu_us
+    dev, g = torch.device("cuda:0"), 128
+    t = {4: [], 8: []}
+    calls = {}
+    for bits in t:
+        desc = binding.make_desc(LayerSpec("pack", 8, i, o, r, 2.0 * r, bits, g, DTYPE_BF16))
+        w = layer_state(i, o, r, bits, g, "moved")
+        packed, ws = torch.empty((o, bits * i // 32), dtype=torch.int32, device=dev), torch.empty(o * i, dtype=torch.uint8, device=dev)
+        calls[bits] = lambda desc=desc, w=w, packed=packed, ws=ws: binding.l4q_export_packed(desc, *w, packed, ws)
+    for _ in range(9):
+        for bits in t:
+            t[bits].append(gpu_us(calls[bits]))
+    four, eight = statistics.median(t[4]), statistics.median(t[8])
+    print(f"{o}x{i} rank {r}: 4 bits {four:.1f} us, 8 bits {eight:.1f} us")
+    assert eight < most * four
