@@ -110,7 +110,7 @@ __global__ __launch_bounds__(T::NT) void dw_fused_kernel(FusedArgs p) {
     ftail.voff_b[c] = ok && m0 + 128 + lr < p.o ? (unsigned)(((int64_t)(m0 + 128 + lr) * p.i + col) * 2)
                                                  : gemm::OOB_OFFSET;
   }
-  gemm::mainloop<T, true, true, FTail>(p.dY, p.o, p.X, p.i, p.o, p.i, p.K, m0, n0, lds, acc, ftail);
+  gemm::mainloop<T, FTail>(p.dY, p.o, p.X, p.i, p.o, p.i, p.K, m0, n0, lds, acc, ftail);
   // the operand stages are consumed (mainloop ends with a barrier after the last fragment read); slots
   // (nk + q) % NS, q = 0 .. 3, hold the factor rows
 

@@ -164,7 +164,8 @@ __device__ __forceinline__ void add_rank_term(gemm::Accum<T>& acc, const RankTer
 
 // One macro tile: main loop, then the store epilogue.  `term` (TERM): added before the main loop, while nothing else
 // of the tile is in registers.
-template <class T, bool OUT_BF16, bool A_KM, bool B_KM, bool MASK_A_K, bool B_BLK, bool TERM = false>
+// Wide tiles: K-contiguous operands, B row-major (ldb) or, B_BLK, in blocks of 32 k-values; others: K-major operands.
+template <class T, bool OUT_BF16, bool MASK_A_K = false, bool B_BLK = false, bool TERM = false>
 __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int64_t lda, const bf16_t* __restrict__ B,
                                           int64_t ldb, int M, int N, int K, int K_a, void* __restrict__ Cout,
                                           int64_t ldc, int m0, int n0, unsigned char* lds,
@@ -177,21 +178,22 @@ __device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int64_t 
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc.v[a][b][e] = 0.f;
   if constexpr (TERM) add_rank_term<T>(acc, term, M, N, m0, n0);
-  gemm::mainloop<T, A_KM, B_KM, gemm::NoTailLoads, MASK_A_K, B_BLK>(A, lda, B, ldb, M, N, K, m0, n0, lds, acc,
-                                                                   gemm::NoTailLoads(), K_a);
+  if constexpr (T::WIDE)
+    gemm::mainloop_wide<T, MASK_A_K, B_BLK>(A, lda, B, ldb, M, N, K, m0, n0, lds, acc, K_a);
+  else
+    gemm::mainloop<T>(A, lda, B, ldb, M, N, K, m0, n0, lds, acc);
   store_tile<T, OUT_BF16, T::LDS_BYTES>(acc, M, N, Cout, ldc, m0, n0, lds);
 }
 
-template <class T, bool OUT_BF16, bool A_KM = false, bool B_KM = false, bool MASK_A_K = false, bool B_BLK = false>
-__global__ __launch_bounds__(T::NT) void gemm_bf16_nt_fast_kernel(const bf16_t* __restrict__ A, int64_t lda,
-                                                                   const bf16_t* __restrict__ B, int64_t ldb, int M,
-                                                                   int N, int K, int K_a, void* __restrict__ Cout,
-                                                                   int64_t ldc, int tiles_m, int tiles_n) {
+template <class T, bool OUT_BF16, bool MASK_A_K = false, bool B_BLK = false>
+__global__ __launch_bounds__(T::NT) void gemm_bf16_fast_kernel(const bf16_t* __restrict__ A, int64_t lda,
+                                                                const bf16_t* __restrict__ B, int64_t ldb, int M, int N,
+                                                                int K, int K_a, void* __restrict__ Cout, int64_t ldc,
+                                                                int tiles_m, int tiles_n) {
   __shared__ __attribute__((aligned(1024))) unsigned char lds[T::LDS_BYTES];
   int tile_m, tile_n;
   gemm::tile_of_block(blockIdx.x, tiles_m, tiles_n, tile_m, tile_n);
-  gemm_tile<T, OUT_BF16, A_KM, B_KM, MASK_A_K, B_BLK>(A, lda, B, ldb, M, N, K, K_a, Cout, ldc, tile_m * T::BM,
-                                                      tile_n * T::BN, lds);
+  gemm_tile<T, OUT_BF16, MASK_A_K, B_BLK>(A, lda, B, ldb, M, N, K, K_a, Cout, ldc, tile_m * T::BM, tile_n * T::BN, lds);
 }
 
 // C = A . B^T + gamma U . M^T: the QAT-LoRA layer's product and its LoRA path in one pass over C.
@@ -203,7 +205,7 @@ __global__ __launch_bounds__(T::NT) void gemm_bf16_nt_rank_kernel(const bf16_t* 
   __shared__ __attribute__((aligned(1024))) unsigned char lds[T::LDS_BYTES];
   int tile_m, tile_n;
   gemm::tile_of_block(blockIdx.x, tiles_m, tiles_n, tile_m, tile_n);
-  gemm_tile<T, true, false, false, MASK_A_K, true, true>(A, lda, B, 0, M, N, K, K_a, C, ldc, tile_m * T::BM,
+  gemm_tile<T, true, MASK_A_K, true, true>(A, lda, B, 0, M, N, K, K_a, C, ldc, tile_m * T::BM,
                                                          tile_n * T::BN, lds, term);
 }
 
@@ -226,7 +228,7 @@ __global__ __launch_bounds__(T::NT) void gemm_bf16_nt_splitk_kernel(const bf16_t
   // rows of A end at K_a: inside the last slice, at or past the end of every other
   const int ka = (K_a < k1 ? K_a : k1) - k0;
   const bf16_t* Bs = B_BLK ? B + (int64_t)(k0 / T::BK) * N * T::BK : B + k0;
-  gemm_tile<T, false, false, false, MASK_A_K, B_BLK>(A + k0, lda, Bs, ldb, M, N, k1 - k0, ka,
+  gemm_tile<T, false, MASK_A_K, B_BLK>(A + k0, lda, Bs, ldb, M, N, k1 - k0, ka,
                                                      part + (int64_t)slice * M * N, N, tile_m * T::BM, tile_n * T::BN, lds);
 }
 
@@ -244,7 +246,7 @@ __global__ __launch_bounds__(T::NT) void gemm_bf16_kmajor_splitk_kernel(const bf
   const int k0 = (int)((int64_t)nk * slice / slices) * T::BK;
   int k1 = (int)((int64_t)nk * (slice + 1) / slices) * T::BK;
   if (k1 > K) k1 = K;
-  gemm_tile<T, false, true, true, false, false>(A + (int64_t)k0 * lda, lda, B + (int64_t)k0 * ldb, ldb, M, N, k1 - k0,
+  gemm_tile<T, false>(A + (int64_t)k0 * lda, lda, B + (int64_t)k0 * ldb, ldb, M, N, k1 - k0,
                                                 k1 - k0, part + (int64_t)slice * M * N, N, tile_m * T::BM,
                                                 tile_n * T::BN, lds);
 }
@@ -323,15 +325,18 @@ int device_compute_units() {
 
 namespace {
 
-// Macro tiles of the K-contiguous products; all load 32-k stages.
+// Macro tiles of the K-contiguous products.
 //   NtFull     256 x 256, 8 waves (2 x 4, two per SIMD, 128 x 64 each): a second wave on the SIMD keeps the matrix pipe busy
-//              while the first waits for a barrier or for operands (1.5 % over 2 x 2); stages loaded in cache-line pairs
-//   NtHalf     128 x 256, 4 waves (64 x 128 each), ring of six stages: 4/7 of a full tile's time for half its work
-//   NtQuarter  128 x 128, 4 waves (64 x 64 each), ring of eight stages: 2/5 of a full tile's time for a quarter of it
-// the smaller ones for products whose full tiles leave compute units idle.
-typedef gemm::Tile<256, 256, 32, 5, true, 4> NtFull;
-typedef gemm::Tile<128, 256, 32, 6, false, 2> NtHalf;
-typedef gemm::Tile<128, 128, 32, 8, false, 2> NtQuarter;
+//              while the first waits for a barrier or for operands (1.5 % over 2 x 2)
+//   NtHalf     128 x 256, 4 waves (64 x 128 each): 4/7 of a full tile's time for half its work
+//   NtQuarter  128 x 128, 4 waves (64 x 64 each): 2/5 of a full tile's time for a quarter of it
+// the smaller ones for products whose full tiles leave compute units idle.  X and dY come in rows of 128 bytes, the rings
+// fill the LDS (mainloop_wide).  Against loads of 64-byte rows (us, kernel times in the step): 2048 x 4096 x 11008 in half
+// tiles 173 -> 160, 2048 x 11008 x 4096 197 -> 172, 301 x 4096 x 4096 in quarter tiles and two slices 21.1 -> 19.0; steps of
+// both directions: 4096 x 11008 x 4096 988 -> 967, 512 x 4096 x 4096 132 -> 122, 1000 x 2048 x 2048 83.7 -> 79.7.
+typedef gemm::WideTile<256, 256, 3, 4, 4> NtFull;
+typedef gemm::WideTile<128, 256, 4, 6, 2> NtHalf;
+typedef gemm::WideTile<128, 128, 5, 8, 2> NtQuarter;
 enum NtForm { kNtFull, kNtHalf, kNtQuarter };
 
 template <class F> int64_t nt_tiles(int64_t M, int64_t N) {
@@ -428,8 +433,8 @@ int gemm_nt_splitk_slices(int64_t M, int64_t N, int64_t K, bool late) { return n
 
 namespace {
 
-// `f` with the tile type and whether rows of A need masking past K_a (an instance of its own, so that the usual shapes do
-// not pay for the selection)
+// `f` with the tile type and whether rows of A need masking past K_a, where that is no multiple of 64 (an instance of its
+// own, so that the usual shapes do not pay for the selection)
 template <class Fn> void nt_dispatch(NtForm form, bool mask, Fn&& f) {
   auto with_mask = [&](auto tile) {
     if (mask) f(tile, std::true_type());
@@ -447,7 +452,7 @@ void launch_gemm_bf16_nt(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t 
   NtPlan plan = nt_plan(M, N, K, late);
   if (plan.slices > 1 && !partial) plan = {nt_one_pass_form(M, N, K, late), 1};
   const int slices = plan.slices;
-  nt_dispatch(plan.form, K_a != K, [&](auto tile, auto mask) {
+  nt_dispatch(plan.form, K_a % 64 != 0, [&](auto tile, auto mask) {
     typedef decltype(tile) F;
     constexpr bool MASK = decltype(mask)::value;
     const int tiles_m = (int)((M + F::BM - 1) / F::BM), tiles_n = (int)((N + F::BN - 1) / F::BN);
@@ -458,7 +463,7 @@ void launch_gemm_bf16_nt(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t 
       hipLaunchKernelGGL(splitk_sum_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream, partial, slices,
                          M, N, C, ldc);
     } else {
-      hipLaunchKernelGGL((gemm_bf16_nt_fast_kernel<F, true, false, false, MASK, true>),
+      hipLaunchKernelGGL((gemm_bf16_fast_kernel<F, true, MASK, true>),
                          dim3((unsigned)(tiles_m * tiles_n)), dim3(F::NT), 0, stream, A, lda, B, ldb, (int)M, (int)N,
                          (int)K, (int)K_a, (void*)C, ldc, tiles_m, tiles_n);
     }
@@ -467,7 +472,7 @@ void launch_gemm_bf16_nt(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t 
 
 void launch_gemm_bf16_nt_rank(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t M, int64_t N, int64_t K, int64_t K_a,
                               bf16_t* C, int64_t ldc, const RankTerm& term, hipStream_t stream) {
-  nt_dispatch(nt_one_pass_form(M, N, K, false), K_a != K, [&](auto tile, auto mask) {
+  nt_dispatch(nt_one_pass_form(M, N, K, false), K_a % 64 != 0, [&](auto tile, auto mask) {
     typedef decltype(tile) F;
     const int tiles_m = (int)((M + F::BM - 1) / F::BM), tiles_n = (int)((N + F::BN - 1) / F::BN);
     hipLaunchKernelGGL((gemm_bf16_nt_rank_kernel<F, decltype(mask)::value>), dim3((unsigned)(tiles_m * tiles_n)),
@@ -479,7 +484,7 @@ void launch_gemm_bf16_kmajor_f32(const bf16_t* A, int64_t lda, const bf16_t* B, 
                                  int64_t K, float* C, int64_t ldc, hipStream_t stream) {
   typedef gemm::Tile<256, 256, 32, 4> F;
   const int tiles_m = (int)((M + F::BM - 1) / F::BM), tiles_n = (int)((N + F::BN - 1) / F::BN);
-  hipLaunchKernelGGL((gemm_bf16_nt_fast_kernel<F, false, true, true>), dim3((unsigned)(tiles_m * tiles_n)),
+  hipLaunchKernelGGL((gemm_bf16_fast_kernel<F, false>), dim3((unsigned)(tiles_m * tiles_n)),
                      dim3(F::NT), 0, stream, A, lda, B, ldb, (int)M, (int)N, (int)K, (int)K, (void*)C, ldc, tiles_m,
                      tiles_n);
 }
@@ -505,17 +510,16 @@ void launch_dw_masked_products(const LayerDims& d, const bf16_t* dWm, const bf16
                                float* rawB, hipStream_t stream) {
   int sa = 1, sb = 1;
   dw_masked_product_slices(d, &sa, &sb);
-  // rawB [sb][o, r] = dWm [o, i] . A [r, i]^T: both K-contiguous, k = i (a multiple of 32: nothing to pad or mask).  Bound
+  // rawB [sb][o, r] = dWm [o, i] . A [r, i]^T: both K-contiguous, k = i (a multiple of 32).  Bound
   // by reading dWm once.  Ranks up to 128 in 128 x 128 tiles: twice the workgroups, and half of a tile's columns at rank 64
   // instead of a quarter (rank 64 on 4096 x 11008: 22 us against 35 in 256 x 256 tiles).
-  auto thin_b = [&](auto tile) {
+  auto thin_b = [&](auto tile, auto mask) {
     typedef decltype(tile) F;
     const int tiles_m = (int)((d.o + F::BM - 1) / F::BM), tiles_n = (d.r + F::BN - 1) / F::BN;
-    hipLaunchKernelGGL((gemm_bf16_nt_splitk_kernel<F, false, false>), dim3((unsigned)(tiles_m * tiles_n), (unsigned)sb),
+    hipLaunchKernelGGL((gemm_bf16_nt_splitk_kernel<F, decltype(mask)::value, false>), dim3((unsigned)(tiles_m * tiles_n), (unsigned)sb),
                        dim3(F::NT), 0, stream, dWm, d.i, A, d.i, (int)d.o, d.r, (int)d.i, (int)d.i, rawB, tiles_m, tiles_n);
   };
-  if (d.r <= 128) thin_b(NtQuarter());
-  else thin_b(NtFull());
+  nt_dispatch(d.r <= 128 ? kNtQuarter : kNtFull, d.i % 64 != 0, thin_b);
   // rawA [sa][r, i] = B [o, r]^T . dWm [o, i]: both K-major, k = o
   {
     typedef gemm::Tile<256, 256, 32, 4> F;
