@@ -50,11 +50,17 @@ __device__ __forceinline__ bf16x8_t code_fragment(const code_chunk_t& w, int f) 
       d[r] = (spread & 0x00070007u) | 0x43004300u;
     }
   } else {
-    const uint32_t v0 = w[(2 * f) & 3], v1 = w[(2 * f + 1) & 3];  // 4 + 4 codes
-    d[0] = pack_bf16x2((float)(v0 & 0xFFu) - 128.f, (float)((v0 >> 8) & 0xFFu) - 128.f);
-    d[1] = pack_bf16x2((float)((v0 >> 16) & 0xFFu) - 128.f, (float)(v0 >> 24) - 128.f);
-    d[2] = pack_bf16x2((float)(v1 & 0xFFu) - 128.f, (float)((v1 >> 8) & 0xFFu) - 128.f);
-    d[3] = pack_bf16x2((float)((v1 >> 16) & 0xFFu) - 128.f, (float)(v1 >> 24) - 128.f);
+    // (u - 128 is the signed byte u ^ 0x80; its binary32 value has its significant bits in the upper half: exact)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const uint32_t v = w[(2 * f + h) & 3] ^ 0x80808080u;  // 4 codes
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        const uint32_t lo = __float_as_uint((float)(int8_t)(v >> (16 * r)));
+        const uint32_t hi = __float_as_uint((float)(int8_t)(v >> (16 * r + 8)));
+        d[2 * h + r] = __builtin_amdgcn_perm(hi, lo, 0x07060302u);
+      }
+    }
   }
   return __builtin_bit_cast(bf16x8_t, d);
 }

@@ -1637,6 +1637,17 @@ void launch_qgemm(const LayerDims& d, const bf16_t* X, const uint32_t* packed, c
     launch_qgemm_prefill(prompt, d, X, packed, scale, zero, Y, stream);
     return;
   }
+  // up to 64 tokens, groups of 64 and more: every byte of X and of the codes to one wave, in whole cache lines
+  const BlocksPlan blocks = qgemm_blocks_plan(d, partial != nullptr && partial_bytes >= qgemm_workspace_bytes(d) ? partial_bytes : 0);
+  if (blocks.nt > 0) {
+    launch_qgemm_blocks(blocks, d, X, packed, scale, zero, Y, partial, stream);
+    if (blocks.slices > 1) {
+      const int64_t quads = d.T * d.o / 4;
+      hipLaunchKernelGGL(qgemm_slices_sum_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream, partial, Y,
+                         blocks.slices, (int)d.T, 0, (int)d.o);
+    }
+    return;
+  }
   dim3 grid((unsigned)((d.o + 31) / 32));
   // a few token blocks at most, groups of 128 and more: the packed codes resident in registers
   if (L4Q_WREG_SWITCH) {

@@ -156,6 +156,17 @@ size_t qgemm_workspace_bytes(const LayerDims& d);
 void launch_qgemm(const LayerDims& d, const bf16_t* X, const uint32_t* packed, const float* scale, const float* zero,
                   bf16_t* Y, float* partial, size_t partial_bytes, hipStream_t stream);
 
+// The same product at one to four token blocks, groups of 64 and more (l4q_infer_blocks.hip).
+struct BlocksPlan {
+  int nt;            // 16-row tiles per workgroup; 0: not this form
+  int slices;        // k-slices: partial sums [slice][token][row] are left in `partial`, and Y is not written
+  int slice_macros;  // runs of 256 k-values of a slice
+};
+// partial_bytes: room for partial sums
+BlocksPlan qgemm_blocks_plan(const LayerDims& d, size_t partial_bytes);
+void launch_qgemm_blocks(const BlocksPlan& plan, const LayerDims& d, const bf16_t* X, const uint32_t* packed,
+                         const float* scale, const float* zero, bf16_t* Y, float* partial, hipStream_t stream);
+
 // The same product at prompt sizes (l4q_prefill.hip; more than 64 tokens, groups of 64 and more, i % 128 == 0).
 struct PrefillPlan {
   int form;   // tile shape, or -1: not covered

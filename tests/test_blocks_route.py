@@ -1,0 +1,71 @@
+"""How a quantized forward of up to 64 tokens goes through the one-pass kernel (l4q::qgemm_blocks_plan): row tiles per workgroup
+and k-slices, at sizes where the choice was measured, and that the GPU cases cover the forms they name.  Host code alone (256
+compute units are assumed)."""
+import ctypes
+
+import pytest
+
+from paper_2402_04902_amd import binding
+from plan_util import _LayerDims
+
+NOT_THIS_FORM = (0, 1)
+
+
+class _BlocksPlan(ctypes.Structure):
+    _fields_ = [("nt", ctypes.c_int), ("slices", ctypes.c_int), ("slice_macros", ctypes.c_int)]
+
+
+def blocks_form(T, i, o, bits, g, partial_bytes=1 << 30):
+    f = getattr(binding.load_library(), "_ZN3l4q17qgemm_blocks_planERKNS_9LayerDimsEm")
+    f.restype, f.argtypes = _BlocksPlan, [ctypes.POINTER(_LayerDims), ctypes.c_size_t]
+    q = float(1 << (bits - 1))
+    p = f(ctypes.byref(_LayerDims(T, i, o, 8, bits, g, 2.0, -q, q - 1.0, False)), partial_bytes)
+    return p.nt, p.slices
+
+
+# (T, in, out, bits, group), (tiles per workgroup, slices): every count of tiles and token blocks, k-slices, each code width in
+# groups of 64 and more; rows of one step to many macros that do not divide among the waves, the last one partial; ragged tiles
+GPU_CASES = [
+    ((3, 128, 40, 4, 128), (1, 1)),       # one code step, seven idle waves
+    ((16, 64, 24, 8, 64), (1, 1)),        # half a load of codes
+    ((5, 320, 72, 2, 64), (1, 1)),
+    ((16, 2176, 4104, 3, 128), (2, 1)),   # 257 tiles
+    ((9, 1600, 9000, 4, 64), (3, 1)),
+    ((33, 192, 88, 4, 64), (1, 1)),
+    ((32, 4352, 2600, 3, 256), (1, 1)),   # 17 macros: three for one wave, two for the others
+    ((31, 2368, 8200, 8, 64), (3, 1)),
+    ((40, 640, 6008, 2, 128), (2, 1)),
+    ((48, 4480, 11000, 4, 128), (3, 1)),
+    ((47, 8704, 520, 4, 512), (1, 4)),   # slices that divide groups
+    ((64, 4352, 4000, 4, 128), (2, 2)),
+    ((48, 11008, 4096, 3, 128), (2, 2)),
+    ((50, 4224, 4096, 2, 128), (1, 1)),
+    ((64, 1088, 10000, 8, 64), (3, 1)),
+    ((64, 3072, 9000, 3, 128), (3, 1)),
+    ((63, 8192, 264, 8, 64), (1, 4)),
+]
+
+
+@pytest.mark.parametrize("case,form", GPU_CASES)
+def test_gpu_cases_take_the_forms_they_name(case, form):
+    assert blocks_form(*case) == form
+
+
+@pytest.mark.parametrize("T,i,o,bits,g", [
+    (1, 4096, 11008, 4, 128),    # 8.0 in registers / 9.9
+    (8, 4096, 11008, 4, 128),    # 9.2 / 9.7
+    (2, 6144, 5120, 3, 128),     # the codes are all there is to load
+    (24, 1024, 11008, 3, 128),   # 7.5 / 8.1
+    (17, 4096, 14336, 4, 128),   # 15.7 / 17.1
+    (43, 4096, 4096, 3, 64),     # no 3 bits in groups of 64
+    (43, 4096, 4096, 4, 32),     # groups below 64
+    (65, 4096, 4096, 4, 128),    # more than four blocks
+])
+def test_other_kernels(T, i, o, bits, g):
+    assert blocks_form(T, i, o, bits, g) == NOT_THIS_FORM
+
+
+def test_slices_only_where_the_partial_sums_have_room():
+    assert blocks_form(48, 11008, 4096, 3, 128, 2 * 48 * 4096 * 4)[1] == 2
+    assert blocks_form(48, 11008, 4096, 3, 128, 2 * 48 * 4096 * 4 - 1)[1] == 1
+    assert blocks_form(64, 4096, 4096, 4, 128, 0)[1] == 1
