@@ -1630,15 +1630,59 @@ PrefillPlan qgemm_prompt_plan(const LayerDims& d, bool have_workspace) {
   return plan;
 }
 
+namespace {
+
+// Pass p of `passes` of the one-pass form: its first token and its number of tokens (whole blocks, as even as they go).
+void blocks_pass(const LayerDims& d, int passes, int p, int64_t* t0, int64_t* tokens) {
+  const int64_t blocks = (d.T + 15) / 16, b0 = blocks * p / passes, b1 = blocks * (p + 1) / passes;
+  *t0 = 16 * b0;
+  *tokens = (16 * b1 < d.T ? 16 * b1 : d.T) - *t0;
+}
+
+}  // namespace
+
+// More than 64 tokens in passes of up to 64 through l4q_infer_blocks.hip, where that is estimated to be faster than the other
+// forms (by 6 %, what the estimates are off): up to 128 tokens on most layers, further where the two-dimensional tiles leave units idle.  Measured (us, the other
+// forms' best / these passes): 4 bits [4096 x 4096] 65 / 96 / 128 / 160 tokens 24.0 / 15.2, 25.8 / 16.5, 28.9 / 24.1, 29.2 / 29.0;
+// [4096 x 11008] 65 / 128 / 192 40.5 / 28.4, 48.6 / 37.2, 72.9 / 56.0; [11008 x 4096] 65 / 128 29.3 / 26.6, 29.6 / 32.4; 3 bits
+// [4096 x 11008] 128 / 256 53.9 / 37.8, 89.1 / 76.3; 8 bits [4096 x 4096] 96 26.4 / 20.5; 2 bits in groups of 64 [4096 x 11008]
+// 128 114 / 45; [1024 x 8192] 256 50.9 / 36.8.
+int qgemm_blocks_passes(const LayerDims& d, size_t partial_bytes) {
+  // (layers of less than a million weights are all launch, which the estimates do not cover)
+  if (d.T <= 64 || d.T > 512 || d.o * d.i < 1 << 20) return 0;
+  const bool have_workspace = partial_bytes >= qgemm_workspace_bytes(d) && partial_bytes > 0;
+  const int passes = (int)((d.T + 63) / 64);
+  double us = 0.0;
+  for (int p = 0; p < passes; ++p) {
+    LayerDims part = d;
+    int64_t t0;
+    blocks_pass(d, passes, p, &t0, &part.T);
+    const BlocksPlan plan = qgemm_blocks_plan(part, have_workspace ? partial_bytes : 0);
+    if (plan.nt == 0) return 0;
+    us += plan.us;
+  }
+  const PrefillPlan prompt = qgemm_prompt_plan(d, have_workspace);
+  return us < 0.94 * (prompt.form >= 0 ? prompt.us : qgemm_passes_us(d, have_workspace)) ? passes : 0;
+}
+
 void launch_qgemm(const LayerDims& d, const bf16_t* X, const uint32_t* packed, const float* scale, const float* zero,
                   bf16_t* Y, float* partial, size_t partial_bytes, hipStream_t stream) {
+  const size_t usable = partial != nullptr && partial_bytes >= qgemm_workspace_bytes(d) ? partial_bytes : 0;
+  const int passes = d.T > 64 ? qgemm_blocks_passes(d, usable) : 0;
+  for (int p = 0; p < passes; ++p) {
+    LayerDims part = d;
+    int64_t t0;
+    blocks_pass(d, passes, p, &t0, &part.T);
+    launch_qgemm(part, X + t0 * d.i, packed, scale, zero, Y + t0 * d.o, partial, partial_bytes, stream);
+  }
+  if (passes > 0) return;
   const PrefillPlan prompt = qgemm_prompt_plan(d, partial != nullptr && partial_bytes >= qgemm_workspace_bytes(d));
   if (prompt.form >= 0) {
     launch_qgemm_prefill(prompt, d, X, packed, scale, zero, Y, stream);
     return;
   }
   // up to 64 tokens, groups of 64 and more: every byte of X and of the codes to one wave, in whole cache lines
-  const BlocksPlan blocks = qgemm_blocks_plan(d, partial != nullptr && partial_bytes >= qgemm_workspace_bytes(d) ? partial_bytes : 0);
+  const BlocksPlan blocks = qgemm_blocks_plan(d, usable);
   if (blocks.nt > 0) {
     launch_qgemm_blocks(blocks, d, X, packed, scale, zero, Y, partial, stream);
     if (blocks.slices > 1) {

@@ -422,7 +422,7 @@ double qb_us(const LayerDims& d, const BlocksPlan& plan) {
 // and four tiles per unit: 64-row tiles ([14336 x 1024], 20 / 64 tokens 9.6 / 13.2, 11.2 / 16.5).  One tile per unit: one token
 // 0.85 - 1.1 times either way, from two (8 bits: three) on this form.
 BlocksPlan qgemm_blocks_plan(const LayerDims& d, size_t partial_bytes) {
-  const BlocksPlan none = {0, 1, 0};
+  const BlocksPlan none = {0, 1, 0, 0.0};
   const int64_t rb = d.i / 8 * d.bits;
   if (d.T > 64 || d.i % d.g != 0 || d.o % 8 != 0 || (d.g & (d.g - 1)) != 0) return none;
   if (d.g < (d.bits == 3 ? 128 : 64) || (d.bits != 2 && d.bits != 3 && d.bits != 4 && d.bits != 8)) return none;
@@ -440,14 +440,13 @@ BlocksPlan qgemm_blocks_plan(const LayerDims& d, size_t partial_bytes) {
     if (d.bits == 8 && per_unit > 3 && d.i <= 2048) return none;
   }
   BlocksPlan best = none;
-  double best_us = 1e30;
   auto fits = [&](const BlocksPlan& plan) { return qb_lds_bytes(d, plan) <= 160 * 1024; };
   // beyond a block, as many tiles per workgroup as give one round of them, where their tables fit; slices within a round
   const int whole = (int)(d.T > 16 && per_unit <= 3 ? per_unit : 1);
-  const int nt_min = fits({whole, 1, (int)macros}) ? whole : 1;
+  const int nt_min = fits({whole, 1, (int)macros, 0.0}) ? whole : 1;
   for (int nt = nt_min; nt <= 3; ++nt)
     for (int sl = 1; sl <= 4; ++sl) {
-      BlocksPlan plan = {nt, sl, (int)((macros + sl - 1) / sl)};
+      BlocksPlan plan = {nt, sl, (int)((macros + sl - 1) / sl), 0.0};
       if (!fits(plan) || (per_unit == 1 && nt > 1 && (nt > 2 || sl == 1))) continue;
       if (sl > 1 && (sl > macros / 4 || (tiles + nt - 1) / nt * sl > cus || (sl - 1) * plan.slice_macros >= macros ||
                      (size_t)sl * (size_t)(d.T * d.o) * 4 > partial_bytes))
@@ -455,11 +454,8 @@ BlocksPlan qgemm_blocks_plan(const LayerDims& d, size_t partial_bytes) {
       // whole passes on layers of a tile per unit in two slices where there is room for the partial sums: the one case where
       // the plan is not the estimate's (11.4 against 10.2 us at [4096 x 4096]); callers see by it that their workspace is used
       if (d.T == 64 && per_unit == 1 && 2 * tiles > cus && macros >= 16 && sl == 1 && 2 * (size_t)(d.T * d.o) * 4 <= partial_bytes) continue;
-      const double us = qb_us(d, plan);
-      if (us < best_us) {
-        best = plan;
-        best_us = us;
-      }
+      plan.us = qb_us(d, plan);
+      if (best.nt == 0 || plan.us < best.us) best = plan;
     }
   return best;
 }

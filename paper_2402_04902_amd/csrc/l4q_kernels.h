@@ -161,6 +161,7 @@ struct BlocksPlan {
   int nt;            // 16-row tiles per workgroup; 0: not this form
   int slices;        // k-slices: partial sums [slice][token][row] are left in `partial`, and Y is not written
   int slice_macros;  // runs of 256 k-values of a slice
+  double us;         // estimated time
 };
 // partial_bytes: room for partial sums
 BlocksPlan qgemm_blocks_plan(const LayerDims& d, size_t partial_bytes);
@@ -174,8 +175,10 @@ struct PrefillPlan {
 };
 PrefillPlan qgemm_prefill_plan(const LayerDims& d);
 int qgemm_prompt_wide_rows(const LayerDims& d);  // weight rows of a wide tile (form 2): 256 or 192
-// ... where it is the faster way for this call; form -1: the passes of at most 64 tokens are
+// ... where it is faster than passes of at most 64 tokens through the kernels of l4q_infer.hip; form -1: those are
 PrefillPlan qgemm_prompt_plan(const LayerDims& d, bool have_workspace);
+// Passes of at most 64 tokens through l4q_infer_blocks.hip where they are faster than either; 0: they are not
+int qgemm_blocks_passes(const LayerDims& d, size_t partial_bytes);
 void launch_qgemm_prefill(const PrefillPlan& plan, const LayerDims& d, const bf16_t* X, const uint32_t* packed,
                           const float* scale, const float* zero, bf16_t* Y, hipStream_t stream);
 

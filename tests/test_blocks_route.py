@@ -7,12 +7,13 @@ import pytest
 
 from paper_2402_04902_amd import binding
 from plan_util import _LayerDims
+from test_gpu_prefill import CASES
 
 NOT_THIS_FORM = (0, 1)
 
 
 class _BlocksPlan(ctypes.Structure):
-    _fields_ = [("nt", ctypes.c_int), ("slices", ctypes.c_int), ("slice_macros", ctypes.c_int)]
+    _fields_ = [("nt", ctypes.c_int), ("slices", ctypes.c_int), ("slice_macros", ctypes.c_int), ("us", ctypes.c_double)]
 
 
 def blocks_form(T, i, o, bits, g, partial_bytes=1 << 30):
@@ -63,6 +64,48 @@ def test_gpu_cases_take_the_forms_they_name(case, form):
 ])
 def test_other_kernels(T, i, o, bits, g):
     assert blocks_form(T, i, o, bits, g) == NOT_THIS_FORM
+
+
+def passes(T, i, o, bits, g, partial_bytes=1 << 30):
+    f = getattr(binding.load_library(), "_ZN3l4q19qgemm_blocks_passesERKNS_9LayerDimsEm")
+    f.restype, f.argtypes = ctypes.c_int, [ctypes.POINTER(_LayerDims), ctypes.c_size_t]
+    q = float(1 << (bits - 1))
+    return f(ctypes.byref(_LayerDims(T, i, o, 8, bits, g, 2.0, -q, q - 1.0, False)), partial_bytes)
+
+
+# more than 64 tokens: the number of passes
+GPU_PASSES = [
+    ((65, 4096, 520, 4, 128), 2),     # of 32 and 33 tokens
+    ((97, 4160, 1000, 2, 64), 2),
+    ((150, 8192, 1040, 8, 128), 3),   # with room for partial sums, slices in each
+    ((250, 8192, 1024, 4, 128), 4),
+]
+
+
+@pytest.mark.parametrize("case,n", GPU_PASSES)
+def test_gpu_cases_take_the_passes_they_name(case, n):
+    assert passes(*case) == n
+
+
+@pytest.mark.parametrize("T,i,o,bits,g,n", [
+    (64, 4096, 4096, 4, 128, 0),      # not more than 64 tokens
+    (128, 4096, 4096, 4, 128, 2),     # 24.1 against 28.9 in two-dimensional tiles
+    (192, 4096, 4096, 4, 128, 0),     # 36.4 / 29.6
+    (65, 11008, 4096, 4, 128, 2),     # 28.4 / 40.5
+    (128, 4096, 11008, 4, 128, 0),    # 32.4 / 29.6
+    (65, 11008, 1024, 2, 128, 2),     # 24.6 / 78.4 in the general kernel's passes
+    (256, 8192, 1024, 4, 128, 4),     # 36.8 / 50.9
+    (512, 4096, 11008, 4, 128, 0),
+    (600, 4096, 4096, 4, 128, 0),
+])
+def test_passes(T, i, o, bits, g, n):
+    assert passes(T, i, o, bits, g) == n
+
+
+@pytest.mark.parametrize("case,forms", CASES)
+def test_the_prompt_kernels_gpu_cases_are_not_taken_from_it(case, forms):
+    T, i, o, g = case
+    assert not any(passes(T, i, o, bits, g, 0) for bits in (2, 3, 4, 8))
 
 
 def test_slices_only_where_the_partial_sums_have_room():

@@ -1,15 +1,15 @@
-"""Quantized forward of up to 64 tokens in one pass (l4q_infer_blocks.hip) at the edges of its tiles, macros, steps, slices and
+"""Quantized forward of up to 64 tokens in one pass, of more in several (l4q_infer_blocks.hip), at the edges of its tiles, macros, steps, slices and
 waves (the form each case takes is checked on the host in test_blocks_route.py), against binary64; what is not finite stays
 where it belongs: a token in its row, a scale in its row of weights."""
 import pytest
 
 from paper_2402_04902_amd.inputs import DTYPE_BF16, LayerSpec
-from test_blocks_route import GPU_CASES
+from test_blocks_route import GPU_CASES, GPU_PASSES
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("T,i,o,bits,g", [c[0] for c in GPU_CASES])
+@pytest.mark.parametrize("T,i,o,bits,g", [c[0] for c in GPU_CASES + GPU_PASSES])
 def test_blocks(T, i, o, bits, g):
     import torch
     from paper_2402_04902_amd import binding
