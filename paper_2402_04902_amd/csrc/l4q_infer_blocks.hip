@@ -30,9 +30,6 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// Groups that a wave can meet in its run of `steps` k-steps, wherever it starts.
-__host__ __device__ constexpr int qb_wave_groups(int steps, int kstep, int g) { return (steps * kstep - 1) / g + 2; }
-
 // The codes of 8 consecutive k-values: 8 BITS bits (8 bits: two dwords).
 template <int BITS> struct CodeWindow { uint32_t v[BITS == 8 ? 2 : 1]; };
 
@@ -82,7 +79,7 @@ struct QbArgs {
   float* part;       // null: one slice
   int T, o, i, gshift;
   int slice_macros;  // runs of 256 k-values of a slice
-  int tab_groups;    // groups of a wave's tables (row pitch: this, made odd)
+  int tab_groups;    // groups that a slice can meet
 };
 
 constexpr int qb_ring(int tb) { return tb <= 2 ? 4 : 2; }  // steps of 64 k-values of X per wave in LDS
@@ -126,8 +123,8 @@ __global__ __launch_bounds__(QB_WAVES * 64) void qgemm_blocks_kernel(QbArgs p) {
 
   unsigned char* const ring = qb_lds + wave * (R * TB * 2048);
   const int pitch = ((p.tab_groups + 1) / 2) | 1;  // pairs of groups, 16 bytes each
-  const int grp0 = k_first >> p.gshift;
-  unsigned char* const tab = qb_lds + QB_WAVES * (R * TB * 2048) + wave * (NT * 16 * pitch * 16);
+  const int grp0 = (sl0 * 256) >> p.gshift;
+  unsigned char* const tab = qb_lds + QB_WAVES * (R * TB * 2048);
   auto row_of = [&](int n) { return ((int)blockIdx.x * NT + n) * 16; };
 
   // X: load c of a step fetches 128 bytes of tokens 8 c .. 8 c + 7; chunk e of token row r at position e ^ (r / 2) % 8
@@ -188,43 +185,46 @@ __global__ __launch_bounds__(QB_WAVES * 64) void qgemm_blocks_kernel(QbArgs p) {
     }
   };
 
-  // scale and zero of the groups this wave meets: lane (row ln, kq) fetches groups 4 kq .. 4 kq + 3 of them (and 16
-  // further on, where there are more), which pass through LDS of the wave's own
+  // scale and zero - K0 scale of the workgroup's rows and the slice's groups, pairs of them, by way of LDS: a thread fetches
+  // four groups of a row.  Requested first, so that nothing behind them is waited for.  (By each wave for itself, its own
+  // groups of 16 rows a load, they took the unit's cache about 1 us.)
   {
-    float4 sv[NT], zv[NT];
-    auto fetch = [&](int c) {
-#pragma unroll
-      for (int n = 0; n < NT; ++n) {
-        const unsigned off = row_of(n) + ln < p.o ? (unsigned)(((row_of(n) + ln) * G + grp0 + c) * 4) : gemm::OOB_OFFSET;
-        sv[n] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rsrcS, (int)off, 0, 0));
-        zv[n] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rsrcZ, (int)off, 0, 0));
-      }
+    const int ppr = (p.tab_groups + 3) / 4, pieces = NT * 16 * ppr;
+    float4 sv, zv;
+    int row, c;
+    auto fetch = [&](int piece) {
+      row = piece / ppr;
+      c = piece - row * ppr;
+      const unsigned off = piece < pieces && row_of(0) + row < p.o ? (unsigned)(((row_of(0) + row) * G + grp0 + 4 * c) * 4) : gemm::OOB_OFFSET;
+      sv = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rsrcS, (int)off, 0, 0));
+      zv = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rsrcZ, (int)off, 0, 0));
     };
-    auto put = [&](int c) {
-#pragma unroll
-      for (int n = 0; n < NT; ++n) {
-        unsigned char* dst = tab + (n * 16 + ln) * pitch * 16 + c * 8;
-        const float s4[4] = {sv[n].x, sv[n].y, sv[n].z, sv[n].w}, z4[4] = {zv[n].x, zv[n].y, zv[n].z, zv[n].w};
+    auto put = [&](int piece) {
+      if (piece < pieces) {
+        unsigned char* dst = tab + (row * pitch + 2 * c) * 16;
+        const float s4[4] = {sv.x, sv.y, sv.z, sv.w}, z4[4] = {zv.x, zv.y, zv.z, zv.w};
 #pragma unroll
         for (int e = 0; e < 4; e += 2)
-          if (c + e < p.tab_groups)
+          if (2 * c + e / 2 < pitch)
             *reinterpret_cast<bf16x8_t*>(dst + 8 * e) = __builtin_bit_cast(
                 bf16x8_t, make_float4(s4[e], z4[e] - K0 * s4[e], s4[e + 1], z4[e + 1] - K0 * s4[e + 1]));
       }
     };
 #pragma unroll 1
-    for (int c = 16 + 4 * kq; c - 4 * kq < p.tab_groups; c += 16) {  // (more than 16 groups: long rows of small groups)
-      fetch(c);
-      put(c);
+    for (int piece = (int)threadIdx.x + QB_WAVES * 64; piece < pieces; piece += QB_WAVES * 64) {  // (small groups)
+      fetch(piece);
+      put(piece);
     }
-    fetch(4 * kq);
+    fetch((int)threadIdx.x);
     __builtin_amdgcn_sched_barrier(0);
     load_w(0, 0);
-    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int x = 0; x < R; ++x) load_x(x, x);
     __builtin_amdgcn_sched_barrier(0);
-    put(4 * kq);
+    put((int)threadIdx.x);
+    __builtin_amdgcn_s_waitcnt(gemm::waitcnt_lgkm0());
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
   }
   const unsigned char* tab_row = tab + ln * pitch * 16;
 
@@ -369,14 +369,17 @@ __global__ __launch_bounds__(QB_WAVES * 64) void qgemm_blocks_kernel(QbArgs p) {
 
 int qb_kstep(const LayerDims& d) { return d.bits == 8 || d.g == 64 ? 64 : 128; }
 
+// groups that a slice can meet, wherever it starts
 int qb_groups(const LayerDims& d, const BlocksPlan& plan) {
-  return qb_wave_groups((plan.slice_macros + QB_WAVES - 1) / QB_WAVES, 256, d.g);
+  if (plan.slices == 1) return (int)(d.i / d.g);
+  const int64_t n = ((int64_t)plan.slice_macros * 256 - 1) / d.g + 2;
+  return (int)(n < d.i / d.g ? n : d.i / d.g);
 }
 
 size_t qb_lds_bytes(const LayerDims& d, const BlocksPlan& plan) {
   const int tb = (int)((d.T + 15) / 16);
   const size_t ring = (size_t)QB_WAVES * qb_ring(tb) * tb * 2048;
-  const size_t tab = (size_t)QB_WAVES * plan.nt * 16 * (((qb_groups(d, plan) + 1) / 2) | 1) * 16;
+  const size_t tab = (size_t)plan.nt * 16 * (((qb_groups(d, plan) + 1) / 2) | 1) * 16;
   const size_t red = (size_t)plan.nt * tb * QB_WAVES * 1024;
   return ring + tab > red ? ring + tab : red;
 }
