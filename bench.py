@@ -322,7 +322,7 @@ def main() -> int:
                                            qfws, tok)
     del packs2
 
-    # the QAT-LoRA layer (Sec. 3.1) on the same workload: separate LoRA path, stored weight gradient
+    # the QAT-LoRA layer (Sec. 3.1) on the same workload: separate LoRA path, room for the weight gradient
     qws_f, qws_b = zip(*[binding.l4q_qatlora_workspace_bytes(l.desc) for l in layers])
     qws = torch.empty(max(max(qws_f), max(qws_b)), dtype=torch.uint8, device="cuda:0")
 

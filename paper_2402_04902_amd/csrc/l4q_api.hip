@@ -259,7 +259,7 @@ struct QlFwdWs {
 struct QlBwdWs {
   float* wq32;    // [o, i]      (binary32 mode)
   bf16_t* wqT;    // [i, opad], in blocks of 32   (bf16)
-  float* dwq;     // [o, i]      the stored weight gradient
+  float* dwq;     // [o, i]      the weight gradient where it is stored; dB's partial sums
   float* dyb;     // [T, r]
   float* xa;      // [T, r]
   float* part;    // [token blocks, r, max(i, o)]
@@ -621,10 +621,14 @@ int l4q_qatlora_backward(const l4q_desc* desc, const void* X, const void* dY, co
     const l4q::LoraDown down[2] = {{dYb, d.o, bT, d.o, w.dyb}, {Xb, d.i, Ab, d.i, w.xa}};
     l4q::launch_lora_down(down, 2, d.T, d.r, stream);
     gemm_nt_rank(dYb, d.o, w.wqT, d.T, d.i, w.opad, d.o, (bf16_t*)dX, {w.dyb, Ab, d.r, d.gamma, false}, stream);
-    // the weight gradient is materialised: scale and zero are updated from it
-    l4q::launch_gemm_bf16_kmajor_f32(dYb, d.o, Xb, d.i, d.o, d.i, d.T, w.dwq, d.i, stream);
-    l4q::launch_quant_grads<bf16_t>(dq, W0b, Ab, Bb, scale, zero, w.dwq, dscale, dzero, nullptr, stream);
-    if (l4q::lora_tn_blocks(d.T) * d.r <= d.i) {  // the weight gradient has been used: its place takes dB's partial sums
+    // scale and zero are updated from the weight gradient, in the product's epilogue where it covers the groups
+    if (l4q::dw_groups_supported(d)) {
+      l4q::launch_dw_groups(dq, dYb, Xb, W0b, scale, zero, dscale, dzero, stream);
+    } else {
+      l4q::launch_gemm_bf16_kmajor_f32(dYb, d.o, Xb, d.i, d.o, d.i, d.T, w.dwq, d.i, stream);
+      l4q::launch_quant_grads<bf16_t>(dq, W0b, Ab, Bb, scale, zero, w.dwq, dscale, dzero, nullptr, stream);
+    }
+    if (l4q::lora_tn_blocks(d.T) * d.r <= d.i) {  // the weight gradient's place, not in use any more, takes dB's partial sums
       l4q::launch_tn_pair(w.dyb, Xb, d.i, dA, w.part, w.xa, dYb, d.o, dB, w.dwq, d.T, d.r, d.gamma, d.accumulate, stream);
     } else {
       l4q::launch_tn<bf16_t, float>(w.dyb, Xb, d.T, d.i, d.r, false, w.part, d.gamma, dA, d.accumulate, stream);

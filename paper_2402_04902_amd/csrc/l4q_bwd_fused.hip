@@ -27,6 +27,13 @@
 // second form: group sums as above, and the masked tile m * dWq, which the epilogue has in LDS anyway, leaves as
 // bfloat16 [o, i] (half of what a stored binary32 dWq would take); dA and dB are then two thin products on the matrix
 // core (launch_dw_masked_products).
+//
+// QAT-LoRA.  A third form keeps the group sums alone.  The quantizer sees W0, so the factor is made in the epilogue, by the
+// stated binary32 operations, from the tile of W0 that takes the factors' way into LDS: no weight gradient is stored and no
+// pass reads it again.  4096 x 4096, 2048 tokens: 66 us, against 62 for the product that stored dWq and 26 - 32 for the pass
+// over it and W0 (16 vector operations for each of a lane's 256 elements, 8 us at full rate).
+#include <type_traits>
+
 #include "l4q_device.h"
 #include "l4q_gemm_core.h"
 #include "l4q_kernels.h"
@@ -52,7 +59,9 @@ struct FusedArgs {
   const bf16_t* X;                    // [T, i]
   int K;                              // T
   int o, i, r, g;
-  const uint16_t* fgrad;              // [o, i] binary16
+  const uint16_t* fgrad;              // [o, i] binary16; kDwGroupsOnly: W0, bfloat16
+  const float* scale; const float* zero;  // kDwGroupsOnly: [o, i/g]
+  float qn, qp;
   const bf16_t* A;                    // [r, i]
   const bf16_t* BT; int64_t ld_bt;    // [r, ld_bt], zero beyond o
   float* dscale; float* dzero;        // [o, i/g]
@@ -69,8 +78,13 @@ __device__ __forceinline__ bf16x8_t as_bf16x8(uint32_t a, uint32_t b, uint32_t c
   return __builtin_bit_cast(bf16x8_t, v);
 }
 
-// STORE_MASKED = false: dA / dB partial sums in the epilogue (rank <= 32).  true: the masked tile is written out.
-template <bool STORE_MASKED>
+// What the epilogue makes of the tile.
+enum DwForm {
+  kDwRankSums,     // dA / dB partial sums (rank <= 32)
+  kDwStoreMasked,  // the masked tile is written out
+  kDwGroupsOnly    // dscale and dzero alone (QAT-LoRA: the quantizer sees W0, its factor is made here from the tile of W0)
+};
+template <DwForm FORM>
 __global__ __launch_bounds__(T::NT) void dw_fused_kernel(FusedArgs p) {
   __shared__ __attribute__((aligned(1024))) unsigned char lds[FUSED_LDS];
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -89,6 +103,7 @@ __global__ __launch_bounds__(T::NT) void dw_fused_kernel(FusedArgs p) {
     for (int b = 0; b < T::TN; ++b)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc.v[a][b][e] = 0.f;
+  const int G = p.i / p.g;
   // The d(Wq)/d(scale) factors of the tile (128 KiB of a weight-sized array streamed once from HBM) are needed right
   // after the main loop.  They ride on the loads the loop issues for the four stages past the
   // end of K: tail stage q brings the factor rows of row block a = q (32 rows of the upper and of the lower wave
@@ -114,6 +129,26 @@ __global__ __launch_bounds__(T::NT) void dw_fused_kernel(FusedArgs p) {
   // the operand stages are consumed (mainloop ends with a barrier after the last fragment read); slots
   // (nk + q) % NS, q = 0 .. 3, hold the factor rows
 
+  // scale and zero of this lane's rows, per 32 columns (rows and columns past the matrix: the last ones')
+  [[maybe_unused]] float gs[T::TM][T::TN], gz[T::TM][T::TN];
+  if constexpr (FORM == kDwGroupsOnly) {
+#pragma unroll
+    for (int a = 0; a < T::TM; ++a) {
+      const int row = m0 + wm * 128 + a * 32 + l32, rc = row < p.o ? row : p.o - 1;
+#pragma unroll
+      for (int b = 0; b < T::TN; ++b) {
+        if (b == 0 || (p.g < 128 && (b % 2 == 0 || p.g == 32))) {
+          const int q = (n0 + wn * 128 + b * 32) / p.g, qc = q < G ? q : G - 1;
+          gs[a][b] = p.scale[(int64_t)rc * G + qc];
+          gz[a][b] = p.zero[(int64_t)rc * G + qc];
+        } else {
+          gs[a][b] = gs[a][b - 1];
+          gz[a][b] = gz[a][b - 1];
+        }
+      }
+    }
+  }
+
   // ---- fragments of the LoRA factor A for the dB product: lane = rank index, 8 k-slots = the same
   //      column pattern the accumulator registers 8h .. 8h+7 of a lane group have
   bf16x8_t afrag[T::TN][2];
@@ -123,7 +158,7 @@ __global__ __launch_bounds__(T::NT) void dw_fused_kernel(FusedArgs p) {
     for (int h = 0; h < 2; ++h) {
       const int j = n0 + wn * 128 + b * 32 + 16 * h + 4 * lh;
       uint2 lo = make_uint2(0, 0), hi = make_uint2(0, 0);
-      if (!STORE_MASKED && l32 < p.r && j < p.i) {  // i is a multiple of 32 here (g >= 32), so a 32-column tile is inside or outside as a whole
+      if (FORM == kDwRankSums && l32 < p.r && j < p.i) {  // i is a multiple of 32 here (g >= 32), so a 32-column tile is inside or outside as a whole
         lo = *reinterpret_cast<const uint2*>(p.A + (int64_t)l32 * p.i + j);
         hi = *reinterpret_cast<const uint2*>(p.A + (int64_t)l32 * p.i + j + 8);
       }
@@ -134,54 +169,95 @@ __global__ __launch_bounds__(T::NT) void dw_fused_kernel(FusedArgs p) {
   // The factors this lane needs: 64 pieces of 4 consecutive columns, one per (row block, column tile, register
   // group), all four row blocks read out of the ring slots (nk + a) % NS, after which the LDS is free for the
   // epilogue.  Rows and columns past the matrix: the LDS pieces are zeros, and so are their accumulators.
+  // (kDwGroupsOnly puts nothing in their place: one row block's at a time.)
   typedef _Float16 h4 __attribute__((ext_vector_type(4)));
   h4 fpre[T::TM][T::TN][4];
-  {
-    const int nk = (p.K + T::BK - 1) / T::BK;
+  const int nk = (p.K + T::BK - 1) / T::BK;
+  auto read_factors = [&](int a) {
+    const unsigned char* rowp = lds + ((nk + a) % T::NS) * T::STAGE + wm * (32 * 512) + l32 * 512 + lh * 8;
 #pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      const unsigned char* rowp = lds + ((nk + a) % T::NS) * T::STAGE + wm * (32 * 512) + l32 * 512 + lh * 8;
+    for (int b = 0; b < T::TN; ++b)
 #pragma unroll
-      for (int b = 0; b < T::TN; ++b)
+      for (int eg = 0; eg < 4; ++eg)
+        fpre[a][b][eg] = *reinterpret_cast<const h4*>(rowp + (((wn * 16 + b * 4 + eg) ^ l32) << 4));
+  };
+  if constexpr (FORM != kDwGroupsOnly) {
 #pragma unroll
-        for (int eg = 0; eg < 4; ++eg)
-          fpre[a][b][eg] = *reinterpret_cast<const h4*>(rowp + (((wn * 16 + b * 4 + eg) ^ l32) << 4));
-    }
+    for (int a = 0; a < T::TM; ++a) read_factors(a);
+    __builtin_amdgcn_s_waitcnt(gemm::waitcnt_lgkm0());
+    __builtin_amdgcn_s_barrier();  // every wave has its factors in registers: the LDS is free from here on
   }
-  __builtin_amdgcn_s_waitcnt(gemm::waitcnt_lgkm0());
-  __builtin_amdgcn_s_barrier();  // every wave has its factors in registers: the LDS is free from here on
 
-  const int G = p.i / p.g;
   auto put = [&](float* dst, float v) { *dst = p.accumulate ? *dst + v : v; };  // each element has one writer
   float keep_ds[T::TM], keep_db[T::TM];  // g == 256: this wave's half of the group, per row block
   f32x16_t accB[T::TM];
 
+  // (kDwGroupsOnly: a scale outside the range of the reciprocal anywhere in the wave takes its IEEE divide)
+  [[maybe_unused]] bool slow = false;
+  if constexpr (FORM == kDwGroupsOnly) {
+    bool bad = false;
+#pragma unroll
+    for (int a = 0; a < T::TM; ++a)
+#pragma unroll
+      for (int b = 0; b < T::TN; ++b) bad |= !scale_in_fast_range(gs[a][b]);
+    slow = __builtin_amdgcn_ballot_w64(bad) != 0;
+  }
 #pragma unroll
   for (int a = 0; a < T::TM; ++a) {
     const int row = m0 + wm * 128 + a * 32 + l32;  // the weight row this lane owns in block a
     const bool row_ok = row < p.o;
     float ds_b[T::TN], db_b[T::TN];
     uint32_t pk[T::TN][8];
+    if constexpr (FORM == kDwGroupsOnly) {
+      __builtin_amdgcn_sched_barrier(0);
+      read_factors(a);
+      auto columns = [&](auto slow_tag) {
 #pragma unroll
-    for (int b = 0; b < T::TN; ++b) {
-      ds_b[b] = 0.f;
-      db_b[b] = 0.f;
+        for (int b = 0; b < T::TN; ++b) {
+          ds_b[b] = 0.f;
+          db_b[b] = 0.f;
+          const float s = gs[a][b], z = gz[a][b], rc = exact_reciprocal(s), hi = s * 1024.f;
 #pragma unroll
-      for (int eg = 0; eg < 4; ++eg) {
-        const h4 fh = fpre[a][b][eg];
-        float xm[4];
+          for (int eg = 0; eg < 4; ++eg) {
+            const uint2 v = __builtin_bit_cast(uint2, fpre[a][b][eg]);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float x = acc.v[a][b][4 * eg + e];
-          const float f = (float)fh[e];
-          // one use of the comparison (a second one keeps 64 lane masks alive in scalar registers and spills them):
-          // x - xm is exactly x where the element is clipped and 0 elsewhere
-          xm[e] = __builtin_fabsf16(fh[e]) > (_Float16)0.75f ? 0.f : x;  // decided on the stored binary16 value
-          ds_b[b] = fmaf(x, f, ds_b[b]);
-          db_b[b] += x - xm[e];
+            for (int e = 0; e < 4; ++e) {
+              const uint32_t two = e < 2 ? v.x : v.y;
+              const float w0 = __uint_as_float(e % 2 ? two & 0xFFFF0000u : two << 16);
+              const float x = acc.v[a][b][4 * eg + e], xz = w0 - z;
+              const float w = decltype(slow_tag)::value ? __fdiv_rn(xz, s) : fast_quotient(xz, s, rc, hi);
+              const float cl = __builtin_amdgcn_fmed3f(w, p.qn, p.qp), code = rintf(cl);
+              const bool in = cl == w;  // in range = the clamp changed nothing
+              ds_b[b] = fmaf(x, in ? code - w : code, ds_b[b]);
+              db_b[b] += in ? 0.f : x;
+            }
+          }
         }
-        pk[b][2 * eg] = pack_bf16x2(xm[0], xm[1]);
-        pk[b][2 * eg + 1] = pack_bf16x2(xm[2], xm[3]);
+      };
+      if (slow) columns(std::true_type());
+      else columns(std::false_type());
+    } else {
+#pragma unroll
+      for (int b = 0; b < T::TN; ++b) {
+        ds_b[b] = 0.f;
+        db_b[b] = 0.f;
+#pragma unroll
+        for (int eg = 0; eg < 4; ++eg) {
+          const h4 fh = fpre[a][b][eg];
+          float xm[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float x = acc.v[a][b][4 * eg + e];
+            const float f = (float)fh[e];
+            // one use of the comparison (a second one keeps 64 lane masks alive in scalar registers and spills them):
+            // x - xm is exactly x where the element is clipped and 0 elsewhere
+            xm[e] = __builtin_fabsf16(fh[e]) > (_Float16)0.75f ? 0.f : x;  // decided on the stored binary16 value
+            ds_b[b] = fmaf(x, f, ds_b[b]);
+            db_b[b] += x - xm[e];
+          }
+          pk[b][2 * eg] = pack_bf16x2(xm[0], xm[1]);
+          pk[b][2 * eg + 1] = pack_bf16x2(xm[2], xm[3]);
+        }
       }
     }
 
@@ -221,15 +297,16 @@ __global__ __launch_bounds__(T::NT) void dw_fused_kernel(FusedArgs p) {
           put(p.dscale + (int64_t)row * G + q, ds);
           put(p.dzero + (int64_t)row * G + q, db);
         }
-      } else if (wn == 1 && lh == 0) {  // g == 256: hand the right half to the left wave
+      } else if (FORM != kDwGroupsOnly && wn == 1 && lh == 0) {  // g == 256: hand the right half to the left wave
         float* sc = reinterpret_cast<float*>(lds + EP_TILE) + (wm * 128 + a * 32 + l32) * 2;
         sc[0] = ds;
         sc[1] = db;
       }
     }
 
+    if constexpr (FORM == kDwGroupsOnly) continue;
     // ---- dB: (masked gradient) x A^T on the matrix core, 2 k-steps of 16 columns per 32-column tile
-    if constexpr (!STORE_MASKED) {
+    if constexpr (FORM == kDwRankSums) {
       f32x16_t cb;
 #pragma unroll
       for (int e = 0; e < 16; ++e) cb[e] = 0.f;
@@ -256,7 +333,19 @@ __global__ __launch_bounds__(T::NT) void dw_fused_kernel(FusedArgs p) {
     }
   }
 
-  if constexpr (STORE_MASKED) {
+  if constexpr (FORM != kDwRankSums) {
+    if constexpr (FORM == kDwGroupsOnly) {
+      if (p.g != 256) return;
+      __syncthreads();  // every wave has read its weights
+      if (wn == 1 && lh == 0) {
+#pragma unroll
+        for (int a = 0; a < T::TM; ++a) {
+          float* sc = reinterpret_cast<float*>(lds + EP_TILE) + (wm * 128 + a * 32 + l32) * 2;
+          sc[0] = keep_ds[a];
+          sc[1] = keep_db[a];
+        }
+      }
+    }
     __syncthreads();
     if (p.g == 256 && wn == 0 && lh == 0) {
       const int q = n0 / 256;
@@ -270,6 +359,7 @@ __global__ __launch_bounds__(T::NT) void dw_fused_kernel(FusedArgs p) {
         }
       }
     }
+    if constexpr (FORM == kDwGroupsOnly) return;
     // ---- the masked tile leaves as it lies in LDS: 16 bytes per lane, a 512-byte row per 32 lanes; rows past o and
     //      columns past i (whole 16-byte pieces: i % 8 == 0) get an out-of-range offset
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(p.dWm, 0, (int)((int64_t)p.o * p.i * 2),
@@ -397,7 +487,7 @@ void dw_fused_tiles(const LayerDims& d, int* tiles_m, int* tiles_n) {
 void launch_dw_fused(const LayerDims& d, const bf16_t* dY, const bf16_t* X, const uint16_t* fgrad, const bf16_t* A,
                      const bf16_t* BT, int64_t ld_bt, float* dscale, float* dzero, float* dA_part, float* dB_part,
                      hipStream_t stream) {
-  FusedArgs p;
+  FusedArgs p = {};
   p.dY = dY;
   p.X = X;
   p.K = (int)d.T;
@@ -407,7 +497,7 @@ void launch_dw_fused(const LayerDims& d, const bf16_t* dY, const bf16_t* X, cons
   p.dWm = nullptr;
   dw_fused_tiles(d, &p.tiles_m, &p.tiles_n);
   p.accumulate = d.accumulate ? 1 : 0;
-  hipLaunchKernelGGL(dw_fused_kernel<false>, dim3((unsigned)(p.tiles_m * p.tiles_n)), dim3(T::NT), 0, stream, p);
+  hipLaunchKernelGGL(dw_fused_kernel<kDwRankSums>, dim3((unsigned)(p.tiles_m * p.tiles_n)), dim3(T::NT), 0, stream, p);
 }
 
 void launch_dw_masked(const LayerDims& d, const bf16_t* dY, const bf16_t* X, const uint16_t* fgrad, float* dscale,
@@ -422,7 +512,27 @@ void launch_dw_masked(const LayerDims& d, const bf16_t* dY, const bf16_t* X, con
   p.dWm = dWm;
   dw_fused_tiles(d, &p.tiles_m, &p.tiles_n);
   p.accumulate = d.accumulate ? 1 : 0;
-  hipLaunchKernelGGL(dw_fused_kernel<true>, dim3((unsigned)(p.tiles_m * p.tiles_n)), dim3(T::NT), 0, stream, p);
+  hipLaunchKernelGGL(dw_fused_kernel<kDwStoreMasked>, dim3((unsigned)(p.tiles_m * p.tiles_n)), dim3(T::NT), 0, stream, p);
+}
+
+bool dw_groups_supported(const LayerDims& d) {
+  return (d.g == 32 || d.g == 64 || d.g == 128 || d.g == 256) && d.i < (1 << 22);
+}
+
+void launch_dw_groups(const LayerDims& d, const bf16_t* dY, const bf16_t* X, const bf16_t* W0, const float* scale,
+                      const float* zero, float* dscale, float* dzero, hipStream_t stream) {
+  FusedArgs p = {};
+  p.dY = dY;
+  p.X = X;
+  p.K = (int)d.T;
+  p.o = (int)d.o; p.i = (int)d.i; p.r = d.r; p.g = d.g;
+  p.fgrad = W0;
+  p.scale = scale; p.zero = zero;
+  p.qn = d.qn; p.qp = d.qp;
+  p.dscale = dscale; p.dzero = dzero;
+  dw_fused_tiles(d, &p.tiles_m, &p.tiles_n);
+  p.accumulate = d.accumulate ? 1 : 0;
+  hipLaunchKernelGGL(dw_fused_kernel<kDwGroupsOnly>, dim3((unsigned)(p.tiles_m * p.tiles_n)), dim3(T::NT), 0, stream, p);
 }
 
 }  // namespace l4q

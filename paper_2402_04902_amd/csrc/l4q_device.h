@@ -94,6 +94,35 @@ __device__ __forceinline__ QuantOut quantize_elem(float wc, float s, float b, fl
   return q;
 }
 
+// ---- the quotient of quantize_elem without the IEEE divide's sequence ----
+// RN(1 / s) for a normal s > 0 whose reciprocal is normal: the hardware estimate is within one unit in the last
+// place, a Newton step brings it to the correctly rounded value or a neighbour, and the exact residuals 1 - s r
+// (a fused multiply-add each; exact where it matters, |residual| <= 2^-24) pick the nearest of the three.
+__device__ __forceinline__ float exact_reciprocal(float s) {
+  const float r0 = __builtin_amdgcn_rcpf(s);
+  const float e = fmaf(-s, r0, 1.f);
+  float r = fmaf(e, r0, r0);
+  const float e0 = fabsf(fmaf(-s, r, 1.f));
+  const float rp = __uint_as_float(__float_as_uint(r) + 1u), rm = __uint_as_float(__float_as_uint(r) - 1u);
+  const float ep = fabsf(fmaf(-s, rp, 1.f)), em = fabsf(fmaf(-s, rm, 1.f));
+  r = ep < e0 ? rp : r;  // at most one neighbour is closer than r
+  r = em < e0 ? rm : r;
+  return r;
+}
+
+// s for which the reciprocal path is used: 2^-60 <= s <= 2^60 (everything in it then stays a normal number)
+__device__ __forceinline__ bool scale_in_fast_range(float s) {
+  return __float_as_uint(s) - 0x21800000u <= 0x5D800000u - 0x21800000u;
+}
+
+// fl(x / s) from the group's (s, r = RN(1 / s), hi = 1024 s); Markstein's division, as at the top of l4q_merge_stream.hip
+__device__ __forceinline__ float fast_quotient(float x, float s, float r, float hi) {
+  const float xc = __builtin_amdgcn_fmed3f(x, -hi, hi);
+  const float q = xc * r;
+  const float t = fmaf(-s, q, xc);
+  return fmaf(t, r, q);
+}
+
 // Eq. l4q_Wdequant
 __device__ __forceinline__ float dequant_elem(float code, float s, float b) { return fmaf(code, s, b); }
 

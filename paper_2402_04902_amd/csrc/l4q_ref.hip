@@ -1,4 +1,4 @@
-// The unfused quantizer-gradient pass (binary32 mode, unfused backward of the bfloat16 mode, QAT-LoRA),
+// The unfused quantizer-gradient pass (binary32 mode, unfused backward of the bfloat16 mode, and there QAT-LoRA too),
 // the fixed-order sums of partial results, and the AdamW step.  No assumption on shapes beyond the
 // library's divisibility rules.
 #include "l4q_device.h"
@@ -19,7 +19,7 @@ namespace {
 // A workgroup takes ROWS weight rows and deals their columns out to its 4 waves in units of 256 (or a whole group where
 // groups are longer), a lane owning 4 consecutive columns of all the rows: A is read once per ROWS rows, and ROWS
 // independent loads per operand are in flight.  One wave per row with one row's loads in flight, the first form, took
-// 137 us on 4096 x 4096 bf16 of the QAT-LoRA layer (now 28: 100 MB at 3.5 TB/s) and 66 us on 2048 x 2048 binary32 at rank
+// 137 us on 4096 x 4096 bf16 without LoRA (28 now: 100 MB at 3.5 TB/s) and 66 us on 2048 x 2048 binary32 at rank
 // 16 (now 27; 4 rows per workgroup 32).
 constexpr int QG_KCHUNK = 16;
 

@@ -1,0 +1,57 @@
+"""dscale and dzero of the QAT-LoRA layer in bfloat16, made in the weight-gradient product's epilogue: tile edges in rows, columns
+and tokens, every group size that the epilogue covers (and one that it does not), scales outside the range of the reciprocal,
+weights that are not finite, against binary64 sums over binary32 quotients."""
+import pytest
+
+from paper_2402_04902_amd.inputs import DTYPE_BF16, LayerSpec
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,i,o,bits,g", [
+    (1, 32, 8, 4, 32), (70, 288, 264, 3, 32), (33, 320, 520, 2, 64), (97, 512, 250 + 6, 4, 128), (64, 768, 72, 8, 256),
+    (161, 1280, 776, 5, 256), (40, 512, 136, 4, 512),
+])
+@pytest.mark.parametrize("kind", ["plain", "tiny_scale", "not_finite", "accumulate"])
+def test_group_gradients(T, i, o, bits, g, kind):
+    import torch
+    from paper_2402_04902_amd import binding
+    r = 8
+    spec = LayerSpec(f"groups_{T}x{i}x{o}_{bits}b_g{g}_{kind}", T, i, o, r, 2.0 * r, bits, g, DTYPE_BF16)
+    print("case", spec.name, flush=True)
+    dev = torch.device("cuda:0")
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(T + i + bits)
+
+    def normal(*shape, std=1.0):
+        return (torch.randn(shape, generator=gen, device=dev) * std).bfloat16()
+    X, dY, W0, A, B = normal(T, i), normal(T, o, std=1e-2), normal(o, i, std=0.02), normal(r, i, std=0.01), normal(o, r, std=1e-3)
+    G = i // g
+    qn, qp = -float(1 << (bits - 1)), float((1 << (bits - 1)) - 1)
+    scale = torch.rand((o, G), generator=gen, device=dev) * 0.02 / qp + 0.02 / qp   # some weights clip
+    zero = torch.randn((o, G), generator=gen, device=dev) * 2e-3
+    if kind == "tiny_scale":
+        scale[o // 2, G - 1] = 1e-30
+        scale[0, 0] = 2e30
+    if kind == "not_finite":
+        W0[o - 1, 0], W0[o // 2, i - 1] = float("nan"), float("-inf")
+    desc = binding.make_desc(spec)
+    grads = [torch.full(s, 0.25, device=dev) for s in ((r, i), (o, r), (o, G), (o, G))]
+    if kind == "accumulate":
+        desc.flags = binding.FLAG_ACCUMULATE_GRADS
+    ws = torch.empty(max(binding.l4q_qatlora_workspace_bytes(desc)), dtype=torch.uint8, device=dev)
+    binding.l4q_qatlora_backward(desc, X, dY, W0, A, B, scale, zero, torch.empty_like(X), *grads, ws)
+    torch.cuda.synchronize()
+    w = (W0.float() - zero.repeat_interleave(g, 1)) / scale.repeat_interleave(g, 1)   # the stated binary32 operations
+    inside = (w >= qn) & (w <= qp)
+    code = torch.round(torch.where(torch.isnan(w), qn, w.clamp(qn, qp)))               # (a NaN: clipped, at the lower end)
+    f = torch.where(inside, code - w, code).double()
+    dW = dY.double().t() @ X.double()
+    mag = dY.double().abs().t() @ X.double().abs()
+    before = 0.25 if kind == "accumulate" else 0.0
+    for name, got, fac in (("dscale", grads[2], f), ("dzero", grads[3], (~inside).double())):
+        want = (dW * fac).view(o, G, g).sum(2) + before
+        # binary32: T products' sum, its product with the factor, the group's sum and the sum over it: each step off by at most
+        # 2^-24 of the magnitudes that it joins
+        bound = (T + g + 4) * 2.0 ** -24 * ((mag * fac.abs()).view(o, G, g).sum(2) + before)
+        assert ((got.double() - want).abs() <= bound + 1e-30).all(), name
