@@ -220,9 +220,10 @@ struct Timed {
 // Enqueue one bf16 GEMM (rows of A end at K_algorithmic, the padded operand B at K).
 // `splitk`: room for the k-slices' tiles where the product has too few tiles for the chip (or null: one pass).
 void gemm_nt(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, int64_t M, int64_t N, int64_t K,
-             int64_t K_algorithmic, bf16_t* C, int64_t ldc, hipStream_t stream, float* splitk, bool late) {
+             int64_t K_algorithmic, bf16_t* C, int64_t ldc, hipStream_t stream, float* splitk, bool late,
+             const l4q::TwoPartials* sums = nullptr) {
   Timed t(stream, kKindGemm, 2.0 * (double)M * (double)N * (double)K_algorithmic);
-  l4q::launch_gemm_bf16_nt(A, lda, B, ldb, M, N, K, K_algorithmic, C, ldc, stream, splitk, late);
+  l4q::launch_gemm_bf16_nt(A, lda, B, ldb, M, N, K, K_algorithmic, C, ldc, stream, splitk, late, sums);
 }
 
 // The same with the QAT-LoRA layer's LoRA term added to the product (not counted in the FLOPs).
@@ -388,10 +389,10 @@ int l4q_backward(const l4q_desc* desc, const void* X, const void* dY, const void
     merge_quant_bf16(d, W0b, Ab, Bb, scale, zero, mq, stream);
     // dWq = dY^T . X, both operands read as they lie in memory.  The fused kernel goes first: the factor array the
     // merge pass has just written is then still in the memory-side cache when the epilogues ask for it.
+    l4q::TwoPartials sums = {};
     if (w.fused) {
       dw_fused(d, w, (const bf16_t*)dY, (const bf16_t*)X, Ab, dscale, dzero, stream);
-      l4q::launch_reduce_two_partials(w.dA_part, w.tiles_m, (int64_t)d.r * d.i, dA, w.dB_part, 2 * w.tiles_n,
-                                      d.o * d.r, dB, d.gamma, d.accumulate, stream);
+      sums = {w.dA_part, w.tiles_m, (int64_t)d.r * d.i, dA, w.dB_part, 2 * w.tiles_n, d.o * d.r, dB, d.gamma, d.accumulate};
     }
     if (w.masked) {
       {
@@ -401,11 +402,12 @@ int l4q_backward(const l4q_desc* desc, const void* X, const void* dY, const void
         l4q::launch_dw_masked(d, (const bf16_t*)dY, (const bf16_t*)X, w.fgrad, dscale, dzero, (bf16_t*)w.fgrad, stream);
       }
       l4q::launch_dw_masked_products(d, (const bf16_t*)w.fgrad, Ab, Bb, w.rawA, w.rawB, stream);
-      l4q::launch_reduce_two_partials(w.rawA, w.slices_a, (int64_t)d.r * d.i, dA, w.rawB, w.slices_b, d.o * d.r, dB, d.gamma,
-                                      d.accumulate, stream);
+      sums = {w.rawA, w.slices_a, (int64_t)d.r * d.i, dA, w.rawB, w.slices_b, d.o * d.r, dB, d.gamma, d.accumulate};
     }
-    gemm_nt((const bf16_t*)dY, d.o, w.wqT, w.opad, d.T, d.i, w.opad, d.o, (bf16_t*)dX, d.i, stream, w.splitk,
-            w.fused || w.masked);
+    const bool partials = w.fused || w.masked, split = w.splitk != nullptr;  // (a split product adds them up beside its own sums)
+    if (partials && !split) l4q::launch_reduce_two_partials(sums, stream);
+    gemm_nt((const bf16_t*)dY, d.o, w.wqT, w.opad, d.T, d.i, w.opad, d.o, (bf16_t*)dX, d.i, stream, w.splitk, partials,
+            partials && split ? &sums : nullptr);
     if (!w.fused && !w.masked) {
       l4q::launch_gemm_bf16_kmajor_f32((const bf16_t*)dY, d.o, (const bf16_t*)X, d.i, d.o, d.i, d.T, w.dwq, d.i, stream);
       l4q::launch_quant_grads<bf16_t>(d, W0b, Ab, Bb, scale, zero, w.dwq, dscale, dzero, dB, stream);

@@ -9,6 +9,7 @@
 #include "l4q_device.h"
 #include "l4q_gemm_core.h"
 #include "l4q_kernels.h"
+#include "l4q_reduce.h"
 
 namespace l4q {
 
@@ -252,9 +253,9 @@ __global__ __launch_bounds__(T::NT) void gemm_bf16_kmajor_splitk_kernel(const bf
 }
 
 // C[m, n] = bf16(sum over the slices, in slice order, of part[slice][m][n]); N % 4 == 0, four columns per thread.
-__global__ __launch_bounds__(256) void splitk_sum_kernel(const float* __restrict__ part, int slices, int64_t M, int64_t N,
-                                                         bf16_t* __restrict__ C, int64_t ldc) {
-  const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
+__device__ __forceinline__ void splitk_sum(int64_t block, const float* __restrict__ part, int slices, int64_t M, int64_t N,
+                                           bf16_t* __restrict__ C, int64_t ldc) {
+  const int64_t q = block * 256 + threadIdx.x;
   if (q >= M * N / 4) return;
   float4 v = reinterpret_cast<const float4*>(part)[q];
   for (int s = 1; s < slices; ++s) {
@@ -264,6 +265,21 @@ __global__ __launch_bounds__(256) void splitk_sum_kernel(const float* __restrict
   const int64_t m = q * 4 / N, n = q * 4 - m * N;
   const float f[4] = {v.x, v.y, v.z, v.w};
   store4(C + m * ldc + n, f);
+}
+__global__ __launch_bounds__(256) void splitk_sum_kernel(const float* __restrict__ part, int slices, int64_t M, int64_t N,
+                                                         bf16_t* __restrict__ C, int64_t ldc) {
+  splitk_sum((int64_t)blockIdx.x, part, slices, M, N, C, ldc);
+}
+
+// The same with the partial sums of dA and dB, which the weight-gradient kernel has left, added by the workgroups after the
+// first `own`: either launch alone is 5 us, most of it latency (301 tokens, 4096 x 4096, rank 16: a training step of 126.7 us
+// takes 124.1 in one).
+__global__ __launch_bounds__(256) void splitk_sum_and_partials_kernel(const float* __restrict__ part, int slices, int64_t M,
+                                                                      int64_t N, bf16_t* __restrict__ C, int64_t ldc, int own,
+                                                                      TwoPartials sums) {
+  __shared__ float4 slice_sum[3][64];
+  if ((int)blockIdx.x < own) splitk_sum((int64_t)blockIdx.x, part, slices, M, N, C, ldc);
+  else reduce_two_block(sums, (int)blockIdx.x - own, slice_sum);
 }
 
 // Matrix-core-only loop with the GEMM's register shape (4 x 4 accumulator tiles, 8 fragments per wave) and
@@ -448,7 +464,8 @@ template <class Fn> void nt_dispatch(NtForm form, bool mask, Fn&& f) {
 }  // namespace
 
 void launch_gemm_bf16_nt(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, int64_t M, int64_t N,
-                         int64_t K, int64_t K_a, bf16_t* C, int64_t ldc, hipStream_t stream, float* partial, bool late) {
+                         int64_t K, int64_t K_a, bf16_t* C, int64_t ldc, hipStream_t stream, float* partial, bool late,
+                         const TwoPartials* sums) {
   NtPlan plan = nt_plan(M, N, K, late);
   if (plan.slices > 1 && !partial) plan = {nt_one_pass_form(M, N, K, late), 1};
   const int slices = plan.slices;
@@ -459,9 +476,12 @@ void launch_gemm_bf16_nt(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t 
     if (slices > 1) {
       hipLaunchKernelGGL((gemm_bf16_nt_splitk_kernel<F, MASK, true>), dim3((unsigned)(tiles_m * tiles_n), (unsigned)slices),
                          dim3(F::NT), 0, stream, A, lda, B, ldb, (int)M, (int)N, (int)K, (int)K_a, partial, tiles_m, tiles_n);
-      const int64_t quads = M * N / 4;
-      hipLaunchKernelGGL(splitk_sum_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream, partial, slices,
-                         M, N, C, ldc);
+      const int own = (int)((M * N / 4 + 255) / 256);
+      if (sums)
+        hipLaunchKernelGGL(splitk_sum_and_partials_kernel, dim3((unsigned)(own + two_partials_blocks(*sums))), dim3(256), 0,
+                           stream, partial, slices, M, N, C, ldc, own, *sums);
+      else
+        hipLaunchKernelGGL(splitk_sum_kernel, dim3((unsigned)own), dim3(256), 0, stream, partial, slices, M, N, C, ldc);
     } else {
       hipLaunchKernelGGL((gemm_bf16_fast_kernel<F, true, MASK, true>),
                          dim3((unsigned)(tiles_m * tiles_n)), dim3(F::NT), 0, stream, A, lda, B, ldb, (int)M, (int)N,

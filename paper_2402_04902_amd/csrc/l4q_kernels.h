@@ -77,6 +77,20 @@ void launch_quant_errors(const LayerDims& d, const T* W0, const T* A, const T* B
 // compute units of the current device (asked once per device, then cached)
 int device_compute_units();
 
+// outa = scale * sum of nba partials of na elements (added to it: accumulate), outb likewise (na, nb multiples of 4)
+struct TwoPartials {
+  const float* pa;
+  int nba;
+  int64_t na;
+  float* outa;
+  const float* pb;
+  int nbb;
+  int64_t nb;
+  float* outb;
+  float scale;
+  bool accumulate;
+};
+
 // ---- bf16 MFMA GEMM  C[M,N] = A[M,K] . B[N,K]^T, fp32 accumulate, bf16 output ----
 // A row-major and K-contiguous with leading dimension lda (elements, a multiple of 8); rows of A end at K_a (a
 // multiple of 8, K - 32 < K_a <= K) and are not read past it.  B K-contiguous in blocks of 32 k-values,
@@ -86,11 +100,12 @@ int device_compute_units();
 // Few tiles (small M: few tokens): the k range is split into `slices` = gemm_nt_splitk_slices(M, N, K, late) > 1 runs of
 // whole stage pairs, one workgroup per (tile, slice); the slices' binary32 tiles go to `partial`
 // [slices][M][N] and a second launch adds them in slice order (the result does not depend on the run) and rounds to
-// bf16.  With `partial` == nullptr, or one slice, the product is a single pass.
+// bf16.  With `partial` == nullptr, or one slice, the product is a single pass.  `sums` (only where the product is split):
+// partial sums that the second launch adds up beside its own.
 int gemm_nt_splitk_slices(int64_t M, int64_t N, int64_t K, bool late);
 void launch_gemm_bf16_nt(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, int64_t M, int64_t N,
                          int64_t K, int64_t K_a, bf16_t* C, int64_t ldc, hipStream_t stream,
-                         float* partial = nullptr, bool late = false);
+                         float* partial = nullptr, bool late = false, const TwoPartials* sums = nullptr);
 
 // The same product in one pass with a term of rank r added before the rounding to bfloat16: C += gamma U . M^T, U [M, r]
 // binary32, M bfloat16 as [N, r] (n_by_r) or [r, N].
@@ -182,9 +197,8 @@ int qgemm_blocks_passes(const LayerDims& d, size_t partial_bytes);
 void launch_qgemm_prefill(const PrefillPlan& plan, const LayerDims& d, const bf16_t* X, const uint32_t* packed,
                           const float* scale, const float* zero, bf16_t* Y, hipStream_t stream);
 
-// outa = scale * sum of nba partials of na elements, outb likewise, in one launch (na, nb multiples of 4)
-void launch_reduce_two_partials(const float* pa, int nba, int64_t na, float* outa, const float* pb, int nbb,
-                                int64_t nb, float* outb, float scale, bool accumulate, hipStream_t stream);
+// both sums of p in one launch
+void launch_reduce_two_partials(const TwoPartials& p, hipStream_t stream);
 
 // ---- weight-gradient GEMM with fused quantizer backward (bf16 mode) ----
 // dY [T, o], X [T, i] as the caller holds them; fgrad [o, i] binary16 from launch_merge_quant;

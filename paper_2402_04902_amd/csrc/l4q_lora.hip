@@ -297,7 +297,7 @@ void launch_tn_pair(const float* Ua, const bf16_t* Xa, int64_t na, float* outa, 
   }
   hipLaunchKernelGGL(tn_pair_kernel<false>, dim3((unsigned)all, (unsigned)blocks), dim3(256), 0, stream, TnJob{Ua, Xa, na, parta},
                      TnJob{Ub, Xb, nb, partb}, cols, T, r, gamma, accumulate);
-  launch_reduce_two_partials(parta, (int)blocks, (int64_t)r * na, outa, partb, (int)blocks, (int64_t)r * nb, outb, gamma, accumulate,
+  launch_reduce_two_partials({parta, (int)blocks, (int64_t)r * na, outa, partb, (int)blocks, (int64_t)r * nb, outb, gamma, accumulate},
                              stream);
 }
 

@@ -3,6 +3,7 @@
 // library's divisibility rules.
 #include "l4q_device.h"
 #include "l4q_kernels.h"
+#include "l4q_reduce.h"
 
 namespace l4q {
 
@@ -183,53 +184,13 @@ void launch_reduce_partials(const float* partial, int64_t nblocks, int64_t n, fl
                      nblocks, n, scale, out, accumulate);
 }
 
-// Both reductions of the fused backward in one launch; 4 consecutive elements per thread (n % 4 == 0).
-// A block is 64 element quads x 4 slices of the partial index: slice q sums partials [q*per, (q+1)*per) in
-// ascending order and the four slice sums are added in ascending q, so the summation order is fixed.
-__global__ __launch_bounds__(256) void reduce_two_partials_kernel(const float* __restrict__ pa, int nba, int64_t na,
-                                                                   float* __restrict__ outa,
-                                                                   const float* __restrict__ pb, int nbb, int64_t nb,
-                                                                   float* __restrict__ outb, float scale,
-                                                                   int blocks_a, bool accumulate) {
+__global__ __launch_bounds__(256) void reduce_two_partials_kernel(TwoPartials p) {
   __shared__ float4 slice_sum[3][64];
-  const bool second = (int)blockIdx.x >= blocks_a;
-  const float* __restrict__ part = second ? pb : pa;
-  float* __restrict__ out = second ? outb : outa;
-  const int nblocks = second ? nbb : nba;
-  const int64_t n = second ? nb : na;
-  const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
-  const int64_t e = ((int64_t)(second ? blockIdx.x - blocks_a : blockIdx.x) * 64 + lane) * 4;
-  const int per = (nblocks + 3) / 4;
-  const int b0 = q * per, b1 = min(nblocks, b0 + per);
-  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (e < n) {
-#pragma unroll 4
-    for (int b = b0; b < b1; ++b) {
-      const float4 v = *reinterpret_cast<const float4*>(part + (int64_t)b * n + e);
-      acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
-    }
-  }
-  if (q > 0) slice_sum[q - 1][lane] = acc;
-  __syncthreads();
-  if (q > 0 || e >= n) return;
-#pragma unroll
-  for (int k = 0; k < 3; ++k) {
-    const float4 v = slice_sum[k][lane];
-    acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
-  }
-  float4 r = make_float4(scale * acc.x, scale * acc.y, scale * acc.z, scale * acc.w);
-  if (accumulate) {
-    const float4 old = *reinterpret_cast<const float4*>(out + e);
-    r = make_float4(old.x + r.x, old.y + r.y, old.z + r.z, old.w + r.w);
-  }
-  *reinterpret_cast<float4*>(out + e) = r;
+  reduce_two_block(p, (int)blockIdx.x, slice_sum);
 }
 
-void launch_reduce_two_partials(const float* pa, int nba, int64_t na, float* outa, const float* pb, int nbb,
-                                int64_t nb, float* outb, float scale, bool accumulate, hipStream_t stream) {
-  const int blocks_a = (int)((na / 4 + 63) / 64), blocks_b = (int)((nb / 4 + 63) / 64);
-  hipLaunchKernelGGL(reduce_two_partials_kernel, dim3((unsigned)(blocks_a + blocks_b)), dim3(256), 0, stream, pa, nba,
-                     na, outa, pb, nbb, nb, outb, scale, blocks_a, accumulate);
+void launch_reduce_two_partials(const TwoPartials& p, hipStream_t stream) {
+  hipLaunchKernelGGL(reduce_two_partials_kernel, dim3((unsigned)two_partials_blocks(p)), dim3(256), 0, stream, p);
 }
 
 // ------------------------------------------------------------------ AdamW step on {A, B, scale, zero}
