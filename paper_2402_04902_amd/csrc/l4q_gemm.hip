@@ -540,13 +540,19 @@ void launch_dw_masked_products(const LayerDims& d, const bf16_t* dWm, const bf16
                        dim3(F::NT), 0, stream, dWm, d.i, A, d.i, (int)d.o, d.r, (int)d.i, (int)d.i, rawB, tiles_m, tiles_n);
   };
   nt_dispatch(d.r <= 128 ? kNtQuarter : kNtFull, d.i % 64 != 0, thin_b);
-  // rawA [sa][r, i] = B [o, r]^T . dWm [o, i]: both K-major, k = o
-  {
-    typedef gemm::Tile<256, 256, 32, 4> F;
+  // rawA [sa][r, i] = B [o, r]^T . dWm [o, i]: both K-major, k = o.  Bound by reading dWm once; with all 256 columns of a tile
+  // multiplied, whatever the rank, the matrix ops of a slice took 11 us at full rate, so up to 128 ranks the waves share out 64
+  // or 128 of them (rank 64 on 4096 x 11008: 27.1 us -> 20.8, steps of drawn layers at ranks 40 .. 128 1.02 times as fast,
+  // the sums the same).
+  auto thin_a = [&](auto tile) {
+    typedef decltype(tile) F;
     const int tiles_m = (d.r + F::BM - 1) / F::BM, tiles_n = (int)((d.i + F::BN - 1) / F::BN);
     hipLaunchKernelGGL((gemm_bf16_kmajor_splitk_kernel<F>), dim3((unsigned)(tiles_m * tiles_n), (unsigned)sa), dim3(F::NT),
                        0, stream, B, (int64_t)d.r, dWm, d.i, d.r, (int)d.i, (int)d.o, rawA, tiles_m, tiles_n);
-  }
+  };
+  if (d.r <= 64) thin_a(gemm::Tile<256, 256, 32, 4, 64>());
+  else if (d.r <= 128) thin_a(gemm::Tile<256, 256, 32, 4, 128>());
+  else thin_a(gemm::Tile<256, 256, 32, 4>());
 }
 
 }  // namespace l4q

@@ -60,15 +60,16 @@ __device__ __forceinline__ void tile_of_block(int pid, int tiles_m, int tiles_n,
   tn = rem / gsz;
 }
 
-// Tile of the loop for K-major operands: BK k-values a stage, ring of NS stages.
-template <int BM_, int BN_, int BK_, int NS_>
+// Tile of the loop for K-major operands: BK k-values a stage, ring of NS stages.  USED < 256: operand A has no more columns
+// than that (a rank), and the waves multiply no others; its place in LDS stays 256 wide.
+template <int BM_, int BN_, int BK_, int NS_, int USED_ = BM_>
 struct Tile {
   static constexpr bool WIDE = false;
-  static constexpr int BM = BM_, BN = BN_, BK = BK_, NS = NS_;
-  static constexpr int WAVES_M = 2, WAVES_N = 2;
+  static constexpr int BM = BM_, BN = BN_, BK = BK_, NS = NS_, USED = USED_;
+  static constexpr int WAVES_M = USED == BM ? 2 : 1, WAVES_N = 4 / WAVES_M;
   static constexpr int NW = WAVES_M * WAVES_N;
   static constexpr int NT = 64 * NW;
-  static constexpr int WTM = BM / WAVES_M, WTN = BN / WAVES_N;  // wave tile
+  static constexpr int WTM = USED / WAVES_M, WTN = BN / WAVES_N;  // wave tile
   static constexpr int TM = WTM / 32, TN = WTN / 32;  // 32 x 32 accumulator tiles per wave
   static constexpr int RPI = 2;                       // LDS rows (one k each) filled by one wave-wide load
   static constexpr int A_INSTR = BK / RPI / NW;       // loads per wave per stage, operand A
@@ -240,8 +241,10 @@ __device__ __forceinline__ void mainloop(const bf16_t* __restrict__ A, int64_t l
   constexpr int LPK = LOADS / T::KK;                 // loads issued per k-step
   constexpr int NDA = 2 * T::TM, NDB = 2 * T::TN;     // LDS read instructions per k-step
   constexpr int NMF = T::TM * T::TN;
+  // with few matrix ops there is nothing to hide the other two kinds behind: the order is the compiler's
+  constexpr bool DEALT = NMF == 16;
   constexpr int EXTRA = NDA + NDB + LPK > NMF ? NDA + NDB + LPK - NMF : 0;  // reads that share a matrix op
-  static_assert(2 * EXTRA <= NDA + NDB, "too many LDS reads per matrix op");
+  static_assert(!DEALT || 2 * EXTRA <= NDA + NDB, "too many LDS reads per matrix op");
 #pragma unroll
   for (int s = 0; s < T::D; ++s) {
     if (s < nk) issue_loads(s, s, 0, 1);
@@ -260,7 +263,7 @@ __device__ __forceinline__ void mainloop(const bf16_t* __restrict__ A, int64_t l
   // at the next stage boundary finds them complete.  Program order is reads, then DMA loads: the DMA
   // loads write LDS and the compiler keeps them behind the reads before them.
   constexpr int REST = NMF - (NDA + NDB - EXTRA + LPK);
-  static_assert(REST >= 0, "more LDS reads and loads than matrix ops to hide them behind");
+  static_assert(!DEALT || REST >= 0, "more LDS reads and loads than matrix ops to hide them behind");
   int slot = 0;
   // one stage; `load_part(kk)` issues part kk of the loads of stage s + D into the slot stage s - 1 has left
   auto stage = [&](auto&& load_part) {
@@ -285,22 +288,24 @@ __device__ __forceinline__ void mainloop(const bf16_t* __restrict__ A, int64_t l
       read_frags_b(last ? nslot : slot, last ? 0 : kk + 1, (kk + 1) & 1);
       load_part(pslot, kk);
       mfma_block(kk & 1);
+      if constexpr (DEALT) {
 #pragma unroll
-      for (int q = 0; q < EXTRA; ++q) {  // where reads outnumber matrix ops, two reads per matrix op
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-      }
+        for (int q = 0; q < EXTRA; ++q) {  // where reads outnumber matrix ops, two reads per matrix op
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+        }
 #pragma unroll
-      for (int q = 0; q < NDA + NDB - 2 * EXTRA; ++q) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-      }
+        for (int q = 0; q < NDA + NDB - 2 * EXTRA; ++q) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
 #pragma unroll
-      for (int q = 0; q < LPK; ++q) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+        for (int q = 0; q < LPK; ++q) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+        }
+        if constexpr (REST > 0) __builtin_amdgcn_sched_group_barrier(0x008, REST, 0);
       }
-      if constexpr (REST > 0) __builtin_amdgcn_sched_group_barrier(0x008, REST, 0);
     }
     slot = nslot;
   };
