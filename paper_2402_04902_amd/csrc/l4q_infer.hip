@@ -1574,7 +1574,7 @@ void blocks_pass(const LayerDims& d, int passes, int p, int64_t* t0, int64_t* to
 
 // More than 64 tokens in passes of up to 64 through l4q_infer_blocks.hip, where that is estimated to be faster than the other
 // forms (by 6 %, what the estimates are off): up to 128 tokens on most layers, further where the two-dimensional tiles leave units idle.  Measured (us, the other
-// forms' best / these passes): 4 bits [4096 x 4096] 65 / 96 / 128 / 160 tokens 24.0 / 15.2, 25.8 / 16.5, 28.9 / 24.1, 29.2 / 29.0;
+// forms' best / these passes): 4 bits [4096 x 4096] 65 / 96 / 128 / 160 tokens 24.0 / 15.2, 25.8 / 16.5, 28.9 / 17.1, 29.2 / 22.3, 192 tokens 27.6 / 25.2;
 // [4096 x 11008] 65 / 128 / 192 40.5 / 28.4, 48.6 / 37.2, 72.9 / 56.0; [11008 x 4096] 65 / 128 29.3 / 26.6, 29.6 / 32.4; 3 bits
 // [4096 x 11008] 128 / 256 53.9 / 37.8, 89.1 / 76.3; 8 bits [4096 x 4096] 96 26.4 / 20.5; 2 bits in groups of 64 [4096 x 11008]
 // 128 114 / 45; [1024 x 8192] 256 50.9 / 36.8.

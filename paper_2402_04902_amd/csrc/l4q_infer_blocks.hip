@@ -454,9 +454,6 @@ BlocksPlan qgemm_blocks_plan(const LayerDims& d, size_t partial_bytes) {
       if (sl > 1 && (sl > macros / 4 || (tiles + nt - 1) / nt * sl > cus || (sl - 1) * plan.slice_macros >= macros ||
                      (size_t)sl * (size_t)(d.T * d.o) * 4 > partial_bytes))
         continue;
-      // whole passes on layers of a tile per unit in two slices where there is room for the partial sums: the one case where
-      // the plan is not the estimate's (11.4 against 10.2 us at [4096 x 4096]); callers see by it that their workspace is used
-      if (d.T == 64 && per_unit == 1 && 2 * tiles > cus && macros >= 16 && sl == 1 && 2 * (size_t)(d.T * d.o) * 4 <= partial_bytes) continue;
       plan.us = qb_us(d, plan);
       if (best.nt == 0 || plan.us < best.us) best = plan;
     }

@@ -16,11 +16,15 @@ class _BlocksPlan(ctypes.Structure):
     _fields_ = [("nt", ctypes.c_int), ("slices", ctypes.c_int), ("slice_macros", ctypes.c_int), ("us", ctypes.c_double)]
 
 
-def blocks_form(T, i, o, bits, g, partial_bytes=1 << 30):
+def blocks_plan(T, i, o, bits, g, partial_bytes=1 << 30):
     f = getattr(binding.load_library(), "_ZN3l4q17qgemm_blocks_planERKNS_9LayerDimsEm")
     f.restype, f.argtypes = _BlocksPlan, [ctypes.POINTER(_LayerDims), ctypes.c_size_t]
     q = float(1 << (bits - 1))
-    p = f(ctypes.byref(_LayerDims(T, i, o, 8, bits, g, 2.0, -q, q - 1.0, False)), partial_bytes)
+    return f(ctypes.byref(_LayerDims(T, i, o, 8, bits, g, 2.0, -q, q - 1.0, False)), partial_bytes)
+
+
+def blocks_form(*call):
+    p = blocks_plan(*call)
     return p.nt, p.slices
 
 
@@ -38,7 +42,8 @@ GPU_CASES = [
     ((40, 640, 6008, 2, 128), (2, 1)),
     ((48, 4480, 11000, 4, 128), (3, 1)),
     ((47, 8704, 520, 4, 512), (1, 4)),   # slices that divide groups
-    ((64, 4352, 4000, 4, 128), (2, 2)),
+    ((64, 4352, 4000, 4, 128), (1, 1)),
+    ((64, 11008, 4096, 4, 128), (2, 2)),
     ((48, 11008, 4096, 3, 128), (2, 2)),
     ((50, 4224, 4096, 2, 128), (1, 1)),
     ((64, 1088, 10000, 8, 64), (3, 1)),
@@ -89,8 +94,8 @@ def test_gpu_cases_take_the_passes_they_name(case, n):
 
 @pytest.mark.parametrize("T,i,o,bits,g,n", [
     (64, 4096, 4096, 4, 128, 0),      # not more than 64 tokens
-    (128, 4096, 4096, 4, 128, 2),     # 24.1 against 28.9 in two-dimensional tiles
-    (192, 4096, 4096, 4, 128, 0),     # 36.4 / 29.6
+    (128, 4096, 4096, 4, 128, 2),     # 17.1 against 28.9 in two-dimensional tiles
+    (256, 4096, 4096, 4, 128, 0),
     (65, 11008, 4096, 4, 128, 2),     # 28.4 / 40.5
     (128, 4096, 11008, 4, 128, 0),    # 32.4 / 29.6
     (65, 11008, 1024, 2, 128, 2),     # 24.6 / 78.4 in the general kernel's passes
@@ -112,3 +117,16 @@ def test_slices_only_where_the_partial_sums_have_room():
     assert blocks_form(48, 11008, 4096, 3, 128, 2 * 48 * 4096 * 4)[1] == 2
     assert blocks_form(48, 11008, 4096, 3, 128, 2 * 48 * 4096 * 4 - 1)[1] == 1
     assert blocks_form(64, 4096, 4096, 4, 128, 0)[1] == 1
+
+
+@pytest.mark.parametrize("T", [16, 63, 64])
+@pytest.mark.parametrize("bits,g", [(2, 64), (3, 128), (4, 128), (8, 64)])
+@pytest.mark.parametrize("i", [3072, 4096, 11008])
+def test_room_for_partial_sums_never_makes_the_plan_slower(T, i, bits, g):
+    for o in range(1032, 8200, 184):
+        assert blocks_plan(T, i, o, bits, g).us <= blocks_plan(T, i, o, bits, g, 0).us
+
+
+@pytest.mark.parametrize("T", [128, 160, 176, 192, 256])
+def test_passes_do_not_depend_on_room_where_one_slice_is_the_faster_plan(T):
+    assert passes(T, 4096, 4096, 4, 128) == passes(T, 4096, 4096, 4, 128, 0)

@@ -284,7 +284,7 @@ def test_quantized_forward_ignores_a_short_workspace():
     and nothing is written past the bytes that were passed."""
     import torch
     from paper_2402_04902_amd import binding
-    T, i, o, bits, g = 64, 4096, 4096, 4, 128   # (a batch the k-sliced tile form takes)
+    T, i, o, bits, g = 64, 11008, 4096, 4, 128   # (two k-slices)
     spec = LayerSpec("qshort_ws", T, i, o, 8, 16.0, bits, g, DTYPE_BF16)
     dev = torch.device("cuda:0")
     gen = torch.Generator(device=dev)
