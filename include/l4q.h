@@ -172,20 +172,21 @@ int l4q_export_packed(const l4q_desc* desc, const void* W0, const void* A, const
 
 /* Forward pass of the fully quantized layer from the packed codes alone (no W0, A, B):
  *   Y[T,o] = X[T,i] . (w~ scale + zero)^T        (Eq. l4q_forward with Eq. l4q_Wdequant)
- * BF16 only (X, Y bfloat16); bits in {2,3,4,8}; in_features % 64 == 0.  Decode sizes stream the packed
- * weights once per pass of at most 64 tokens (32 or 48 for some shapes); prompts (groups of 64 and more,
- * in_features % 128 == 0) run as one pass in two-dimensional tiles from where that is faster.
+ * BF16 only (X, Y bfloat16); bits in {2,3,4,8}; in_features % 64 == 0.  Up to 64 tokens the packed weights are read
+ * once (once per 32 or 48 tokens for some shapes); 65 to 512 tokens go in passes of up to 64 where those are estimated
+ * to be faster than prompts' two-dimensional tiles (groups of 64 and more, in_features % 128 == 0), and longer prompts
+ * in one pass of these tiles from where that is faster.
  * workspace (device memory, 256-byte aligned) is optional: NULL / 0 is always accepted.  Layers with few output
- * rows and long rows run faster from about 8 tokens on when given
- * l4q_quantized_forward_workspace_bytes() of it
- * (the row is then cut into k-slices over the compute units, whose partial sums are added in a fixed order);
- * a workspace smaller than that is ignored.  The result does not depend on the stream's other work, but with and
- * without the workspace it may differ in the last bit of the fp32 sum before the rounding to bfloat16. */
+ * rows and long rows run faster at most token counts when given l4q_quantized_forward_workspace_bytes() of it
+ * (the row is then cut into k-slices over the compute units where that is estimated to be faster; their partial sums are
+ * added in a fixed order).  A workspace smaller than that is ignored, and a larger one is used no further: the result
+ * depends on whether the told size was passed, not on how much was.  It does not depend on the stream's other work, but
+ * with and without the workspace it may differ in the last bit of the fp32 sum before the rounding to bfloat16. */
 int l4q_quantized_forward(const l4q_desc* desc, const void* X, const uint32_t* packed,
                           const float* scale, const float* zero, void* Y,
                           void* workspace, size_t workspace_bytes, void* hip_stream);
 
-/* Bytes of workspace l4q_quantized_forward can make use of for this layer (0 for most shapes; does not depend on
+/* Bytes of workspace l4q_quantized_forward can make use of for this layer (0 for wide layers and short rows; does not depend on
  * `tokens`). */
 int l4q_quantized_forward_workspace_bytes(const l4q_desc* desc, size_t* bytes);
 

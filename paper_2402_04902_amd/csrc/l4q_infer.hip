@@ -1501,14 +1501,10 @@ bool qgemm_supported(const LayerDims& d) { return (d.bits == 2 || d.bits == 3 ||
 
 size_t qgemm_workspace_bytes(const LayerDims& d) {
   const TilePlan plan = qgemm_tile_plan(d);
-  size_t tile_bytes = 0, slice_bytes = 0;
+  const size_t slice_bytes = qgemm_blocks_workspace_bytes(d);
+  size_t tile_bytes = 0;
   if (plan.tb_max > 0 && plan.slices > 1)
     tile_bytes = (size_t)plan.slices * 16 * plan.tb_max * (size_t)d.o * sizeof(float);  // [slice][token of a pass][row]
-  // rows of more than 4096 where the row tiles do not fill the compute units more than once: up to 4 slices of two token blocks
-  // (callers keep the size that they were told, so it does not follow the plan)
-  const int64_t tiles = (d.o + 15) / 16, cus = device_compute_units(), slices = (d.i + 4095) / 4096;
-  if (d.bits != 8 && slices >= 2 && slices <= 4 && tiles <= cus && 2 * tiles >= cus)
-    slice_bytes = (size_t)slices * 32 * (size_t)d.o * sizeof(float);
   return tile_bytes > slice_bytes ? tile_bytes : slice_bytes;
 }
 
@@ -1578,17 +1574,16 @@ void blocks_pass(const LayerDims& d, int passes, int p, int64_t* t0, int64_t* to
 // [4096 x 11008] 65 / 128 / 192 40.5 / 28.4, 48.6 / 37.2, 72.9 / 56.0; [11008 x 4096] 65 / 128 29.3 / 26.6, 29.6 / 32.4; 3 bits
 // [4096 x 11008] 128 / 256 53.9 / 37.8, 89.1 / 76.3; 8 bits [4096 x 4096] 96 26.4 / 20.5; 2 bits in groups of 64 [4096 x 11008]
 // 128 114 / 45; [1024 x 8192] 256 50.9 / 36.8.
-int qgemm_blocks_passes(const LayerDims& d, size_t partial_bytes) {
+int qgemm_blocks_passes(const LayerDims& d, bool have_workspace) {
   // (layers of less than a million weights are all launch, which the estimates do not cover)
   if (d.T <= 64 || d.T > 512 || d.o * d.i < 1 << 20) return 0;
-  const bool have_workspace = partial_bytes >= qgemm_workspace_bytes(d) && partial_bytes > 0;
   const int passes = (int)((d.T + 63) / 64);
   double us = 0.0;
   for (int p = 0; p < passes; ++p) {
     LayerDims part = d;
     int64_t t0;
     blocks_pass(d, passes, p, &t0, &part.T);
-    const BlocksPlan plan = qgemm_blocks_plan(part, have_workspace ? partial_bytes : 0);
+    const BlocksPlan plan = qgemm_blocks_plan(part, have_workspace);
     if (plan.nt == 0) return 0;
     us += plan.us;
   }
@@ -1598,8 +1593,9 @@ int qgemm_blocks_passes(const LayerDims& d, size_t partial_bytes) {
 
 void launch_qgemm(const LayerDims& d, const bf16_t* X, const uint32_t* packed, const float* scale, const float* zero,
                   bf16_t* Y, float* partial, size_t partial_bytes, hipStream_t stream) {
-  const size_t usable = partial != nullptr && partial_bytes >= qgemm_workspace_bytes(d) ? partial_bytes : 0;
-  const int passes = d.T > 64 ? qgemm_blocks_passes(d, usable) : 0;
+  const size_t told = qgemm_workspace_bytes(d);
+  const bool have_workspace = partial != nullptr && told > 0 && partial_bytes >= told;
+  const int passes = d.T > 64 ? qgemm_blocks_passes(d, have_workspace) : 0;
   for (int p = 0; p < passes; ++p) {
     LayerDims part = d;
     int64_t t0;
@@ -1607,13 +1603,13 @@ void launch_qgemm(const LayerDims& d, const bf16_t* X, const uint32_t* packed, c
     launch_qgemm(part, X + t0 * d.i, packed, scale, zero, Y + t0 * d.o, partial, partial_bytes, stream);
   }
   if (passes > 0) return;
-  const PrefillPlan prompt = qgemm_prompt_plan(d, partial != nullptr && partial_bytes >= qgemm_workspace_bytes(d));
+  const PrefillPlan prompt = qgemm_prompt_plan(d, have_workspace);
   if (prompt.form >= 0) {
     launch_qgemm_prefill(prompt, d, X, packed, scale, zero, Y, stream);
     return;
   }
   // up to 64 tokens, groups of 64 and more: every byte of X and of the codes to one wave, in whole cache lines
-  const BlocksPlan blocks = qgemm_blocks_plan(d, usable);
+  const BlocksPlan blocks = qgemm_blocks_plan(d, have_workspace);
   if (blocks.nt > 0) {
     launch_qgemm_blocks(blocks, d, X, packed, scale, zero, Y, partial, stream);
     if (blocks.slices > 1) {
@@ -1676,7 +1672,7 @@ void launch_qgemm(const LayerDims& d, const bf16_t* X, const uint32_t* packed, c
     int tb_max = plan.tb_max, slices = 1;
     if (plan.slices > 1) {  // too few row tiles for one k-slice each: split, if the caller gave room for the partial sums
       // (at 16 tokens or fewer the k-split inside a workgroup wins where it exists: 4 and 8 bits)
-      if ((d.T > 16 || d.bits == 3) && partial != nullptr && partial_bytes >= qgemm_workspace_bytes(d)) slices = plan.slices;
+      if ((d.T > 16 || d.bits == 3) && have_workspace) slices = plan.slices;
       else tb_max = 0;
     }
     if (tb_max > 0) {

@@ -367,6 +367,23 @@ __global__ __launch_bounds__(QB_WAVES * 64) void qgemm_blocks_kernel(QbArgs p) {
 #endif
 }
 
+// layers that this form covers
+bool qb_layer(const LayerDims& d) {
+  const int64_t rb = d.i / 8 * d.bits;
+  if (d.i % d.g != 0 || d.o % 8 != 0 || (d.g & (d.g - 1)) != 0) return false;
+  if (d.g < (d.bits == 3 ? 128 : 64) || (d.bits != 2 && d.bits != 3 && d.bits != 4 && d.bits != 8)) return false;
+  return d.o * rb < (1ll << 31) && d.o * (d.i / d.g) * 4 < (1ll << 31);
+}
+
+constexpr int QB_SLICES_MAX = 4;
+int qb_tiles_max(const LayerDims& d) { return (d.o + 15) / 16 <= device_compute_units() ? 2 : 3; }
+
+// k-slices of at least four macros, none of them empty, whose workgroups all run at once
+bool qb_slices_ok(const LayerDims& d, int nt, int sl) {
+  const int64_t tiles = (d.o + 15) / 16, macros = (d.i + 255) / 256;
+  return sl <= macros / 4 && (tiles + nt - 1) / nt * sl <= device_compute_units() && (sl - 1) * ((macros + sl - 1) / sl) < macros;
+}
+
 int qb_kstep(const LayerDims& d) { return d.bits == 8 || d.g == 64 ? 64 : 128; }
 
 // groups that a slice can meet, wherever it starts
@@ -412,6 +429,13 @@ double qb_us(const LayerDims& d, const BlocksPlan& plan) {
 
 }  // namespace
 
+size_t qgemm_blocks_workspace_bytes(const LayerDims& d) {
+  if (!qb_layer(d)) return 0;
+  for (int sl = QB_SLICES_MAX; sl > 1; --sl)
+    if (qb_slices_ok(d, qb_tiles_max(d), sl)) return (size_t)sl * 64 * (size_t)d.o * sizeof(float);
+  return 0;
+}
+
 // Which calls take this form, and how.  Measured (us, the other kernels' best / this one):
 //   4 bits, groups of 128  [4096 x 4096]  16 / 32 / 43 / 64 tokens 6.4 / 5.6, 11.3 / 7.4, 13.5 / 8.3, 13.8 / 10.2;
 //                          [11008 x 4096] 10.9 / 10.3, 15.0 / 13.1, 19.7 / 14.2, 23.2 / 16.8;  groups of 64 [4096 x 4096]
@@ -424,12 +448,9 @@ double qb_us(const LayerDims& d, const BlocksPlan& plan) {
 // short rows (up to 2048: 1.05 - 1.14 times up to 32 tokens) and, up to 24 tokens, with four tiles per unit.  8 bits, short rows
 // and four tiles per unit: 64-row tiles ([14336 x 1024], 20 / 64 tokens 9.6 / 13.2, 11.2 / 16.5).  One tile per unit: one token
 // 0.85 - 1.1 times either way, from two (8 bits: three) on this form.
-BlocksPlan qgemm_blocks_plan(const LayerDims& d, size_t partial_bytes) {
+BlocksPlan qgemm_blocks_plan(const LayerDims& d, bool have_workspace) {
   const BlocksPlan none = {0, 1, 0, 0.0};
-  const int64_t rb = d.i / 8 * d.bits;
-  if (d.T > 64 || d.i % d.g != 0 || d.o % 8 != 0 || (d.g & (d.g - 1)) != 0) return none;
-  if (d.g < (d.bits == 3 ? 128 : 64) || (d.bits != 2 && d.bits != 3 && d.bits != 4 && d.bits != 8)) return none;
-  if (d.o * rb >= (1ll << 31) || d.T * d.i * 2 >= (1ll << 31) || d.o * (d.i / d.g) * 4 >= (1ll << 31)) return none;
+  if (d.T > 64 || !qb_layer(d) || d.T * d.i * 2 >= (1ll << 31)) return none;
   const int64_t tiles = (d.o + 15) / 16, cus = device_compute_units(), macros = (d.i + 255) / 256;
   const int64_t per_unit = (tiles + cus - 1) / cus;
   if (d.g >= 128 || d.bits == 8) {  // (2 and 4 bits in groups of 64 have no other fast form)
@@ -442,22 +463,24 @@ BlocksPlan qgemm_blocks_plan(const LayerDims& d, size_t partial_bytes) {
       return none;
     if (d.bits == 8 && per_unit > 3 && d.i <= 2048) return none;
   }
-  BlocksPlan best = none;
+  BlocksPlan best = none, best_split = none;
   auto fits = [&](const BlocksPlan& plan) { return qb_lds_bytes(d, plan) <= 160 * 1024; };
   // beyond a block, as many tiles per workgroup as give one round of them, where their tables fit; slices within a round
   const int whole = (int)(d.T > 16 && per_unit <= 3 ? per_unit : 1);
   const int nt_min = fits({whole, 1, (int)macros, 0.0}) ? whole : 1;
-  for (int nt = nt_min; nt <= 3; ++nt)
-    for (int sl = 1; sl <= 4; ++sl) {
+  for (int nt = nt_min; nt <= qb_tiles_max(d); ++nt)
+    for (int sl = 1; sl <= QB_SLICES_MAX; ++sl) {
       BlocksPlan plan = {nt, sl, (int)((macros + sl - 1) / sl), 0.0};
-      if (!fits(plan) || (per_unit == 1 && nt > 1 && (nt > 2 || sl == 1))) continue;
-      if (sl > 1 && (sl > macros / 4 || (tiles + nt - 1) / nt * sl > cus || (sl - 1) * plan.slice_macros >= macros ||
-                     (size_t)sl * (size_t)(d.T * d.o) * 4 > partial_bytes))
-        continue;
+      if (!fits(plan) || (per_unit == 1 && nt > 1 && sl == 1)) continue;
+      if (sl > 1 && (!have_workspace || !qb_slices_ok(d, nt, sl))) continue;
       plan.us = qb_us(d, plan);
-      if (best.nt == 0 || plan.us < best.us) best = plan;
+      BlocksPlan& b = sl > 1 ? best_split : best;
+      if (b.nt == 0 || plan.us < b.us) b = plan;
     }
-  return best;
+  // (at four token blocks the estimate is 0.2 us too good for slices: of 4700 layers with both measured, the slices it takes are
+  // more than 3 % slower than one slice on 31 and up to 2.2 times as fast on the others)
+  const double off = d.T > 48 ? 0.2 : 0.0;
+  return best_split.nt > 0 && (best.nt == 0 || best_split.us + off < best.us) ? best_split : best;
 }
 
 void launch_qgemm_blocks(const BlocksPlan& plan, const LayerDims& d, const bf16_t* X, const uint32_t* packed,

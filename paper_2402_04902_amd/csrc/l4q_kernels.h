@@ -178,8 +178,10 @@ struct BlocksPlan {
   int slice_macros;  // runs of 256 k-values of a slice
   double us;         // estimated time
 };
-// partial_bytes: room for partial sums
-BlocksPlan qgemm_blocks_plan(const LayerDims& d, size_t partial_bytes);
+// room for the partial sums of 64 tokens in the most k-slices that a plan for this layer can have (0: it has none)
+size_t qgemm_blocks_workspace_bytes(const LayerDims& d);
+// have_workspace: that room is there
+BlocksPlan qgemm_blocks_plan(const LayerDims& d, bool have_workspace);
 void launch_qgemm_blocks(const BlocksPlan& plan, const LayerDims& d, const bf16_t* X, const uint32_t* packed,
                          const float* scale, const float* zero, bf16_t* Y, float* partial, hipStream_t stream);
 
@@ -193,7 +195,7 @@ int qgemm_prompt_wide_rows(const LayerDims& d);  // weight rows of a wide tile (
 // ... where it is faster than passes of at most 64 tokens through the kernels of l4q_infer.hip; form -1: those are
 PrefillPlan qgemm_prompt_plan(const LayerDims& d, bool have_workspace);
 // Passes of at most 64 tokens through l4q_infer_blocks.hip where they are faster than either; 0: they are not
-int qgemm_blocks_passes(const LayerDims& d, size_t partial_bytes);
+int qgemm_blocks_passes(const LayerDims& d, bool have_workspace);
 void launch_qgemm_prefill(const PrefillPlan& plan, const LayerDims& d, const bf16_t* X, const uint32_t* packed,
                           const float* scale, const float* zero, bf16_t* Y, hipStream_t stream);
 

@@ -6,6 +6,7 @@ import ctypes
 import pytest
 
 from paper_2402_04902_amd import binding
+from paper_2402_04902_amd.inputs import DTYPE_BF16, LayerSpec
 from plan_util import _LayerDims
 from test_gpu_prefill import CASES
 
@@ -16,11 +17,17 @@ class _BlocksPlan(ctypes.Structure):
     _fields_ = [("nt", ctypes.c_int), ("slices", ctypes.c_int), ("slice_macros", ctypes.c_int), ("us", ctypes.c_double)]
 
 
-def blocks_plan(T, i, o, bits, g, partial_bytes=1 << 30):
-    f = getattr(binding.load_library(), "_ZN3l4q17qgemm_blocks_planERKNS_9LayerDimsEm")
-    f.restype, f.argtypes = _BlocksPlan, [ctypes.POINTER(_LayerDims), ctypes.c_size_t]
+def workspace_bytes(T, i, o, bits, g):
+    return binding.l4q_quantized_forward_workspace_bytes(binding.make_desc(LayerSpec("plan", T, i, o, 8, 16.0, bits, g, DTYPE_BF16)))
+
+
+def blocks_plan(T, i, o, bits, g, workspace=None):  # None: as given what the query tells
+    if workspace is None:
+        workspace = workspace_bytes(T, i, o, bits, g) > 0
+    f = getattr(binding.load_library(), "_ZN3l4q17qgemm_blocks_planERKNS_9LayerDimsEb")
+    f.restype, f.argtypes = _BlocksPlan, [ctypes.POINTER(_LayerDims), ctypes.c_bool]
     q = float(1 << (bits - 1))
-    return f(ctypes.byref(_LayerDims(T, i, o, 8, bits, g, 2.0, -q, q - 1.0, False)), partial_bytes)
+    return f(ctypes.byref(_LayerDims(T, i, o, 8, bits, g, 2.0, -q, q - 1.0, False)), workspace)
 
 
 def blocks_form(*call):
@@ -43,8 +50,8 @@ GPU_CASES = [
     ((48, 4480, 11000, 4, 128), (3, 1)),
     ((47, 8704, 520, 4, 512), (1, 4)),   # slices that divide groups
     ((64, 4352, 4000, 4, 128), (1, 1)),
-    ((64, 11008, 4096, 4, 128), (2, 2)),
-    ((48, 11008, 4096, 3, 128), (2, 2)),
+    ((64, 8704, 2600, 4, 128), (2, 3)),
+    ((48, 11008, 4352, 3, 128), (3, 2)),
     ((50, 4224, 4096, 2, 128), (1, 1)),
     ((64, 1088, 10000, 8, 64), (3, 1)),
     ((64, 3072, 9000, 3, 128), (3, 1)),
@@ -71,11 +78,13 @@ def test_other_kernels(T, i, o, bits, g):
     assert blocks_form(T, i, o, bits, g) == NOT_THIS_FORM
 
 
-def passes(T, i, o, bits, g, partial_bytes=1 << 30):
-    f = getattr(binding.load_library(), "_ZN3l4q19qgemm_blocks_passesERKNS_9LayerDimsEm")
-    f.restype, f.argtypes = ctypes.c_int, [ctypes.POINTER(_LayerDims), ctypes.c_size_t]
+def passes(T, i, o, bits, g, workspace=None):
+    if workspace is None:
+        workspace = workspace_bytes(T, i, o, bits, g) > 0
+    f = getattr(binding.load_library(), "_ZN3l4q19qgemm_blocks_passesERKNS_9LayerDimsEb")
+    f.restype, f.argtypes = ctypes.c_int, [ctypes.POINTER(_LayerDims), ctypes.c_bool]
     q = float(1 << (bits - 1))
-    return f(ctypes.byref(_LayerDims(T, i, o, 8, bits, g, 2.0, -q, q - 1.0, False)), partial_bytes)
+    return f(ctypes.byref(_LayerDims(T, i, o, 8, bits, g, 2.0, -q, q - 1.0, False)), workspace)
 
 
 # more than 64 tokens: the number of passes
@@ -110,13 +119,31 @@ def test_passes(T, i, o, bits, g, n):
 @pytest.mark.parametrize("case,forms", CASES)
 def test_the_prompt_kernels_gpu_cases_are_not_taken_from_it(case, forms):
     T, i, o, g = case
-    assert not any(passes(T, i, o, bits, g, 0) for bits in (2, 3, 4, 8))
+    assert not any(passes(T, i, o, bits, g, False) for bits in (2, 3, 4, 8))
 
 
-def test_slices_only_where_the_partial_sums_have_room():
-    assert blocks_form(48, 11008, 4096, 3, 128, 2 * 48 * 4096 * 4)[1] == 2
-    assert blocks_form(48, 11008, 4096, 3, 128, 2 * 48 * 4096 * 4 - 1)[1] == 1
-    assert blocks_form(64, 4096, 4096, 4, 128, 0)[1] == 1
+def test_slices_only_with_a_workspace():
+    assert blocks_form(48, 11008, 4352, 3, 128)[1] == 2
+    assert blocks_form(48, 11008, 4352, 3, 128, False)[1] == 1
+
+
+@pytest.mark.parametrize("i", [1024, 4096, 5120, 11264, 16384])
+@pytest.mark.parametrize("bits,g", [(2, 64), (3, 128), (4, 128), (4, 1024), (8, 64)])
+def test_the_workspace_that_is_told_has_room_for_every_plans_slices(i, bits, g):
+    for o in (8, 264, 1328, 2048, 3000, 4096, 6008, 11008):
+        told = [workspace_bytes(T, i, o, bits, g) for T in (1, 53, 64, 300)]
+        assert len(set(told)) == 1  # (it does not depend on the tokens)
+        for T in (2, 5, 16, 17, 33, 53, 64):
+            slices = blocks_plan(T, i, o, bits, g, True).slices
+            assert slices == 1 or slices * T * o * 4 <= told[0]
+
+
+@pytest.mark.parametrize("T,i,o,bits,g,slices", [
+    (53, 10816, 1328, 2, 64, 3),   # 11.8 us (estimated) against 19.5 in one slice
+    (17, 8192, 264, 8, 64, 4),
+])
+def test_a_caller_with_the_workspace_that_is_told_gets_the_slices(T, i, o, bits, g, slices):
+    assert blocks_form(T, i, o, bits, g)[1] == slices
 
 
 @pytest.mark.parametrize("T", [16, 63, 64])
@@ -124,9 +151,9 @@ def test_slices_only_where_the_partial_sums_have_room():
 @pytest.mark.parametrize("i", [3072, 4096, 11008])
 def test_room_for_partial_sums_never_makes_the_plan_slower(T, i, bits, g):
     for o in range(1032, 8200, 184):
-        assert blocks_plan(T, i, o, bits, g).us <= blocks_plan(T, i, o, bits, g, 0).us
+        assert blocks_plan(T, i, o, bits, g, True).us <= blocks_plan(T, i, o, bits, g, False).us
 
 
 @pytest.mark.parametrize("T", [128, 160, 176, 192, 256])
 def test_passes_do_not_depend_on_room_where_one_slice_is_the_faster_plan(T):
-    assert passes(T, 4096, 4096, 4, 128) == passes(T, 4096, 4096, 4, 128, 0)
+    assert passes(T, 4096, 4096, 4, 128) == passes(T, 4096, 4096, 4, 128, False)

@@ -240,7 +240,8 @@ def test_quantized_forward_matches_oracle_and_training_forward(T, i, o, bits, g)
 @pytest.mark.parametrize("T,i,o,bits,g", [
     (1, 4096, 11008, 4, 128),     # activations resident in LDS
     (16, 4096, 10240, 4, 128),    # 64-row tiles
-    (48, 5120, 5000, 4, 1024),    # k-slices into the workspace + the sum over the slices
+    (48, 8704, 2600, 4, 512),     # k-slices into the workspace + the sum over the slices
+    (48, 5120, 5000, 4, 1024),    # one pass in one slice
     (20, 512, 264, 3, 64),        # general kernel
 ])
 def test_quantized_forward_replayed_from_a_graph(T, i, o, bits, g):
@@ -284,7 +285,7 @@ def test_quantized_forward_ignores_a_short_workspace():
     and nothing is written past the bytes that were passed."""
     import torch
     from paper_2402_04902_amd import binding
-    T, i, o, bits, g = 64, 11008, 4096, 4, 128   # (two k-slices)
+    T, i, o, bits, g = 64, 8704, 2600, 4, 128   # (three k-slices)
     spec = LayerSpec("qshort_ws", T, i, o, 8, 16.0, bits, g, DTYPE_BF16)
     dev = torch.device("cuda:0")
     gen = torch.Generator(device=dev)
