@@ -1553,7 +1553,8 @@ PrefillPlan qgemm_prompt_plan(const LayerDims& d, bool have_workspace) {
   PrefillPlan plan = {-1, 0.0};
   if (d.T <= 64) return plan;
   plan = qgemm_prefill_plan(d);
-  if (plan.form >= 0 && plan.us >= qgemm_passes_us(d, have_workspace)) plan.form = -1;
+  const double passes_us = qgemm_passes_us(d, have_workspace);
+  if (plan.form < 0 || plan.us >= passes_us) plan = {-1, passes_us};
   return plan;
 }
 
@@ -1574,49 +1575,62 @@ void blocks_pass(const LayerDims& d, int passes, int p, int64_t* t0, int64_t* to
 // [4096 x 11008] 65 / 128 / 192 40.5 / 28.4, 48.6 / 37.2, 72.9 / 56.0; [11008 x 4096] 65 / 128 29.3 / 26.6, 29.6 / 32.4; 3 bits
 // [4096 x 11008] 128 / 256 53.9 / 37.8, 89.1 / 76.3; 8 bits [4096 x 4096] 96 26.4 / 20.5; 2 bits in groups of 64 [4096 x 11008]
 // 128 114 / 45; [1024 x 8192] 256 50.9 / 36.8.
-int qgemm_blocks_passes(const LayerDims& d, bool have_workspace) {
+int qgemm_blocks_passes(const LayerDims& d, bool have_workspace, double other_us, BlocksPlan* plans) {
   // (layers of less than a million weights are all launch, which the estimates do not cover)
-  if (d.T <= 64 || d.T > 512 || d.o * d.i < 1 << 20) return 0;
+  if (d.T <= 64 || d.T > 64 * QB_PASSES_MAX || d.o * d.i < 1 << 20) return 0;
   const int passes = (int)((d.T + 63) / 64);
   double us = 0.0;
+  int64_t last = 0;
   for (int p = 0; p < passes; ++p) {
     LayerDims part = d;
     int64_t t0;
     blocks_pass(d, passes, p, &t0, &part.T);
-    const BlocksPlan plan = qgemm_blocks_plan(part, have_workspace);
-    if (plan.nt == 0) return 0;
-    us += plan.us;
+    plans[p] = part.T == last ? plans[p - 1] : qgemm_blocks_plan(part, have_workspace);
+    last = part.T;
+    us += plans[p].us;
+    if (plans[p].nt == 0 || us >= 0.94 * other_us) return 0;
   }
-  const PrefillPlan prompt = qgemm_prompt_plan(d, have_workspace);
-  return us < 0.94 * (prompt.form >= 0 ? prompt.us : qgemm_passes_us(d, have_workspace)) ? passes : 0;
+  return passes;
 }
+
+namespace {
+
+void launch_blocks(const BlocksPlan& plan, const LayerDims& d, const bf16_t* X, const uint32_t* packed, const float* scale,
+                   const float* zero, bf16_t* Y, float* partial, hipStream_t stream) {
+  launch_qgemm_blocks(plan, d, X, packed, scale, zero, Y, partial, stream);
+  if (plan.slices > 1) {
+    const int64_t quads = d.T * d.o / 4;
+    hipLaunchKernelGGL(qgemm_slices_sum_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream, partial, Y,
+                       plan.slices, (int)d.T, 0, (int)d.o);
+  }
+}
+
+}  // namespace
 
 void launch_qgemm(const LayerDims& d, const bf16_t* X, const uint32_t* packed, const float* scale, const float* zero,
                   bf16_t* Y, float* partial, size_t partial_bytes, hipStream_t stream) {
   const size_t told = qgemm_workspace_bytes(d);
   const bool have_workspace = partial != nullptr && told > 0 && partial_bytes >= told;
-  const int passes = d.T > 64 ? qgemm_blocks_passes(d, have_workspace) : 0;
-  for (int p = 0; p < passes; ++p) {
-    LayerDims part = d;
-    int64_t t0;
-    blocks_pass(d, passes, p, &t0, &part.T);
-    launch_qgemm(part, X + t0 * d.i, packed, scale, zero, Y + t0 * d.o, partial, partial_bytes, stream);
-  }
-  if (passes > 0) return;
-  const PrefillPlan prompt = qgemm_prompt_plan(d, have_workspace);
-  if (prompt.form >= 0) {
-    launch_qgemm_prefill(prompt, d, X, packed, scale, zero, Y, stream);
-    return;
+  if (d.T > 64) {
+    const PrefillPlan prompt = qgemm_prompt_plan(d, have_workspace);
+    BlocksPlan plans[QB_PASSES_MAX];
+    const int passes = qgemm_blocks_passes(d, have_workspace, prompt.us, plans);
+    for (int p = 0; p < passes; ++p) {  // (the next pass reuses the partial sums' memory: stream order keeps the two apart)
+      LayerDims part = d;
+      int64_t t0;
+      blocks_pass(d, passes, p, &t0, &part.T);
+      launch_blocks(plans[p], part, X + t0 * d.i, packed, scale, zero, Y + t0 * d.o, partial, stream);
+    }
+    if (passes > 0) return;
+    if (prompt.form >= 0) {
+      launch_qgemm_prefill(prompt, d, X, packed, scale, zero, Y, stream);
+      return;
+    }
   }
   // up to 64 tokens, groups of 64 and more: every byte of X and of the codes to one wave, in whole cache lines
   const BlocksPlan blocks = qgemm_blocks_plan(d, have_workspace);
   if (blocks.nt > 0) {
-    launch_qgemm_blocks(blocks, d, X, packed, scale, zero, Y, partial, stream);
-    if (blocks.slices > 1) {
-      const int64_t quads = d.T * d.o / 4;
-      hipLaunchKernelGGL(qgemm_slices_sum_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream, partial, Y,
-                         blocks.slices, (int)d.T, 0, (int)d.o);
-    }
+    launch_blocks(blocks, d, X, packed, scale, zero, Y, partial, stream);
     return;
   }
   dim3 grid((unsigned)((d.o + 31) / 32));

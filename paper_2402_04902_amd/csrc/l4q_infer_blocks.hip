@@ -376,12 +376,12 @@ bool qb_layer(const LayerDims& d) {
 }
 
 constexpr int QB_SLICES_MAX = 4;
-int qb_tiles_max(const LayerDims& d) { return (d.o + 15) / 16 <= device_compute_units() ? 2 : 3; }
+int qb_tiles_max(const LayerDims& d, int64_t cus) { return (d.o + 15) / 16 <= cus ? 2 : 3; }
 
 // k-slices of at least four macros, none of them empty, whose workgroups all run at once
-bool qb_slices_ok(const LayerDims& d, int nt, int sl) {
+bool qb_slices_ok(const LayerDims& d, int64_t cus, int nt, int sl) {
   const int64_t tiles = (d.o + 15) / 16, macros = (d.i + 255) / 256;
-  return sl <= macros / 4 && (tiles + nt - 1) / nt * sl <= device_compute_units() && (sl - 1) * ((macros + sl - 1) / sl) < macros;
+  return sl <= macros / 4 && (tiles + nt - 1) / nt * sl <= cus && (sl - 1) * ((macros + sl - 1) / sl) < macros;
 }
 
 int qb_kstep(const LayerDims& d) { return d.bits == 8 || d.g == 64 ? 64 : 128; }
@@ -404,7 +404,7 @@ size_t qb_lds_bytes(const LayerDims& d, const BlocksPlan& plan) {
 // Estimated time (us), within 9 % (one token block; 5 % for more) rms of 11600 measured calls of 260 layers: workgroups that
 // run one after the other on a unit (two share one where registers and LDS allow: `sets` counts the latencies), their bytes of
 // X, their waves' matrix ops, conversions and scalings, their outputs; the matrix' bytes; with k-slices the second launch.
-double qb_us(const LayerDims& d, const BlocksPlan& plan) {
+double qb_us(const LayerDims& d, int64_t cus, const BlocksPlan& plan) {
   static const double c[4][10] = {
       // fixed, set, 100 KB of X, tiles + 1, conversions, scalings, slices, 4 MB of partial sums, 4 MB of codes, output blocks
       {2.43, 1.09, 0.29, 0.000, 0.32, 0.17, 1.98, 1.33, 0.24, 0.14},
@@ -412,7 +412,7 @@ double qb_us(const LayerDims& d, const BlocksPlan& plan) {
       {1.59, 1.10, 0.52, 0.071, 0.10, 0.07, 2.25, 0.20, 0.37, 0.29},
       {1.61, 1.39, 0.61, 0.012, 0.31, 0.06, 1.91, 0.85, 0.37, 0.25},
   };
-  const int64_t cus = device_compute_units(), tb = (d.T + 15) / 16;
+  const int64_t tb = (d.T + 15) / 16;
   const double* k = c[tb - 1];
   const int64_t wgs = ((d.o + 15) / 16 + plan.nt - 1) / plan.nt * plan.slices;
   const bool two = tb == 1 && qb_lds_bytes(d, plan) <= 80 * 1024 && plan.nt * (d.bits == 8 ? 2 : 1) <= 2;
@@ -431,8 +431,9 @@ double qb_us(const LayerDims& d, const BlocksPlan& plan) {
 
 size_t qgemm_blocks_workspace_bytes(const LayerDims& d) {
   if (!qb_layer(d)) return 0;
+  const int64_t cus = device_compute_units();
   for (int sl = QB_SLICES_MAX; sl > 1; --sl)
-    if (qb_slices_ok(d, qb_tiles_max(d), sl)) return (size_t)sl * 64 * (size_t)d.o * sizeof(float);
+    if (qb_slices_ok(d, cus, qb_tiles_max(d, cus), sl)) return (size_t)sl * 64 * (size_t)d.o * sizeof(float);
   return 0;
 }
 
@@ -468,12 +469,12 @@ BlocksPlan qgemm_blocks_plan(const LayerDims& d, bool have_workspace) {
   // beyond a block, as many tiles per workgroup as give one round of them, where their tables fit; slices within a round
   const int whole = (int)(d.T > 16 && per_unit <= 3 ? per_unit : 1);
   const int nt_min = fits({whole, 1, (int)macros, 0.0}) ? whole : 1;
-  for (int nt = nt_min; nt <= qb_tiles_max(d); ++nt)
+  for (int nt = nt_min; nt <= qb_tiles_max(d, cus); ++nt)
     for (int sl = 1; sl <= QB_SLICES_MAX; ++sl) {
       BlocksPlan plan = {nt, sl, (int)((macros + sl - 1) / sl), 0.0};
       if (!fits(plan) || (per_unit == 1 && nt > 1 && sl == 1)) continue;
-      if (sl > 1 && (!have_workspace || !qb_slices_ok(d, nt, sl))) continue;
-      plan.us = qb_us(d, plan);
+      if (sl > 1 && (!have_workspace || !qb_slices_ok(d, cus, nt, sl))) continue;
+      plan.us = qb_us(d, cus, plan);
       BlocksPlan& b = sl > 1 ? best_split : best;
       if (b.nt == 0 || plan.us < b.us) b = plan;
     }

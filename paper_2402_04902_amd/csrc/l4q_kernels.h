@@ -192,10 +192,12 @@ struct PrefillPlan {
 };
 PrefillPlan qgemm_prefill_plan(const LayerDims& d);
 int qgemm_prompt_wide_rows(const LayerDims& d);  // weight rows of a wide tile (form 2): 256 or 192
-// ... where it is faster than passes of at most 64 tokens through the kernels of l4q_infer.hip; form -1: those are
+// ... where it is faster than passes of at most 64 tokens through the kernels of l4q_infer.hip; form -1: those are, and us theirs
 PrefillPlan qgemm_prompt_plan(const LayerDims& d, bool have_workspace);
-// Passes of at most 64 tokens through l4q_infer_blocks.hip where they are faster than either; 0: they are not
-int qgemm_blocks_passes(const LayerDims& d, bool have_workspace);
+// Passes of at most 64 tokens through l4q_infer_blocks.hip where they are faster than either; 0: they are not.  plans: one per
+// pass; other_us: estimated time of the others
+constexpr int QB_PASSES_MAX = 8;
+int qgemm_blocks_passes(const LayerDims& d, bool have_workspace, double other_us, BlocksPlan* plans);
 void launch_qgemm_prefill(const PrefillPlan& plan, const LayerDims& d, const bf16_t* X, const uint32_t* packed,
                           const float* scale, const float* zero, bf16_t* Y, hipStream_t stream);
 

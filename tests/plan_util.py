@@ -17,12 +17,17 @@ class _PrefillPlan(ctypes.Structure):
 PASSES, TILES_64x128, TILES_128x128, TILES_128x256 = -1, 0, 1, 2
 
 
-def prompt_form(T, i, o, bits, g, workspace=True):
-    """l4q::qgemm_prompt_plan: the tile shape a quantized forward of more than 64 tokens takes, or PASSES."""
+def prompt_plan(T, i, o, bits, g, workspace=True):
+    """l4q::qgemm_prompt_plan"""
     f = getattr(binding.load_library(), "_ZN3l4q17qgemm_prompt_planERKNS_9LayerDimsEb")
     f.restype, f.argtypes = _PrefillPlan, [ctypes.POINTER(_LayerDims), ctypes.c_bool]
     q = float(1 << (bits - 1))
-    return f(ctypes.byref(_LayerDims(T, i, o, 8, bits, g, 2.0, -q, q - 1.0, False)), workspace).form
+    return f(ctypes.byref(_LayerDims(T, i, o, 8, bits, g, 2.0, -q, q - 1.0, False)), workspace)
+
+
+def prompt_form(*call):
+    """The tile shape a quantized forward of more than 64 tokens takes, or PASSES."""
+    return prompt_plan(*call).form
 
 
 def wide_tile_rows(T, i, o, bits, g):

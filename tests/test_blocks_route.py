@@ -2,12 +2,13 @@
 and k-slices, at sizes where the choice was measured, and that the GPU cases cover the forms they name.  Host code alone (256
 compute units are assumed)."""
 import ctypes
+import timeit
 
 import pytest
 
 from paper_2402_04902_amd import binding
 from paper_2402_04902_amd.inputs import DTYPE_BF16, LayerSpec
-from plan_util import _LayerDims
+from plan_util import _LayerDims, prompt_plan
 from test_gpu_prefill import CASES
 
 NOT_THIS_FORM = (0, 1)
@@ -79,12 +80,18 @@ def test_other_kernels(T, i, o, bits, g):
 
 
 def passes(T, i, o, bits, g, workspace=None):
+    return planned_passes(T, i, o, bits, g, workspace)()
+
+
+def planned_passes(T, i, o, bits, g, workspace=None):
     if workspace is None:
         workspace = workspace_bytes(T, i, o, bits, g) > 0
-    f = getattr(binding.load_library(), "_ZN3l4q19qgemm_blocks_passesERKNS_9LayerDimsEb")
-    f.restype, f.argtypes = ctypes.c_int, [ctypes.POINTER(_LayerDims), ctypes.c_bool]
+    f = getattr(binding.load_library(), "_ZN3l4q19qgemm_blocks_passesERKNS_9LayerDimsEbdPNS_10BlocksPlanE")
+    f.restype, f.argtypes = ctypes.c_int, [ctypes.POINTER(_LayerDims), ctypes.c_bool, ctypes.c_double, ctypes.POINTER(_BlocksPlan)]
     q = float(1 << (bits - 1))
-    return f(ctypes.byref(_LayerDims(T, i, o, 8, bits, g, 2.0, -q, q - 1.0, False)), workspace)
+    dims, plans = _LayerDims(T, i, o, 8, bits, g, 2.0, -q, q - 1.0, False), (_BlocksPlan * 8)()
+    other_us = prompt_plan(T, i, o, bits, g, workspace).us
+    return lambda: f(ctypes.byref(dims), workspace, other_us, plans)
 
 
 # more than 64 tokens: the number of passes
@@ -114,6 +121,15 @@ def test_gpu_cases_take_the_passes_they_name(case, n):
 ])
 def test_passes(T, i, o, bits, g, n):
     assert passes(T, i, o, bits, g) == n
+
+
+def test_passes_of_the_same_size_are_planned_once():
+    """Host time of the plan for eight passes of 64 tokens against one pass: the loop's own steps, not eight plans (5 to 6 times)."""
+    def us(call):
+        return min(timeit.repeat(call, number=300, repeat=15))
+    eight, one = planned_passes(512, 16384, 256, 2, 64), planned_passes(65, 16384, 256, 2, 64)  # (65: two plans)
+    assert eight() == 8 and one() == 2
+    assert us(eight) <= 1.5 * us(one)
 
 
 @pytest.mark.parametrize("case,forms", CASES)
