@@ -481,7 +481,11 @@ BlocksPlan qgemm_blocks_plan(const LayerDims& d, bool have_workspace) {
   // (at four token blocks the estimate is 0.2 us too good for slices: of 4700 layers with both measured, the slices it takes are
   // more than 3 % slower than one slice on 31 and up to 2.2 times as fast on the others)
   const double off = d.T > 48 ? 0.2 : 0.0;
-  return best_split.nt > 0 && (best.nt == 0 || best_split.us + off < best.us) ? best_split : best;
+  // (a second launch is 2.7 us of the caller's time: in a loop of eager calls one launch takes 7.8 us, two 10.4, whatever the
+  // kernels take; in a graph slices gain 0.7 us on layers of 7 to 8 us in one slice, 1.4 on those of 9 to 10.  At 8.5 what the
+  // one loses is what the other gains)
+  if (best.nt > 0 && (best_split.nt == 0 || best.us < 8.5 || best.us <= best_split.us + off)) return best;
+  return best_split;
 }
 
 void launch_qgemm_blocks(const BlocksPlan& plan, const LayerDims& d, const bf16_t* X, const uint32_t* packed,

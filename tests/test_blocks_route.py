@@ -143,6 +143,12 @@ def test_slices_only_with_a_workspace():
     assert blocks_form(48, 11008, 4352, 3, 128, False)[1] == 1
 
 
+def test_short_calls_have_one_launch():
+    assert blocks_form(8, 8192, 1024, 4, 128)[1] == 1   # eager 7.9 us, in two launches 10.2
+    assert blocks_form(3, 4224, 232, 8, 64)[1] == 1     # 7.9 / 10.2
+    assert blocks_form(16, 11008, 1024, 4, 64)[1] > 1
+
+
 @pytest.mark.parametrize("i", [1024, 4096, 5120, 11264, 16384])
 @pytest.mark.parametrize("bits,g", [(2, 64), (3, 128), (4, 128), (4, 1024), (8, 64)])
 def test_the_workspace_that_is_told_has_room_for_every_plans_slices(i, bits, g):
