@@ -1432,7 +1432,7 @@ WregPlan qgemm_wreg_plan(const LayerDims& d) {
   } else if (d.bits == 3) {
     if (many && cpw < 3) to = 16;
   } else if (d.bits == 2) {
-    if ((nt == 1 && cpw == 1) || few_tiles) return plan;  // (from 3 or 17 tokens at the earliest)
+    if (nt == 1 && cpw == 1 ? d.T <= 16 || chunks > 8 : few_tiles) return plan;  // (short rows, two token blocks: below)
     if (many) from = 2;
   } else {
     if (few_tiles) return plan;  // (from 17 tokens)
@@ -1445,7 +1445,7 @@ WregPlan qgemm_wreg_plan(const LayerDims& d) {
   plan.grid = (unsigned)((tiles + nt - 1) / nt);
   // Whole passes of two token blocks (17 .. 32 tokens) on short rows: 8 waves with a chunk each convert the codes once for both
   // blocks (4 bits: [4096 x 4096] with two chunks 7.7 / 10.3 us at 17 / 32 tokens against 8.3 / 10.7).
-  if (d.bits != 8 && d.T > 16 && chunks <= 8 && (nt == 2 || nt == 3) && nt * 16 * ((d.i / d.g + 3) / 4) <= 512) {
+  if (d.bits != 8 && d.T > 16 && chunks <= 8 && nt <= 3) {
     plan.wv = 8;
     plan.tbp = 2;
   }
@@ -1470,7 +1470,8 @@ void launch_qgemm_wreg(const WregPlan& plan, const LayerDims& d, const bf16_t* X
   // (every combination qgemm_wreg_plan can return, and no other)
   if (plan.wv == 8) {
     if constexpr (BITS != 8) {
-      if (key == 21) L4Q_WR(2, 1, 8, 2); else L4Q_WR(3, 1, 8, 2);
+      if (key == 11) { if constexpr (BITS != 4) L4Q_WR(1, 1, 8, 2); }
+      else if (key == 21) L4Q_WR(2, 1, 8, 2); else L4Q_WR(3, 1, 8, 2);
     }
   } else if (key == 21) {
     L4Q_WR(2, 1, 16, 1);

@@ -446,9 +446,17 @@ size_t qgemm_blocks_workspace_bytes(const LayerDims& d) {
 // At few tokens, where the matrix is all there is to load, the in-register form's sixteen waves with every request in the
 // first instructions stay ahead on layers of more row tiles than units: 1.1 - 1.4 times up to 2 tokens (8 bits: 3), on rows of one chunk per
 // wave (4096) up to 8 tokens with two tiles per unit (8 bits: 16), 12 with three and more (8 bits: 4; in groups of 64, 8); and its two-block form on
-// short rows (up to 2048: 1.05 - 1.14 times up to 32 tokens) and, up to 24 tokens, with four tiles per unit.  8 bits, short rows
-// and four tiles per unit: 64-row tiles ([14336 x 1024], 20 / 64 tokens 9.6 / 13.2, 11.2 / 16.5).  One tile per unit: one token
-// 0.85 - 1.1 times either way, from two (8 bits: three) on this form.
+// short rows (up to 2048: 1.05 - 1.14 times up to 32 tokens; 2 and 3 bits with one tile per unit up to 512 and 1024, 1.05 times)
+// and, up to 24 tokens, with four tiles per unit.  8 bits, short rows and four tiles per unit: 64-row tiles ([14336 x 1024], 20 / 64
+// tokens 9.6 / 13.2, 11.2 / 16.5), and with three where these fill most units ([11184 x 512] 31 tokens 7.4 / 8.6, [11808 x 256] 50 6.1 /
+// 10.1).  Rows of 128 or 384, whose last macro is half empty, 17 to 32 tokens: the streaming form ([8848 x 128], 8 bits, 5.2 / 6.6;
+// 4 bits in groups of 64, rows up to 256 [12000 x 256] 6.0 / 6.9).  One tile per unit: one token
+// 0.85 - 1.1 times either way, from two (8 bits: three) on this form; but 4 and 8 bits with the activations in LDS
+// (qgemm_decode_kernel) where a wave has one macro of a short row or some waves have one macro more than others: in a graph, us,
+// that kernel / this one, 4 bits [512 x 512] 4 tokens 3.7 / 4.0, [4096 x 1024] 2 3.7 / 4.2, [2048 x 3072] 2 4.7 / 5.1, [2048 x 5120]
+// 2 5.4 / 5.8; 8 bits [2048 x 512] 3 3.6 / 4.4, 16 3.9 / 4.5, [512 x 1536] 4 4.0 / 4.3, groups of 64 [8192 x 384] 16 4.4 / 5.6.
+// 2 and 3 bits, two tiles per unit, rows of two chunks per wave (6144 to 8192): in registers up to 7 tokens ([8192 x 8192], 3 bits,
+// 3 tokens 11.3 / 11.9).
 BlocksPlan qgemm_blocks_plan(const LayerDims& d, bool have_workspace) {
   const BlocksPlan none = {0, 1, 0, 0.0};
   if (d.T > 64 || !qb_layer(d) || d.T * d.i * 2 >= (1ll << 31)) return none;
@@ -458,11 +466,30 @@ BlocksPlan qgemm_blocks_plan(const LayerDims& d, bool have_workspace) {
     int from = d.bits == 8 ? 3 : 2;
     if (per_unit > 1 && d.i > 4096) from = d.bits == 8 ? 4 : 3;
     else if (per_unit > 1) from = d.g < 128 ? 9 : per_unit == 2 ? (d.bits == 8 ? 17 : 9) : d.bits == 8 ? 5 : 13;
+    if ((d.bits == 2 || d.bits == 3) && per_unit == 2 && d.i > 6144 && d.i <= 8192) from = 8;
+    if (d.bits == 8 && d.g < 128 && per_unit > 1 && d.i <= 1024) from = 17;
     if (d.T < from) return none;
+    // (calls that the in-register form does not take: qgemm_decode_kernel's)
+    if (per_unit == 1 && d.T <= 16 && (d.bits == 4 || (d.bits == 8 && (2 * tiles < cus || d.g < 128)))) {
+      if (d.i <= 1024 && d.T <= (d.bits == 8 || d.i <= 512 ? 16 : 12)) return none;
+      if ((d.bits == 8 && d.i <= 1536) || (d.i > 2048 && d.i <= 3072)) {
+        if (d.T <= (d.bits == 8 ? 6 : 4)) return none;
+      }
+      if (d.T == 2 && d.i > 4096 && d.i <= 5120) return none;
+    }
     if (d.g >= 128 && d.bits != 8 && d.T > 16 &&
         ((per_unit > 1 && d.i <= 2048 && d.T <= 32) || (per_unit > 3 && d.i <= 4096 && d.T <= 24)))
       return none;
+    if (d.g >= 128 && d.bits < 4 && d.T > 16 && d.T <= 32 && per_unit == 1 && d.i <= (d.bits == 3 ? 1024 : 512)) return none;
     if (d.bits == 8 && per_unit > 3 && d.i <= 2048) return none;
+    if (d.bits == 8 && per_unit == 3 && d.i % 128 == 0 && (d.i <= 512 || (d.i <= 1024 && d.T > 48)) && d.T > 16) {
+      const int64_t wide = (d.o + 63) / 64;
+      if (8 * wide >= 5 * ((wide + cus - 1) / cus) * cus) return none;
+    }
+    if (d.bits == 8 && per_unit > 1 && d.T > 16 && d.T <= 32 && d.i < 512 && d.i % 256 == 128 && (d.g < 128 || (per_unit == 3 && d.i == 128)))
+      return none;
+  } else if (d.bits == 4 && per_unit > 2 && d.T > 16 && d.T <= 32 && d.i <= 256) {
+    return none;
   }
   BlocksPlan best = none, best_split = none;
   auto fits = [&](const BlocksPlan& plan) { return qb_lds_bytes(d, plan) <= 160 * 1024; };

@@ -39,8 +39,8 @@ def blocks_form(*call):
 # (T, in, out, bits, group), (tiles per workgroup, slices): every count of tiles and token blocks, k-slices, each code width in
 # groups of 64 and more; rows of one step to many macros that do not divide among the waves, the last one partial; ragged tiles
 GPU_CASES = [
-    ((3, 128, 40, 4, 128), (1, 1)),       # one code step, seven idle waves
-    ((16, 64, 24, 8, 64), (1, 1)),        # half a load of codes
+    ((33, 128, 40, 4, 128), (1, 1)),      # one code step, seven idle waves
+    ((48, 64, 24, 8, 64), (1, 1)),        # half a load of codes
     ((5, 320, 72, 2, 64), (1, 1)),
     ((16, 2176, 4104, 3, 128), (2, 1)),   # 257 tiles
     ((9, 1600, 9000, 4, 64), (3, 1)),
@@ -74,9 +74,38 @@ def test_gpu_cases_take_the_forms_they_name(case, form):
     (43, 4096, 4096, 3, 64),     # no 3 bits in groups of 64
     (43, 4096, 4096, 4, 32),     # groups below 64
     (65, 4096, 4096, 4, 128),    # more than four blocks
+    # short rows, a tile per unit: activations in LDS (us in a graph, that kernel / this one)
+    (4, 512, 512, 4, 128),       # 3.7 / 4.0
+    (12, 1024, 4096, 4, 256),    # 4.0 / 4.2
+    (2, 3072, 2048, 4, 128),     # 4.7 / 5.1
+    (2, 5120, 2048, 4, 128),     # 5.4 / 5.8
+    (3, 512, 2048, 8, 64),       # 3.6 / 4.4
+    (16, 1024, 512, 8, 128),     # 4.3 / 4.6
+    (6, 2560, 1000, 8, 128),     # 5.0 / 5.4
+    (16, 384, 8192, 8, 64),      # 4.4 / 5.6
+    # two chunks per wave in registers
+    (3, 8192, 8192, 3, 128),     # 11.3 / 11.9
+    (7, 7424, 6144, 2, 128),     # 0.95 times
+    # two token blocks in registers, the streaming form, 64-row tiles
+    (17, 512, 3944, 3, 256),     # 4.7 / 5.1
+    (20, 512, 1000, 2, 128),
+    (17, 128, 8848, 8, 128),     # 5.2 / 6.6
+    (32, 256, 12000, 4, 64),     # 6.0 / 6.9
+    (50, 256, 11808, 8, 256),    # 6.1 / 10.1
+    (64, 1024, 11280, 8, 256),   # 11.2 / 12.7
 ])
 def test_other_kernels(T, i, o, bits, g):
     assert blocks_form(T, i, o, bits, g) == NOT_THIS_FORM
+
+
+@pytest.mark.parametrize("T,i,o,bits,g", [
+    # ... and beside those
+    (13, 1024, 4096, 4, 256), (5, 3072, 2048, 4, 128), (3, 5120, 2048, 4, 128), (2, 2048, 2048, 4, 128), (7, 2560, 1000, 8, 128),
+    (3, 512, 2048, 8, 128), (17, 1024, 8192, 8, 64), (8, 8192, 8192, 3, 128), (33, 512, 3944, 3, 256), (17, 1152, 3944, 3, 128),
+    (33, 256, 12000, 4, 64), (33, 128, 8000, 8, 128), (50, 256, 10000, 8, 256), (48, 1024, 11280, 8, 256),
+])
+def test_this_kernel_beside_other_kernels(T, i, o, bits, g):
+    assert blocks_form(T, i, o, bits, g) != NOT_THIS_FORM
 
 
 def passes(T, i, o, bits, g, workspace=None):
