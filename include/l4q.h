@@ -137,8 +137,8 @@ int l4q_backward(const l4q_desc* desc, const void* X, const void* dY, const void
  * goes through the quantizer and the LoRA path stays next to it in high precision,
  *   Y  = X . Q(W0)^T + gamma (X A^T) B^T
  *   dX = dY . Q(W0) + gamma (dY B) A;   d(scale), d(zero) are taken from dWq = dY^T X in binary32 with Eq. quant_lsq_s /
- *   quant_lsq_b.  The workspace has room for dWq (the memory overhead the section names); it is written there in F32 mode and
- *   for groups other than 32 .. 256, otherwise it stays in the product's registers.
+ *   quant_lsq_b.  The workspace has room for dWq (the memory overhead the section names); it is written there in F32 mode, for
+ *   groups other than 32 .. 256 and on small layers, otherwise it stays in the product's registers.
  *   dA = gamma (dY B)^T X,  dB = gamma dY^T (X A^T)              (Eq. lora_backward).
  * Arguments, layouts, dtypes, flags (L4Q_FLAG_ACCUMULATE_GRADS) and error behaviour as l4q_forward / l4q_backward;
  * L4Q_FLAG_UNFUSED_BACKWARD has no effect.  The side products X A^T and dY B are binary32; in BF16 mode the LoRA term

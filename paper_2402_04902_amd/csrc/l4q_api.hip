@@ -623,8 +623,8 @@ int l4q_qatlora_backward(const l4q_desc* desc, const void* X, const void* dY, co
     const l4q::LoraDown down[2] = {{dYb, d.o, bT, d.o, w.dyb}, {Xb, d.i, Ab, d.i, w.xa}};
     l4q::launch_lora_down(down, 2, d.T, d.r, stream);
     gemm_nt_rank(dYb, d.o, w.wqT, d.T, d.i, w.opad, d.o, (bf16_t*)dX, {w.dyb, Ab, d.r, d.gamma, false}, stream);
-    // scale and zero are updated from the weight gradient, in the product's epilogue where it covers the groups
-    if (l4q::dw_groups_supported(d)) {
+    // scale and zero are updated from the weight gradient, in the product's epilogue where that is faster
+    if (l4q::dw_groups_used(d)) {
       l4q::launch_dw_groups(dq, dYb, Xb, W0b, scale, zero, dscale, dzero, stream);
     } else {
       l4q::launch_gemm_bf16_kmajor_f32(dYb, d.o, Xb, d.i, d.o, d.i, d.T, w.dwq, d.i, stream);

@@ -221,8 +221,9 @@ void launch_dw_fused(const LayerDims& d, const bf16_t* dY, const bf16_t* X, cons
 // with the library's GEMM kernels, each product split along k into dw_masked_product_slices() partial results that
 // the caller adds in slice order.
 bool dw_masked_supported(const LayerDims& d);
-// dscale and dzero of a quantizer that sees W0 alone (QAT-LoRA), for the same groups; no other output
-bool dw_groups_supported(const LayerDims& d);
+// dscale and dzero of a quantizer that sees W0 alone (QAT-LoRA); no other output.  dw_groups_used: for the same groups, where it
+// is faster than storing dWq
+bool dw_groups_used(const LayerDims& d);
 void launch_dw_groups(const LayerDims& d, const bf16_t* dY, const bf16_t* X, const bf16_t* W0, const float* scale,
                       const float* zero, float* dscale, float* dzero, hipStream_t stream);
 void launch_dw_masked(const LayerDims& d, const bf16_t* dY, const bf16_t* X, const uint16_t* fgrad, float* dscale,

@@ -1,17 +1,15 @@
-"""dscale and dzero of the QAT-LoRA layer in bfloat16, made in the weight-gradient product's epilogue: tile edges in rows, columns
-and tokens, every group size that the epilogue covers (and one that it does not), scales outside the range of the reciprocal,
-weights that are not finite, against binary64 sums over binary32 quotients."""
+"""dscale and dzero of the QAT-LoRA layer in bfloat16, made in the weight-gradient product's epilogue or, on layers of few tiles
+and groups that it does not cover, from the stored gradient: tile edges in rows, columns and tokens, every group size of the
+epilogue, scales outside the range of the reciprocal, weights that are not finite, against binary64 sums over binary32 quotients."""
 import pytest
 
 from paper_2402_04902_amd.inputs import DTYPE_BF16, LayerSpec
+from test_qatlora_route import EPILOGUE, STORED
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("T,i,o,bits,g", [
-    (1, 32, 8, 4, 32), (70, 288, 264, 3, 32), (33, 320, 520, 2, 64), (97, 512, 250 + 6, 4, 128), (64, 768, 72, 8, 256),
-    (161, 1280, 776, 5, 256), (40, 512, 136, 4, 512),
-])
+@pytest.mark.parametrize("T,i,o,bits,g", EPILOGUE + STORED)
 @pytest.mark.parametrize("kind", ["plain", "tiny_scale", "not_finite", "accumulate"])
 def test_group_gradients(T, i, o, bits, g, kind):
     import torch
