@@ -37,9 +37,11 @@ def test_group_gradients(T, i, o, bits, g, kind):
     grads = [torch.full(s, 0.25, device=dev) for s in ((r, i), (o, r), (o, G), (o, G))]
     if kind == "accumulate":
         desc.flags = binding.FLAG_ACCUMULATE_GRADS
-    ws = torch.empty(max(binding.l4q_qatlora_workspace_bytes(desc)), dtype=torch.uint8, device=dev)
-    binding.l4q_qatlora_backward(desc, X, dY, W0, A, B, scale, zero, torch.empty_like(X), *grads, ws)
+    told = binding.l4q_qatlora_workspace_bytes(desc)[1]
+    ws = torch.full((told + 4096,), 0x5A, dtype=torch.uint8, device=dev)
+    binding.l4q_qatlora_backward(desc, X, dY, W0, A, B, scale, zero, torch.empty_like(X), *grads, ws[:told])
     torch.cuda.synchronize()
+    assert bool((ws[told:] == 0x5A).all())
     w = (W0.float() - zero.repeat_interleave(g, 1)) / scale.repeat_interleave(g, 1)   # the stated binary32 operations
     inside = (w >= qn) & (w <= qp)
     code = torch.round(torch.where(torch.isnan(w), qn, w.clamp(qn, qp)))               # (a NaN: clipped, at the lower end)

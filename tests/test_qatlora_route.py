@@ -8,7 +8,7 @@ from paper_2402_04902_amd import binding
 from plan_util import _LayerDims
 
 EPILOGUE = [(1, 1056, 2056, 4, 32), (70, 1312, 1288, 3, 32), (33, 1088, 1032, 2, 64), (97, 640, 776, 4, 128), (64, 768, 776, 8, 256),
-            (161, 1280, 776, 5, 256)]
+            (161, 1280, 776, 5, 256), (600, 2048, 520, 4, 32)]  # (600 tokens: dB in partial sums)
 STORED = [(1, 32, 8, 4, 32), (70, 288, 264, 3, 32), (33, 320, 520, 2, 64), (97, 512, 256, 4, 128), (64, 768, 72, 8, 256),
           (40, 512, 136, 4, 512)]
 
