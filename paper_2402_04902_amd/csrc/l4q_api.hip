@@ -528,9 +528,10 @@ int l4q_quantized_forward(const l4q_desc* desc, const void* X, const uint32_t* p
     if (!aligned(p, 16)) return L4Q_ERR_ALIGN;
   if (workspace && !aligned(workspace, kWsAlign)) return L4Q_ERR_ALIGN;
   (void)hipGetLastError();
-  l4q::launch_qgemm(d, (const bf16_t*)X, packed, scale, zero, (bf16_t*)Y, static_cast<float*>(workspace),
-                    workspace ? workspace_bytes : 0, static_cast<hipStream_t>(hip_stream));
-  return launch_status();
+  const bool launched =
+      l4q::launch_qgemm(d, (const bf16_t*)X, packed, scale, zero, (bf16_t*)Y, static_cast<float*>(workspace),
+                        workspace ? workspace_bytes : 0, static_cast<hipStream_t>(hip_stream));
+  return launched ? launch_status() : L4Q_ERR_LAUNCH;
 }
 
 int l4q_quantized_forward_workspace_bytes(const l4q_desc* desc, size_t* bytes) {

@@ -1381,27 +1381,18 @@ TilePlan qgemm_tile_plan(const LayerDims& d) {
   return plan;
 }
 
+inline int64_t plan_grid_rounds(int64_t tiles, int64_t nt, int64_t cus) { return ((tiles + nt - 1) / nt + cus - 1) / cus; }
+
+}  // namespace
+
 // How the weights-in-registers kernel would run this layer: tiles per workgroup and chunks per wave (nt = 0: not at
 // all, or not faster than the streaming forms), among the calls that qgemm_blocks_plan leaves: one or two tokens (8 bits: three),
-// more on layers of several row tiles per unit (see there).  Measured against the streaming forms (us; T = 1 / 5 / 16 / 33 / 64):
-//   4 bits [11008 x 4096] (3 tiles, 1 chunk): 6.9 / 7.6 / 9.9 / 18.2 / 23.9 against 7.2 / 12.6 / 16.9 / 27.1 / 28.1;
-//          [16384 x 4096] (4, 1): 8.5 / 9.5 / 11.7 / 21.7 / 28.3 against 9.6 / 17.1 / 22.5 / 27.9 / 29.6;
-//          [4096 x 4096] (1, 1): 4.7 / 5.6 / 6.9 / 12.1 / 17.8 against 4.7 / 5.3 / 6.4 / 12.9 / 14.2;
-//          [8192 x 8192] (2, 2): 10.2 / 11.0 / 15.0 / 27.5 / 38.6 against 10.0 / 14.6 / 28.6 / 30.1 / 31.5;
-//          [4096 x 11008] (1, 3): 9.0 / 10.4 / 15.4 / 30.1 / 45.1 against 8.6 / 9.9 / 15.6 / 24.1 / 25.3 (every
-//          compute unit reads the whole of X for its 16 rows: the time per token block grows with the chunks per wave);
-//   3 bits [11008 x 4096]: 7.5 / 8.2 / 10.5 / 20.2 / 26.0 against 9.7 / 15.2 / 22.2 / 33.0 / 35.8;
-//          [4096 x 11008]: 9.0 / 10.1 / 14.9 / 29.8 / 44.7 against 11.6 / 19.9 / 20.1 / 28.5 / 27.4;
-//   2 bits [11008 x 4096]: 7.3 / 8.2 / 10.2 / 20.1 / 25.7 against 7.7 / 13.8 / 18.3 / 43.6 / 54.0;
-//          [4096 x 11008]: 8.6 / 9.9 / 14.7 / 29.7 / 44.8 against 10.0 / 11.3 / 25.5 / 40.0 / 55.0;
-//   8 bits [4096 x 4096]: 5.7 / 6.2 / 8.3 / 13.8 / 19.1 against 7.3 / 8.2 / 8.6 / 14.5 / 15.0;
-//          [8192 x 4096] (2, 1): 7.5 / 8.0 / 10.1 / 19.9 / 25.8 against 9.0 / 13.0 / 16.1 / 22.8 / 22.8.
-struct WregPlan {
-  int nt, cpw;
-  unsigned grid;
-  int wv, tbp;  // waves per workgroup, token blocks per pass
-};
-inline int64_t plan_grid_rounds(int64_t tiles, int64_t nt, int64_t cus) { return ((tiles + nt - 1) / nt + cus - 1) / cus; }
+// more on layers of several row tiles per unit (see there).  Measured against the streaming forms (us):
+//   4 bits [11008 x 4096] (3 tiles, 1 chunk) 1 / 5 tokens 6.9 / 7.6 against 7.2 / 12.6; [16384 x 4096] (4, 1) 8.5 / 9.5 against
+//          9.6 / 17.1;
+//   3 bits [11008 x 4096] 1 / 5 tokens 7.5 / 8.2 against 9.7 / 15.2; [4096 x 11008] (1, 3) one token 9.0 against 11.6;
+//   2 bits [11008 x 4096] 1 / 5 tokens 7.3 / 8.2 against 7.7 / 13.8; [4096 x 11008] one token 8.6 against 10.0;
+//   8 bits [4096 x 4096] one token 5.7 against 7.3; [8192 x 4096] (2, 1) 1 / 5 / 16 tokens 7.5 / 8.0 / 10.1 against 9.0 / 13.0 / 16.1.
 WregPlan qgemm_wreg_plan(const LayerDims& d) {
   WregPlan plan = {0, 0, 0, WR_WAVES, 1};
   if (d.bits != 2 && d.bits != 3 && d.bits != 4 && d.bits != 8) return plan;
@@ -1418,11 +1409,8 @@ WregPlan qgemm_wreg_plan(const LayerDims& d) {
     if (cpw > 1) return plan;
     if (nt > 2) nt = 2;
   }
-  // More workgroups than compute units (13B / 70B-class projections; us at 4 / 16 / 24 / 40 tokens): the later rounds
-  // do not overlap the first one's latency, and the streaming forms catch up beyond a token block -
-  // 4 bits [28672 x 8192] 39.5 / 55.9 / 76.8 / 105 against 46.6 / 67.4 / 76.0 / 98.7, [13824 x 5120] 18.0 / 22.8 /
-  // 31.5 / 42.7 against 18.9 / 23.1 / 26.0 / 33.6; 3 bits [13824 x 5120] 19.6 / 24.3 / 34.6 / 46.5 against 26.8 / 26.9 / 28.8 / 40.0;
-  // 2 bits [5120 x 13824], one token 17 - 37 against 12 - 30.
+  // More workgroups than compute units: the later rounds do not overlap the first one's latency, and the streaming forms catch
+  // up beyond a token block (2 bits [5120 x 13824] at one token already: 17 - 37 us against 12 - 30).
   const bool many = plan_grid_rounds(tiles, nt, cus) > 1;
   const bool few_tiles = 2 * tiles < cus;  // (the streaming forms split k further over the idle units)
   int64_t from = 1, to = 64;
@@ -1452,42 +1440,49 @@ WregPlan qgemm_wreg_plan(const LayerDims& d) {
   return plan;
 }
 
+namespace {
+
+// The instances there are: every combination that qgemm_wreg_plan returns, and no other (waves of 8: two token blocks per pass).
+constexpr bool wreg_instance(int bits, int nt, int cpw, int wv) {
+  if (wv == 8) return cpw == 1 && nt <= 3 && bits != 8 && (bits != 4 || nt > 1);
+  if (bits == 8) return cpw == 1 && nt <= 2;
+  if (bits == 4) return cpw == 1 && nt >= 2;
+  return nt * cpw <= WR_UNITS_MAX && !(bits == 2 && nt == 1 && cpw == 1);
+}
+
+// false: there is no such instance, nothing is launched
 template <int BITS>
-void launch_qgemm_wreg(const WregPlan& plan, const LayerDims& d, const bf16_t* X, const uint32_t* packed,
+bool launch_qgemm_wreg(const WregPlan& plan, const LayerDims& d, const bf16_t* X, const uint32_t* packed,
                        const float* scale, const float* zero, bf16_t* Y, hipStream_t stream) {
   const int64_t G = d.i / d.g;
   const size_t lds_bytes =
       ((size_t)2 * plan.nt * plan.tbp * plan.wv * 256 + (size_t)2 * plan.nt * 16 * (G | 1)) * sizeof(float);
-#define L4Q_WR(N, C, W, P)                                                                                          \
-  do {                                                                                                               \
-    if (lds_bytes > 64 * 1024)                                                                                       \
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&qgemm_wreg_kernel<BITS, N, C, W, P>),                 \
-                                hipFuncAttributeMaxDynamicSharedMemorySize, QD_LDS_MAX);                             \
-    hipLaunchKernelGGL((qgemm_wreg_kernel<BITS, N, C, W, P>), dim3(plan.grid), dim3(W * 64), lds_bytes,              \
-                       stream, X, packed, scale, zero, Y, (int)d.T, (int)d.o, (int)d.i, d.g);                        \
-  } while (0)
-  const int key = plan.nt * 10 + plan.cpw;
-  // (every combination qgemm_wreg_plan can return, and no other)
-  if (plan.wv == 8) {
-    if constexpr (BITS != 8) {
-      if (key == 11) { if constexpr (BITS != 4) L4Q_WR(1, 1, 8, 2); }
-      else if (key == 21) L4Q_WR(2, 1, 8, 2); else L4Q_WR(3, 1, 8, 2);
+  bool launched = false;
+  auto instance = [&](auto nt, auto cpw, auto wv) {
+    constexpr int N = decltype(nt)::value, C = decltype(cpw)::value, W = decltype(wv)::value;
+    if constexpr (wreg_instance(BITS, N, C, W)) {
+      if (plan.nt != N || plan.cpw != C || plan.wv != W) return;
+      if (lds_bytes > 64 * 1024)
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&qgemm_wreg_kernel<BITS, N, C, W, W == 8 ? 2 : 1>),
+                                  hipFuncAttributeMaxDynamicSharedMemorySize, QD_LDS_MAX);
+      hipLaunchKernelGGL((qgemm_wreg_kernel<BITS, N, C, W, W == 8 ? 2 : 1>), dim3(plan.grid), dim3(W * 64), lds_bytes, stream,
+                         X, packed, scale, zero, Y, (int)d.T, (int)d.o, (int)d.i, d.g);
+      launched = true;
     }
-  } else if (key == 21) {
-    L4Q_WR(2, 1, 16, 1);
-  } else if constexpr (BITS == 8) {
-    L4Q_WR(1, 1, 16, 1);
-  } else if (key == 31) {
-    L4Q_WR(3, 1, 16, 1);
-  } else if constexpr (BITS == 4) {
-    L4Q_WR(4, 1, 16, 1);
-  } else {
-    if (key == 41) L4Q_WR(4, 1, 16, 1); else if (key == 12) L4Q_WR(1, 2, 16, 1); else if (key == 22) L4Q_WR(2, 2, 16, 1);
-    else if (key == 14) L4Q_WR(1, 4, 16, 1);
-    else if constexpr (BITS == 3) { if (key == 13) L4Q_WR(1, 3, 16, 1); else L4Q_WR(1, 1, 16, 1); }
-    else L4Q_WR(1, 3, 16, 1);
-  }
-#undef L4Q_WR
+  };
+  auto tiles = [&](auto cpw, auto wv) {
+    instance(std::integral_constant<int, 1>(), cpw, wv);
+    instance(std::integral_constant<int, 2>(), cpw, wv);
+    instance(std::integral_constant<int, 3>(), cpw, wv);
+    instance(std::integral_constant<int, 4>(), cpw, wv);
+  };
+  typedef std::integral_constant<int, WR_WAVES> Waves;
+  tiles(std::integral_constant<int, 1>(), std::integral_constant<int, 8>());
+  tiles(std::integral_constant<int, 1>(), Waves());
+  tiles(std::integral_constant<int, 2>(), Waves());
+  tiles(std::integral_constant<int, 3>(), Waves());
+  tiles(std::integral_constant<int, 4>(), Waves());
+  return launched;
 }
 
 }  // namespace
@@ -1608,7 +1603,7 @@ void launch_blocks(const BlocksPlan& plan, const LayerDims& d, const bf16_t* X, 
 
 }  // namespace
 
-void launch_qgemm(const LayerDims& d, const bf16_t* X, const uint32_t* packed, const float* scale, const float* zero,
+bool launch_qgemm(const LayerDims& d, const bf16_t* X, const uint32_t* packed, const float* scale, const float* zero,
                   bf16_t* Y, float* partial, size_t partial_bytes, hipStream_t stream) {
   const size_t told = qgemm_workspace_bytes(d);
   const bool have_workspace = partial != nullptr && told > 0 && partial_bytes >= told;
@@ -1622,27 +1617,26 @@ void launch_qgemm(const LayerDims& d, const bf16_t* X, const uint32_t* packed, c
       blocks_pass(d, passes, p, &t0, &part.T);
       launch_blocks(plans[p], part, X + t0 * d.i, packed, scale, zero, Y + t0 * d.o, partial, stream);
     }
-    if (passes > 0) return;
+    if (passes > 0) return true;
     if (prompt.form >= 0) {
       launch_qgemm_prefill(prompt, d, X, packed, scale, zero, Y, stream);
-      return;
+      return true;
     }
   }
   // up to 64 tokens, groups of 64 and more: every byte of X and of the codes to one wave, in whole cache lines
   const BlocksPlan blocks = qgemm_blocks_plan(d, have_workspace);
   if (blocks.nt > 0) {
     launch_blocks(blocks, d, X, packed, scale, zero, Y, partial, stream);
-    return;
+    return true;
   }
   dim3 grid((unsigned)((d.o + 31) / 32));
   // the fewest tokens, groups of 128 and more: the packed codes resident in registers
   const WregPlan wr = qgemm_wreg_plan(d);
   if (wr.nt > 0) {
-    if (d.bits == 2) launch_qgemm_wreg<2>(wr, d, X, packed, scale, zero, Y, stream);
-    else if (d.bits == 3) launch_qgemm_wreg<3>(wr, d, X, packed, scale, zero, Y, stream);
-    else if (d.bits == 4) launch_qgemm_wreg<4>(wr, d, X, packed, scale, zero, Y, stream);
-    else launch_qgemm_wreg<8>(wr, d, X, packed, scale, zero, Y, stream);
-    return;
+    if (d.bits == 2) return launch_qgemm_wreg<2>(wr, d, X, packed, scale, zero, Y, stream);
+    if (d.bits == 3) return launch_qgemm_wreg<3>(wr, d, X, packed, scale, zero, Y, stream);
+    if (d.bits == 4) return launch_qgemm_wreg<4>(wr, d, X, packed, scale, zero, Y, stream);
+    return launch_qgemm_wreg<8>(wr, d, X, packed, scale, zero, Y, stream);
   }
   // more than 32 tokens: the general kernel reads the weights once per 64 tokens, the streaming form once per 32
   // smallest batches: activations and the tile's scale / zero in LDS
@@ -1678,7 +1672,7 @@ void launch_qgemm(const LayerDims& d, const bf16_t* X, const uint32_t* packed, c
       else if (nsw == 4) L4Q_QD(8, 4);
       else L4Q_QD(8, 8);
 #undef L4Q_QD
-      return;
+      return true;
     }
   }
   // larger batches: 64-row tiles that share each activation stage through LDS, up to 64 tokens per pass
@@ -1721,7 +1715,7 @@ void launch_qgemm(const LayerDims& d, const bf16_t* X, const uint32_t* packed, c
                              partial, Y, slices, n, t0, (int)d.o);
         }
       }
-      return;
+      return true;
     }
   }
   if (qgemm_stream_rows(d, 32) != 0 && (d.T <= 32 || d.g < 64)) {
@@ -1738,7 +1732,7 @@ void launch_qgemm(const LayerDims& d, const bf16_t* X, const uint32_t* packed, c
       else L4Q_QS(8, 32);
 #undef L4Q_QS
     }
-    return;
+    return true;
   }
 #define L4Q_QGEMM(B, N, F)                                                                                  \
   hipLaunchKernelGGL((qgemm_kernel<B, N, F>), grid, dim3(QG_WAVES * 64), 0, stream, X, packed, scale, zero, Y, \
@@ -1755,6 +1749,7 @@ void launch_qgemm(const LayerDims& d, const bf16_t* X, const uint32_t* packed, c
   else L4Q_QGEMM_B(8);
 #undef L4Q_QGEMM_B
 #undef L4Q_QGEMM
+  return true;
 }
 
 }  // namespace l4q

@@ -168,7 +168,8 @@ void launch_pack_codes(const int8_t* codes, int64_t o, int64_t i, int bits, uint
 bool qgemm_supported(const LayerDims& d);
 // partial: optional room for fp32 partial sums (qgemm_workspace_bytes(d); ignored when null or smaller)
 size_t qgemm_workspace_bytes(const LayerDims& d);
-void launch_qgemm(const LayerDims& d, const bf16_t* X, const uint32_t* packed, const float* scale, const float* zero,
+// false: nothing was launched
+bool launch_qgemm(const LayerDims& d, const bf16_t* X, const uint32_t* packed, const float* scale, const float* zero,
                   bf16_t* Y, float* partial, size_t partial_bytes, hipStream_t stream);
 
 // The same product at one to four token blocks, groups of 64 and more (l4q_infer_blocks.hip).
@@ -184,6 +185,14 @@ size_t qgemm_blocks_workspace_bytes(const LayerDims& d);
 BlocksPlan qgemm_blocks_plan(const LayerDims& d, bool have_workspace);
 void launch_qgemm_blocks(const BlocksPlan& plan, const LayerDims& d, const bf16_t* X, const uint32_t* packed,
                          const float* scale, const float* zero, bf16_t* Y, float* partial, hipStream_t stream);
+
+// The same product of the fewest tokens with the codes resident in registers (l4q_infer.hip).
+struct WregPlan {
+  int nt, cpw;    // 16-row tiles per workgroup (0: not this form), chunks of 256 k-values per wave
+  unsigned grid;
+  int wv, tbp;    // waves per workgroup, token blocks per pass
+};
+WregPlan qgemm_wreg_plan(const LayerDims& d);
 
 // The same product at prompt sizes (l4q_prefill.hip; more than 64 tokens, groups of 64 and more, i % 128 == 0).
 struct PrefillPlan {

@@ -1,0 +1,38 @@
+"""The in-register quantized forward (l4q::qgemm_wreg_plan): every plan it can return has an instance of the kernel, since a launch
+of any other is refused.  Host code alone (256 compute units are assumed)."""
+import ctypes
+import random
+
+from paper_2402_04902_amd import binding
+from plan_util import _LayerDims
+
+
+class _WregPlan(ctypes.Structure):
+    _fields_ = [("nt", ctypes.c_int), ("cpw", ctypes.c_int), ("grid", ctypes.c_uint), ("wv", ctypes.c_int), ("tbp", ctypes.c_int)]
+
+
+# (tiles per workgroup, chunks per wave, waves) by code width
+ONE_CHUNK = [(n, 1, 16) for n in (1, 2, 3, 4)]
+MORE_CHUNKS = [(1, 2, 16), (2, 2, 16), (1, 3, 16), (1, 4, 16)]
+TWO_BLOCKS = [(n, 1, 8) for n in (1, 2, 3)]
+INSTANCES = {2: set(ONE_CHUNK[1:] + MORE_CHUNKS + TWO_BLOCKS), 3: set(ONE_CHUNK + MORE_CHUNKS + TWO_BLOCKS),
+             4: set(ONE_CHUNK[1:] + TWO_BLOCKS[1:]), 8: set(ONE_CHUNK[:2])}
+
+
+def wreg_form(T, i, o, bits, g):
+    f = getattr(binding.load_library(), "_ZN3l4q15qgemm_wreg_planERKNS_9LayerDimsE")
+    f.restype, f.argtypes = _WregPlan, [ctypes.POINTER(_LayerDims)]
+    q = float(1 << (bits - 1))
+    p = f(ctypes.byref(_LayerDims(T, i, o, 8, bits, g, 2.0, -q, q - 1.0, False)))
+    return (p.nt, p.cpw, p.wv) if p.nt else None
+
+
+def test_plans_are_the_instances_there_are():
+    rng, met = random.Random(355), {bits: set() for bits in INSTANCES}
+    for _ in range(40000):
+        bits = rng.choice([2, 3, 4, 8])
+        g = 128 << rng.randrange(4)
+        form = wreg_form(rng.randint(1, 64), g * rng.randint(1, max(1, 17000 // g)), 8 * rng.randint(1, 2500), bits, g)
+        if form:
+            met[bits].add(form)
+    assert met == INSTANCES
