@@ -1334,12 +1334,6 @@ bool qgemm_decode_ok(const LayerDims& d) {
 // the rounds they need.  Measured at [11008 x 4096] (172 tiles on 256 units) against the k-split streaming kernel:
 // 17 vs 23 us at 16 tokens, 23 vs 31 at 32, 33 vs 59 at 64; at [8192 x 8192] (128 tiles) 29 vs 29, 40 vs 30, 59 vs 59.
 // With fewer tiles, as many k-slices as fill the units, each at least four stages long.
-struct TilePlan {
-  int tb_max, slices;
-  int64_t klen;  // k-values of the longest slice
-  int pitch[5];
-  int64_t lds[5];
-};
 TilePlan qgemm_tile_plan(const LayerDims& d) {
   TilePlan plan = {0, 1, 0, {1, 1, 1, 1, 1}, {0, 0, 0, 0, 0}};
   // 3 bits: activation stages of 256 k-values, weights in units of three 128-byte stages = four activation stages
@@ -1379,6 +1373,23 @@ TilePlan qgemm_tile_plan(const LayerDims& d) {
     }
   }
   return plan;
+}
+
+// How qgemm_decode_kernel would run this layer: ring stages per wave as far as activations and tables leave room for them.
+DecodePlan qgemm_decode_plan(const LayerDims& d) {
+  if (d.T > 16 || !qgemm_decode_ok(d)) return {0, 0, 0, 0};
+  const int64_t rb = d.i / 8 * d.bits, ks = 128 * 8 / d.bits, nst = (rb + 127) / 128;
+  const int64_t xpitch = (nst * ks * 2 + 1023) / 1024 * 1024 + 16;  // a token's row up to the end of its last stage
+  const int64_t xb = d.T * xpitch;
+  const int64_t Gp = (nst * ks + d.g - 1) / d.g, pitch = 64 * ((Gp + 63) / 64) + 1;  // whole 64-lane loads per row, odd: no bank conflicts
+  const int64_t sbb = 2 * 16 * pitch * 4;
+  const int64_t tiles = (d.o + 15) / 16;
+  int nsw = tiles <= device_compute_units() ? 8 : 4;
+  if (4 * nsw * 16 * 128 + xb + sbb > QD_LDS_MAX) nsw = 4;
+  if (4 * nsw * 16 * 128 + xb + sbb > QD_LDS_MAX) nsw = 2;  // (16 tokens of a 4096-wide layer: 17.0 against 18.3 us in 64-row tiles)
+  const int64_t lds = 4 * nsw * 16 * 128 + xb + sbb;
+  if (xb > QD_X_MAX || sbb > QD_SB_MAX || lds > QD_LDS_MAX) return {0, 0, 0, 0};
+  return {nsw, (int)xpitch, (int)pitch, (int)lds};
 }
 
 inline int64_t plan_grid_rounds(int64_t tiles, int64_t nt, int64_t cus) { return ((tiles + nt - 1) / nt + cus - 1) / cus; }
@@ -1603,96 +1614,97 @@ void launch_blocks(const BlocksPlan& plan, const LayerDims& d, const bf16_t* X, 
 
 }  // namespace
 
+void qgemm_route(const LayerDims& d, bool have_workspace, QgemmRoute* route) {
+  if (d.T > 64) {
+    route->prompt = qgemm_prompt_plan(d, have_workspace);
+    route->passes = qgemm_blocks_passes(d, have_workspace, route->prompt.us, route->blocks);
+    route->kernel = route->passes > 0 ? kQgBlocks : kQgPrompt;
+    if (route->passes > 0 || route->prompt.form >= 0) return;
+  }
+  // up to 64 tokens, groups of 64 and more: every byte of X and of the codes to one wave, in whole cache lines
+  route->kernel = kQgBlocks;
+  route->passes = 1;
+  route->blocks[0] = qgemm_blocks_plan(d, have_workspace);
+  if (route->blocks[0].nt > 0) return;
+  // the fewest tokens, groups of 128 and more: the packed codes resident in registers
+  route->kernel = kQgWreg;
+  route->wreg = qgemm_wreg_plan(d);
+  if (route->wreg.nt > 0) return;
+  // smallest batches: activations and the tile's scale / zero in LDS
+  route->kernel = kQgDecode;
+  route->decode = qgemm_decode_plan(d);
+  if (route->decode.nsw > 0) return;
+  // larger batches: 64-row tiles that share each activation stage through LDS, up to 64 tokens per pass
+  route->kernel = kQgTile;
+  route->tile = qgemm_tile_plan(d);
+  // too few row tiles for one k-slice each: split, if the caller gave room for the partial sums
+  // (at 16 tokens or fewer the k-split inside a workgroup wins where it exists: 4 and 8 bits)
+  if (route->tile.slices > 1 && !((d.T > 16 || d.bits == 3) && have_workspace)) route->tile.tb_max = 0;
+  if (route->tile.tb_max > 0) return;
+  // more than 32 tokens: the general kernel reads the weights once per 64 tokens, the streaming form once per 32
+  route->kernel = qgemm_stream_rows(d, 32) != 0 && (d.T <= 32 || d.g < 64) ? kQgStream : kQgGeneral;
+  route->stream_tokens = d.T <= 16 && qgemm_stream_rows(d, 16) == 16 ? 16 : 32;
+}
+
 bool launch_qgemm(const LayerDims& d, const bf16_t* X, const uint32_t* packed, const float* scale, const float* zero,
                   bf16_t* Y, float* partial, size_t partial_bytes, hipStream_t stream) {
   const size_t told = qgemm_workspace_bytes(d);
-  const bool have_workspace = partial != nullptr && told > 0 && partial_bytes >= told;
-  if (d.T > 64) {
-    const PrefillPlan prompt = qgemm_prompt_plan(d, have_workspace);
-    BlocksPlan plans[QB_PASSES_MAX];
-    const int passes = qgemm_blocks_passes(d, have_workspace, prompt.us, plans);
-    for (int p = 0; p < passes; ++p) {  // (the next pass reuses the partial sums' memory: stream order keeps the two apart)
+  QgemmRoute route;
+  qgemm_route(d, partial != nullptr && told > 0 && partial_bytes >= told, &route);
+  if (route.kernel == kQgBlocks) {
+    for (int p = 0; p < route.passes; ++p) {  // (the next pass reuses the partial sums' memory: stream order keeps the two apart)
       LayerDims part = d;
       int64_t t0;
-      blocks_pass(d, passes, p, &t0, &part.T);
-      launch_blocks(plans[p], part, X + t0 * d.i, packed, scale, zero, Y + t0 * d.o, partial, stream);
+      blocks_pass(d, route.passes, p, &t0, &part.T);
+      launch_blocks(route.blocks[p], part, X + t0 * d.i, packed, scale, zero, Y + t0 * d.o, partial, stream);
     }
-    if (passes > 0) return true;
-    if (prompt.form >= 0) {
-      launch_qgemm_prefill(prompt, d, X, packed, scale, zero, Y, stream);
-      return true;
-    }
-  }
-  // up to 64 tokens, groups of 64 and more: every byte of X and of the codes to one wave, in whole cache lines
-  const BlocksPlan blocks = qgemm_blocks_plan(d, have_workspace);
-  if (blocks.nt > 0) {
-    launch_blocks(blocks, d, X, packed, scale, zero, Y, partial, stream);
     return true;
   }
-  dim3 grid((unsigned)((d.o + 31) / 32));
-  // the fewest tokens, groups of 128 and more: the packed codes resident in registers
-  const WregPlan wr = qgemm_wreg_plan(d);
-  if (wr.nt > 0) {
-    if (d.bits == 2) return launch_qgemm_wreg<2>(wr, d, X, packed, scale, zero, Y, stream);
-    if (d.bits == 3) return launch_qgemm_wreg<3>(wr, d, X, packed, scale, zero, Y, stream);
-    if (d.bits == 4) return launch_qgemm_wreg<4>(wr, d, X, packed, scale, zero, Y, stream);
-    return launch_qgemm_wreg<8>(wr, d, X, packed, scale, zero, Y, stream);
+  if (route.kernel == kQgPrompt) {
+    launch_qgemm_prefill(route.prompt, d, X, packed, scale, zero, Y, stream);
+    return true;
   }
-  // more than 32 tokens: the general kernel reads the weights once per 64 tokens, the streaming form once per 32
-  // smallest batches: activations and the tile's scale / zero in LDS
-  if (d.T <= 16 && qgemm_decode_ok(d)) {
-    const int64_t rb = d.i / 8 * d.bits, ks = 128 * 8 / d.bits, nst = (rb + 127) / 128;
-    const int64_t xpitch = (nst * ks * 2 + 1023) / 1024 * 1024 + 16;  // a token's row up to the end of its last stage
-    const int64_t xb = d.T * xpitch;
-    const int64_t Gp = (nst * ks + d.g - 1) / d.g, pitch = 64 * ((Gp + 63) / 64) + 1;  // whole 64-lane loads per row, odd: no bank conflicts
-    const int64_t sbb = 2 * 16 * pitch * 4;
-    const int64_t tiles = (d.o + 15) / 16;
-    int nsw = tiles <= device_compute_units() ? 8 : 4;
-    if (4 * nsw * 16 * 128 + xb + sbb > QD_LDS_MAX) nsw = 4;
-    if (4 * nsw * 16 * 128 + xb + sbb > QD_LDS_MAX) nsw = 2;  // (16 tokens of a 4096-wide layer: 17.0 against 18.3 us in 64-row tiles)
-    if (xb <= QD_X_MAX && sbb <= QD_SB_MAX && 4 * nsw * 16 * 128 + xb + sbb <= QD_LDS_MAX) {
-      const size_t lds_bytes = (size_t)(4 * nsw * 16 * 128 + xb + sbb);
-      dim3 sgrid((unsigned)tiles);
-      // more than 64 KiB of dynamic LDS has to be allowed per function and device
+  if (route.kernel == kQgWreg) {
+    if (d.bits == 2) return launch_qgemm_wreg<2>(route.wreg, d, X, packed, scale, zero, Y, stream);
+    if (d.bits == 3) return launch_qgemm_wreg<3>(route.wreg, d, X, packed, scale, zero, Y, stream);
+    if (d.bits == 4) return launch_qgemm_wreg<4>(route.wreg, d, X, packed, scale, zero, Y, stream);
+    return launch_qgemm_wreg<8>(route.wreg, d, X, packed, scale, zero, Y, stream);
+  }
+  if (route.kernel == kQgDecode) {
+    const DecodePlan& plan = route.decode;
+    const size_t lds_bytes = (size_t)plan.lds;
+    dim3 sgrid((unsigned)((d.o + 15) / 16));
+    // more than 64 KiB of dynamic LDS has to be allowed per function and device
 #define L4Q_QD(B, N)                                                                                                \
   do {                                                                                                              \
     if (lds_bytes > 64 * 1024)                                                                                      \
       (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&qgemm_decode_kernel<B, N>),                          \
                                 hipFuncAttributeMaxDynamicSharedMemorySize, QD_LDS_MAX);                                   \
     hipLaunchKernelGGL((qgemm_decode_kernel<B, N>), sgrid, dim3(256), lds_bytes, stream, X, packed, scale, zero, Y, \
-                       (int)d.T, (int)d.o, (int)d.i, d.g, (int)xpitch, (int)pitch);                                 \
+                       (int)d.T, (int)d.o, (int)d.i, d.g, plan.xpitch, plan.pitch);                                 \
   } while (0)
-      if (d.bits == 2 && nsw == 2) L4Q_QD(2, 2);
-      else if (d.bits == 2 && nsw == 4) L4Q_QD(2, 4);
-      else if (d.bits == 2) L4Q_QD(2, 8);
-      else if (d.bits == 4 && nsw == 2) L4Q_QD(4, 2);
-      else if (d.bits == 4 && nsw == 4) L4Q_QD(4, 4);
-      else if (d.bits == 4) L4Q_QD(4, 8);
-      else if (nsw == 2) L4Q_QD(8, 2);
-      else if (nsw == 4) L4Q_QD(8, 4);
-      else L4Q_QD(8, 8);
+    if (d.bits == 2 && plan.nsw == 2) L4Q_QD(2, 2);
+    else if (d.bits == 2 && plan.nsw == 4) L4Q_QD(2, 4);
+    else if (d.bits == 2) L4Q_QD(2, 8);
+    else if (d.bits == 4 && plan.nsw == 2) L4Q_QD(4, 2);
+    else if (d.bits == 4 && plan.nsw == 4) L4Q_QD(4, 4);
+    else if (d.bits == 4) L4Q_QD(4, 8);
+    else if (plan.nsw == 2) L4Q_QD(8, 2);
+    else if (plan.nsw == 4) L4Q_QD(8, 4);
+    else L4Q_QD(8, 8);
 #undef L4Q_QD
-      return true;
-    }
+    return true;
   }
-  // larger batches: 64-row tiles that share each activation stage through LDS, up to 64 tokens per pass
-  {
-    const TilePlan plan = qgemm_tile_plan(d);
-    int tb_max = plan.tb_max, slices = 1;
-    if (plan.slices > 1) {  // too few row tiles for one k-slice each: split, if the caller gave room for the partial sums
-      // (at 16 tokens or fewer the k-split inside a workgroup wins where it exists: 4 and 8 bits)
-      if ((d.T > 16 || d.bits == 3) && have_workspace) slices = plan.slices;
-      else tb_max = 0;
-    }
-    if (tb_max > 0) {
-      dim3 tgrid((unsigned)((d.o + 63) / 64), (unsigned)slices);
-      float* part = slices > 1 ? partial : nullptr;
-      for (int t0 = 0; t0 < d.T; t0 += 16 * tb_max) {
-        const int n = (int)d.T - t0 < 16 * tb_max ? (int)d.T - t0 : 16 * tb_max;
-        int tb = (n + 15) / 16;
-        while (plan.lds[tb] == 0) ++tb;  // a form that does not fit: the next larger one (tb_max fits) masks the tokens
-        const size_t lds_bytes = (size_t)plan.lds[tb];
-        const int pitch = plan.pitch[tb];
+  if (route.kernel == kQgTile) {
+    const TilePlan& plan = route.tile;
+    dim3 tgrid((unsigned)((d.o + 63) / 64), (unsigned)plan.slices);
+    float* part = plan.slices > 1 ? partial : nullptr;
+    for (int t0 = 0; t0 < d.T; t0 += 16 * plan.tb_max) {
+      const int n = (int)d.T - t0 < 16 * plan.tb_max ? (int)d.T - t0 : 16 * plan.tb_max;
+      int tb = (n + 15) / 16;
+      while (plan.lds[tb] == 0) ++tb;  // a form that does not fit: the next larger one (tb_max fits) masks the tokens
+      const size_t lds_bytes = (size_t)plan.lds[tb];
+      const int pitch = plan.pitch[tb];
 #define L4Q_QT(B, N, W)                                                                                               \
   do {                                                                                                               \
     if (lds_bytes > 64 * 1024)                                                                                       \
@@ -1701,25 +1713,24 @@ bool launch_qgemm(const LayerDims& d, const bf16_t* X, const uint32_t* packed, c
     hipLaunchKernelGGL((qgemm_tile_kernel<B, N, W>), tgrid, dim3(W * 64), lds_bytes, stream, X, packed, scale, zero, \
                        Y, part, (int)d.T, t0, (int)d.o, (int)d.i, d.g, pitch);                                       \
   } while (0)
-        if (d.bits == 3) {
-          if (tb == 1) L4Q_QT(3, 1, 4); else if (tb == 2) L4Q_QT(3, 2, 8); else if (tb == 3) L4Q_QT(3, 3, 4); else L4Q_QT(3, 4, 8);
-        } else if (d.bits == 4) {
-          if (tb == 1) L4Q_QT(4, 1, 4); else if (tb == 2) L4Q_QT(4, 2, 8); else if (tb == 3) L4Q_QT(4, 3, 4); else L4Q_QT(4, 4, 8);
-        } else {
-          if (tb == 1) L4Q_QT(8, 1, 4); else if (tb == 2) L4Q_QT(8, 2, 8); else if (tb == 3) L4Q_QT(8, 3, 4); else L4Q_QT(8, 4, 8);
-        }
-#undef L4Q_QT
-        if (slices > 1) {  // the next pass reuses the partial sums' memory: stream order keeps the two apart
-          const int64_t quads = (int64_t)n * d.o / 4;
-          hipLaunchKernelGGL(qgemm_slices_sum_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream,
-                             partial, Y, slices, n, t0, (int)d.o);
-        }
+      if (d.bits == 3) {
+        if (tb == 1) L4Q_QT(3, 1, 4); else if (tb == 2) L4Q_QT(3, 2, 8); else if (tb == 3) L4Q_QT(3, 3, 4); else L4Q_QT(3, 4, 8);
+      } else if (d.bits == 4) {
+        if (tb == 1) L4Q_QT(4, 1, 4); else if (tb == 2) L4Q_QT(4, 2, 8); else if (tb == 3) L4Q_QT(4, 3, 4); else L4Q_QT(4, 4, 8);
+      } else {
+        if (tb == 1) L4Q_QT(8, 1, 4); else if (tb == 2) L4Q_QT(8, 2, 8); else if (tb == 3) L4Q_QT(8, 3, 4); else L4Q_QT(8, 4, 8);
       }
-      return true;
+#undef L4Q_QT
+      if (plan.slices > 1) {  // the next pass reuses the partial sums' memory: stream order keeps the two apart
+        const int64_t quads = (int64_t)n * d.o / 4;
+        hipLaunchKernelGGL(qgemm_slices_sum_kernel, dim3((unsigned)((quads + 255) / 256)), dim3(256), 0, stream,
+                           partial, Y, plan.slices, n, t0, (int)d.o);
+      }
     }
+    return true;
   }
-  if (qgemm_stream_rows(d, 32) != 0 && (d.T <= 32 || d.g < 64)) {
-    const int step = d.T <= 16 && qgemm_stream_rows(d, 16) == 16 ? 16 : 32;
+  if (route.kernel == kQgStream) {
+    const int step = route.stream_tokens;
     for (int t0 = 0; t0 < d.T; t0 += step) {  // the weight stream is read once per pass
       const int rows = qgemm_stream_rows(d, (int)d.T - t0 < step ? (int)d.T - t0 : step);
       dim3 sgrid((unsigned)((d.o + rows - 1) / rows));
@@ -1734,6 +1745,7 @@ bool launch_qgemm(const LayerDims& d, const bf16_t* X, const uint32_t* packed, c
     }
     return true;
   }
+  dim3 grid((unsigned)((d.o + 31) / 32));
 #define L4Q_QGEMM(B, N, F)                                                                                  \
   hipLaunchKernelGGL((qgemm_kernel<B, N, F>), grid, dim3(QG_WAVES * 64), 0, stream, X, packed, scale, zero, Y, \
                      (int)d.T, (int)d.o, (int)d.i, d.g, d.qn)

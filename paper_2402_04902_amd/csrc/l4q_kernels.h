@@ -207,6 +207,30 @@ PrefillPlan qgemm_prompt_plan(const LayerDims& d, bool have_workspace);
 // pass; other_us: estimated time of the others
 constexpr int QB_PASSES_MAX = 8;
 int qgemm_blocks_passes(const LayerDims& d, bool have_workspace, double other_us, BlocksPlan* plans);
+// ... and the other kernels of l4q_infer.hip, and how a call goes.
+struct DecodePlan {  // activations in LDS, up to 16 tokens
+  int nsw;           // ring stages per wave (0: not this form)
+  int xpitch, pitch, lds;
+};
+struct TilePlan {    // 64-row tiles
+  int tb_max, slices;  // token blocks per pass (0: not this form), k-slices per row tile
+  int64_t klen;        // k-values of the longest slice
+  int pitch[5];        // by token blocks of a pass: pitch of its tables in LDS,
+  int64_t lds[5];      // its LDS (0: such a pass does not fit)
+};
+enum QgemmKernel { kQgBlocks, kQgPrompt, kQgWreg, kQgDecode, kQgTile, kQgStream, kQgGeneral };
+struct QgemmRoute {
+  int kernel;                         // one of QgemmKernel; of what follows, that kernel's part is set
+  int passes;                         // kQgBlocks, and a plan per pass
+  BlocksPlan blocks[QB_PASSES_MAX];
+  PrefillPlan prompt;
+  WregPlan wreg;
+  DecodePlan decode;
+  TilePlan tile;
+  int stream_tokens;                  // kQgStream: tokens per pass
+};
+// have_workspace: qgemm_workspace_bytes(d) were passed
+void qgemm_route(const LayerDims& d, bool have_workspace, QgemmRoute* route);
 void launch_qgemm_prefill(const PrefillPlan& plan, const LayerDims& d, const bf16_t* X, const uint32_t* packed,
                           const float* scale, const float* zero, bf16_t* Y, hipStream_t stream);
 

@@ -7,19 +7,10 @@ import timeit
 import pytest
 
 from paper_2402_04902_amd import binding
-from paper_2402_04902_amd.inputs import DTYPE_BF16, LayerSpec
-from plan_util import _LayerDims, prompt_plan
+from plan_util import _BlocksPlan, _LayerDims, prompt_plan, workspace_bytes
 from test_gpu_prefill import CASES
 
 NOT_THIS_FORM = (0, 1)
-
-
-class _BlocksPlan(ctypes.Structure):
-    _fields_ = [("nt", ctypes.c_int), ("slices", ctypes.c_int), ("slice_macros", ctypes.c_int), ("us", ctypes.c_double)]
-
-
-def workspace_bytes(T, i, o, bits, g):
-    return binding.l4q_quantized_forward_workspace_bytes(binding.make_desc(LayerSpec("plan", T, i, o, 8, 16.0, bits, g, DTYPE_BF16)))
 
 
 def blocks_plan(T, i, o, bits, g, workspace=None):  # None: as given what the query tells

@@ -61,10 +61,9 @@ def test_quantized_forward_random_shapes(k, T, i, o, bits, g):
 
 
 def _random_tile_cases(count=18, seed=2402):
-    """Seeded draw of problems for the 64-row tile kernel: wide layers (every compute unit gets a tile) and narrow
-    ones with long rows (k-slices through the workspace), 3, 4 and 8 bits, groups of one to four sub-steps, 1 .. 100
-    tokens (every count of token blocks; above 64 two passes where the two-dimensional tiles of prompts are not
-    faster), ragged last row tiles."""
+    """Seeded draw of wide layers (every compute unit gets a tile) and narrow ones with long rows (k-slices through the
+    workspace), 3, 4 and 8 bits, groups of one to four sub-steps, 1 .. 100 tokens (every count of token blocks; two passes
+    above 64 where those are faster), ragged last row tiles.  Most take the one-pass kernel, the others 64-row tiles."""
     rng = np.random.default_rng(seed)
     cases = []
     for k in range(count):
@@ -90,12 +89,12 @@ def test_quantized_forward_random_tile_shapes(k, T, i, o, bits, g):
 
 
 def _random_in_register_cases(count=24, seed=355):
-    """Seeded draw over the domain of the in-register form: every code width, power-of-two groups from 128 up to the
-    row length, rows of 1 .. 64 chunks of 256 (with half chunks), 128 .. 16800 output rows in steps of 8 (one to four
-    tiles per workgroup, ragged last tiles, layers too small to fill the chip), 1 .. 64 tokens around the block and
-    pass boundaries; at most 48 M weights
-    so that the oracle stays fast.  The library picks the form (and its shape) per case; with the workspace the k-sliced
-    forms run as well."""
+    """Seeded draw over the domain of the one-pass and the in-register kernel: every code width, power-of-two groups from 128
+    up to the row length, rows of 1 .. 64 chunks of 256 (with half chunks), 128 .. 16800 output rows in steps of 8 (one to four
+    tiles per workgroup, ragged last tiles, layers too small to fill the chip), 1 .. 64 tokens around the block
+    boundaries; at most 48 M weights
+    so that the oracle stays fast.  The library picks the kernel and its shape per case; with the workspace k-slices
+    run as well."""
     rng = np.random.default_rng(seed)
     cases = []
     while len(cases) < count:
@@ -117,39 +116,38 @@ def test_quantized_forward_random_in_register_shapes(k, T, i, o, bits, g):
 
 
 @pytest.mark.parametrize("T,i,o,bits,g", [
-    # Shapes and batches the weights-in-registers form takes (groups of 128 and more, a few token blocks), one per
-    # combination of row tiles per workgroup (1 .. 4: up to 4096 / 8192 / 12288 / more rows on 256 compute units) and
-    # 256-wide chunks per wave (1 .. 4: up to 4096 / 8192 / 12288 / 16384 columns), for every code width that has it.
-    # 4 bits: three tiles at 33 tokens with a ragged last tile; two tiles with half a chunk at the end of k; four
-    # tiles with groups of 256; (1, 2); (2, 2) with groups of 512; three chunks (4 bits: a streaming form); (1, 4); (1, 4) with groups of 1024 and a
-    # ragged tile; two token blocks on a 256-tile layer; four tiles over three token blocks; one token
+    # Groups of 128 and more, up to 64 tokens, both the kernel with the weights in registers and the one-pass kernel that has
+    # taken its place at most of these sizes (which one a call takes: plan_util.quantized_instances), over row tiles per compute
+    # unit (1 .. 4: up to 4096 / 8192 / 12288 / more rows on 256 units) and rows of up to 4096 / 8192 / 12288 / 16384.
+    # 4 bits: three tiles at 33 tokens with a ragged last one; two tiles in registers with half a chunk at the end of k; four
+    # tiles with groups of 256; long rows with groups of 512 and of 1024 and ragged tiles; two token blocks on 256 tiles; four
+    # tiles over three token blocks; one token in registers
     (33, 4096, 11000, 4, 128), (5, 2048 + 128, 6000, 4, 128), (40, 1024, 13000, 4, 256), (9, 8192, 3000, 4, 128),
     (20, 5120, 8000, 4, 512), (5, 11008, 4096, 3, 128), (7, 14336, 2400, 4, 128), (3, 16384, 2056, 4, 1024),
     (20, 4096, 4096, 4, 128), (48, 4096, 12296, 4, 128), (1, 4096, 11008, 4, 128),
-    # 3 bits (12-byte pieces): (3, 1) over three token blocks, (1, 3), (2, 2), (1, 4) with groups of 256, one token
+    # 3 bits (12-byte pieces): three tiles over three token blocks, one and two tiles with long rows, groups of 256; one token in
+    # registers
     (48, 4096, 11000, 3, 128), (16, 11008, 4096, 3, 128), (30, 8192, 8192, 3, 128), (2, 16384, 2056, 3, 256),
     (1, 4096, 4000, 3, 128),
-    # 2 bits (8-byte pieces): (3, 1), (2, 1) over four token blocks, (1, 3), (2, 2) with groups of 256, three tokens
+    # 2 bits (8-byte pieces): three tiles in registers, two over four token blocks, long rows, groups of 256, three tokens
     (5, 4096, 11008, 2, 128), (64, 4096, 6000, 2, 128), (16, 11008, 4096, 2, 128), (33, 8192, 8192, 2, 256),
     (3, 4096, 4000, 2, 128),
-    # 8 bits (one tile, one chunk only): one token, half a chunk at the end of k, groups of 256 with a ragged tile
+    # 8 bits: one token in registers, half a macro at the end of k, groups of 256 with a ragged tile
     (1, 4096, 4096, 8, 128), (20, 2048 + 128, 4000, 8, 128), (32, 4096, 2072, 8, 256),
-    # 17 .. 32 tokens on layers of up to 4096 columns: the 8-wave shape of the same kernel (two chunks per wave, two
-    # token blocks per pass), every tiles x chunks combination it has, at 4, 3 and 2 bits; a ragged last tile, half a
-    # chunk at the end of k, groups of 256, a partial second block
+    # 17 .. 32 tokens on rows of up to 4096 at 4, 3 and 2 bits: one to three tiles, a ragged last tile, half a macro at the end of
+    # k, a partial second block; rows of 2048 and 1024 with three and two tiles in registers (8 waves, both blocks in a pass)
     (24, 4096, 11000, 4, 128), (24, 4096, 11000, 3, 128), (24, 4096, 11000, 2, 128),
     (17, 4096, 6000, 4, 128), (17, 4096, 6000, 3, 128), (17, 4096, 6000, 2, 128),
     (32, 2176, 4000, 4, 128), (32, 2176, 4000, 3, 128), (32, 2176, 4000, 2, 128),
     (20, 2048, 11008, 4, 128), (20, 2048, 11008, 3, 128), (20, 2048, 11008, 2, 128),
     (25, 1024, 6008, 4, 256), (25, 1024, 6008, 3, 256), (25, 1024, 6008, 2, 256),
     (31, 1152, 1000, 4, 128), (31, 1152, 1000, 3, 128), (31, 1152, 1000, 2, 128),
-    # long rows on layers of 128 .. 256 row tiles, with the workspace: k-slices of 16 chunks (3, 2, 4 and 3 slices; the
-    # last slice short; 16- and 8-wave shapes; groups of 256, of 512, and of 8192, which span two slices; a ragged
+    # long rows on layers of 128 .. 256 row tiles (three k-slices in one of them; groups of 256, of 512 and of 8192; a ragged
     # last tile)
     (12, 11008, 4096, 4, 128), (12, 11008, 4096, 3, 128), (12, 11008, 4096, 2, 128), (24, 8192, 4096, 4, 128),
     (9, 14336, 2400, 4, 128), (20, 14336, 2400, 3, 256), (16, 12288, 3000, 2, 128), (10, 11264, 4096, 4, 512),
     (8, 16384, 2056, 4, 8192),
-    # ... and two passes of it (49 .. 64 tokens), the last block partial
+    # ... and four token blocks, the last one partial
     (64, 4096, 11000, 4, 128), (64, 4096, 11000, 3, 128), (64, 4096, 11000, 2, 128), (50, 4096, 6000, 2, 128),
 ])
 def test_quantized_forward_weights_in_registers(T, i, o, bits, g):
@@ -159,50 +157,45 @@ def test_quantized_forward_weights_in_registers(T, i, o, bits, g):
 @pytest.mark.parametrize("T,i,o,bits,g", [
     (1, 256, 72, 4, 64), (7, 512, 264, 4, 128), (64, 1024, 520, 3, 64), (33, 256, 40, 2, 8), (100, 320 * 2, 96, 8, 32),
     (16, 4096, 11008, 4, 128),      # LLaMA-7B up projection at a decode batch
-    (64, 4096, 1024, 3, 128),       # 3-bit, 64 tokens
+    (64, 4096, 1024, 3, 128),       # 3-bit, 64 tokens, four k-slices
     (1, 4096, 11008, 4, 128), (1, 11008, 4096, 4, 128),   # single-token decode, both projections
-    (17, 11008, 1000, 4, 64),       # odd stage count (43), 17 tokens -> 32-row tiles, ragged rows
-    (5, 640, 88, 8, 64), (40, 1280, 200, 8, 128),         # 8-bit streaming form, 16- and 32-row tiles
-    (16, 384, 48, 4, 128),          # packed rows not a whole number of cache lines -> general kernel
+    (17, 11008, 1000, 4, 64),       # 43 macros in four k-slices, ragged rows
+    (5, 640, 88, 8, 64), (40, 1280, 200, 8, 128),         # 8 bits: activations in LDS, three token blocks
+    (16, 384, 48, 4, 128),          # packed rows not a whole number of cache lines
     (3, 256, 8, 4, 128),            # one stage, a single partial row tile
-    # activations held in LDS (small batches): both projections at 2..12 tokens, ragged row tile, even and odd
-    # group counts per row, 8-bit, a row length whose activations no longer fit (falls back to register fragments)
+    # small batches: both projections at 2..12 tokens, ragged row tiles, even and odd group counts per row, 8 bits (short
+    # rows and few tokens: activations in LDS), a row whose activations do not fit there (streaming form)
     (2, 4096, 11008, 4, 128), (12, 4096, 11008, 4, 128), (4, 11008, 4096, 4, 128), (5, 11008, 4096, 4, 128),
     (3, 1024, 1000, 4, 128), (2, 768, 40, 4, 256), (9, 2048, 520, 8, 64), (13, 4096, 264, 4, 64),
     (1, 28672, 64, 4, 128), (16, 4096, 72, 4, 128),
-    # wide layers (enough 64-row tiles for most compute units): tiles sharing the activation stage, 4, 3, 2 and 1
-    # token blocks per pass, a ragged last row tile, odd stage count, 8-bit, groups of two sub-steps (4-bit g = 256,
-    # 8-bit g = 128), long rows that leave LDS for two token blocks only, a small batch too long for the LDS-resident
-    # form (70 tokens: a prompt, in two-dimensional tiles)
+    # wide layers: 1 .. 4 token blocks, a ragged last row tile, rows that end inside a macro, 8 bits, groups of 256 at 4 bits and of
+    # 64 and 128 at 8, long rows (70 tokens: a prompt, in two-dimensional tiles)
     (64, 4096, 11008, 4, 128), (70, 1024, 10248, 4, 128), (40, 896, 10312, 8, 128), (48, 11008, 10240, 4, 128),
     (24, 2048, 10304, 4, 256), (13, 4096, 10240, 4, 64), (30, 1024, 10240, 8, 64),
-    # few row tiles and long rows with a workspace: k-slices over the compute units (4, 2 and 3 slices; a slice
-    # boundary inside a group (g = 1024); 8-bit; two passes; stage counts that do not divide by the slices)
+    # few row tiles and long rows with a workspace: two k-slices; one slice of two tiles per workgroup; 64-row tiles in k-slices
+    # and two passes (80 tokens, 8 bits)
     (64, 11008, 4096, 4, 128), (33, 8192, 8192, 4, 128), (48, 5120, 5000, 4, 1024), (80, 2304, 4104, 8, 128),
     (17, 4096, 4096, 4, 128),
     # 3 bits at the smallest batches: both projections (rows of 11008 codes are neither whole cache lines nor whole
     # three-stage units), ragged row tiles, row lengths of 1.125, 2 and 1/8 units, groups of 256, 16 tokens
     (1, 4096, 11008, 3, 128), (1, 11008, 4096, 3, 128), (12, 4096, 1000, 3, 128), (5, 1152, 264, 3, 128),
     (16, 2048, 72, 3, 256), (3, 128, 40, 3, 128), (4, 11008, 4096, 3, 128),
-    # 3 bits at larger batches (64-row tiles with weights in units of three stages where the in-register form does
-    # not take the case): both projections (the narrow one in k-slices of whole units, the last one short), one to
-    # three token blocks per pass, a row of less than one unit, ragged last row tile, groups of 256 (70 tokens: a prompt)
+    # 3 bits at larger batches: both projections, one to four token blocks, ragged last row tiles, groups of 256; two blocks of a
+    # short row in registers; a row of 768 (70 tokens: a prompt)
     (64, 4096, 11008, 3, 128), (40, 11008, 4096, 3, 128), (16, 4096, 10240, 3, 128), (33, 1024, 10312, 3, 256),
     (24, 2048, 10304, 3, 128), (70, 768, 10248, 3, 128),
-    # ... and two passes in k-slices, at 4 bits too
+    # ... and two passes, at 4 bits too
     (100, 3072, 2048, 3, 512), (100, 3072, 2048, 4, 256),
     # ... and few tokens on narrow layers
     (16, 4096, 4096, 3, 128), (7, 11008, 4096, 3, 128),
-    # 70B-class projections: the widest layer at a small batch, the longest rows (too many groups for the tile kernel's
-    # tables: the streaming forms take it)
+    # 70B-class projections: the widest layer at a small batch, the longest rows
     (4, 8192, 28672, 4, 128), (40, 28672, 8192, 4, 128),
-    # 2 bits at small batches (the LDS-resident form with half-chunk sub-steps on narrow layers, else the in-register
-    # form): both projections at one token and a few (rows of 11008 codes are 21.5 stages: the last stage runs into
-    # the next row), groups of 256, a ragged row tile, a row of less than one stage, 12 tokens of a short row
+    # 2 bits at small batches: both projections at one token and a few, groups of 256, a ragged row tile, a row of one macro, 12
+    # tokens of a short row
     (1, 4096, 11008, 2, 128), (1, 11008, 4096, 2, 128), (4, 4096, 11008, 2, 128), (8, 11008, 4096, 2, 128),
     (3, 2048, 1000, 2, 256), (5, 256, 40, 2, 128), (12, 1024, 264, 2, 128), (16, 4096, 520, 2, 128),
-    # 4 and 8 bits with packed rows that are not whole stages (16-byte aligned only): the last stage is shared with
-    # the next row; the last row's runs past the matrix
+    # 4 and 8 bits with packed rows that are not whole stages (16-byte aligned only): with activations in LDS the last stage is
+    # shared with the next row, and the last row's runs past the matrix
     (2, 4096 + 128, 1000, 4, 128), (7, 1152, 264, 4, 128), (3, 2048 + 64, 72, 8, 64), (1, 11008 + 128, 4096, 4, 128),
 ])
 def test_quantized_forward_matches_oracle_and_training_forward(T, i, o, bits, g):
@@ -238,9 +231,12 @@ def test_quantized_forward_matches_oracle_and_training_forward(T, i, o, bits, g)
 
 
 @pytest.mark.parametrize("T,i,o,bits,g", [
-    (1, 4096, 11008, 4, 128),     # activations resident in LDS
-    (16, 4096, 10240, 4, 128),    # 64-row tiles
-    (48, 8704, 2600, 4, 512),     # k-slices into the workspace + the sum over the slices
+    (1, 4096, 11008, 4, 128),     # weights in registers
+    (3, 1024, 1000, 4, 128),      # activations resident in LDS
+    (16, 4096, 10240, 4, 128),    # one pass, three tiles
+    (29, 768, 22232, 3, 128),     # 64-row tiles
+    (103, 3584, 168, 4, 128),     # ... in k-slices into the workspace and two passes
+    (48, 8704, 2600, 4, 512),     # one pass in k-slices into the workspace + the sum over the slices
     (48, 5120, 5000, 4, 1024),    # one pass in one slice
     (20, 512, 264, 3, 64),        # general kernel
 ])

@@ -4,11 +4,7 @@ import ctypes
 import random
 
 from paper_2402_04902_amd import binding
-from plan_util import _LayerDims
-
-
-class _WregPlan(ctypes.Structure):
-    _fields_ = [("nt", ctypes.c_int), ("cpw", ctypes.c_int), ("grid", ctypes.c_uint), ("wv", ctypes.c_int), ("tbp", ctypes.c_int)]
+from plan_util import _LayerDims, _WregPlan
 
 
 # (tiles per workgroup, chunks per wave, waves) by code width
