@@ -30,7 +30,7 @@
 //
 // QAT-LoRA.  A third form keeps the group sums alone.  The quantizer sees W0, so the factor is made in the epilogue, by the
 // stated binary32 operations, from the tile of W0 that takes the factors' way into LDS: no weight gradient is stored and no
-// pass reads it again.  4096 x 4096, 2048 tokens: 66 us, against 62 for the product that stored dWq and 26 - 32 for the pass
+// pass reads it again.  4096 x 4096, 2048 tokens: 73 us, against 68 for the product that stored dWq and 30 for the pass
 // over it and W0 (16 vector operations for each of a lane's 256 elements, 8 us at full rate).
 #include <type_traits>
 

@@ -5,7 +5,7 @@
 //   dWq       dWq[o,i] = dY [T,o]^T . X [T,i]           both operands K-major (unfused backward only;
 //                                                       the fused form lives in l4q_bwd_fused.hip)
 // The workspace operand (Wq, WqT) is zero-padded along k to the 32-wide k-step; the caller's operand is
-// not: its 16-byte chunks past the row end are masked (read as zeros) in the last stage.
+// not: its 16-byte chunks past the row end are masked (read as zeros) in the last unit of 64 k-values.
 #include "l4q_device.h"
 #include "l4q_gemm_core.h"
 #include "l4q_kernels.h"
@@ -363,16 +363,18 @@ template <class F> int64_t nt_tiles(int64_t M, int64_t N) {
 // In a training step the merge pass reads W0 from memory and writes Wq right before the forward product (4 N K bytes):
 // felt from 40 M weights on, complete at 107 M.  Between it and the dX product (`late`) lie the weight-gradient kernel and
 // its factor array, another 4 N K bytes: from 30 M on, complete at 60 M.  A stage's loads then take about 2.6 us instead of
-// 1.3, which a full tile's ring (four stages of 0.52 us ahead) nearly covers and the smaller tiles' (0.28, 0.19 us a stage)
-// do not: per 1024 k a full / half / quarter tile takes 16.6 / 9 / 6.2 us from the cache and 20.6 / 15 .. 17 / 12 from memory
-// (late, quarter tiles come off better than that: 9).
+// 1.3, which a full tile's rings (operand B three stages of 0.52 us ahead, A two units of two stages) nearly cover and the
+// smaller tiles' (0.28, 0.19 us a stage) do not: per 1024 k a full / half / quarter tile takes 16.6 / 9 / 6.2 us from the cache
+// and 20.6 / 15 .. 17 / 12 from memory (late, quarter tiles come off better than that: 9).
 double nt_uncached(int64_t N, int64_t K, bool late) {
   const double weights = (double)N * (double)K;
   const double c = late ? (weights - 30e6) / 30e6 : (weights - 40e6) / 67e6;
   return c < 0.0 ? 0.0 : c > 1.0 ? 1.0 : c;
 }
 
-// One pass over k: which tile.  In us (full / half / quarter; their numbers on 256 compute units; M x N x K):
+// One pass over k: which tile.  In us (full / half / quarter; their numbers on 256 compute units; M x N x K), as is what follows
+// up to nt_plan measured with X and dY in rows of 64 bytes; with whole cache lines all three forms are 4 to 10 % faster, and
+// constants fitted to that would gain 0.4 % at most:
 //    32,   64,  128   72 /  41 / 29    512 x  4096 x 4096      172,  344,  688    80 /  94 /  92   1024 x 11008 x 4096
 //    32,   64,  128   39 /  23 / 15   1000 x  2048 x 2048      192,  384,  768    84 /  95 /   -   3000 x  4096 x 4096
 //    64,  128,  256   73 /  42 / 33   1024 x  4096 x 4096      240,  440,  880   118 / 123 / 156   1328 x 10224 x 5120

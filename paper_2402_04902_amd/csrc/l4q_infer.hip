@@ -1421,7 +1421,8 @@ WregPlan qgemm_wreg_plan(const LayerDims& d) {
     if (nt > 2) nt = 2;
   }
   // More workgroups than compute units: the later rounds do not overlap the first one's latency, and the streaming forms catch
-  // up beyond a token block (2 bits [5120 x 13824] at one token already: 17 - 37 us against 12 - 30).
+  // up beyond a token block (3 bits [24000 x 1024] 24 tokens 26.7 us against 16.6; 4 bits [20000 x 2048] 20 / 31 tokens 22.9 /
+  // 24.3 against 23.2 / 27.0; 2 bits [5120 x 13824] at one token already: 17 - 37 against 12 - 30).
   const bool many = plan_grid_rounds(tiles, nt, cus) > 1;
   const bool few_tiles = 2 * tiles < cus;  // (the streaming forms split k further over the idle units)
   int64_t from = 1, to = 64;
@@ -1443,7 +1444,7 @@ WregPlan qgemm_wreg_plan(const LayerDims& d) {
   plan.cpw = (int)cpw;
   plan.grid = (unsigned)((tiles + nt - 1) / nt);
   // Whole passes of two token blocks (17 .. 32 tokens) on short rows: 8 waves with a chunk each convert the codes once for both
-  // blocks (4 bits: [4096 x 4096] with two chunks 7.7 / 10.3 us at 17 / 32 tokens against 8.3 / 10.7).
+  // blocks (4 bits [11008 x 2048] 20 / 32 tokens 7.6 / 8.8 us against 10.8 / 12.0 with 16 waves, a block after the other).
   if (d.bits != 8 && d.T > 16 && chunks <= 8 && nt <= 3) {
     plan.wv = 8;
     plan.tbp = 2;
